@@ -18,8 +18,8 @@ typedef uint16_t f16_t;    // raw bits
 constexpr int kThreads = 256;            // threads per workgroup (4 waves, one per SIMD)
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxBatch = 4;        // sequences one pass of the row-partitioned paths works on
-constexpr int kMaxBatchFused = 8;   // sequences the regular RoPE / position / mailbox regions of the fused kernel's LDS are laid out for
-constexpr int kMaxBatchWide = 16;   // sequences of a wide pass (bf16 weights, see ff_wide.h)
+constexpr int kMaxBatchFused = 8;   // sequences the RoPE / position regions of the fused kernel's LDS are laid out for
+constexpr int kMaxBatchWide = 16;   // sequences of a wide pass (ff_wide.h)
 constexpr int kMaxBatchApi = 16;    // sequences one decode step accepts (one wide pass, or passes of kMaxBatch)
 constexpr int kMaxSplits = 64;           // max KV splits per (sequence, kv head)
 #ifndef FF_MIN_SPLIT
@@ -96,10 +96,9 @@ struct DevModel {
     // counter in its lowest mantissa bits): residual stream (two buffers), sublayer output, merged
     // attention output, SwiGLU output
     u32* cx;  u32* cx2;  u32* cdelta;  u32* cattn_o;  u32* ch;
-    // wide pass (ff_wide.h): residual rows [16][d] (each row touched by its owning workgroup only), images of
-    // the consumers' LDS layout for the d-wide inputs, the merged attention output and the SwiGLU output, the
-    // workgroups' partial sums of squares [workgroups][16], one epoch word per workgroup
-    float* wxres;  uint8_t* wimg_x;  uint8_t* wimg_a;  uint8_t* wimg_h;  float* wsspart;  u32* wflag;  float* wxch;  u32* wpflag;
+    // wide pass (ff_wide.h): exchange images and sums of squares, wring blocks (one per layer and one for the LM head,
+    // or 1: reused by every layer); one epoch word per workgroup
+    uint8_t* wimg;  u32* wflag;  int wring;
     u32* stepctr;    // [0] fused launches executed so far on these buffers (skipped steps do not count); [1] sequences the last one served
     u32x2* tpart_m;  u32x2* tpart_l;  u32x2* tpart_o;
     int* status;

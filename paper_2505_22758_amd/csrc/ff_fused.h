@@ -1,7 +1,7 @@
 // The fused whole-model decode kernel (one persistent launch per decode step).
 #pragma once
 #include <mutex>
-#include "ff_kernels.h"
+#include "ff_wide.h"
 
 namespace ff {
 
@@ -35,12 +35,6 @@ __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory")
 //
 // The projections of all phases run through ONE instance of the streaming loop; what differs per
 // phase (input, epilogue) is selected at run time once per row pair.
-enum { PH_QKV = 0, PH_O = 1, PH_GU = 2, PH_DOWN = 3, PH_LM = 4 };
-// Measurement switches of a launch (debug entry points): tiles requested only after the input has
-// arrived; attention shares equal for every sequence instead of by length (attn_share_of).
-enum { kSwNoOverlap = 1, kSwUniformShares = 2 };
-enum { TAG_QKV = 0, TAG_ATT = 1, TAG_O = 2, TAG_GU = 3, TAG_DOWN = 4 };
-
 // Optional profile (100 MHz wall clock), written only while a buffer is set through the debug entry
 // point.  Layout in uint64 words, P = number of projection phases, W = workgroups:
 //   [0, 12P)             workgroup 0, wave 0: kEvSlots stamps per phase (EV_* below)
@@ -51,7 +45,6 @@ enum { TAG_QKV = 0, TAG_ATT = 1, TAG_O = 2, TAG_GU = 3, TAG_DOWN = 4 };
 //                        3 all tags fresh, 4 staged, 5 number of stale passes; then 8 words about
 //                        its attention work: 0 start, 1 queries seen, 2 rows done, 3 partial stored,
 //                        4 (merging workgroups) split maxima seen, 5 merged output stored, 6 end
-enum { EV_SYNCED = 0, EV_RUN_DONE = 1, EV_PF_ISSUED = 2, EV_H_START = 3, EV_ATT_START = 6, EV_ATT_END = 7, kEvSlots = 12 };
 __device__ __forceinline__ void dbg_event(const DevModel& M, int ph, int ev, int lane) {
     if (M.dbg && blockIdx.x == 0 && lane == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64();
 }
@@ -95,7 +88,6 @@ __device__ __forceinline__ PhaseState phase_state(const DevModel& M, int ph) {
     const bool odd = k == 1 || k == 2;
     return odd ? PhaseState{M.cx2, M.cx} : PhaseState{M.cx, M.cx2};
 }
-__device__ __forceinline__ u32 tag_of(u32 tag_base, int l, int k) { return tag_base + 1u + (u32)(l * kTagsPerLayer + k); }
 
 // `sl` = (steps executed so far) * L: the write counters of the compact vectors are sl + layer for the
 // buffers written once per layer and 2 * (sl + layer) + {0, 1} for the sublayer output (O, then DOWN).
@@ -143,113 +135,6 @@ __device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* to
     return D;
 }
 
-// The whole step of a wide pass (see ff_wide.h): the same phases, with activations exchanged as
-// images of the consumers' LDS layout, epochs instead of per-word counters, and the residual stream
-// kept by the workgroups that own its rows.  The step's embedding rows (residual rows, first image,
-// partial sums of squares) are prepared by k_wide_embed, launched in front of the fused kernel.
-// n_lm: LM-head phases (row blocks of at most kDenseMaxTiles tiles per workgroup), 0 = not here.
-// Returns false after a time-out (status is set).
-#ifndef FF_WIDE_SPLIT
-#define FF_WIDE_SPLIT 1   // K split of the wide pass's output and down projections (0: every workgroup multiplies its own rows over all of K)
-#endif
-template <int WD, int HD, int G>
-__device__ __forceinline__ bool wide_loop(const DevModel& M, const DevKV& KV, const int* pos_lds, const int* share_lds, const float2* rope_lds, float* logits, int batch,
-                                          int n_lm, int ncta, uint8_t* lds, WgVote& vote, u32 steps_done, u32 sl, u32 tag_base) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const UDiv n_ctas = UDiv::of((u32)ncta);
-    float4* xs = (float4*)lds;
-    float* rs = (float*)(lds + kLdsActBytes);   // aux region: 1/rms per sequence, scratch of the reduction, verdict word
-    float* part = rs + 16;
-    const WideSync sync{M.wflag, ncta, (lds_u32*)(part + 256), M.wpflag};
-    float* ssl = (float*)(lds + 64 * 1024);     // behind the partial tiles of the reduction (at most 56 KB)
-    const u32 ebase = steps_done * (u32)(4 * M.L);   // epochs of this step: ebase + 4 l + {1: attention, 2: O, 3: gate/up, 4: down}
-    const int n_phases = 4 * M.L + n_lm;
-    mfma_f4 acc[kDenseMaxTiles];
-    typename WideStageOf<WD>::type ring[2];
-    DenseCursor cur{0, 0};   // int8, int4: next stage to load
-    for (int ph = 0; ph < n_phases; ph++) {
-        const int lm_block = max(ph - 4 * M.L, 0);
-        PhaseDesc D = phase_desc(M, nullptr, tag_base, sl, ph - lm_block, 1, phase_state(M, ph - lm_block), true);
-        EpiFused epf{D.kind, D.out_tag, D.out_cnt, M, KV, pos_lds, D.layer, rope_lds, logits};
-        if (D.kind == PH_LM) {
-            const int block_rows = kDenseMaxTiles * 16 * ncta, row0 = lm_block * block_rows;
-            D.W.w += (size_t)row0 * D.W.row_bytes();
-            if constexpr (WD == W_INT8) D.W.s += row0;   // row scales of the block
-            if constexpr (WD == W_INT4) { D.W.s += (size_t)row0 * (D.W.k / 128); D.W.z += (size_t)row0 * (D.W.k / 128); }   // group scales and zeros
-            D.W.n = min(block_rows, D.W.n - row0);
-            epf.pair0 = row0 >> 1;
-        }
-        const int l = D.layer;
-        const FF_CONST PLayer* Lp = as_const(M.layers) + min(l, M.L - 1);
-        // output and down projection: K split between the workgroups of a pair where the shapes allow (see DenseStream)
-        const bool split = FF_WIDE_SPLIT && (D.kind == PH_O || D.kind == PH_DOWN) && DenseStream::can_split(D.W, n_ctas);
-        DenseStream DS = DenseStream::make<WD>(D.W, 0, n_ctas, split);
-        const int seg0 = DS.seg0, seg1 = DS.seg1;
-        DS = DenseStream::make<WD>(D.W, seg0, n_ctas, split);
-        if constexpr (WD == W_INT4) dense_prefetch_i4(DS, cur, ring, wave, lane);
-        else if constexpr (WD == W_INT8) dense_prefetch_i8(DS, cur, ring, wave, lane);
-        else dense_prefetch(DS, ring, wave, lane);
-        u32 wait_epoch = 0;
-        const uint8_t* img = M.wimg_x;
-        bool normed = true;
-        if (D.kind == PH_QKV) wait_epoch = l > 0 ? ebase + 4u * (u32)l : 0u;
-        else if (D.kind == PH_O) {
-            __syncthreads();   // the previous projection's epilogue has read its sums out of LDS
-            const bool ok = attention_phase_tagged<kFusedWaves, HD, G, 2>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT),
-                                                                      sl + l, n_ctas, vote, nullptr, M.wimg_a);
-            if (!ok) return false;
-            sync.arrive(ebase + 4u * (u32)l + 1u);
-            wait_epoch = ebase + 4u * (u32)l + 1u; img = M.wimg_a; normed = false;
-        } else if (D.kind == PH_GU) wait_epoch = ebase + 4u * (u32)l + 2u;
-        else if (D.kind == PH_DOWN) { wait_epoch = ebase + 4u * (u32)l + 3u; img = M.wimg_h; normed = false; }
-        else wait_epoch = ebase + 4u * (u32)M.L;
-        if (wait_epoch) {
-            if (!sync.wait(wait_epoch, wave, lane)) {
-                if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);
-                return false;
-            }
-        } else __syncthreads();
-        if (normed) wide_rms(M.wsspart, ncta, D.W.k, M.eps, part, rs, threadIdx.x);
-#pragma unroll
-        for (int t = 0; t < kDenseMaxTiles; t++) acc[t] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-        bool run_ok = true;
-        for (int seg = seg0; seg < seg1; seg++) {
-            DS = DenseStream::make<WD>(D.W, seg, n_ctas, split);
-            if (DS.T > 0) wide_copy_quarter(img + (size_t)seg * kWideSegBytes, lds, wave, lane, batch);   // (private to the wave: no barrier)
-            const float* rsp = normed ? rs : nullptr;
-            const int par = ((seg - seg0) * (WD == W_INT4 ? (DS.T + 1) >> 1 : DS.T)) & 1;   // int8, int4: ring slot of the segment's first stage
-            if (D.kind == PH_GU) dense_run_wide<WD>(DS, ring, xs, acc, batch, wave, lane, WideEpiSwiGLU{M.wimg_h, M.gu}, rsp, nullptr, nullptr, 0u, &cur, par);
-            else if (D.kind == PH_O)
-                run_ok = dense_run_wide<WD>(DS, ring, xs, acc, batch, wave, lane, WideEpiResidual{M.wxres, M.d, Lp->g2, M.wimg_x, ssl, DS.own0}, rsp,
-                                            M.wxch, &sync, ebase + 4u * (u32)l + 2u, &cur, par);
-            else if (D.kind == PH_DOWN)
-                run_ok = dense_run_wide<WD>(DS, ring, xs, acc, batch, wave, lane,
-                                            WideEpiResidual{M.wxres, M.d, l + 1 < M.L ? (as_const(M.layers) + l + 1)->g1 : M.gf, M.wimg_x, ssl, DS.own0}, rsp,
-                                            M.wxch, &sync, ebase + 4u * (u32)l + 4u, &cur, par);
-            else dense_run_wide<WD>(DS, ring, xs, acc, batch, wave, lane, WideEpiPairs<EpiFused>{epf}, rsp, nullptr, nullptr, 0u, &cur, par);
-        }
-        if (!run_ok) {   // (uniform) the partner of a K-split projection did not deliver
-            if (threadIdx.x == 0) atomicCAS(M.status, 0, -58 - 10 * ph);
-            return false;
-        }
-        if (D.kind == PH_O || D.kind == PH_DOWN) {
-            // this workgroup's share of every sequence's sum of squares of the new residual rows
-            __syncthreads();
-            if (threadIdx.x < kMaxBatchWide) {
-                float t = 0.f;
-                const int ngrp = (DS.own1 - DS.own0) >> 2;
-                if ((int)threadIdx.x < batch) for (int q = 0; q < ngrp; q++) t += ssl[q * kMaxBatchWide + threadIdx.x];
-                xst(M.wsspart + (size_t)blockIdx.x * kMaxBatchWide + threadIdx.x, t);
-            }
-        }
-        if (D.kind == PH_O) sync.arrive(ebase + 4u * (u32)l + 2u);
-        else if (D.kind == PH_GU) sync.arrive(ebase + 4u * (u32)l + 3u);
-        else if (D.kind == PH_DOWN) sync.arrive(ebase + 4u * (u32)l + 4u);
-    }
-    return true;
-}
-
 // Attention form of the passes of up to four sequences (see attn_item): 0 = row by row on the vector
 // ALU, 1 = scores of 16 cached rows at a time on the matrix cores (head dimension 128 only).  With
 // eight query heads per KV head the row-wise form is bound by the vector ALU (the 70B shape at batch
@@ -278,13 +163,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float4* xs = (float4*)lds;
-    // The wide instance (up to 16 sequences, bf16 weights) keeps its RoPE rows in the tail of the aux
-    // region that only int4 weights use plus the regular RoPE region behind it, and its positions
-    // in the mailbox region (no wave pairs share a row group there).
-    constexpr bool kWide = B > kMaxBatchFused;
-    static_assert(!kWide || (kLdsXsumBytes + kLdsRopeBytes >= B * 64 * (int)sizeof(float2) && kLdsPairBytes >= B * 4 && B <= kMaxBatchWide),
-                  "LDS layout of the wide pass");
-    float2* rope_lds = (float2*)(lds + kLdsActBytes + kLdsAuxBytes - (kWide ? kLdsXsumBytes : 0));   // [batch][hd/2]
+    float2* rope_lds = (float2*)(lds + kLdsActBytes + kLdsAuxBytes);   // [batch][hd/2]
     for (int i = threadIdx.x; i < batch * (M.hd / 2); i += kFusedThreads) {
         int b = i / (M.hd / 2), f = i % (M.hd / 2);
         rope_lds[i] = KV.rope[(size_t)max(step_pos(tokens, pos, b), 0) * (M.hd / 2) + f];
@@ -293,22 +172,19 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     // make the wave wait for everything it has in flight (its prefetched weight tiles included), so
     // the grid size is a kernel argument and the positions are staged in LDS once.
     static_assert(kLdsRopeBytes == kMaxBatchFused * 64 * sizeof(float2) && kLdsMiscBytes >= (16 + 2 * (1 + WgVote::kMaxSums) * kFusedWaves) * 4, "LDS layout");
-    int* pos_lds = kWide ? (int*)(lds + kLdsActBytes + kLdsAuxBytes + kLdsRopeBytes + kLdsMiscBytes)
-                         : (int*)((float*)(lds + kLdsActBytes + kLdsAuxBytes) + 2 * kMaxBatchFused * 64 + 8);
-    int* share_lds = pos_lds + (kWide ? kMaxBatchWide : kMaxBatch);   // workgroups per kv head of each sequence's attention (attn_share_of)
-    static_assert(kLdsPairBytes >= 2 * kMaxBatchWide * 4 && 2 * kMaxBatch <= 8, "positions and attention shares in LDS");
+    int* pos_lds = (int*)((float*)(lds + kLdsActBytes + kLdsAuxBytes) + 2 * kMaxBatchFused * 64 + 8);
+    int* share_lds = pos_lds + kMaxBatch;   // workgroups per kv head of each sequence's attention (attn_share_of)
+    static_assert(2 * kMaxBatch <= 8, "positions and attention shares in LDS");
     if ((int)threadIdx.x < batch) {
         pos_lds[threadIdx.x] = step_pos(tokens, pos, threadIdx.x);   // -1: the sequence sits this step out
         share_lds[threadIdx.x] = attn_share_of(tokens, pos, batch, threadIdx.x, ncta, M.Hkv, (switches & kSwUniformShares) != 0);
     }
-    if (!kWide && threadIdx.x < 2) ((lds_u32*)(pairbox_of(xs) + 4 * kPairBoxFloats))[threadIdx.x] = 0u;
+    if (threadIdx.x < 2) ((lds_u32*)(pairbox_of(xs) + 4 * kPairBoxFloats))[threadIdx.x] = 0u;
     if (B == 1 && threadIdx.x < kGluMaxChunks) ((lds_u32*)pairbox_of(xs))[threadIdx.x] = 0u;   // arrival counters of the staged h chunks (glu_run)
     __syncthreads();
     // projections only; attention runs right after each PH_QKV.  The LM head runs here unless its
     // weight type differs from the layers' (then the host launches it separately).
-    // (lm_in_kernel: number of LM-head phases; 1, or with a wide pass the number of row blocks)
-    const int n_phases = 4 * M.L + (kWide ? lm_in_kernel : lm_in_kernel ? 1 : 0);
-    const int dbg_phases = 4 * M.L + (lm_in_kernel ? 1 : 0);   // phases the optional timeline buffer has slots for (further LM blocks share the last)
+    const int n_phases = 4 * M.L + lm_in_kernel;
     // steps executed so far on the compact buffers (kept on the device: a skipped step does not count)
     const u32 steps_done = (u32)__builtin_amdgcn_readfirstlane(xld_u32(M.stepctr));
     const u32 sl = steps_done * (u32)M.L;
@@ -335,14 +211,6 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     // the previous projection), so batch 1 keeps the unpinned form.
     constexpr bool kScalarState = B > 1;
     constexpr bool kQuad = kQuadOf<WD, B>;   // matrix-core GEMV on groups of four rows, split-bf16 staged input
-    if constexpr (kWide) {
-        if (!wide_loop<WD, HD, G>(M, KV, pos_lds, share_lds, rope_lds, logits, batch, lm_in_kernel, ncta, lds, vote, steps_done, sl, tag_base)) return;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            xst_u32(M.stepctr + 1, 0u);   // the compact exchange rows were not written: the next narrow pass re-initialises its rows
-            xst_u32(M.stepctr, steps_done + 1u);
-        }
-        return;
-    } else {
     int ph = 0, seg = 0;
     for (;;) {
         if constexpr (kScalarState) {
@@ -366,7 +234,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         // after the input has arrived, as in a fused kernel without cross-layer memory overlap)
         constexpr bool kHasSwitch = B == 1 && WD == W_BF16;
         if (!kHasSwitch || !(switches & kSwNoOverlap)) prefetch_stream<kQuad>(S, ring, lane, 0, kPrefetchOf<WD>);
-        if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_PF_ISSUED, lane);
+        if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_PF_ISSUED, lane);
         // Touch the descriptor the NEXT phase will fetch, so that it sits in the scalar cache by
         // then instead of costing a trip to memory at the head of that phase.
         u32 warm = 0;
@@ -377,18 +245,18 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         if (att_first) {
             // split-KV attention + merge of this layer (the ring holds the output projection's tiles)
             __syncthreads();   // every wave has finished reading the staged input: LDS is free
-            if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_ATT_START, lane);
-            u64* aev = dbg_stage_slots(M, dbg_phases, ncta, D.layer, 4);
+            if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_ATT_START, lane);
+            u64* aev = dbg_stage_slots(M, n_phases, ncta, D.layer, 4);
             if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
             const bool ok = attention_phase_tagged<kFusedWaves, HD, G, kAttnModeOf<WD>>(M, KV, pos_lds, share_lds, batch, D.layer, lds, tag_of(tag_base, D.layer, TAG_QKV),
                                                                 tag_of(tag_base, D.layer, TAG_ATT), sl + D.layer, n_ctas, vote, aev);
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
-            if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_ATT_END, lane);
+            if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_ATT_END, lane);
             if (!ok) return;
         }
-        if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_H_START, lane);
+        if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_H_START, lane);
         bool ok;
-        u64* ev = dbg_stage_slots(M, dbg_phases, ncta, D.layer, D.kind);
+        u64* ev = dbg_stage_slots(M, n_phases, ncta, D.layer, D.kind);
         if (src.add) ok = stage_tagged<EPU, true, kFusedThreads, kQuad, B>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
         else ok = stage_tagged<EPU, false, kFusedThreads, kQuad, B>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
         if (ev && threadIdx.x == 0) as_global(ev)[4] = wall_clock64();
@@ -396,10 +264,10 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
             if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);
             return;
         }
-        if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_SYNCED, lane);
+        if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_SYNCED, lane);
         if (kHasSwitch && (switches & kSwNoOverlap)) prefetch_stream<kQuad>(S, ring, lane, 0, kPrefetchOf<WD>);
         if constexpr (kPrefetchOf<WD> < kDepthOf<WD>) prefetch_stream<kQuad>(S, ring, lane, kPrefetchOf<WD>, kDepthOf<WD>);   // the rest of the ring, behind the input
-        u64* wv = D.kind < 4 ? dbg_wave_slots(M, dbg_phases, D.layer, wave) : nullptr;
+        u64* wv = D.kind < 4 ? dbg_wave_slots(M, n_phases, D.layer, wave) : nullptr;
         if (wv && lane == 0) as_global(wv)[4 + D.kind] = wall_clock64();
         bool glu_done = false;
         if constexpr (B == 1) {
@@ -427,7 +295,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         else if constexpr (kQuad) gemv_run_quad<WD, B>(S, ring, xs, myacc, batch, lane, epi);
         else gemv_run<WD, B>(S, ring, xs, myacc, batch, lane, epi);
         asm volatile("" ::"s"(warm));   // keeps the touch alive
-        if (wave == 0) dbg_event(M, min(ph, dbg_phases - 1), EV_RUN_DONE, lane);
+        if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_RUN_DONE, lane);
         if (wv && lane == 0) as_global(wv)[D.kind] = wall_clock64();
         // next iteration: further K segment of the same projection, or the next projection
         if (glu_done) ++ph;   // the down projection ran inside glu_run
@@ -443,7 +311,6 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         xst_u32(M.stepctr + 1, (u32)batch);
         xst_u32(M.stepctr, steps_done + 1u);
     }
-    }   // (!kWide)
 }
 
 // Host-side launcher of one weight-type family; defined once per weight type in its own
@@ -452,35 +319,51 @@ struct FusedLaunch {
     DevModel M; DevKV KV; const int* tokens; const int* pos; float* logits;
     int batch; int lm_in_kernel; int n_cta; size_t lds_bytes; hipStream_t stream; int mute_wg; int switches;   // switches: kSw* bits
     int glu_off;   // >= 0: single-sequence passes run gate/up + down as one stream (glu_run), staged h at this LDS offset
-    int wide;      // the pass runs on the wide instance (K-segmented inputs, LM head outside the kernel)
+    int wide;      // the pass runs on the wide kernel (ff_wide.h)
+};
+// One-time set-up of a kernel (thread-safe; a failure is remembered and reported by every call).
+struct KernelSetup {
+    std::once_flag once;
+    hipError_t err = hipSuccess;
+    const char* what = "";
+    hipError_t run(const void* kern, int threads, size_t lds_bytes) {
+        std::call_once(once, [&] {
+            err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+            if (err != hipSuccess) { what = "hipFuncSetAttribute"; return; }
+            int occ = 0;
+            err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, threads, lds_bytes);
+            if (err != hipSuccess) { what = "hipOccupancyMaxActiveBlocksPerMultiprocessor"; return; }
+            if (occ < 1) { what = "fused kernel does not fit on a compute unit"; err = hipErrorLaunchOutOfResources; }
+        });
+        return err;
+    }
 };
 template <int WD, int B, int HD, int G>
 inline hipError_t launch_fused_instance(const FusedLaunch& a, const char** what) {
     auto kern = fused_decode_kernel<WD, B, HD, G>;
-    // one-time set-up per instance (thread-safe; a failure is remembered and reported by every call)
-    static std::once_flag once;
-    static hipError_t setup_err = hipSuccess;
-    static const char* setup_what = "";
-    std::call_once(once, [&] {
-        setup_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds_bytes);
-        if (setup_err != hipSuccess) { setup_what = "hipFuncSetAttribute"; return; }
-        int occ = 0;
-        setup_err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, kFusedThreads, a.lds_bytes);
-        if (setup_err != hipSuccess) { setup_what = "hipOccupancyMaxActiveBlocksPerMultiprocessor"; return; }
-        if (occ < 1) { setup_what = "fused kernel does not fit on a compute unit"; setup_err = hipErrorLaunchOutOfResources; }
-    });
-    if (setup_err != hipSuccess) { *what = setup_what; return setup_err; }
+    static KernelSetup setup;
+    if (hipError_t e = setup.run((const void*)kern, kFusedThreads, a.lds_bytes)) { *what = setup.what; return e; }
     kern<<<a.n_cta, kFusedThreads, a.lds_bytes, a.stream>>>(a.M, a.KV, a.tokens, a.pos, a.logits, a.batch, a.lm_in_kernel, a.n_cta, a.mute_wg, a.switches, a.glu_off);
     *what = "fused kernel launch";
     return hipGetLastError();
 }
+template <int WD, int NC, int HD, int G>
+inline hipError_t launch_wide_instance(const FusedLaunch& a, const char** what) {
+    auto kern = wide_decode_kernel<WD, NC, HD, G>;
+    static KernelSetup setup;
+    if (hipError_t e = setup.run((const void*)kern, kWideThreads, kWideLdsBytes)) { *what = setup.what; return e; }
+    kern<<<a.n_cta, kWideThreads, kWideLdsBytes, a.stream>>>(a.M, a.KV, a.tokens, a.pos, a.logits, a.batch, a.lm_in_kernel, a.n_cta, a.mute_wg, a.switches);
+    *what = "wide kernel launch";
+    return hipGetLastError();
+}
 template <int WD, int HD, int G>
 inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
-    if (a.wide) return launch_fused_instance<WD, kMaxBatchWide, HD, G>(a, what);   // (the host decides, and sizes lm_in_kernel and the buffers for it)
+    // (the host decides whether a pass is wide, and sizes the buffers for it; up to eight sequences share an operand tile with their remainders)
+    if (a.wide) return a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
     if (a.batch == 1) return launch_fused_instance<WD, 1, HD, G>(a, what);
     if (a.batch == 2) return launch_fused_instance<WD, 2, HD, G>(a, what);
     if (a.batch > kMaxBatch) {
-        *what = "more than four sequences per pass without the wide instance";
+        *what = "more than four sequences per pass without the wide kernel";
         return hipErrorInvalidValue;
     }
     return launch_fused_instance<WD, 4, HD, G>(a, what);

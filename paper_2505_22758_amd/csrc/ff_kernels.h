@@ -2,12 +2,18 @@
 #pragma once
 #include "ff_phases.h"
 #include "ff_glu.h"
-#include "ff_dense.h"
-#include "ff_wide.h"
 
 namespace ff {
 
 constexpr int kTagsPerLayer = 5;   // phase instances (= exchange tags) per layer of the fused kernel
+enum { PH_QKV = 0, PH_O = 1, PH_GU = 2, PH_DOWN = 3, PH_LM = 4 };
+// Measurement switches of a launch (debug entry points): tiles requested only after the input has
+// arrived; attention shares equal for every sequence instead of by length (attn_share_of).
+enum { kSwNoOverlap = 1, kSwUniformShares = 2 };
+enum { TAG_QKV = 0, TAG_ATT = 1, TAG_O = 2, TAG_GU = 3, TAG_DOWN = 4 };
+__device__ __forceinline__ u32 tag_of(u32 tag_base, int l, int k) { return tag_base + 1u + (u32)(l * kTagsPerLayer + k); }
+// Stamps of workgroup 0 per projection phase in the optional timeline buffer (layout: ff_fused.h).
+enum { EV_SYNCED = 0, EV_RUN_DONE = 1, EV_PF_ISSUED = 2, EV_H_START = 3, EV_ATT_START = 6, EV_ATT_END = 7, kEvSlots = 12 };
 
 // status codes written by kernels (mirror the C ABI's FF_ERR_*)
 constexpr int kStatusRange = -3;
@@ -81,7 +87,7 @@ __device__ __forceinline__ int attn_share_of(const int* tokens, const int* pos, 
 template <int NW, int HD, int G, int MODE = 0>
 __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const DevKV& KV, const int* pos, const int* share, int batch, int layer,
                                                        uint8_t* lds, u32 in_tag, u32 out_tag, u32 out_cnt, const UDiv& nc, WgVote& vote, u64* ev = nullptr,
-                                                       uint8_t* merged_img = nullptr) {
+                                                       const WideImg* merged_img = nullptr) {
     constexpr int NT = NW * 64;
     const int ncta = (int)nc.n;
     int base = 0;

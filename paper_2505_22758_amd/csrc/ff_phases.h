@@ -156,15 +156,20 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, u32& hi, u32& lo)
     hi = pack_bf16(a, b);
     lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
-// Wide pass (see ff_wide.h): byte offset of column `col` of sequence n in a global image of the
-// consumers' LDS layout (plane 0: heads, 1: remainders): K segment of 2048 columns, then plane-major
-// with 16-byte unit j at index j ^ n.
-constexpr int kWideSegUnits = 256;
-constexpr int kWideSegBytes = kLdsActBytes;
-__device__ __forceinline__ size_t wide_img_off(int n, int plane, int col) {
-    const int j = col >> 3;
-    return (size_t)(j >> 8) * kWideSegBytes + ((size_t)((2 * n + plane) * kWideSegUnits + ((j & 255) ^ n))) * 16 + (size_t)(col & 7) * 2;
-}
+// Wide pass (see ff_wide.h): a global image of a projection's inputs in the matrix cores' operand order.
+// A k-step (32 columns) is kWideStepBytes: lane (row, g) of the operand finds its 16 bytes (8 columns) at
+// (16 g + row) * 16 of the heads' and, 1 KB further, of the remainders' kilobyte; with up to eight
+// sequences (half) rows 0..7 are the heads and rows 8..15 the remainders, both in the first kilobyte.
+// Which 8 columns lane group g multiplies in a k-step follows from the weights it loads, 16 bytes per lane:
+// 8 << e columns (e = 0 bf16, 1 int8, 2 int4) used up in 1 << e k-steps.
+constexpr int kWideStepBytes = 2048;
+struct WideImg {
+    uint8_t* p; int e; bool half;
+    __device__ __forceinline__ uint8_t* at(int n, int plane, int col) const {
+        const int j = col >> 3, unit = j >> e, step = ((unit >> 2) << e) + (j & ((1 << e) - 1));
+        return p + (size_t)step * kWideStepBytes + (half ? ((unit & 3) * 16 + n + 8 * plane) * 16 : plane * 1024 + ((unit & 3) * 16 + n) * 16) + (col & 7) * 2;
+    }
+};
 
 // Writes quad qi (elements 4*qi .. 4*qi+3) of sequence b into the staged vector.  Plain form: the
 // quad-planar fp32 layout of stage_act.  SPLIT form (input of gemv_run_quad): every value v is
@@ -884,11 +889,11 @@ __device__ void attn_merge(const DevModel& M, int b, int j, int nsplit, float* l
 // The same merge on tagged partials (fused kernel): the workgroup that computed the LAST split of
 // (b, j) gathers all splits, re-reading until every partial carries this layer's attention tag,
 // and publishes attn_o with the same tag.  Returns false on a time-out.
-template <int HD, int G, int NT>
 // img (wide pass): the merged output goes into the output projection's input image as bf16 head +
 // remainder instead of the compact vector.
+template <int HD, int G, int NT>
 __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, int b, int j, int nsplit, u32 tag, u32 out_cnt, float* lds, WgVote& vote, u64* ev = nullptr,
-                                                  uint8_t* img = nullptr) {
+                                                  const WideImg* img = nullptr) {
     float* ms = lds;
     float* ls = lds + G * kMaxSplits;
     constexpr int kSB = 16;   // splits gathered per batch of loads
@@ -972,8 +977,8 @@ __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, int b, int 
             u32 hi, lo;
             split_bf16x2(a0, a1, hi, lo);
             const int col = (j * G + g) * HD + d2;
-            xst_u32((u32*)(img + wide_img_off(b, 0, col)), hi);
-            xst_u32((u32*)(img + wide_img_off(b, 1, col)), lo);
+            xst_u32((u32*)img->at(b, 0, col), hi);
+            xst_u32((u32*)img->at(b, 1, col), lo);
         } else {
             cst2(M.cattn_o + ((size_t)b * M.Hq + (j * G + g)) * HD + d2, a0, a1, out_cnt);
         }

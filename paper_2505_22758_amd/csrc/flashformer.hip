@@ -55,7 +55,8 @@ struct Plan {
     // scratch
     size_t x, xn, q, kvcur, attn_o, h, y, part_m, part_l, part_o, status, scratch_bytes;
     size_t cx, cx2, cdelta, tq, tkvcur, cattn_o, ch, stepctr, tpart_m, tpart_l, tpart_o;
-    size_t wxres, wimg_x, wimg_a, wimg_h, wsspart, wflag, wxch, wpflag;   // wide pass only (zero bytes otherwise)
+    size_t wimg, wflag;   // wide pass only (zero bytes otherwise)
+    int wring;
 };
 
 size_t mat_w_bytes(int n, int k, int wd) { return wd == W_BF16 ? (size_t)n * k * 2 : wd == W_INT8 ? (size_t)n * k : (size_t)n * k / 2; }
@@ -96,20 +97,23 @@ int check_config(const ff_config* c) {
     return FF_OK;
 }
 
-// The wide instance gives every workgroup a contiguous range of rows of each projection, in tiles
-// of 16 whose accumulators stay in registers: at most kDenseMaxTiles tiles per workgroup (on a grid
-// of n_cta workgroups), and whole groups of four rows of the d-wide projections.
+// The wide kernel gives every workgroup a contiguous range of rows of each projection (whole groups of
+// four) and keeps its residual rows in LDS: at most kWideResRows of them on a grid of n_cta workgroups.
+// The int4 scales of a panel of rows must fit their LDS region (two panels of the wider projections).
 bool wide_fits(const ff_config& c, int n_cta) {
-    const int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+    const int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, qd = c.n_q_heads * c.head_dim;
     const int rows = std::max(std::max(qkv_rows, c.d_model), 2 * c.d_ffn);
-    const int groups = ((rows + 3) / 4 + n_cta - 1) / n_cta;
-    return (4 * groups + 15) / 16 <= kDenseMaxTiles && c.d_model % 8 == 0 && qkv_rows % 4 == 0;
+    const auto share = [&](int n) { return 4 * (((n + 3) / 4 + n_cta - 1) / n_cta); };
+    if (share(rows) > 224 || share(c.d_model) > kWideResRows || c.d_model % 8 || qkv_rows % 4) return false;
+    if (c.wdtype != W_INT4) return true;
+    const auto tile_rows = [&](int n) { return std::min((share(n) + 15) / 16, kPanelTiles) * 16; };
+    const size_t wide_in = (size_t)16 * kPanelTiles * (c.d_model / 128) * 4, long_in = (size_t)tile_rows(c.d_model) * (std::max(qd, c.d_ffn) / 128) * 4;
+    return 2 * wide_in <= (size_t)kWideSzBytes && long_in <= (size_t)kWideSzBytes;
 }
 constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the chip the kernels are built for
 
 // Sequences one pass of the fused kernel serves: up to 4 on the row-partitioned paths (paper Section
-// 5.2), or, with bf16 or int8 weights and a model created for more than that, up to 16 in one wide
-// pass.
+// 5.2), or, for a model created for more than that, up to 16 in one wide pass.
 // FF_WIDE_MIN (experiments): smallest batch that takes the wide pass (default 5; it measured equal
 // to the former eight-sequence instance at 5 sequences and faster from 6 on, slower than the
 // four-sequence path below that).
@@ -120,9 +124,7 @@ int wide_min_batch() {
 }
 int fused_pass_rows(const ff_config& c) {
     // (quantised layers with a bf16 LM head keep the passes of four: the wide pass runs the LM head inside the kernel, in the layers' format)
-    // (int4: the wide pass takes a row's scales and zeros four groups at a time: every input width a multiple of 512)
-    const bool k512 = c.d_model % 512 == 0 && (c.n_q_heads * c.head_dim) % 512 == 0 && c.d_ffn % 512 == 0;
-    const bool fmt_ok = c.wdtype == W_BF16 || ((c.wdtype == W_INT8 || (c.wdtype == W_INT4 && k512)) && c.quant_lm_head);
+    const bool fmt_ok = c.wdtype == W_BF16 || c.quant_lm_head;
     if (fmt_ok && c.max_batch >= wide_min_batch() && wide_fits(c, kGridCtas)) return kMaxBatchWide;
     return std::min(c.max_batch, kMaxBatch);
 }
@@ -135,7 +137,8 @@ bool pass_is_wide(const ff_config& c, int batch) {
     return fused_pass_rows(c) == kMaxBatchWide && batch >= (!env && c.wdtype == W_INT8 ? kMaxBatch : wide_min_batch());
 }
 
-Plan make_plan(const ff_config& c) {
+// wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
+Plan make_plan(const ff_config& c, int wring = 0) {
     Plan P;
     size_t off = 0;
     P.layers_tab = off; off = align256(off + sizeof(PLayer) * c.n_layers);
@@ -181,14 +184,9 @@ Plan make_plan(const ff_config& c) {
     P.tpart_l = take(mb * c.n_q_heads * kMaxSplits * 8);
     P.tpart_o = take(mb * c.n_q_heads * kMaxSplits * c.head_dim * 8);
     const bool wide = mb == (size_t)kMaxBatchWide;
-    P.wxres = take(wide ? mb * c.d_model * 4 : 0);
-    P.wimg_x = take(wide ? wide_img_bytes(c.d_model) : 0);
-    P.wimg_a = take(wide ? wide_img_bytes(qd) : 0);
-    P.wimg_h = take(wide ? wide_img_bytes(c.d_ffn) : 0);
-    P.wsspart = take(wide ? (size_t)kGridCtas * kMaxBatchWide * 4 : 0);
+    P.wring = wring ? wring : c.n_layers + 1;
+    P.wimg = take(wide ? WideLayout::of(c.d_model, qd, c.d_ffn, c.wdtype, kGridCtas).bytes * P.wring : 0);
     P.wflag = take(wide ? (size_t)kGridCtas * 4 : 0);
-    P.wxch = take(wide ? (size_t)kGridCtas * kWideXchFloats * 4 : 0);   // partial sums handed to the partner workgroup (K-split projections)
-    P.wpflag = take(wide ? (size_t)kGridCtas * 4 : 0);
     P.status = take(256);
     P.scratch_bytes = s;
     return P;
@@ -378,8 +376,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
     D.status = (int*)(s + P.status);
     D.cx = (u32*)(s + P.cx); D.cx2 = (u32*)(s + P.cx2); D.cdelta = (u32*)(s + P.cdelta); D.tq = (u32x2*)(s + P.tq);
     D.tkvcur = (u32x2*)(s + P.tkvcur); D.cattn_o = (u32*)(s + P.cattn_o); D.ch = (u32*)(s + P.ch);
-    D.wxres = (float*)(s + P.wxres); D.wimg_x = s + P.wimg_x; D.wimg_a = s + P.wimg_a; D.wimg_h = s + P.wimg_h;
-    D.wsspart = (float*)(s + P.wsspart); D.wflag = (u32*)(s + P.wflag); D.wxch = (float*)(s + P.wxch); D.wpflag = (u32*)(s + P.wpflag);
+    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring;
     D.stepctr = (u32*)(s + P.stepctr);
     D.tpart_m = (u32x2*)(s + P.tpart_m); D.tpart_l = (u32x2*)(s + P.tpart_l); D.tpart_o = (u32x2*)(s + P.tpart_o);
     D.dbg = nullptr;
@@ -641,17 +638,11 @@ namespace {
 int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, int seq0,
                int step_batch, hipStream_t st) {
     const bool wide = pass_is_wide(m->cfg, batch);   // (batch <= fused_pass_rows: a wide pass only where the wide instance fits)
-    // LM head inside the fused kernel when its weights have the layers' type: one phase, or with a
-    // wide pass one phase per block of kDenseMaxTiles tiles per workgroup
-    const int lm_block_rows = kDenseMaxTiles * 16 * m->n_cta;
-    const int lm_in_kernel = D.lm.wd != m->cfg.wdtype ? 0 : wide ? (m->cfg.vocab + lm_block_rows - 1) / lm_block_rows : 1;
+    const int lm_in_kernel = D.lm.wd == m->cfg.wdtype;   // LM head inside the fused kernel when its weights have the layers' type
     DevKV kvd = kv->dev;
     kvd.seq0 = seq0;
     kvd.step_batch = step_batch;
-    if (wide) {   // the step's embedding rows in the wide pass's exchange form
-        k_wide_embed<<<m->n_cta, kThreads, 0, st>>>(D, tokens_dev, batch);
-        HIPCHK(hipGetLastError());
-    } else if (m->cfg.max_batch > 1) {   // rows a smaller batch left behind: see k_scrub_rows (decides on the device)
+    if (!wide && m->cfg.max_batch > 1) {   // rows a smaller batch left behind: see k_scrub_rows (decides on the device)
         k_scrub_rows<<<64, kThreads, 0, st>>>(D, batch);
         HIPCHK(hipGetLastError());
     }
@@ -775,7 +766,8 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
                           void* stream) {
     int rc = check_step_args(m, tokens_dev, positions_dev, kv, logits_dev, batch);
     if (rc) return rc;
-    const Plan& P = m->plan;
+    Plan P = m->plan;   // (the wide pass's images: one block for all layers where one per layer does not fit the array)
+    if (P.scratch_bytes > kStaticScratchBytes) P = make_plan(m->cfg, 1);
     if (P.scratch_bytes > kStaticScratchBytes)
         return fail(FF_ERR_NOMEM, "this configuration needs %zu bytes of exchange scratch, the static array holds %zu", P.scratch_bytes,
                     kStaticScratchBytes);
@@ -790,8 +782,7 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
     D.part_m = (float*)(s + P.part_m); D.part_l = (float*)(s + P.part_l); D.part_o = (float*)(s + P.part_o);
     D.cx = (u32*)(s + P.cx); D.cx2 = (u32*)(s + P.cx2); D.cdelta = (u32*)(s + P.cdelta); D.tq = (u32x2*)(s + P.tq);
     D.tkvcur = (u32x2*)(s + P.tkvcur); D.cattn_o = (u32*)(s + P.cattn_o); D.ch = (u32*)(s + P.ch);
-    D.wxres = (float*)(s + P.wxres); D.wimg_x = s + P.wimg_x; D.wimg_a = s + P.wimg_a; D.wimg_h = s + P.wimg_h;
-    D.wsspart = (float*)(s + P.wsspart); D.wflag = (u32*)(s + P.wflag); D.wxch = (float*)(s + P.wxch); D.wpflag = (u32*)(s + P.wpflag);
+    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring;
     D.stepctr = (u32*)(s + P.stepctr);
     D.tpart_m = (u32x2*)(s + P.tpart_m); D.tpart_l = (u32x2*)(s + P.tpart_l); D.tpart_o = (u32x2*)(s + P.tpart_o);
     // The array keeps whatever the last call (of any model) left: everything this step's kernels
