@@ -152,13 +152,14 @@ int ff_kv_free(ff_kv *kv);
  * model's status word (see ff_status).  Steps on one model must not overlap.
  * A step's launches carry no host-side per-step state (exchange tags and write counters derive
  * from a counter in the model's scratch), so a step may be recorded into a HIP graph and replayed.
- * One kernel pass serves up to 4 sequences (paper Section 5.2: batches 2-4 replicate the inputs and
- * read every weight once); with max_batch > 4, batches of 5 to 16 run as ONE "wide" pass (the paper
- * stops at 4): projections on 16x16x32 matrix-core tiles (int8 and int4 codes converted to bf16 in
- * registers), activations exchanged in the matrix cores' operand order by the workgroups that own them.
- * The wide pass needs the LM head in the layers' format (quant_lm_head for int8 / int4); otherwise a
- * batch above 4 runs as consecutive passes of 4 on the
- * stream, each streaming the weights again. */
+ * A model created for more than one sequence runs every step, of 1 to max_batch sequences, as ONE
+ * "wide" pass (paper Section 5.2 reads the weights once up to batch 4 and stops there): weights packed
+ * as matrix-core operand tiles, projections on 16x16x32 tiles (int8 and int4 codes converted to bf16 in
+ * registers), activations exchanged in operand order by the workgroups that own them.  Models for one
+ * sequence run the row-partitioned pass on row-major weights.  (Where the wide pass does not fit -- int4
+ * with d_model above 8192 / 128 groups a row -- up to 4 sequences share a row-partitioned pass and a larger
+ * batch runs as consecutive passes on the
+ * stream, each streaming the weights again.) */
 int ff_decode_step(ff_model *m, const int32_t *tokens_dev, const int32_t *positions_dev, ff_kv *kv,
                    float *logits_dev, int32_t batch, void *stream);
 
@@ -195,9 +196,9 @@ int ff_debug_dequant(const ff_model *m, int32_t layer, int32_t which, float *out
 
 /* Runs the decode kernels' own projection code on caller input: out_dev[b][n] = sum_k W[n][k] *
  * in_dev[b][k] for matrix `which` of `layer`, fp32 in_dev [batch][K], fp32 out_dev [batch][N] with
- * rows in canonical order.  path 0: the vector-ALU streaming GEMV (batch 1..4) used at batch 1 and
- * by the per-operation baseline; path 1: the matrix-core GEMV of batches >= 2 (batch 2..4, input
- * staged as bf16 head + remainder; K * 4 bytes * batch must fit the 128 KiB input buffer).  Fed with
+ * rows in canonical order.  path 0: the vector-ALU GEMV (batch 1..4) used at batch 1 and
+ * by the per-operation baseline; path 1: the matrix-core projection of models for several sequences
+ * (batch 2..4, inputs as bf16 head + remainder; K * 4 bytes * batch at most 128 KiB).  Fed with
  * unit vectors it returns the columns of W exactly as the hot path dequantises them (the int8 row
  * scale and the int4 group scale / zero are applied to sums there, which for a unit vector is the
  * single product of the defining formula).  Uses the model's scratch: must not overlap a decode
@@ -258,7 +259,8 @@ int ff_debug_mute_workgroup(ff_model *m, int32_t workgroup);
 
 /* Number of device-wide barriers one fused step executes (0: phases are ordered by tagged dataflow;
  * kept for tests of the schedule), and the number of
- * workgroups / threads per workgroup the fused kernel launches with. */
+ * workgroups / threads per workgroup the row-partitioned kernel launches with (a wide pass: the same
+ * workgroups, twice the threads). */
 int ff_fused_schedule(const ff_model *m, int32_t *barriers_per_step, int32_t *n_workgroups,
                       int32_t *threads_per_workgroup);
 

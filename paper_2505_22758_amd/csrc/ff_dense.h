@@ -9,12 +9,14 @@
 //     needed by exactly one wave of the workgroup, which loads it straight from the global image
 //     (ff_wide.h: written in operand order, 1 KB per load, the workgroups of an XCD share it in
 //     their L2) into registers and reuses it for every tile: nothing is staged through LDS;
-//   * lane (r = lane % 16, g = lane / 16) loads 16 bytes of weight row r per load; the accumulators of
-//     lane (r, g) hold row r for sequences 4 g .. 4 g + 3, so what belongs to a weight row (int4
-//     scales and zeros) belongs to the lane that loaded the row;
-//   * a wave keeps D iterations of weights (and of the inputs they meet) in flight in a register ring
-//     whose refills run unconditionally; the last D iterations are peeled off the loop (where code
-//     paths that issued different numbers of loads meet, the compiler waits for all of them);
+//   * weights are stored tile by tile in operand order (PMat): a load is one contiguous kilobyte, lane
+//     (r = lane % 16, g = lane / 16) getting 16 bytes of weight row r.  From row-major weights (64 bytes
+//     of each of 16 rows per load) the same loop streams at 3.8 TB/s, from tiles at 6.6 (8B gate/up).
+//     The accumulators of lane (r, g) hold row r for sequences 4 g .. 4 g + 3, so what belongs to a
+//     weight row (int4 scales and zeros) belongs to the lane that loaded the row;
+//   * a wave keeps D iterations of weights (and of the inputs they meet) in flight in a register ring,
+//     refilled tile by tile behind its products, unconditionally; the last iterations are peeled off the
+//     loop (where code paths that issued different numbers of loads meet, the compiler waits for all);
 //   * the waves' partial tiles meet in LDS, wave t adds and finishes tile t.
 // Two waves per SIMD: the eight waves' rings hold up to 128 KB per compute unit in flight, and one
 // wave's conversions overlap the other's matrix-core work.
@@ -39,60 +41,85 @@ typedef __bf16 mfma_bf8 __attribute__((ext_vector_type(8)));
 template <int WD> constexpr int kWLoads = WD == W_BF16 ? 2 : 1;
 template <int WD> constexpr int kWSteps = WD == W_INT4 ? 4 : 2;
 template <int WD> constexpr int kWCols = 32 * kWSteps<WD>;
-// Ring depth in iterations: what about 144 registers hold, at least two.
+// Ring depth in iterations: about 14 weight loads (14 KB) per wave in flight, i.e. 112 KB per compute unit, as far
+// as the registers go.  Twice as many measured slower everywhere (8B bf16 x 2, x 8, 70B x 16, us a pass: 14 loads 1541,
+// 1729, 5396; 28 loads 1693, 1914, 5735; 8 loads 1563, 1775, 5464): requests that wait for the memory pipe block the
+// younger wave of a SIMD, which then finishes alone, and stand in front of the next hand-over.
 template <int WD, int NC, int T> constexpr int kWDepth = [] {
-    const int regs = 4 * (T * kWLoads<WD> + kWSteps<WD> * (NC / 8)), d = (WD == W_INT4 && T >= 4 ? 112 : 144) / regs;
-    return d < 2 ? 2 : d > 6 ? 6 : d;
+    const int want = (14 + T * kWLoads<WD> - 1) / (T * kWLoads<WD>);
+    const int regs = 4 * (T * kWLoads<WD> + kWSteps<WD> * (NC / 8)), fit = (WD == W_INT4 ? 112 : 144) / regs;
+    const int d = want < fit ? want : fit;
+    return d < 1 ? 1 : d > 6 ? 6 : d;
 }();
 
-// Rows [own0, own1) of a projection that this workgroup computes: whole groups of four.
+// Rows [r0, r1) of a projection that this workgroup computes: whole groups of four (PMat::cta_rows).
 struct RowRange { int r0, r1; };
 __device__ __forceinline__ RowRange wide_rows(int n, const UDiv& n_ctas) {
     const u32 ngroups = (u32)(n + 3) / 4;
     return RowRange{4 * (int)n_ctas.div(ngroups * blockIdx.x), min(4 * (int)n_ctas.div(ngroups * (blockIdx.x + 1)), n)};
 }
 
-// One panel's weights as a wave sees them.
-template <int WD, int T>
+// One panel's weights as a wave sees them (tiled layout): load j of tile t is 64 bytes times the tile's rows, contiguous.
+template <int T>
 struct PanelSrc {
-    const uint8_t* base;   // first row of the panel (uniform)
-    u32 row[T];            // byte offset of this lane's row of tile t (rows past the end repeat the last one)
-    int units;             // 16-byte units per row
+    __amdgpu_buffer_rsrc_t base;   // from the panel's first row on
+    u32 tile[T], step[T];          // tile's first byte, bytes per load (uniform)
+    u32 lane_off[T];               // lane (r, g): unit g of row r (rows past the end repeat the last one)
     __device__ __forceinline__ static PanelSrc make(const PMat& M, int p0, int r1, int lane) {
         PanelSrc S;
         const u32 rowb = (u32)M.row_bytes();
-        S.base = M.w + (size_t)p0 * rowb;
-        S.units = (int)(rowb >> 4);
+        const size_t left = (size_t)(M.n - p0) * rowb;
+        S.base = __builtin_amdgcn_make_buffer_rsrc((void*)(M.w + (size_t)p0 * rowb), 0, (int)(u32)(left < 0xFFFFFFFFu ? left : 0xFFFFFFFFu), 0x00020000);
 #pragma unroll
-        for (int t = 0; t < T; t++) S.row[t] = (u32)(max(min(p0 + 16 * t + (lane & 15), r1 - 1), p0) - p0) * rowb;
+        for (int t = 0; t < T; t++) {
+            const bool some = p0 + 16 * t < r1;               // a tile past the workgroup's rows repeats the first one
+            const int nt = min(r1 - (some ? p0 + 16 * t : p0), 16);
+            S.tile[t] = some ? (u32)(16 * t) * rowb : 0u;
+            S.step[t] = (u32)nt * 64u;
+            S.lane_off[t] = (u32)((lane >> 4) * nt + min(lane & 15, nt - 1)) * 16u;
+        }
         return S;
+    }
+};
+
+// A projection's input image as a wave reads it: lanes of sequences beyond the batch repeat the last one
+// (rows of the operand do not mix, theirs are never looked at).
+struct PanelImg {
+    __amdgpu_buffer_rsrc_t base;
+    int step;        // bytes per k-step
+    int lane_off;
+    template <int WD, int NC>
+    __device__ __forceinline__ static PanelImg make(const uint8_t* img, int K, int batch, int lane) {
+        const int r = lane & 15, g = lane >> 4, step = wide_step_bytes(batch);
+        const int steps = (K + kWCols<WD> - 1) / kWCols<WD> * kWSteps<WD>;
+        const int piece = NC == 8 ? (2 * g + (r >> 3)) * batch + min(r & 7, batch - 1) : g * batch + min(r, batch - 1);
+        return PanelImg{__builtin_amdgcn_make_buffer_rsrc((void*)img, 0, steps * step, 0x00020000), step, piece * 16};
     }
 };
 
 template <int WD, int NC, int T>
 struct PanelRing {
-    static constexpr int D = kWDepth<WD, NC, T>, L = kWLoads<WD>, NB = kWSteps<WD> * (NC / 8);
+    static constexpr int D = kWDepth<WD, NC, T>, DX = D < 2 ? 2 : D, L = kWLoads<WD>, NB = kWSteps<WD> * (NC / 8);
     u32x4 w[D][T][L];
-    u32x4 x[D][NB];
-    // (Cacheable loads: a load takes 64 bytes of each of 16 rows, and the other half of the 128-byte lines follows in the
-    // next load or in the neighbouring wave's.  As streaming loads, 8B bf16 x 8: 2206 instead of 2004 us a pass.)
-    // Weights of iteration it (columns past the end of a row repeat its last unit and meet zeros in the image).
-    __device__ __forceinline__ void load_w(const PanelSrc<WD, T>& S, int slot, int it, int lane) {
-        u32 col[L];
+    u32x4 x[DX][NB];
+    // Weights of iteration it.
+    __device__ __forceinline__ void load_w(const PanelSrc<T>& S, int slot, int it) {
 #pragma unroll
-        for (int l = 0; l < L; l++) col[l] = (u32)min((it * L + l) * 4 + (lane >> 4), S.units - 1) * 16u;
+        for (int t = 0; t < T; t++) load_wt(S, slot, it, t);
+    }
+    __device__ __forceinline__ void load_wt(const PanelSrc<T>& S, int slot, int it, int t) {
 #pragma unroll
-        for (int t = 0; t < T; t++)
-#pragma unroll
-            for (int l = 0; l < L; l++) w[slot][t][l] = *as_global((const u32x4*)(S.base + (S.row[t] + col[l])));
+        for (int l = 0; l < L; l++)
+                w[slot][t][l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S.base, S.lane_off[t], S.tile[t] + (u32)(it * L + l) * S.step[t], 2))   /* streaming */;
     }
     // Inputs of iteration it.  (Buffer loads: base and iteration are scalar operands, the lane's offset one register.)
-    __device__ __forceinline__ void load_x(__amdgpu_buffer_rsrc_t img, int slot, int it, int lane) {
+    __device__ __forceinline__ void load_x(const PanelImg& I, int slot, int it) {
 #pragma unroll
         for (int k = 0; k < kWSteps<WD>; k++)
 #pragma unroll
             for (int h = 0; h < NC / 8; h++)
-                x[slot][k * (NC / 8) + h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(img, lane * 16 + h * 1024, (it * kWSteps<WD> + k) * kWideStepBytes, 0));
+                x[slot][k * (NC / 8) + h] =
+                    __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(I.base, I.lane_off, (it * kWSteps<WD> + k) * I.step + h * (I.step >> 1), 0));
     }
 };
 
@@ -105,11 +132,10 @@ __device__ __forceinline__ u32x4 i8_to_bf16(u32 wa, u32 wb) {
     return u32x4{pack((float)(int)(int8_t)wa, (float)(int)(int8_t)(wa >> 8)), pack((float)(int)(int8_t)(wa >> 16), (float)((int)wa >> 24)),
                  pack((float)(int)(int8_t)wb, (float)(int)(int8_t)(wb >> 8)), pack((float)(int)(int8_t)(wb >> 16), (float)((int)wb >> 24))};
 }
-// Eight int4 codes n as the bf16 numbers 128 + n (0x4300 | n), in column order.
+// Eight int4 codes n (tiled order) as the bf16 numbers 128 + n (0x4300 | n), in column order.
 __device__ __forceinline__ u32x4 i4_to_bf16(u32 w) {
-    const u32 e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;   // codes 0,2,4,6 / 1,3,5,7 as bytes
-    return u32x4{__builtin_amdgcn_perm(o, e, 0x0c040c00u) | 0x43004300u, __builtin_amdgcn_perm(o, e, 0x0c050c01u) | 0x43004300u,
-                 __builtin_amdgcn_perm(o, e, 0x0c060c02u) | 0x43004300u, __builtin_amdgcn_perm(o, e, 0x0c070c03u) | 0x43004300u};
+    return u32x4{(w & 0x000F000Fu) | 0x43004300u, ((w >> 4) & 0x000F000Fu) | 0x43004300u, ((w >> 8) & 0x000F000Fu) | 0x43004300u,
+                 ((w >> 12) & 0x000F000Fu) | 0x43004300u};
 }
 
 // acc[t] += (inputs of iteration it) x (weights of tile t).
@@ -117,35 +143,37 @@ __device__ __forceinline__ u32x4 i4_to_bf16(u32 w) {
 // int4 group-128: an iteration is one group; with the codes n as 128 + n the four k-steps yield
 // d = sum (128 + n) x, and with X = sum x of the group (the same instruction with a weight operand of ones)
 //     sum s (n - z) x  =  s (d - (128 + z) X).
-// sz: this panel's (scale | zero << 16) words in LDS, [group][16 T rows].
-template <int WD, int NC, int T>
-__device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, int slot, int it, const lds_u32* sz, int lane, mfma_f4 (&acc)[T]) {
+// Where a wave finds a panel's int4 scales and zeros.
+struct PanelSz {
+    const lds_u32* lds;          // (scale | zero << 16) words, [group][16 T rows]; null: too many of them, read in place
+    const PMat* M; int p0, r1;
+};
+template <int WD, int NC, int T, class Refill>
+__device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, int slot, int xslot, int it, const PanelSz& sz, int lane, mfma_f4 (&acc)[T], Refill&& refill) {
     constexpr int NP = NC / 8;
-    if constexpr (WD == W_BF16) {
+    mfma_f4 X = {0.f, 0.f, 0.f, 0.f};
+    const lds_u32* szp = nullptr;
+    if constexpr (WD == W_INT4) {
+        const u32x4 ones{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 #pragma unroll
-        for (int k = 0; k < 2; k++)
+        for (int i = 0; i < 4 * NP; i++) X = mfma16(R.x[xslot][i], ones, X);
+        szp = sz.lds + (size_t)it * (16 * T) + (lane & 15);
+    }
 #pragma unroll
-            for (int h = 0; h < NP; h++)
+    for (int t = 0; t < T; t++) {
+        if constexpr (WD == W_BF16) {
 #pragma unroll
-                for (int t = 0; t < T; t++) acc[t] = mfma16(R.x[slot][k * NP + h], R.w[slot][t][k], acc[t]);
-    } else if constexpr (WD == W_INT8) {
+            for (int k = 0; k < 2; k++)
 #pragma unroll
-        for (int t = 0; t < T; t++) {
+                for (int h = 0; h < NP; h++) acc[t] = mfma16(R.x[xslot][k * NP + h], R.w[slot][t][k], acc[t]);
+        } else if constexpr (WD == W_INT8) {
             const u32x4 w = R.w[slot][t][0];
             const u32x4 b0 = i8_to_bf16(w.x, w.y), b1 = i8_to_bf16(w.z, w.w);
 #pragma unroll
-            for (int h = 0; h < NP; h++) acc[t] = mfma16(R.x[slot][h], b0, acc[t]);
+            for (int h = 0; h < NP; h++) acc[t] = mfma16(R.x[xslot][h], b0, acc[t]);
 #pragma unroll
-            for (int h = 0; h < NP; h++) acc[t] = mfma16(R.x[slot][NP + h], b1, acc[t]);
-        }
-    } else {
-        const u32x4 ones{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-        mfma_f4 X = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 4 * NP; i++) X = mfma16(R.x[slot][i], ones, X);
-        const lds_u32* szp = sz + (size_t)it * (16 * T) + (lane & 15);
-#pragma unroll
-        for (int t = 0; t < T; t++) {
+            for (int h = 0; h < NP; h++) acc[t] = mfma16(R.x[xslot][NP + h], b1, acc[t]);
+        } else {
             const u32x4 w = R.w[slot][t][0];
             const u32 ww[4] = {w.x, w.y, w.z, w.w};
             mfma_f4 d = {0.f, 0.f, 0.f, 0.f};
@@ -153,13 +181,19 @@ __device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, in
             for (int q = 0; q < 4; q++) {
                 const u32x4 b = i4_to_bf16(ww[q]);
 #pragma unroll
-                for (int h = 0; h < NP; h++) d = mfma16(R.x[slot][q * NP + h], b, d);
+                for (int h = 0; h < NP; h++) d = mfma16(R.x[xslot][q * NP + h], b, d);
             }
-            const u32 v = szp[16 * t];
+            u32 v;
+            if (T > 2 || sz.lds) v = szp[16 * t];
+            else {   // (only rows much longer than their number: one or two tiles)
+                const size_t e = (size_t)max(min(sz.p0 + 16 * t + (lane & 15), sz.r1 - 1), 0) * (sz.M->k / 128) + it;
+                v = (u32)as_global(sz.M->s)[e] | ((u32)as_global(sz.M->z)[e] << 16);
+            }
             const float s = f16_to_f((f16_t)(v & 0xFFFFu)), zp = 128.f + f16_to_f((f16_t)(v >> 16));
 #pragma unroll
             for (int i = 0; i < 4; i++) acc[t][i] = fmaf(s, fmaf(-zp, X[i], d[i]), acc[t][i]);
         }
+        refill(t);
     }
 }
 
@@ -207,61 +241,52 @@ struct PanelScales {
     }
 };
 
-// A wave's iterations of a panel: every eighth one (the workgroup's waves together read contiguous
-// pieces of each row), starting at a place that differs from workgroup to workgroup (rows are a power
-// of two apart at the usual widths: in step, all workgroups would read from a few memory channels).
+// A wave's iterations of a panel: every eighth one, so that the workgroup's waves together read contiguous pieces of
+// each tile (8B bf16 x 8, int4 x 16, us a pass: 1729, 1591; each wave a contiguous eighth of K: 1730, 1598).
 struct WaveIters {
-    int n, first, rot;
+    int n, first;
     __device__ __forceinline__ static WaveIters of(int ni, int wave) {
-        WaveIters I;
-        I.n = (ni - wave + kWideWaves - 1) / kWideWaves;
-        I.first = I.n > 0 ? wave : 0;
-        I.rot = (int)(((u32)blockIdx.x * (u32)I.n >> 8) % (u32)max(I.n, 1));
-        return I;
+        const int n = (ni - wave + kWideWaves - 1) / kWideWaves;
+        return WaveIters{n, n > 0 ? wave : 0};
     }
     // iteration number i (in the wave's order) as an iteration of the panel; past the end: the last one again
-    __device__ __forceinline__ int at(int i) const {
-        int c = min(i, n - 1) + rot;
-        if (c >= n) c -= n;
-        return max(c, 0) * kWideWaves + first;
-    }
+    __device__ __forceinline__ int at(int i) const { return max(min(i, n - 1), 0) * kWideWaves + first; }
 };
 
-// The wave's iterations of a panel; the ring's first D slots of weights and inputs have been
-// requested (slots past the end hold repeats).
+// The wave's iterations of a panel; the first D slots of weights and DX of inputs have been requested
+// (slots past the end hold repeats).
 template <int WD, int NC, int T>
-__device__ __forceinline__ void panel_run(const PanelSrc<WD, T>& S, PanelRing<WD, NC, T>& R, __amdgpu_buffer_rsrc_t img, const WaveIters& I, const lds_u32* sz, int lane,
+__device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC, T>& R, const PanelImg& img, const WaveIters& I, const PanelSz& sz, int lane,
                                           mfma_f4 (&acc)[T]) {
-    constexpr int D = PanelRing<WD, NC, T>::D;
+    constexpr int D = PanelRing<WD, NC, T>::D, DX = PanelRing<WD, NC, T>::DX;
+    static_assert(DX % D == 0, "slots");
+    const auto keep = [](int) {};
     int i = 0;
-    for (; i + 2 * D <= I.n; i += D) {
+    for (; i + DX + D <= I.n; i += DX) {
 #pragma unroll
-        for (int j = 0; j < D; j++) {
-            panel_multiply<WD, NC, T>(R, j, I.at(i + j), sz, lane, acc);
-            __builtin_amdgcn_sched_barrier(0);
-            const int nx = I.at(i + D + j);
-            R.load_w(S, j, nx, lane);
-            R.load_x(img, j, nx, lane);
+        for (int j = 0; j < DX; j++) {
+            const int nw = I.at(i + j + D), nx = I.at(i + j + DX);
+            // a tile's weights are requested again right behind its products
+            panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz, lane, acc, [&](int t) {
+                __builtin_amdgcn_sched_barrier(0);
+                R.load_wt(S, j % D, nw, t);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            R.load_x(img, j, nx);   // (past the end: the last one again)
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // fewer than 2 D iterations left: slot j holds iteration i + j
+    // fewer than DX + D iterations left
 #pragma unroll
-    for (int j = 0; j < D; j++) {
+    for (int j = 0; j < DX + D - 1; j++) {
         if (i + j < I.n) {
-            panel_multiply<WD, NC, T>(R, j, I.at(i + j), sz, lane, acc);
+            panel_multiply<WD, NC, T>(R, j % D, j % DX, I.at(i + j), sz, lane, acc, keep);
             __builtin_amdgcn_sched_barrier(0);
-            if (i + D + j < I.n) {
-                const int nx = I.at(i + D + j);
-                R.load_w(S, j, nx, lane);
-                R.load_x(img, j, nx, lane);
-            }
+            if (i + j + D < I.n) R.load_w(S, j % D, I.at(i + j + D));
+            if (i + j + DX < I.n) R.load_x(img, j % DX, I.at(i + j + DX));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-#pragma unroll
-    for (int j = 0; j < D - 1; j++)
-        if (i + D + j < I.n) panel_multiply<WD, NC, T>(R, j, I.at(i + D + j), sz, lane, acc);
 }
 
 // A wave's partial tiles into LDS: [wave][tile][sequence % 4][lane].

@@ -38,16 +38,58 @@ constexpr int kSpinLimit = 1 << 16;
 
 enum { W_BF16 = 0, W_INT8 = 1, W_INT4 = 2 };
 
-// A projection matrix in packed (device-private) row order.
+// A projection matrix in packed (device-private) row order.  Two layouts of the weights:
+//   row-major (tiled == 0), streamed row by row by the row-partitioned passes;
+//   tiled for the wide pass (tiled == workgroups of the grid): every workgroup's rows (whole groups of
+//   four, see cta_rows) are cut into tiles of 16 (the last one may be shorter), and a tile holds its rows'
+//   16-byte units column by column: unit 0 of all rows, unit 1 of all rows, ...  A matrix-core operand (16
+//   rows x 4 units) is then one contiguous kilobyte and a wave's whole share of a tile one stream.  Rows
+//   are padded with zero units to whole iterations of the wide pass.  int4 words hold code 2 p in
+//   nibble p and code 2 p + 1 in nibble p + 4, so that one mask yields two codes in the halves of a word.
+// Scales and zeros are row-major either way.
 struct PMat {
-    const uint8_t* w;   // rows of row_bytes each
+    const uint8_t* w;
     const f16_t* s;     // int8: [n]; int4: [n][k/128]
     const f16_t* z;     // int4: [n][k/128]
     int n, k;           // rows (outputs), columns (inputs)
     int wd;
-    __host__ __device__ size_t row_bytes() const { return wd == W_BF16 ? (size_t)k * 2 : wd == W_INT8 ? (size_t)k : (size_t)k / 2; }
+    int tiled;
+    __host__ __device__ static size_t row_bytes_of(int k, int wd, int tiled) {
+        if (!tiled) return wd == W_BF16 ? (size_t)k * 2 : wd == W_INT8 ? (size_t)k : (size_t)k / 2;
+        const size_t cols = wd == W_INT4 ? 128 : 64, pad = (k + cols - 1) / cols * cols;
+        return wd == W_BF16 ? pad * 2 : wd == W_INT8 ? pad : pad / 2;
+    }
+    __host__ __device__ size_t row_bytes() const { return row_bytes_of(k, wd, tiled); }
+    struct Rows { int r0, r1; };
+    // Rows of workgroup c of the grid (tiled layout).
+    __host__ __device__ Rows cta_rows(int c) const {
+        const u64 g = (u64)(n + 3) / 4;
+        const int r1 = 4 * (int)(g * (u64)(c + 1) / (u64)tiled);
+        return Rows{4 * (int)(g * (u64)c / (u64)tiled), r1 < n ? r1 : n};
+    }
+    // Byte offset of unit 0 of a row; consecutive units of the row are `stride` bytes apart.
+    __host__ __device__ size_t row_off(int row, size_t* stride) const {
+        if (!tiled) { *stride = 16; return (size_t)row * row_bytes(); }
+        const u64 g = (u64)(n + 3) / 4;
+        const Rows r = cta_rows((int)(((u64)(row / 4 + 1) * (u64)tiled - 1) / g));
+        const int t0 = r.r0 + (row - r.r0) / 16 * 16, nt = r.r1 - t0 < 16 ? r.r1 - t0 : 16;
+        *stride = (size_t)nt * 16;
+        return (size_t)t0 * row_bytes() + (size_t)(row - t0) * 16;
+    }
 };
-#define FF_PMAT_FIELDS(p) PMat{(p).w, (p).s, (p).z, (p).n, (p).k, (p).wd}
+#define FF_PMAT_FIELDS(p) PMat{(p).w, (p).s, (p).z, (p).n, (p).k, (p).wd, (p).tiled}
+// int4 codes of a canonical word (nibble i = code i) in the tiled layout's order.
+__host__ __device__ inline u32 i4_tiled_word(u32 w) {
+    u32 e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
+    e = (e | (e >> 4)) & 0x00FF00FFu; o = (o | (o >> 4)) & 0x00FF00FFu;
+    e = (e | (e >> 8)) & 0xFFFFu; o = (o | (o >> 8)) & 0xFFFFu;
+    return e | (o << 16);
+}
+__host__ __device__ inline u32 i4_canonical_word(u32 w) {
+    u32 r = 0;
+    for (int p = 0; p < 4; p++) r |= ((w >> (4 * p)) & 15u) << (8 * p) | ((w >> (16 + 4 * p)) & 15u) << (8 * p + 4);
+    return r;
+}
 
 struct PLayer {
     const bf16_t* g1;   // attention pre-norm gain
@@ -98,7 +140,7 @@ struct DevModel {
     u32* cx;  u32* cx2;  u32* cdelta;  u32* cattn_o;  u32* ch;
     // wide pass (ff_wide.h): exchange images and sums of squares, wring blocks (one per layer and one for the LM head,
     // or 1: reused by every layer); one epoch word per workgroup
-    uint8_t* wimg;  u32* wflag;  int wring;
+    uint8_t* wimg;  u32* wflag;  int wring, wbatch;   // wbatch: sequences the images have room for
     u32* stepctr;    // [0] fused launches executed so far on these buffers (skipped steps do not count); [1] sequences the last one served
     u32x2* tpart_m;  u32x2* tpart_l;  u32x2* tpart_o;
     int* status;

@@ -1,6 +1,6 @@
 // Per-operation baseline kernels (one launch per operation of the decode step) and the loaders.
 #pragma once
-#include "ff_kernels.h"
+#include "ff_wide.h"
 
 namespace ff {
 
@@ -101,6 +101,97 @@ __global__ void __launch_bounds__(kThreads) op_gemv(PMat W, const float* in, int
         op_gemv_body<WD, B>(W, src, batch, lds, epi);
     }
 }
+// The same on a tiled matrix (models for several sequences): a workgroup multiplies the tiles of its own
+// rows, its four waves taking every fourth block of four units; lane (r, g) works on unit g of row r on the
+// vector ALU, the inputs come from LDS (as much of K at a time as fits), the lanes g and the waves are added at the end.
+constexpr int kOpTileBlocks = 4;   // 1 KB blocks a wave has in flight
+template <int WD, int B>
+__global__ void __launch_bounds__(kThreads) op_gemv_tiled(PMat W, const float* in, int in_stride, float* out, int batch, int epi_kind, const int* skip_tokens) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    constexpr int EPU = WTraits<WD>::EPU, COLS = 4 * EPU;   // columns of a block
+    float* xs = (float*)lds;                                // [B][seg]
+    float* red = (float*)(lds + kLdsActBytes);              // [wave][16 rows][B]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4;
+    const int padk = (int)(W.row_bytes() / 16) * EPU;
+    const int seg = min(padk, kLdsActBytes / 4 / B / COLS * COLS), nseg = (padk + seg - 1) / seg;
+    const PMat::Rows rr = W.cta_rows(blockIdx.x);
+    for (int t0 = rr.r0; t0 < rr.r1; t0 += 16) {
+        const int nt = min(rr.r1 - t0, 16), row = t0 + min(lane & 15, nt - 1);
+        size_t stride;
+        const uint8_t* wp = W.w + W.row_off(row, &stride);
+        float acc[B];
+#pragma unroll
+        for (int b = 0; b < B; b++) acc[b] = 0.f;
+        for (int s = 0; s < nseg; s++) {
+            const int k0 = s * seg, nk = min(seg, padk - k0);
+            if (nseg > 1 || t0 == rr.r0) {
+                __syncthreads();
+                for (int b = 0; b < batch; b++)
+                    for (int i = threadIdx.x; i < nk; i += kThreads) xs[b * seg + i] = k0 + i < W.k ? as_global(in)[(size_t)b * in_stride + k0 + i] : 0.f;
+                __syncthreads();
+            }
+            const int j0 = k0 / COLS, nj = nk / COLS;
+            for (int j = wave; j < nj; j += kWaves * kOpTileBlocks) {
+                u32x4 w[kOpTileBlocks];
+#pragma unroll
+                for (int u = 0; u < kOpTileBlocks; u++) w[u] = ldg_stream(wp + (size_t)(4 * (j0 + min(j + u * kWaves, nj - 1)) + g) * stride);
+#pragma unroll
+                for (int u = 0; u < kOpTileBlocks; u++) {
+                    const int jj = j + u * kWaves;
+                    if (jj >= nj) break;
+                    float sc = 1.f, zp = 0.f;
+                    if constexpr (WD == W_INT4) {
+                        const size_t e = (size_t)row * (W.k / 128) + j0 + jj;
+                        sc = f16_to_f(as_global(W.s)[e]); zp = f16_to_f(as_global(W.z)[e]);
+                    }
+#pragma unroll
+                    for (int b = 0; b < B; b++) {
+                        const float4* x = (const float4*)(xs + min(b, batch - 1) * seg + jj * COLS + g * EPU);
+                        if constexpr (WD == W_BF16) acc[b] = dot_bf16(w[u], x[0], x[1], acc[b]);
+                        else if constexpr (WD == W_INT8)
+                            acc[b] = dot_i8x4(w[u].w, x[3], dot_i8x4(w[u].z, x[2], dot_i8x4(w[u].y, x[1], dot_i8x4(w[u].x, x[0], acc[b]))));
+                        else {   // (code - zero is exact; the sum of the group's share is scaled)
+                            const u32 ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+                            float t = 0.f;
+#pragma unroll
+                            for (int q = 0; q < 4; q++) {
+                                const u32 c = i4_canonical_word(ww[q]);
+                                const float4 x0 = x[2 * q], x1 = x[2 * q + 1];
+                                t = fmaf((float)(c & 15u) - zp, x0.x, t); t = fmaf((float)((c >> 4) & 15u) - zp, x0.y, t);
+                                t = fmaf((float)((c >> 8) & 15u) - zp, x0.z, t); t = fmaf((float)((c >> 12) & 15u) - zp, x0.w, t);
+                                t = fmaf((float)((c >> 16) & 15u) - zp, x1.x, t); t = fmaf((float)((c >> 20) & 15u) - zp, x1.y, t);
+                                t = fmaf((float)((c >> 24) & 15u) - zp, x1.z, t); t = fmaf((float)(c >> 28) - zp, x1.w, t);
+                            }
+                            acc[b] = fmaf(sc, t, acc[b]);
+                        }
+                    }
+                }
+            }
+        }
+        if constexpr (WD == W_INT8) {
+            const float rs = f16_to_f(as_global(W.s)[row]);
+#pragma unroll
+            for (int b = 0; b < B; b++) acc[b] *= rs;
+        }
+#pragma unroll
+        for (int b = 0; b < B; b++) {
+            acc[b] += __shfl_xor(acc[b], 16);
+            acc[b] += __shfl_xor(acc[b], 32);
+            if (lane < 16) red[(wave * 16 + lane) * B + b] = acc[b];
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < nt * batch; i += kThreads) {
+            const int r = i % nt, b = i / nt;
+            float v = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; w++) v += red[(w * 16 + r) * B + b];
+            float* o = out + (size_t)b * W.n + t0 + r;
+            if (epi_kind == EPI_RESIDUAL) *o += v;
+            else if (!skip_tokens || skip_tokens[b] != kTokenSkip) *o = v;
+        }
+        __syncthreads();
+    }
+}
 // Debug: the matrix-core GEMV of the fused kernel (gemv_run_quad on the split-bf16 staged input) as
 // a kernel of its own on plain fp32 input rows; out[b][row] in packed row order.  The projection
 // must fit one K segment.
@@ -128,6 +219,29 @@ __global__ void __launch_bounds__(kThreads) k_debug_gemv_quad(PMat W, const floa
     __syncthreads();
     EpiStore epi{out, W.n};
     gemv_run_quad<WD, B>(S, ring, xs, myacc, batch, lane, epi);
+}
+// Debug: one projection of the wide pass on its own, out[n][row] in packed row order (rows of out: M.V = W.n floats), input image in img.
+template <int WD, int NC>
+__global__ void __launch_bounds__(kWideThreads) wide_gemv_kernel(DevModel M, DevKV KV, PMat W, const uint8_t* img, float* out, int batch, int ncta) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int* pos_lds = (int*)(lds + kWideIntOff);
+    if (threadIdx.x < kMaxBatchWide) pos_lds[threadIdx.x] = 0;
+    const UDiv n_ctas = UDiv::of((u32)ncta);
+    WideSync sync{nullptr, ncta, false, nullptr, 0u};
+    const WideCtx C{M, KV, pos_lds, nullptr, out, batch, 0, PH_LM, 0u, WideImg{nullptr, 0, 1, false}, nullptr, nullptr, RowRange{0, 0}};
+    wide_project_any<WD, NC>(W, img, nullptr, nullptr, 0u, sync, C, lds, n_ctas, wave, lane, 0);
+}
+// Its input: rows of fp32 [img.batch][K] as a wide image of cols columns (those behind K: zero).
+__global__ void __launch_bounds__(256) wide_image_kernel(WideImg img, const float* in, int K, int cols) {
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < cols * img.batch; i += gridDim.x * 256) {
+        const int n = i / cols, c = i - n * cols;
+        u32 hi, lo;
+        split_bf16x2(c < K ? as_global(in)[(size_t)n * K + c] : 0.f, 0.f, hi, lo);
+        *as_global((uint16_t*)img.at(n, 0, c)) = (uint16_t)hi;
+        *as_global((uint16_t*)img.at(n, 1, c)) = (uint16_t)lo;
+    }
 }
 // Debug: rows of a raw projection output y[b][packed rows] in canonical order (same maps as k_dequant).
 __global__ void k_unmap_rows(const float* y, int y_stride, float* out, int n_can, int map, int parity, int row_off, int hd, int batch, GuPerm perm) {
@@ -205,6 +319,41 @@ __global__ void __launch_bounds__(kThreads) k_repack_rows(uint8_t* dst, const ui
         }
     }
 }
+// Weight rows of part [row0, row0 + n_rows) of a tiled matrix (see PMat), one tile per block (grid: workgroups
+// of the decode grid x tiles): unit u of packed row r comes from the source row of r - row0 by the same maps.
+struct RowMap {
+    int mode, hd; GuPerm perm;
+    // canonical row of packed row r of a part; *second: it is a row of the second source (interleaved mode)
+    __device__ __forceinline__ int source(int r, bool* second) const {
+        *second = false;
+        if (mode == REPACK_ROPE) { const int head = r / hd, within = r % hd; return head * hd + within / 2 + (within & 1) * (hd / 2); }
+        if (mode == REPACK_INTERLEAVE) { *second = (r & 1) != 0; return perm.unit_of_pair(r / 2); }
+        return r;
+    }
+};
+template <class F>
+__device__ __forceinline__ void for_tile_units(const PMat& W, int row0, int n_rows, F&& f) {   // f(r - row0, unit, destination)
+    const PMat::Rows rr = W.cta_rows(blockIdx.x);
+    const int t0 = rr.r0 + 16 * (int)blockIdx.y;
+    if (t0 >= rr.r1 || t0 + 16 <= row0 || t0 >= row0 + n_rows) return;
+    const int nt = min(rr.r1 - t0, 16), units = (int)(W.row_bytes() / 16);
+    u32x4* dst = (u32x4*)(W.w + (size_t)t0 * W.row_bytes());
+    for (int i = threadIdx.x; i < units * nt; i += kThreads) {
+        const int u = i / nt, r = t0 + i - u * nt - row0;
+        if (r >= 0 && r < n_rows) f(r, u, dst + i);
+    }
+}
+__global__ void __launch_bounds__(kThreads) k_repack_tiles(PMat W, int row0, int n_rows, const uint8_t* src_a, const uint8_t* src_b, RowMap map) {
+    const size_t rb = PMat::row_bytes_of(W.k, W.wd, 0);
+    for_tile_units(W, row0, n_rows, [&](int r, int u, u32x4* dst) {
+        bool second;
+        const int sr = map.source(r, &second);
+        u32x4 v = {0u, 0u, 0u, 0u};   // (units behind the row's end)
+        if ((size_t)(u + 1) * 16 <= rb) v = *(const u32x4*)((second ? src_b : src_a) + (size_t)sr * rb + (size_t)u * 16);
+        if (W.wd == W_INT4) v = u32x4{i4_tiled_word(v.x), i4_tiled_word(v.y), i4_tiled_word(v.z), i4_tiled_word(v.w)};
+        *dst = v;
+    });
+}
 __global__ void k_rope_table(float2* rope, int max_ctx, int hd, double theta) {
     int half = hd / 2;
     int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -237,14 +386,17 @@ __global__ void k_dequant(PMat W, float* out, int n_can, int map, int parity, in
         else if (map == 2) pr = 2 * perm.pair_of_unit(r) + parity;
         else pr = r;
         pr += row_off;
-        const uint8_t* row = W.w + (size_t)pr * W.row_bytes();
+        const int epu = W.wd == W_BF16 ? 8 : W.wd == W_INT8 ? 16 : 32, e = c % epu;   // element of its 16-byte unit
+        size_t stride;
+        const size_t off = W.row_off(pr, &stride);
+        const uint8_t* unit = W.w + off + (size_t)(c / epu) * stride;
         float v;
-        if (W.wd == W_BF16) v = bf_to_f(((const bf16_t*)row)[c]);
-        else if (W.wd == W_INT8) v = (float)(int)((const int8_t*)row)[c] * f16_to_f(W.s[pr]);
+        if (W.wd == W_BF16) v = bf_to_f(((const bf16_t*)unit)[e]);
+        else if (W.wd == W_INT8) v = (float)(int)((const int8_t*)unit)[e] * f16_to_f(W.s[pr]);
         else {
             int ng = W.k / 128;
-            uint8_t byte = row[c >> 1];
-            int code = (c & 1) ? (byte >> 4) : (byte & 15);
+            const u32 word = ((const u32*)unit)[e / 8];
+            const int code = (int)((W.tiled ? i4_canonical_word(word) : word) >> (4 * (e % 8))) & 15;
             v = ((float)code - f16_to_f(W.z[(size_t)pr * ng + c / 128])) * f16_to_f(W.s[(size_t)pr * ng + c / 128]);
         }
         out[i] = v;
@@ -327,6 +479,45 @@ __global__ void __launch_bounds__(kThreads) k_synth_rows(uint8_t* dst_w, f16_t* 
             for (int g = threadIdx.x; g < ng; g += kThreads) {
                 dst_s[(size_t)r * ng + g] = synth_scale_f16(Mt->key_s, (u64)sr * ng + g, Mt->c_scale);
                 const _Float16 z = (_Float16)(float)synth_uniform_int(Mt->key_z, (u64)sr * ng + g, 0, 15);
+                f16_t zb;
+                __builtin_memcpy(&zb, &z, 2);
+                dst_z[(size_t)r * ng + g] = zb;
+            }
+        }
+    }
+}
+// The same for a tiled matrix: weights by 16-byte units (grid as k_repack_tiles) ...
+__global__ void __launch_bounds__(kThreads) k_synth_tiles(PMat W, int row0, int n_rows, SynthMat A, SynthMat B, RowMap map, float w_scale) {
+    for_tile_units(W, row0, n_rows, [&](int r, int u, u32x4* dst) {
+        bool second;
+        const int sr = map.source(r, &second), k = W.k;
+        const u32 key = second ? B.key_w : A.key_w;
+        const u64 e0 = (u64)sr * (u64)k;
+        u32 v[4] = {0u, 0u, 0u, 0u};
+        const int epw = W.wd == W_BF16 ? 2 : W.wd == W_INT8 ? 4 : 8;   // elements of a word
+        for (int i = 0; i < 4; i++)
+            for (int j = 0; j < epw; j++) {
+                const int c = (u * 4 + i) * epw + j;
+                if (c >= k) break;
+                if (W.wd == W_BF16) v[i] |= (u32)synth_normal_bf16(key, e0 + c, w_scale, 0.f) << (16 * j);
+                else if (W.wd == W_INT8) v[i] |= (u32)(uint8_t)(int8_t)synth_uniform_int(key, e0 + c, -127, 127) << (8 * j);
+                else v[i] |= (u32)synth_uniform_int(key, e0 + c, 0, 15) << (4 * j);
+            }
+        if (W.wd == W_INT4) for (int i = 0; i < 4; i++) v[i] = i4_tiled_word(v[i]);
+        *dst = u32x4{v[0], v[1], v[2], v[3]};
+    });
+}
+// ... and the scales and zeros of rows [0, n_rows) of a part (row-major in either layout).
+__global__ void __launch_bounds__(kThreads) k_synth_scales(f16_t* dst_s, f16_t* dst_z, int n_rows, int wd, SynthMat A, SynthMat B, RowMap map) {
+    for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
+        bool second;
+        const int sr = map.source(r, &second);
+        const SynthMat& Mt = second ? B : A;
+        const int ng = wd == W_INT4 ? Mt.k / 128 : 1;
+        for (int g = threadIdx.x; g < ng; g += kThreads) {
+            dst_s[(size_t)r * ng + g] = synth_scale_f16(Mt.key_s, (u64)sr * ng + g, Mt.c_scale);
+            if (wd == W_INT4) {
+                const _Float16 z = (_Float16)(float)synth_uniform_int(Mt.key_z, (u64)sr * ng + g, 0, 15);
                 f16_t zb;
                 __builtin_memcpy(&zb, &z, 2);
                 dst_z[(size_t)r * ng + g] = zb;

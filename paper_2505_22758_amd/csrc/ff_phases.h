@@ -156,18 +156,20 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, u32& hi, u32& lo)
     hi = pack_bf16(a, b);
     lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
-// Wide pass (see ff_wide.h): a global image of a projection's inputs in the matrix cores' operand order.
-// A k-step (32 columns) is kWideStepBytes: lane (row, g) of the operand finds its 16 bytes (8 columns) at
-// (16 g + row) * 16 of the heads' and, 1 KB further, of the remainders' kilobyte; with up to eight
-// sequences (half) rows 0..7 are the heads and rows 8..15 the remainders, both in the first kilobyte.
+// Wide pass (see ff_wide.h): a global image of a projection's inputs in the matrix cores' operand order,
+// for `batch` sequences.  A k-step (32 columns) takes wide_step_bytes(batch): 16-byte pieces (8 columns of one
+// sequence) for each of the operand's four lane groups g.  Up to eight sequences (half): group by group the
+// heads of all sequences, then their remainders (operand rows 0..7 and 8..15); more: the heads of all
+// groups, then the remainders of all groups (an operand each).
 // Which 8 columns lane group g multiplies in a k-step follows from the weights it loads, 16 bytes per lane:
 // 8 << e columns (e = 0 bf16, 1 int8, 2 int4) used up in 1 << e k-steps.
-constexpr int kWideStepBytes = 2048;
+__host__ __device__ __forceinline__ int wide_step_bytes(int batch) { return 128 * batch; }
 struct WideImg {
-    uint8_t* p; int e; bool half;
+    uint8_t* p; int e; int batch; bool half;
     __device__ __forceinline__ uint8_t* at(int n, int plane, int col) const {
-        const int j = col >> 3, unit = j >> e, step = ((unit >> 2) << e) + (j & ((1 << e) - 1));
-        return p + (size_t)step * kWideStepBytes + (half ? ((unit & 3) * 16 + n + 8 * plane) * 16 : plane * 1024 + ((unit & 3) * 16 + n) * 16) + (col & 7) * 2;
+        const int j = col >> 3, unit = j >> e, step = ((unit >> 2) << e) + (j & ((1 << e) - 1)), g = unit & 3;
+        const int piece = half ? (2 * g + plane) * batch + n : (4 * plane + g) * batch + n;
+        return p + (size_t)step * wide_step_bytes(batch) + (piece * 16 + (col & 7) * 2);
     }
 };
 

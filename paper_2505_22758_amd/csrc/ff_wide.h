@@ -24,9 +24,10 @@
 // epochs (an image is rewritten only by workgroups that have waited for an epoch which every
 // reader of the old contents published after its last read).
 // Queries, keys, values and attention partials keep their tagged 8-byte format.
-// Measured against the form before it (four waves, inputs copied through LDS once per 2048 columns, one acquire fence
-// per wait), us per step of an 8-layer block: 8B bf16 x 8 1127 -> 1003, int8 x 11 992 -> 936, int4 x 16 1628 -> 978,
-// 70B bf16 x 16 3283 -> 3098.  What bounds it: the weight stream (64-byte pieces of 16 rows per load).
+// Measured us per step of an 8-layer block, before (four waves, images copied through LDS, row-major weights) / with
+// this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 865, int8 x 11 992 / 936 / 780, int4 x 16 1628 / 978 /
+// 796, 70B bf16 x 16 3283 / 3098 / 2715; against the row-partitioned pass: bf16 x 2 865 -> 788, int4 x 4 1044 -> 595, int8 x 4
+// 875 -> 597.  What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
 #pragma once
 #include "ff_dense.h"
 
@@ -39,6 +40,7 @@ constexpr int kWideResOff = kWideRopeOff + kMaxBatchWide * 64 * 8;     // residu
 constexpr int kWideResRows = 32;
 constexpr int kWideRmsOff = kWideResOff + kMaxBatchWide * kWideResRows * 4;   // sums of squares: [wave][sequence]
 constexpr int kWideIntOff = kWideRmsOff + kWideWaves * kMaxBatchWide * 4;     // positions, attention shares, epoch verdicts, arrival counter, vote slots
+constexpr int kWideMaxCtas = 256;   // workgroups whose sums of squares a consumer gathers in one round (wide_project)
 constexpr int kWideLdsBytes = kWideIntOff + 1024;
 static_assert(kWideRedBytes + kWideSzBytes <= kWideAttnBytes && kWideLdsBytes <= 160 * 1024, "LDS layout of the wide pass");
 static_assert((2 * 32 * 8 + 32 * 8 * 128 + (8 + 2) * 128 + kWideWaves * 128) * 4 <= kWideAttnBytes, "attention state");
@@ -63,6 +65,7 @@ struct WideSync {
     // (Four flags per lane; workgroups beyond ncta do not exist.  The verdict slots alternate, so one barrier will do:
     // a slot is rewritten two waits later, behind the barrier of the wait in between.)
     __device__ __forceinline__ bool wait(u32 epoch, int wave, int lane) {
+        if (!flags) { __syncthreads(); return true; }   // (a projection on its own: nothing to wait for)
         par ^= 1u;
         if (wave == 0) {
             bool ok = false;
@@ -89,19 +92,20 @@ struct WideSync {
 // ---------------------------------------------------------------- images
 // Layer l's block of the exchange region: input images of the QKV (block L: LM head), gate/up, output and
 // down projections, and the workgroups' sums of squares of the first two ([tile of the workgroup's rows][workgroup][16]).
-__host__ __device__ inline size_t wide_img_bytes(int K, int wd) {
-    const int steps = wd == W_INT4 ? 4 : 2;
-    return (size_t)((K + 32 * steps - 1) / (32 * steps)) * steps * kWideStepBytes;
+__host__ __device__ inline int wide_img_cols(int K, int wd) {   // whole iterations
+    const int cols = wd == W_INT4 ? 128 : 64;
+    return (K + cols - 1) / cols * cols;
 }
+__host__ __device__ inline size_t wide_img_bytes(int K, int wd, int max_batch) { return (size_t)wide_img_cols(K, wd) / 32 * wide_step_bytes(max_batch); }
 struct WideLayout {
     size_t x1, x2, a, h, ss1, ss2, bytes;
-    __host__ __device__ static WideLayout of(int d, int qd, int F, int wd, int ncta) {
+    __host__ __device__ static WideLayout of(int d, int qd, int F, int wd, int max_batch, int ncta) {
         WideLayout W;
         size_t o = 0;
-        W.x1 = o; o += wide_img_bytes(d, wd);
-        W.x2 = o; o += wide_img_bytes(d, wd);
-        W.a = o; o += wide_img_bytes(qd, wd);
-        W.h = o; o += wide_img_bytes(F, wd);
+        W.x1 = o; o += wide_img_bytes(d, wd, max_batch);
+        W.x2 = o; o += wide_img_bytes(d, wd, max_batch);
+        W.a = o; o += wide_img_bytes(qd, wd, max_batch);
+        W.h = o; o += wide_img_bytes(F, wd, max_batch);
         W.ss1 = o; o += (size_t)2 * ncta * kMaxBatchWide * 4;
         W.ss2 = o; o += (size_t)2 * ncta * kMaxBatchWide * 4;
         W.bytes = (o + 255) & ~(size_t)255;
@@ -114,7 +118,6 @@ struct WideCtx {
     const DevModel& M; const DevKV& KV; const int* pos; const float2* rope; float* logits;
     int batch, layer, kind;
     u32 tag;               // of q, k, v
-    int pair0;             // unused rows in front of this projection (0)
     WideImg out;           // image this projection writes (SwiGLU, residual)
     float* ss;             // sums of squares beside it (residual)
     float* xres;           // LDS: residual rows of this workgroup
@@ -133,13 +136,13 @@ __device__ __forceinline__ float wide_residual(const WideCtx& C, int row, int n,
     xst2((float*)C.out.at(n, 1, row), __uint_as_float(l0), __uint_as_float(l1));
     return (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
 }
-__device__ __forceinline__ void wide_swiglu(const WideCtx& C, int pair, int n, float g, float u) {
-    const float h = g / (1.0f + expf(-g)) * u;
+// Packed pair q of a tiled gate/up matrix is FFN unit q; a quad of rows gives the neighbouring units f, f + 1 (f even).
+__device__ __forceinline__ void wide_swiglu(const WideCtx& C, int f, int n, const f32x4& c, bool two) {
+    const float h0 = c.x / (1.0f + expf(-c.x)) * c.y, h1 = two ? c.z / (1.0f + expf(-c.z)) * c.w : 0.f;
     u32 hi, lo;
-    split_bf16x2(h, 0.f, hi, lo);
-    const int f = C.M.gu.unit_of_pair(pair);
-    __hip_atomic_store(as_global((uint16_t*)C.out.at(n, 0, f)), (uint16_t)hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(as_global((uint16_t*)C.out.at(n, 1, f)), (uint16_t)lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    split_bf16x2(h0, h1, hi, lo);
+    xst_u32((u32*)C.out.at(n, 0, f), hi);   // (a missing second unit is padding, zero in the image)
+    xst_u32((u32*)C.out.at(n, 1, f), lo);
 }
 __device__ __forceinline__ void wide_epilogue(const WideCtx& C, int row, int n, const f32x4& c, int nv) {
     const int pair = row >> 1;
@@ -148,8 +151,7 @@ __device__ __forceinline__ void wide_epilogue(const WideCtx& C, int row, int n, 
         e(pair, n, c.x, c.y);
         if (nv > 2) e(pair + 1, n, c.z, c.w);
     } else if (C.kind == PH_GU) {
-        wide_swiglu(C, pair, n, c.x, c.y);
-        if (nv > 2) wide_swiglu(C, pair + 1, n, c.z, c.w);
+        wide_swiglu(C, pair, n, c, nv > 2);
     } else if (C.pos[n] >= 0) {   // LM head (no logits for a sequence that sits the step out)
         FF_GLOBAL float* y = as_global(C.logits + (size_t)n * C.M.V + row);
         if (nv == 4 && (C.M.V & 3) == 0 && ((uintptr_t)C.logits & 15) == 0) *(FF_GLOBAL f32x4*)y = c;
@@ -187,8 +189,9 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     const int q = lane >> 4, seq = lane & 15;
     constexpr int D = PanelRing<WD, NC, T>::D;
     constexpr int kSzStride = kWideSzBytes / 8;   // (words) two panels' scales: one being multiplied, one being filled
+    const bool sz_fits = T > 2 || (W.k / 128) * 16 * T <= (npanels > 1 ? kSzStride : 2 * kSzStride);   // (long rows: the host checks the wider panels)
     PanelRing<WD, NC, T> R;
-    PanelSrc<WD, T> S;
+    PanelSrc<T> S;
     u32x2 pre = {0u, 0u}, gpre = {0u, 0u};
     auto prows = [&](int p) { return min(16 * T, rr.r1 - (rr.r0 + 16 * T * p)); };   // rows of panel p (<= 0 for a workgroup without rows)
     auto item_row = [&](int p) { return rr.r0 + 16 * (T * p + wave) + 4 * q; };      // first row of the item this thread finishes
@@ -197,13 +200,13 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         const int p0 = min(rr.r0 + 16 * T * p, W.n - 1), nr = prows(p);
         if constexpr (WD == W_INT8) pre = *as_global((const u32x2*)(W.s + (min(item_row(p), W.n - 1) & ~3)));   // row scales of the item
         PanelScales<T> sc;
-        if constexpr (WD == W_INT4) sc.load(W, tid, p0, max(nr, 1), 0);
+        if constexpr (WD == W_INT4) if (sz_fits) sc.load(W, tid, p0, max(nr, 1), 0);
         __builtin_amdgcn_sched_barrier(0);
-        S = PanelSrc<WD, T>::make(W, p0, max(rr.r1, p0 + 1), lane);
+        S = PanelSrc<T>::make(W, p0, max(rr.r1, p0 + 1), lane);
 #pragma unroll
-        for (int j = 0; j < D; j++) R.load_w(S, j, I.at(j), lane);
+        for (int j = 0; j < D; j++) R.load_w(S, j, I.at(j));
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (WD == W_INT4) {
+        if constexpr (WD == W_INT4) if (sz_fits) {
             lds_u32* szp = sz + (p & 1) * kSzStride;
             sc.store(W, tid, p0, nr, 0, szp);
             for (int i0 = kSzItems * kWideThreads; i0 < PanelScales<T>::items(W, nr); i0 += kSzItems * kWideThreads) {
@@ -217,16 +220,17 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     timed(EV_PF_ISSUED);
     if (!sync.wait(epoch, wave, lane)) return false;
     timed(EV_SYNCED);
-    const __amdgpu_buffer_rsrc_t ximg = __builtin_amdgcn_make_buffer_rsrc((void*)img, 0, ni * kWSteps<WD> * kWideStepBytes, 0x00020000);
+    const PanelImg X = PanelImg::make<WD, NC>(img, W.k, C.batch, lane);
     for (int p = 0;; p++) {
         mfma_f4 acc[T];
 #pragma unroll
         for (int t = 0; t < T; t++) acc[t] = mfma_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < D; j++) R.load_x(ximg, j, I.at(j), lane);
+        for (int j = 0; j < PanelRing<WD, NC, T>::DX; j++) R.load_x(X, j, I.at(j));
         __builtin_amdgcn_sched_barrier(0);
-        panel_run<WD, NC, T>(S, R, ximg, I, sz + (p & 1) * kSzStride, lane, acc);
+        panel_run<WD, NC, T>(S, R, X, I, PanelSz{sz_fits ? sz + (p & 1) * kSzStride : (const lds_u32*)nullptr, &W, min(rr.r0 + 16 * T * p, W.n - 1), rr.r1}, lane, acc);
         timed(p == 0 ? 4 : 8);
+        if (p == 0 && C.M.dbg && C.layer == 1 && lane == 0) as_global(C.M.dbg)[(size_t)(4 * C.M.L + 1) * kEvSlots + (blockIdx.x * kWideWaves + wave) * 4 + (C.kind & 3)] = wall_clock64();
         __builtin_amdgcn_sched_barrier(0);
         if (p == 0 && ssin) {   // the workgroups' sums of squares, in a fixed order
             float ssv[16], t = 0.f;
@@ -268,6 +272,19 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     }
 }
 
+// Picks the panels: as few as possible, of equal size (the same for every workgroup: the largest share decides).
+template <int WD, int NC>
+__device__ __forceinline__ bool wide_project_any(const PMat& W, const uint8_t* img, const float* ssin, const bf16_t* gain, u32 epoch, WideSync& sync, const WideCtx& C,
+                                                 uint8_t* lds, const UDiv& n_ctas, int wave, int lane, int ph) {
+    const RowRange rr = wide_rows(W.n, n_ctas);
+    const int tiles = ((4 * (int)n_ctas.div((u32)(W.n + 3) / 4 + n_ctas.n - 1u)) + 15) >> 4;
+    const int np = (tiles + kPanelTiles - 1) / kPanelTiles, T = (tiles + np - 1) / np;
+#define FF_WIDE_T(t) case t: return wide_project<WD, NC, t>(W, rr, np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph);
+    switch (T) { FF_WIDE_T(1) FF_WIDE_T(2) FF_WIDE_T(3) FF_WIDE_T(4) FF_WIDE_T(5) FF_WIDE_T(6) FF_WIDE_T(7) }
+#undef FF_WIDE_T
+    return false;
+}
+
 // ---------------------------------------------------------------- the kernel
 // One launch = one step of up to NC sequences (phases as in fused_decode_kernel).
 // n_lm: 1 = the LM head runs here, 0 = launched separately.
@@ -302,14 +319,14 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     const UDiv n_ctas = UDiv::of((u32)ncta);
     WideSync sync{M.wflag, ncta, M.wring == 1, slots, 0u};
     WgVote vote{(u32*)(slots + 4), 0u};
-    const WideLayout WL = WideLayout::of(M.d, M.Hq * M.hd, M.F, WD, ncta);
+    const WideLayout WL = WideLayout::of(M.d, M.Hq * M.hd, M.F, WD, M.wbatch, ncta);
     constexpr int kImgE = WD == W_BF16 ? 0 : WD == W_INT8 ? 1 : 2;
     const RowRange own = wide_rows(M.d, n_ctas);
     auto block = [&](int l) { return M.wimg + (size_t)(M.wring == 1 ? 0 : l) * WL.bytes; };
-    auto image = [&](uint8_t* p) { return WideImg{p, kImgE, NC == 8}; };
+    auto image = [&](uint8_t* p) { return WideImg{p, kImgE, batch, NC == 8}; };
     auto timed = [&](int ph, int ev) { if (M.dbg && blockIdx.x == 0 && threadIdx.x == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64(); };
     __syncthreads();
-    WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, 0, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own};
+    WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own};
     // the step's embedding rows enter like the output of a projection onto zero
     if (16 * wave < kWideResRows) {
         const int row = own.r0 + 16 * wave + 4 * (lane >> 4), seq = lane & 15;
@@ -321,6 +338,19 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             v = wide_residual(C, row, seq, f32x4{bf_lo(e.x), bf_hi(e.x), bf_lo(e.y), bf_hi(e.y)}, g);
         }
         wide_store_ss(C.ss, ncta, wave, lane, v);
+    }
+    // Columns behind the end of a width that is not a whole number of iterations meet zero weights and have to be finite:
+    // the images' layout follows the batch, so their place holds what steps of other batches left.
+    {
+        const int widths[4] = {M.d, M.d, M.Hq * M.hd, M.F};
+        const size_t offs[4] = {WL.x1, WL.x2, WL.a, WL.h};
+        for (int l = blockIdx.x; l < M.wring; l += ncta)
+            for (int i = 0; i < 4; i++) {
+                const int pad = wide_img_cols(widths[i], WD) - widths[i];   // (even)
+                const WideImg im = image(M.wimg + (size_t)l * WL.bytes + offs[i]);
+                for (int e = threadIdx.x; e < pad * batch; e += kWideThreads)   // (batch x pad / 2 pairs of columns x 2 planes)
+                    xst_u32((u32*)im.at(e % batch, (e / batch) & 1, widths[i] + 2 * (e / batch >> 1)), 0u);
+            }
     }
     sync.arrive(ebase, lane);
     const int n_phases = 4 * M.L + lm_in_kernel;
@@ -341,8 +371,11 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         else if (C.kind == PH_O) {
             __syncthreads();   // the QKV epilogues have read their sums out of LDS
             const WideImg ai = image(blk + WL.a);
+            u64* aev = M.dbg && l == 1 ? M.dbg + (size_t)(4 * M.L + 1) * kEvSlots + (size_t)ncta * 32 + ((size_t)blockIdx.x * 5 + 4) * 8 : nullptr;
+            if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
             if (!attention_phase_tagged<kWideWaves, HD, G, 2>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
-                                                              n_ctas, vote, nullptr, &ai)) return;
+                                                              n_ctas, vote, aev, &ai)) return;
+            if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
             sync.arrive(e0 + 1u, lane);
             timed(ph, EV_ATT_END);
             __syncthreads();   // LDS goes back to the projections
@@ -359,15 +392,8 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             uint8_t* nb = block(l + 1);
             C.out = image(nb + WL.x1); C.ss = (float*)(nb + WL.ss1);
         } else { W = FF_PMAT_FIELDS(M.lm); img = blk + WL.x1; ssin = (const float*)(blk + WL.ss1); }
-        const RowRange rr = wide_rows(W.n, n_ctas);
-        // panels: as few as possible, of equal size (the same for every workgroup: the largest share decides)
-        const int tiles = ((4 * (int)n_ctas.div((u32)(W.n + 3) / 4 + n_ctas.n - 1u)) + 15) >> 4;
-        const int np = (tiles + kPanelTiles - 1) / kPanelTiles, T = (tiles + np - 1) / np;
-        bool ok = false;
         timed(ph, EV_H_START);
-#define FF_WIDE_T(t) case t: ok = wide_project<WD, NC, t>(W, rr, np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph); break;
-        switch (T) { FF_WIDE_T(1) FF_WIDE_T(2) FF_WIDE_T(3) FF_WIDE_T(4) FF_WIDE_T(5) FF_WIDE_T(6) FF_WIDE_T(7) }
-#undef FF_WIDE_T
+        const bool ok = wide_project_any<WD, NC>(W, img, ssin, gain, epoch, sync, C, lds, n_ctas, wave, lane, ph);
         timed(ph, EV_RUN_DONE);
         if (!ok) {
             if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);
@@ -376,6 +402,17 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         if (C.kind == PH_O) sync.arrive(e0 + 2u, lane);
         else if (C.kind == PH_GU) sync.arrive(e0 + 3u, lane);
         else if (C.kind == PH_DOWN) sync.arrive(e0 + 4u, lane);
+    }
+    if (!lm_in_kernel) {   // LM head launched separately: the final residual rows (the last down projection's epilogues are behind this workgroup's own epoch)
+        if (!sync.wait(ebase + 4u * (u32)M.L, wave, lane)) {
+            if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * n_phases);
+            return;
+        }
+        const int nrows = own.r1 - own.r0;
+        for (int i = threadIdx.x; i < batch * nrows; i += kWideThreads) {
+            const int b = i / nrows, r = i - b * nrows;
+            as_global(M.x)[(size_t)b * M.d + own.r0 + r] = xres[b * kWideResRows + r];
+        }
     }
     // workgroup 0 can only get here after every workgroup has taken part in every phase, i.e. has read the counter
     if (blockIdx.x == 0 && threadIdx.x == 0) {

@@ -44,7 +44,7 @@ int fail(int code, const char* fmt, ...) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-struct MatPlan { size_t w, s, z; int n, k, wd; };   // byte offsets into packed_dev
+struct MatPlan { size_t w, s, z; int n, k, wd, tiled; };   // byte offsets into packed_dev
 struct LayerPlan { size_t g1, g2; MatPlan qkv, o, gu, down; };
 struct Plan {
     size_t layers_tab;
@@ -57,14 +57,15 @@ struct Plan {
     size_t cx, cx2, cdelta, tq, tkvcur, cattn_o, ch, stepctr, tpart_m, tpart_l, tpart_o;
     size_t wimg, wflag;   // wide pass only (zero bytes otherwise)
     int wring;
+    bool wide;
 };
 
-size_t mat_w_bytes(int n, int k, int wd) { return wd == W_BF16 ? (size_t)n * k * 2 : wd == W_INT8 ? (size_t)n * k : (size_t)n * k / 2; }
 size_t mat_s_bytes(int n, int k, int wd) { return wd == W_INT8 ? (size_t)n * 2 : wd == W_INT4 ? (size_t)n * (k / 128) * 2 : 0; }
 
-MatPlan plan_mat(size_t& off, int n, int k, int wd) {
-    MatPlan p{0, 0, 0, n, k, wd};
-    p.w = off; off = align256(off + mat_w_bytes(n, k, wd));
+// tiled: workgroups of the grid the wide pass's layout is cut for, 0 = row-major
+MatPlan plan_mat(size_t& off, int n, int k, int wd, int tiled) {
+    MatPlan p{0, 0, 0, n, k, wd, tiled};
+    p.w = off; off = align256(off + (size_t)n * PMat::row_bytes_of(k, wd, tiled));
     p.s = off; off = align256(off + mat_s_bytes(n, k, wd));
     p.z = off; off = align256(off + (wd == W_INT4 ? mat_s_bytes(n, k, wd) : 0));
     return p;
@@ -99,47 +100,32 @@ int check_config(const ff_config* c) {
 
 // The wide kernel gives every workgroup a contiguous range of rows of each projection (whole groups of
 // four) and keeps its residual rows in LDS: at most kWideResRows of them on a grid of n_cta workgroups.
-// The int4 scales of a panel of rows must fit their LDS region (two panels of the wider projections).
+// The int4 scales of two panels of the projections of a d-wide input must fit their LDS region.
 bool wide_fits(const ff_config& c, int n_cta) {
-    const int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, qd = c.n_q_heads * c.head_dim;
-    const int rows = std::max(std::max(qkv_rows, c.d_model), 2 * c.d_ffn);
-    const auto share = [&](int n) { return 4 * (((n + 3) / 4 + n_cta - 1) / n_cta); };
-    if (share(rows) > 224 || share(c.d_model) > kWideResRows || c.d_model % 8 || qkv_rows % 4) return false;
-    if (c.wdtype != W_INT4) return true;
-    const auto tile_rows = [&](int n) { return std::min((share(n) + 15) / 16, kPanelTiles) * 16; };
-    const size_t wide_in = (size_t)16 * kPanelTiles * (c.d_model / 128) * 4, long_in = (size_t)tile_rows(c.d_model) * (std::max(qd, c.d_ffn) / 128) * 4;
-    return 2 * wide_in <= (size_t)kWideSzBytes && long_in <= (size_t)kWideSzBytes;
+    const int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+    const int res_rows = 4 * ((c.d_model / 4 + n_cta - 1) / n_cta);
+    if (n_cta > kWideMaxCtas || res_rows > kWideResRows || c.d_model % 8 || qkv_rows % 4) return false;
+    return c.wdtype != W_INT4 || (size_t)2 * 16 * kPanelTiles * (c.d_model / 128) * 4 <= (size_t)kWideSzBytes;
 }
 constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the chip the kernels are built for
 
-// Sequences one pass of the fused kernel serves: up to 4 on the row-partitioned paths (paper Section
-// 5.2), or, for a model created for more than that, up to 16 in one wide pass.
-// FF_WIDE_MIN (experiments): smallest batch that takes the wide pass (default 5; it measured equal
-// to the former eight-sequence instance at 5 sequences and faster from 6 on, slower than the
-// four-sequence path below that).
+// Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout);
+// the others run row-partitioned passes of up to four sequences (paper Section 5.2) on row-major weights.
+// FF_WIDE_MIN (experiments): smallest max_batch that takes the wide pass.
 int wide_min_batch() {
     const char* e = getenv("FF_WIDE_MIN");
     const int v = e ? atoi(e) : 0;
-    return v > 0 ? v : kMaxBatch + 1;
+    return v > 0 ? v : 2;
 }
-int fused_pass_rows(const ff_config& c) {
-    // (quantised layers with a bf16 LM head keep the passes of four: the wide pass runs the LM head inside the kernel, in the layers' format)
-    const bool fmt_ok = c.wdtype == W_BF16 || c.quant_lm_head;
-    if (fmt_ok && c.max_batch >= wide_min_batch() && wide_fits(c, kGridCtas)) return kMaxBatchWide;
-    return std::min(c.max_batch, kMaxBatch);
-}
-// Does a pass of `batch` sequences (batch <= fused_pass_rows) run on the wide instance?  A model created
-// for more than four sequences has the wide pass's buffers; with int8 weights its passes of four take the
-// wide instance too (8B shape, context 4096: 3.53 ms against 3.87 ms on the row-partitioned path; at
-// three sequences the two are equal, below that and with bf16 weights the row-partitioned path is faster).
-bool pass_is_wide(const ff_config& c, int batch) {
-    const bool env = getenv("FF_WIDE_MIN") != nullptr;
-    return fused_pass_rows(c) == kMaxBatchWide && batch >= (!env && c.wdtype == W_INT8 ? kMaxBatch : wide_min_batch());
-}
+bool wide_model(const ff_config& c) { return c.max_batch >= wide_min_batch() && wide_fits(c, kGridCtas); }
+int fused_pass_rows(const ff_config& c, bool wide) { return wide ? c.max_batch : std::min(c.max_batch, kMaxBatch); }
 
 // wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
-Plan make_plan(const ff_config& c, int wring = 0) {
+// n_cta: workgroups of the grid (sizes are largest for kGridCtas); perop: with the per-operation path's buffers
+Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool perop = true) {
     Plan P;
+    P.wide = wide_model(c);
+    const int tiled = P.wide ? n_cta : 0;
     size_t off = 0;
     P.layers_tab = off; off = align256(off + sizeof(PLayer) * c.n_layers);
     int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, qd = c.n_q_heads * c.head_dim;
@@ -147,46 +133,47 @@ Plan make_plan(const ff_config& c, int wring = 0) {
         LayerPlan L;
         L.g1 = off; off = align256(off + (size_t)c.d_model * 2);
         L.g2 = off; off = align256(off + (size_t)c.d_model * 2);
-        L.qkv = plan_mat(off, qkv_rows, c.d_model, c.wdtype);
-        L.o = plan_mat(off, c.d_model, qd, c.wdtype);
-        L.gu = plan_mat(off, 2 * c.d_ffn, c.d_model, c.wdtype);
-        L.down = plan_mat(off, c.d_model, c.d_ffn, c.wdtype);
+        L.qkv = plan_mat(off, qkv_rows, c.d_model, c.wdtype, tiled);
+        L.o = plan_mat(off, c.d_model, qd, c.wdtype, tiled);
+        L.gu = plan_mat(off, 2 * c.d_ffn, c.d_model, c.wdtype, tiled);
+        L.down = plan_mat(off, c.d_model, c.d_ffn, c.wdtype, tiled);
         P.layers.push_back(L);
     }
     P.embed = off; off = align256(off + (size_t)c.vocab * c.d_model * 2);
     P.gf = off; off = align256(off + (size_t)c.d_model * 2);
-    P.lm = plan_mat(off, c.vocab, c.d_model, c.quant_lm_head ? c.wdtype : W_BF16);
+    const int lm_wd = c.quant_lm_head ? c.wdtype : W_BF16;
+    P.lm = plan_mat(off, c.vocab, c.d_model, lm_wd, lm_wd == c.wdtype ? tiled : 0);   // (a head of another type runs as separate launches)
     P.packed_bytes = off;
 
     size_t s = 0;
-    size_t mb = fused_pass_rows(c);   // exchange buffers hold one pass
+    const size_t mb = fused_pass_rows(c, P.wide), pb = perop ? mb : 0;   // exchange buffers hold one pass
     auto take = [&](size_t bytes) { size_t o = s; s = align256(s + bytes); return o; };
     P.x = take(mb * c.d_model * 4);
     P.xn = take(mb * c.d_model * 4);
-    P.q = take(mb * qd * 4);
-    P.kvcur = take(mb * 2 * c.n_kv_heads * c.head_dim * 4);
-    P.attn_o = take(mb * qd * 4);
-    P.h = take(mb * c.d_ffn * 4);
+    P.q = take(pb * qd * 4);
+    P.kvcur = take(pb * 2 * c.n_kv_heads * c.head_dim * 4);
+    P.attn_o = take(pb * qd * 4);
+    P.h = take(pb * c.d_ffn * 4);
     size_t ymax = std::max((size_t)qkv_rows, (size_t)2 * c.d_ffn);
-    P.y = take(mb * ymax * 4);
-    P.part_m = take(mb * c.n_q_heads * kMaxSplits * 4);
-    P.part_l = take(mb * c.n_q_heads * kMaxSplits * 4);
-    P.part_o = take(mb * c.n_q_heads * kMaxSplits * c.head_dim * 4);
-    P.cx = take(mb * c.d_model * 4);
-    P.cx2 = take(mb * c.d_model * 4);
-    P.cdelta = take(mb * c.d_model * 4);
+    P.y = take(pb * ymax * 4);
+    P.part_m = take(pb * c.n_q_heads * kMaxSplits * 4);
+    P.part_l = take(pb * c.n_q_heads * kMaxSplits * 4);
+    P.part_o = take(pb * c.n_q_heads * kMaxSplits * c.head_dim * 4);
+    const size_t cb = P.wide ? 0 : mb;   // compact exchange rows: row-partitioned passes only
+    P.cx = take(cb * c.d_model * 4);
+    P.cx2 = take(cb * c.d_model * 4);
+    P.cdelta = take(cb * c.d_model * 4);
     P.tq = take(mb * qd * 8);
     P.tkvcur = take(mb * 2 * c.n_kv_heads * c.head_dim * 8);
-    P.cattn_o = take(mb * qd * 4);
-    P.ch = take(mb * c.d_ffn * 4);
+    P.cattn_o = take(cb * qd * 4);
+    P.ch = take(cb * c.d_ffn * 4);
     P.stepctr = take(256);
     P.tpart_m = take(mb * c.n_q_heads * kMaxSplits * 8);
     P.tpart_l = take(mb * c.n_q_heads * kMaxSplits * 8);
     P.tpart_o = take(mb * c.n_q_heads * kMaxSplits * c.head_dim * 8);
-    const bool wide = mb == (size_t)kMaxBatchWide;
     P.wring = wring ? wring : c.n_layers + 1;
-    P.wimg = take(wide ? WideLayout::of(c.d_model, qd, c.d_ffn, c.wdtype, kGridCtas).bytes * P.wring : 0);
-    P.wflag = take(wide ? (size_t)kGridCtas * 4 : 0);
+    P.wimg = take(P.wide ? WideLayout::of(c.d_model, qd, c.d_ffn, c.wdtype, c.max_batch, n_cta).bytes * P.wring : 0);
+    P.wflag = take(P.wide ? (size_t)kGridCtas * 4 : 0);
     P.status = take(256);
     P.scratch_bytes = s;
     return P;
@@ -222,17 +209,25 @@ PMat to_pmat(const MatPlan& p, uint8_t* base) {
     m.w = base + p.w;
     m.s = (const f16_t*)(base + p.s);
     m.z = (const f16_t*)(base + p.z);
-    m.n = p.n; m.k = p.k; m.wd = p.wd;
+    m.n = p.n; m.k = p.k; m.wd = p.wd; m.tiled = p.tiled;
     return m;
 }
 
+// one block per (workgroup of the decode grid, tile of its rows)
+dim3 tile_grid(const MatPlan& p) {
+    const int rows = 4 * (((p.n + 3) / 4 + p.tiled - 1) / p.tiled);
+    return dim3((unsigned)p.tiled, (unsigned)((rows + 15) / 16));
+}
 // copy canonical rows [n_rows] of `src` into packed rows starting at dst_row, with row mapping
 int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const ff_matrix& a, const ff_matrix* b, int mode, int hd,
            const GuPerm& perm, hipStream_t st) {
     if (!a.w || (b && !b->w)) return fail(FF_ERR_ARG, "matrix pointer is null");
-    size_t rb = dst.wd == W_BF16 ? (size_t)dst.k * 2 : dst.wd == W_INT8 ? (size_t)dst.k : (size_t)dst.k / 2;
+    size_t rb = PMat::row_bytes_of(dst.k, dst.wd, 0);
     int grid = std::min(n_rows, 4096);
-    k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.w + (size_t)dst_row * rb, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr,
+    if (dst.tiled)
+        k_repack_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr, RowMap{mode, hd, perm});
+    else
+        k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.w + (size_t)dst_row * rb, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr,
                                              n_rows, rb, mode, hd, perm);
     if (dst.wd != W_BF16) {
         if (!a.s || (b && !b->s)) return fail(FF_ERR_ARG, "scale pointer is null for a quantised matrix");
@@ -276,8 +271,24 @@ int launch_gemv(ff_model* m, const PMat& W, const float* in, int in_stride, floa
     kern<<<m->n_cta, kThreads, m->lds_bytes, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
     return FF_OK;
 }
+template <int WD, int B>
+int launch_gemv_tiled(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
+    auto kern = op_gemv_tiled<WD, B>;
+    constexpr size_t lds = kLdsActBytes + (size_t)kWaves * 16 * B * 4;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); });
+    if (attr_err != hipSuccess) return fail(FF_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
+    kern<<<W.tiled, kThreads, lds, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
+    return FF_OK;
+}
 template <int B>
 int gemv_any(ff_model* m, const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
+    if (W.tiled) switch (W.wd) {
+        case W_BF16: return launch_gemv_tiled<W_BF16, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        case W_INT8: return launch_gemv_tiled<W_INT8, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        default: return launch_gemv_tiled<W_INT4, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    }
     switch (W.wd) {
         case W_BF16: return launch_gemv<W_BF16, B>(m, W, in, in_stride, out, batch, epi, st, skip_tokens);
         case W_INT8: return launch_gemv<W_INT8, B>(m, W, in, in_stride, out, batch, epi, st, skip_tokens);
@@ -334,9 +345,12 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
     m->n_cta = prop.multiProcessorCount;
     m->lds_bytes = kLdsFusedBytes;
     if ((size_t)prop.sharedMemPerBlock < m->lds_bytes + 256) { delete m; return fail(FF_ERR_UNSUPPORTED, "device LDS per workgroup too small"); }
-    if (fused_pass_rows(*cfg) == kMaxBatchWide && (!wide_fits(*cfg, m->n_cta) || m->n_cta > kGridCtas)) {
-        delete m;
-        return fail(FF_ERR_UNSUPPORTED, "max_batch %d needs the wide pass, whose row tiles do not fit a grid of %d workgroups", cfg->max_batch, prop.multiProcessorCount);
+    if (P.wide) {
+        if (!wide_fits(*cfg, m->n_cta)) {
+            delete m;
+            return fail(FF_ERR_UNSUPPORTED, "max_batch %d needs the wide pass, which does not fit a grid of %d workgroups", cfg->max_batch, prop.multiProcessorCount);
+        }
+        m->plan = P = make_plan(*cfg, m->n_cta);
     }
 
     DevModel& D = m->dev;
@@ -351,7 +365,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
         // is only 14 stages long there, too few to stage the four chunks of h behind it) and is off by default
         const char* pipe = getenv("FF_GLU_PIPE");
         const bool pipe_off = pipe && pipe[0] == '0', pipe_all = pipe && pipe[0] == 'a';
-        const bool ok = cfg->d_ffn % nw == 0 && chunk_elems % nw == 0 && !pipe_off;
+        const bool ok = !P.wide && cfg->d_ffn % nw == 0 && chunk_elems % nw == 0 && !pipe_off;
         D.gu = ok ? GuPerm{cfg->d_ffn / nw, nw} : GuPerm{0, 0};
         // glu_run (single-sequence passes) needs the staged h beside the staged projection input, the
         // per-lane partial sums of a wave's down-projection rows at the end of the aux region, at most
@@ -376,7 +390,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
     D.status = (int*)(s + P.status);
     D.cx = (u32*)(s + P.cx); D.cx2 = (u32*)(s + P.cx2); D.cdelta = (u32*)(s + P.cdelta); D.tq = (u32x2*)(s + P.tq);
     D.tkvcur = (u32x2*)(s + P.tkvcur); D.cattn_o = (u32*)(s + P.cattn_o); D.ch = (u32*)(s + P.ch);
-    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring;
+    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring; D.wbatch = m->cfg.max_batch;
     D.stepctr = (u32*)(s + P.stepctr);
     D.tpart_m = (u32x2*)(s + P.tpart_m); D.tpart_l = (u32x2*)(s + P.tpart_l); D.tpart_o = (u32x2*)(s + P.tpart_o);
     D.dbg = nullptr;
@@ -394,7 +408,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
         k_fill_u32<<<256, 256, 0, st>>>((u32*)m->scratch, P.scratch_bytes / 4, 0u);
         // a model for single sequences never sees its batch grow: its one row is initialised here
         // and ff_decode_step launches no k_scrub_rows
-        if (cfg->max_batch == 1) k_scrub_rows<<<64, kThreads, 0, st>>>(m->dev, 1);
+        if (cfg->max_batch == 1 && !P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(m->dev, 1);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);   // host_layers is pageable: finish the copy before returning
@@ -487,8 +501,17 @@ SynthMat synth_mat(uint64_t seed, int layer, const char* which, int k, int wd) {
 }
 int synth_part(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const SynthMat& a, const SynthMat& b, int mode, int hd,
                const GuPerm& perm, hipStream_t st) {
-    const size_t rb = dst.wd == W_BF16 ? (size_t)dst.k * 2 : dst.wd == W_INT8 ? (size_t)dst.k : (size_t)dst.k / 2;
+    const size_t rb = PMat::row_bytes_of(dst.k, dst.wd, 0);
     const size_t sb = dst.wd == W_INT8 ? 2 : (size_t)(dst.k / 128) * 2;
+    if (dst.tiled) {
+        const RowMap map{mode, hd, perm};
+        k_synth_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, a, b, map, (float)(0.02 / kIh4Std));
+        if (dst.wd != W_BF16)
+            k_synth_scales<<<std::min(n_rows, 8192), kThreads, 0, st>>>((f16_t*)(packed + dst.s + (size_t)dst_row * sb), (f16_t*)(packed + dst.z + (size_t)dst_row * sb),
+                                                                       n_rows, dst.wd, a, b, map);
+        HIPCHK(hipGetLastError());
+        return FF_OK;
+    }
     k_synth_rows<<<std::min(n_rows, 8192), kThreads, 0, st>>>(packed + dst.w + (size_t)dst_row * rb, (f16_t*)(packed + dst.s + (size_t)dst_row * sb),
                                                              (f16_t*)(packed + dst.z + (size_t)dst_row * sb), n_rows, dst.wd, a, b, mode, hd,
                                                              (float)(0.02 / kIh4Std), perm);
@@ -637,7 +660,7 @@ namespace {
 // counters kept on the device), so the launches of a step may be recorded into a HIP graph.
 int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, int seq0,
                int step_batch, hipStream_t st) {
-    const bool wide = pass_is_wide(m->cfg, batch);   // (batch <= fused_pass_rows: a wide pass only where the wide instance fits)
+    const bool wide = m->plan.wide;
     const int lm_in_kernel = D.lm.wd == m->cfg.wdtype;   // LM head inside the fused kernel when its weights have the layers' type
     DevKV kvd = kv->dev;
     kvd.seq0 = seq0;
@@ -659,7 +682,7 @@ int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const 
     if (e != hipSuccess) return fail(e == hipErrorLaunchOutOfResources ? FF_ERR_UNSUPPORTED : FF_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
     if (!lm_in_kernel) {   // LM head of a different weight type than the layers: separate launches
         const ff_config& c = m->cfg;
-        op_final_x<<<16, kThreads, 0, st>>>(D.x, D.cx, D.cdelta, batch * c.d_model);
+        if (!wide) op_final_x<<<16, kThreads, 0, st>>>(D.x, D.cx, D.cdelta, batch * c.d_model);   // (the wide kernel leaves the final rows in x)
         op_rmsnorm<<<batch, kThreads, 0, st>>>(D.x, D.gf, D.xn, c.d_model, c.rms_eps);
         for (int b0 = 0; b0 < batch; b0 += kMaxBatch) {
             int rc = gemv_op(m, D.lm, D.xn + (size_t)b0 * c.d_model, c.d_model, logits_dev + (size_t)b0 * c.vocab, std::min(kMaxBatch, batch - b0), EPI_STORE, st,
@@ -678,7 +701,7 @@ int ff_decode_step(ff_model* m, const int32_t* tokens_dev, const int32_t* positi
                    void* stream) {
     int rc = check_step_args(m, tokens_dev, positions_dev, kv, logits_dev, batch);
     if (rc) return rc;
-    const int rows = fused_pass_rows(m->cfg);
+    const int rows = fused_pass_rows(m->cfg, m->plan.wide);
     for (int s0 = 0; s0 < batch; s0 += rows) {
         rc = fused_pass(m, m->dev, tokens_dev + s0, positions_dev + s0, kv, logits_dev + (size_t)s0 * m->cfg.vocab, std::min(rows, batch - s0),
                         s0, batch, (hipStream_t)stream);
@@ -766,8 +789,11 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
                           void* stream) {
     int rc = check_step_args(m, tokens_dev, positions_dev, kv, logits_dev, batch);
     if (rc) return rc;
-    Plan P = m->plan;   // (the wide pass's images: one block for all layers where one per layer does not fit the array)
-    if (P.scratch_bytes > kStaticScratchBytes) P = make_plan(m->cfg, 1);
+    Plan P = m->plan;
+    if (P.wide) {   // no buffers for the per-operation path; one block of images for all layers where one per layer does not fit the array
+        P = make_plan(m->cfg, m->n_cta, 0, false);
+        if (P.scratch_bytes > kStaticScratchBytes) P = make_plan(m->cfg, m->n_cta, 1, false);
+    }
     if (P.scratch_bytes > kStaticScratchBytes)
         return fail(FF_ERR_NOMEM, "this configuration needs %zu bytes of exchange scratch, the static array holds %zu", P.scratch_bytes,
                     kStaticScratchBytes);
@@ -782,7 +808,7 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
     D.part_m = (float*)(s + P.part_m); D.part_l = (float*)(s + P.part_l); D.part_o = (float*)(s + P.part_o);
     D.cx = (u32*)(s + P.cx); D.cx2 = (u32*)(s + P.cx2); D.cdelta = (u32*)(s + P.cdelta); D.tq = (u32x2*)(s + P.tq);
     D.tkvcur = (u32x2*)(s + P.tkvcur); D.cattn_o = (u32*)(s + P.cattn_o); D.ch = (u32*)(s + P.ch);
-    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring;
+    D.wimg = s + P.wimg; D.wflag = (u32*)(s + P.wflag); D.wring = P.wring; D.wbatch = m->cfg.max_batch;
     D.stepctr = (u32*)(s + P.stepctr);
     D.tpart_m = (u32x2*)(s + P.tpart_m); D.tpart_l = (u32x2*)(s + P.tpart_l); D.tpart_o = (u32x2*)(s + P.tpart_o);
     // The array keeps whatever the last call (of any model) left: everything this step's kernels
@@ -790,9 +816,9 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
     // not a memset node, so the call may be recorded into a HIP graph), then the write-counter
     // bits of the compact rows (k_scrub_rows sees "0 rows clean").
     k_fill_u32<<<256, 256, 0, st>>>((u32*)s, P.scratch_bytes / 4, 0u);
-    k_scrub_rows<<<64, kThreads, 0, st>>>(D, std::min(batch, fused_pass_rows(m->cfg)));
+    if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(D, std::min(batch, fused_pass_rows(m->cfg, false)));
     HIPCHK(hipGetLastError());
-    const int rows = fused_pass_rows(m->cfg);
+    const int rows = fused_pass_rows(m->cfg, m->plan.wide);
     for (int s0 = 0; s0 < batch; s0 += rows) {
         rc = fused_pass(m, D, tokens_dev + s0, positions_dev + s0, kv, logits_dev + (size_t)s0 * m->cfg.vocab, std::min(rows, batch - s0), s0,
                         batch, st);
@@ -852,6 +878,21 @@ int launch_debug_quad(ff_model* m, const PMat& W, const float* in, float* out, i
     kern<<<m->n_cta, kThreads, m->lds_bytes, st>>>(W, in, W.k, out, batch);
     return FF_OK;
 }
+// The wide pass's projection on a tiled matrix: the inputs become a wide image in the model's scratch (region of the matrix's own input).
+template <int WD>
+int debug_wide(ff_model* m, const PMat& W, size_t img_off, const float* in, float* out, int batch, hipStream_t st) {
+    auto kern = wide_gemv_kernel<WD, 8>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kWideLdsBytes); });
+    if (attr_err != hipSuccess) return fail(FF_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
+    uint8_t* img = m->dev.wimg + img_off;
+    wide_image_kernel<<<256, 256, 0, st>>>(WideImg{img, WD == W_BF16 ? 0 : WD == W_INT8 ? 1 : 2, batch, true}, in, W.k, wide_img_cols(W.k, WD));
+    DevModel D = m->dev;
+    D.V = W.n;   // rows of the output
+    kern<<<W.tiled, kWideThreads, kWideLdsBytes, st>>>(D, DevKV{}, W, img, out, batch, m->n_cta);
+    return FF_OK;
+}
 template <int WD>
 int debug_quad_any(ff_model* m, const PMat& W, const float* in, float* out, int batch, hipStream_t st) {
     if (batch == 2) return launch_debug_quad<WD, 2>(m, W, in, out, batch, st);
@@ -880,6 +921,13 @@ int ff_debug_gemv(ff_model* m, int32_t layer, int32_t which, const float* in_dev
     const bool direct = s.map == 0 && s.row_off == 0 && W.n == s.n_can;
     float* raw = direct ? out_dev : m->dev.y;
     if (path == 0) rc = gemv_op(m, W, in_dev, W.k, raw, batch, EPI_STORE, st);
+    else if (W.tiled) {
+        const ff_config& c = m->cfg;
+        const WideLayout wl = WideLayout::of(c.d_model, c.n_q_heads * c.head_dim, c.d_ffn, c.wdtype, c.max_batch, m->n_cta);
+        const size_t off = which == FF_MAT_WO ? wl.a : which == FF_MAT_WDOWN ? wl.h : wl.x1;
+        rc = W.wd == W_BF16 ? debug_wide<W_BF16>(m, W, off, in_dev, raw, batch, st)
+             : W.wd == W_INT8 ? debug_wide<W_INT8>(m, W, off, in_dev, raw, batch, st) : debug_wide<W_INT4>(m, W, off, in_dev, raw, batch, st);
+    }
     else if (W.wd == W_BF16) rc = debug_quad_any<W_BF16>(m, W, in_dev, raw, batch, st);
     else if (W.wd == W_INT8) rc = debug_quad_any<W_INT8>(m, W, in_dev, raw, batch, st);
     else rc = debug_quad_any<W_INT4>(m, W, in_dev, raw, batch, st);
