@@ -343,16 +343,46 @@ __device__ __forceinline__ void for_tile_units(const PMat& W, int row0, int n_ro
         if (r >= 0 && r < n_rows) f(r, u, dst + i);
     }
 }
+// (A wave copies 8 units x 8 rows at a time: whole 128-byte lines on both sides.)
 __global__ void __launch_bounds__(kThreads) k_repack_tiles(PMat W, int row0, int n_rows, const uint8_t* src_a, const uint8_t* src_b, RowMap map) {
     const size_t rb = PMat::row_bytes_of(W.k, W.wd, 0);
-    for_tile_units(W, row0, n_rows, [&](int r, int u, u32x4* dst) {
+    const PMat::Rows rr = W.cta_rows(blockIdx.x);
+    const int t0 = rr.r0 + 16 * (int)blockIdx.y;
+    if (t0 >= rr.r1 || t0 + 16 <= row0 || t0 >= row0 + n_rows) return;
+    const int nt = min(rr.r1 - t0, 16), units = (int)(W.row_bytes() / 16), src_units = (int)(rb / 16);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r8 = lane & 7, u8 = lane >> 3;
+    FF_GLOBAL u32x4* dst = as_global((u32x4*)(W.w + (size_t)t0 * W.row_bytes()));
+    const FF_GLOBAL u32x4* src[2];
+    bool mine[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int r = t0 + r8 + 8 * h - row0;
+        mine[h] = r8 + 8 * h < nt && r >= 0 && r < n_rows;
         bool second;
-        const int sr = map.source(r, &second);
-        u32x4 v = {0u, 0u, 0u, 0u};   // (units behind the row's end)
-        if ((size_t)(u + 1) * 16 <= rb) v = *(const u32x4*)((second ? src_b : src_a) + (size_t)sr * rb + (size_t)u * 16);
-        if (W.wd == W_INT4) v = u32x4{i4_tiled_word(v.x), i4_tiled_word(v.y), i4_tiled_word(v.z), i4_tiled_word(v.w)};
-        *dst = v;
-    });
+        const int sr = map.source(mine[h] ? r : 0, &second);
+        src[h] = as_global((const u32x4*)((second ? src_b : src_a) + (size_t)sr * rb));
+    }
+    constexpr int NB = 4;   // blocks in flight
+    for (int u0 = wave * 8 + u8; u0 - u8 < units; u0 += kWaves * 8 * NB) {
+        u32x4 v[NB][2];
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const int u = u0 + i * kWaves * 8;
+                v[i][h] = u32x4{0u, 0u, 0u, 0u};   // (units behind the row's end)
+                if (mine[h] && u < src_units) v[i][h] = src[h][u];
+            }
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const int u = u0 + i * kWaves * 8;
+                u32x4 w = v[i][h];
+                if (W.wd == W_INT4) w = u32x4{i4_tiled_word(w.x), i4_tiled_word(w.y), i4_tiled_word(w.z), i4_tiled_word(w.w)};
+                if (mine[h] && u < units) dst[(size_t)u * nt + r8 + 8 * h] = w;
+            }
+    }
 }
 __global__ void k_rope_table(float2* rope, int max_ctx, int hd, double theta) {
     int half = hd / 2;
