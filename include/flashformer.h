@@ -156,10 +156,7 @@ int ff_kv_free(ff_kv *kv);
  * "wide" pass (paper Section 5.2 reads the weights once up to batch 4 and stops there): weights packed
  * as matrix-core operand tiles, projections on 16x16x32 tiles (int8 and int4 codes converted to bf16 in
  * registers), activations exchanged in operand order by the workgroups that own them.  Models for one
- * sequence run the row-partitioned pass on row-major weights.  (Where the wide pass does not fit -- int4
- * with d_model above 8192 / 128 groups a row -- up to 4 sequences share a row-partitioned pass and a larger
- * batch runs as consecutive passes on the
- * stream, each streaming the weights again.) */
+ * sequence run the row-partitioned pass on row-major weights. */
 int ff_decode_step(ff_model *m, const int32_t *tokens_dev, const int32_t *positions_dev, ff_kv *kv,
                    float *logits_dev, int32_t batch, void *stream);
 
@@ -198,7 +195,8 @@ int ff_debug_dequant(const ff_model *m, int32_t layer, int32_t which, float *out
  * in_dev[b][k] for matrix `which` of `layer`, fp32 in_dev [batch][K], fp32 out_dev [batch][N] with
  * rows in canonical order.  path 0: the vector-ALU GEMV (batch 1..4) used at batch 1 and
  * by the per-operation baseline; path 1: the matrix-core projection of models for several sequences
- * (batch 2..4, inputs as bf16 head + remainder; K * 4 bytes * batch at most 128 KiB).  Fed with
+ * (batch 2..4, inputs as bf16 head + remainder; K * 4 bytes * batch at most 128 KiB; a bf16 LM head
+ * over quantised layers stays on the vector ALU).  Fed with
  * unit vectors it returns the columns of W exactly as the hot path dequantises them (the int8 row
  * scale and the int4 group scale / zero are applied to sums there, which for a unit vector is the
  * single product of the defining formula).  Uses the model's scratch: must not overlap a decode

@@ -17,29 +17,29 @@ typedef uint16_t f16_t;    // raw bits
 
 constexpr int kThreads = 256;            // threads per workgroup (4 waves, one per SIMD)
 constexpr int kWaves = kThreads / 64;
-constexpr int kMaxBatch = 4;        // sequences one pass of the row-partitioned paths works on
+constexpr int kMaxBatch = 4;        // sequences one pass of the per-operation path works on
 constexpr int kMaxBatchFused = 8;   // sequences the RoPE / position regions of the fused kernel's LDS are laid out for
 constexpr int kMaxBatchWide = 16;   // sequences of a wide pass (ff_wide.h)
-constexpr int kMaxBatchApi = 16;    // sequences one decode step accepts (one wide pass, or passes of kMaxBatch)
+constexpr int kMaxBatchApi = 16;    // sequences one decode step accepts
 constexpr int kMaxSplits = 64;           // max KV splits per (sequence, kv head)
 #ifndef FF_MIN_SPLIT
 #define FF_MIN_SPLIT 64   // can be overridden at build time for sweeps (32 and 128 both measured 2 % slower at ctx 1024)
 #endif
 constexpr int kMinSplitLen = FF_MIN_SPLIT;   // do not split the cache finer than this many rows
 constexpr int kLdsActBytes = 128 * 1024; // LDS region holding the staged activation vector(s)
-constexpr int kLdsAuxBytes = 24 * 1024;  // partial sums of earlier K segments (per wave), then kLdsXsumBytes of per-unit input sums
-constexpr int kLdsXsumBytes = 4 * 1024;  // tail of the aux region: sum of every staged 32-element unit (int4 matrix-core path)
+constexpr int kLdsAuxBytes = 24 * 1024;  // partial sums of earlier K segments (per wave), then kLdsAuxTailBytes (with them: glu_run's down-projection sums)
+constexpr int kLdsAuxTailBytes = 4 * 1024;
 constexpr int kLdsRopeBytes = 8 * 64 * 8;   // behind the aux region: (cos, sin) rows of up to 8 sequences
 constexpr int kLdsMiscBytes = 256;          // then: reduction scratch, positions, vote slots
-constexpr int kLdsPairBytes = 1024;         // then: mailboxes of wave pairs that share a row group (gemv_run_quad)
-constexpr int kLdsFusedBytes = kLdsActBytes + kLdsAuxBytes + kLdsRopeBytes + kLdsMiscBytes + kLdsPairBytes;
+constexpr int kLdsGluBytes = 1024;         // then: arrival counters of the staged chunks (glu_run)
+constexpr int kLdsFusedBytes = kLdsActBytes + kLdsAuxBytes + kLdsRopeBytes + kLdsMiscBytes + kLdsGluBytes;
 constexpr int kSpinLimit = 1 << 16;
 
 
 enum { W_BF16 = 0, W_INT8 = 1, W_INT4 = 2 };
 
 // A projection matrix in packed (device-private) row order.  Two layouts of the weights:
-//   row-major (tiled == 0), streamed row by row by the row-partitioned passes;
+//   row-major (tiled == 0), streamed row by row by the single-sequence kernel and the per-operation path;
 //   tiled for the wide pass (tiled == workgroups of the grid): every workgroup's rows (whole groups of
 //   four, see cta_rows) are cut into tiles of 16 (the last one may be shorter), and a tile holds its rows'
 //   16-byte units column by column: unit 0 of all rows, unit 1 of all rows, ...  A matrix-core operand (16

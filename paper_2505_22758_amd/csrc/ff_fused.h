@@ -91,7 +91,7 @@ __device__ __forceinline__ PhaseState phase_state(const DevModel& M, int ph) {
 
 // `sl` = (steps executed so far) * L: the write counters of the compact vectors are sl + layer for the
 // buffers written once per layer and 2 * (sl + layer) + {0, 1} for the sublayer output (O, then DOWN).
-__device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* tokens, u32 tb, u32 sl, int ph, int lm_in_kernel, const PhaseState& X, bool eager_attn) {
+__device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* tokens, u32 tb, u32 sl, int ph, int lm_in_kernel, const PhaseState& X) {
     PhaseDesc D;
     const int l = ph >> 2;
     const FF_CONST PLayer* Lp = as_const(M.layers) + min(l, M.L - 1);   // scalar loads (see as_const)
@@ -112,7 +112,6 @@ __device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* to
         D.W = FF_PMAT_FIELDS(Lp->qkv);
     } else if (D.kind == PH_O) {
         src.base = M.cattn_o; src.stride = (size_t)M.Hq * M.hd; src.tag = sl + l;
-        src.eager = eager_attn;
         D.out_cnt = 2 * (sl + l);
         D.W = FF_PMAT_FIELDS(Lp->o);
     } else if (D.kind == PH_GU) {
@@ -135,7 +134,7 @@ __device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* to
     return D;
 }
 
-// Attention form of the passes of up to four sequences (see attn_item): 0 = row by row on the vector
+// Attention form of the single-sequence kernel (see attn_item): 0 = row by row on the vector
 // ALU, 1 = scores of 16 cached rows at a time on the matrix cores (head dimension 128 only).  With
 // eight query heads per KV head the row-wise form is bound by the vector ALU (the 70B shape at batch
 // 1: 23.8 -> 23.3 ms per step with form 1); with four, form 1 is ahead by 0.2 % (8B bf16, batch 1,
@@ -144,10 +143,10 @@ __device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* to
 #define FF_ATTN_MODE 1
 #endif
 #ifndef FF_ATTN_MODE_I4
-#define FF_ATTN_MODE_I4 0   // int4 instances: form 1 spills a few registers at batch 2-4 and measured 1 % slower there
+#define FF_ATTN_MODE_I4 0   // int4 instances: form 1 was not faster
 #endif
 template <int WD> constexpr int kAttnModeOf = WD == W_INT4 ? FF_ATTN_MODE_I4 : FF_ATTN_MODE;
-template <int WD, int B, int HD, int G>
+template <int WD, int HD, int G>
 __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M, DevKV KV, const int* __restrict__ tokens,
                                                                      const int* __restrict__ pos, float* __restrict__ logits,
                                                                      int batch, int lm_in_kernel, int ncta, int mute_wg, int switches, int glu_off) {
@@ -159,6 +158,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     // Test hook for the time-out path: the muted workgroup publishes nothing, so every workgroup
     // that needs its output runs into its own bounded wait, records the time-out and leaves.
     if ((int)blockIdx.x == mute_wg) return;
+    constexpr int B = 1;   // (batch is 1)
     constexpr int EPU = WTraits<WD>::EPU;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -179,8 +179,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         pos_lds[threadIdx.x] = step_pos(tokens, pos, threadIdx.x);   // -1: the sequence sits this step out
         share_lds[threadIdx.x] = attn_share_of(tokens, pos, batch, threadIdx.x, ncta, M.Hkv, (switches & kSwUniformShares) != 0);
     }
-    if (threadIdx.x < 2) ((lds_u32*)(pairbox_of(xs) + 4 * kPairBoxFloats))[threadIdx.x] = 0u;
-    if (B == 1 && threadIdx.x < kGluMaxChunks) ((lds_u32*)pairbox_of(xs))[threadIdx.x] = 0u;   // arrival counters of the staged h chunks (glu_run)
+    if (threadIdx.x < kGluMaxChunks) glu_counters_of(xs)[threadIdx.x] = 0u;
     __syncthreads();
     // projections only; attention runs right after each PH_QKV.  The LM head runs here unless its
     // weight type differs from the layers' (then the host launches it separately).
@@ -201,25 +200,12 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     float* red = (float*)(lds + kLdsActBytes + kLdsAuxBytes) + 2 * kMaxBatchFused * 64;   // behind the RoPE rows
     WgVote vote{(u32*)(red + 16), 0u};   // behind the reduction scratch and the positions
     // One iteration = one K segment of one projection; only (phase, segment) are carried from one
-    // iteration to the next.  With kScalarState they are pinned to scalar registers, so that all
-    // that derives from them (the layer's descriptor, the wave's share) is fetched and computed on
-    // the scalar unit, the next descriptor is touched ahead of time, and the wait for the merged
-    // attention output re-reads eagerly.  Each of the three shortens the path from the end of one
-    // projection to the first tile requests of the next; with several sequences per pass that
-    // pays (8B bf16, batch 4: 5.70 -> 5.61 ms); with a single one the step measured slower
-    // (3.26 -> 3.30 ms; presumably the earlier requests compete with the workgroups still finishing
-    // the previous projection), so batch 1 keeps the unpinned form.
-    constexpr bool kScalarState = B > 1;
-    constexpr bool kQuad = kQuadOf<WD, B>;   // matrix-core GEMV on groups of four rows, split-bf16 staged input
+    // iteration to the next (pinning both to scalar registers measured slower for one sequence: 3.26 -> 3.30 ms).
     int ph = 0, seg = 0;
     for (;;) {
-        if constexpr (kScalarState) {
-            ph = __builtin_amdgcn_readfirstlane(ph);
-            seg = __builtin_amdgcn_readfirstlane(seg);
-        }
-        const PhaseDesc D = phase_desc(M, tokens, tag_base, sl, ph, lm_in_kernel, phase_state(M, ph), kScalarState);
+        const PhaseDesc D = phase_desc(M, tokens, tag_base, sl, ph, lm_in_kernel, phase_state(M, ph));
         EpiFused epi{D.kind, D.out_tag, D.out_cnt, M, KV, pos_lds, D.layer, rope_lds, logits};
-        const Stream<WD, B> S = Stream<WD, B>::make(D.W, seg, gwave, n_gwaves, kQuad);
+        const Stream<WD, B> S = Stream<WD, B>::make(D.W, seg, gwave, n_gwaves);
         // The wave's first tiles of this projection are requested before anything it has to wait
         // for (its input vector; for the output projection the whole attention), so the memory
         // pipe has work while the dependency resolves.  The ring lives from here to the end of
@@ -232,16 +218,9 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         Stage<WD> ring[kDepthOf<WD>];
         // (ablation switch, single-sequence bf16 instances only: with kSwNoOverlap the tiles are requested
         // after the input has arrived, as in a fused kernel without cross-layer memory overlap)
-        constexpr bool kHasSwitch = B == 1 && WD == W_BF16;
-        if (!kHasSwitch || !(switches & kSwNoOverlap)) prefetch_stream<kQuad>(S, ring, lane, 0, kPrefetchOf<WD>);
+        constexpr bool kHasSwitch = WD == W_BF16;
+        if (!kHasSwitch || !(switches & kSwNoOverlap)) prefetch_stream(S, ring, lane, 0, kPrefetchOf<WD>);
         if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_PF_ISSUED, lane);
-        // Touch the descriptor the NEXT phase will fetch, so that it sits in the scalar cache by
-        // then instead of costing a trip to memory at the head of that phase.
-        u32 warm = 0;
-        if constexpr (kScalarState) {
-            const FF_CONST u32* nd = (const FF_CONST u32*)(as_const(M.layers) + min((ph + 1) >> 2, M.L - 1));
-            warm = nd[0] ^ nd[16] ^ nd[32] ^ nd[sizeof(PLayer) / 4 - 1];
-        }
         if (att_first) {
             // split-KV attention + merge of this layer (the ring holds the output projection's tiles)
             __syncthreads();   // every wave has finished reading the staged input: LDS is free
@@ -257,44 +236,40 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
         if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_H_START, lane);
         bool ok;
         u64* ev = dbg_stage_slots(M, n_phases, ncta, D.layer, D.kind);
-        if (src.add) ok = stage_tagged<EPU, true, kFusedThreads, kQuad, B>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
-        else ok = stage_tagged<EPU, false, kFusedThreads, kQuad, B>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
+        if (src.add) ok = stage_tagged<EPU, true, kFusedThreads>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
+        else ok = stage_tagged<EPU, false, kFusedThreads>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x, vote, ev);
         if (ev && threadIdx.x == 0) as_global(ev)[4] = wall_clock64();
         if (!ok) {
             if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);
             return;
         }
         if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_SYNCED, lane);
-        if (kHasSwitch && (switches & kSwNoOverlap)) prefetch_stream<kQuad>(S, ring, lane, 0, kPrefetchOf<WD>);
-        if constexpr (kPrefetchOf<WD> < kDepthOf<WD>) prefetch_stream<kQuad>(S, ring, lane, kPrefetchOf<WD>, kDepthOf<WD>);   // the rest of the ring, behind the input
+        if (kHasSwitch && (switches & kSwNoOverlap)) prefetch_stream(S, ring, lane, 0, kPrefetchOf<WD>);
+        if constexpr (kPrefetchOf<WD> < kDepthOf<WD>) prefetch_stream(S, ring, lane, kPrefetchOf<WD>, kDepthOf<WD>);   // the rest of the ring, behind the input
         u64* wv = D.kind < 4 ? dbg_wave_slots(M, n_phases, D.layer, wave) : nullptr;
         if (wv && lane == 0) as_global(wv)[4 + D.kind] = wall_clock64();
         bool glu_done = false;
-        if constexpr (B == 1) {
-            if (glu_off >= 0 && D.kind == PH_GU) {
-                // gate/up, SwiGLU and down projection as one stream, the down projection's input
-                // staged chunk by chunk on the way (glu_run); the DOWN phase below is skipped
-                const PhaseDesc Dd = phase_desc(M, tokens, tag_base, sl, ph + 1, lm_in_kernel, phase_state(M, ph + 1), false);
-                const Stream<WD, B> Sd = Stream<WD, B>::make(Dd.W, 0, gwave, n_gwaves, false);
-                const int pd = (int)n_gwaves.div((u32)(M.d / 2) + n_gwaves.n - 1u);   // most down-projection row pairs a wave owns
-                float* lacc = (float*)(lds + kLdsActBytes + kLdsAuxBytes) - (size_t)(kFusedWaves - wave) * pd * 128;
-                GluStager<WD> stg{M.ch, sl + (u32)D.layer, M.F, Sd.nup, Sd.cpr, (float4*)(lds + glu_off), (lds_u32*)pairbox_of(xs)};
-                EpiSwiGLUTagged epig{M.ch, M.F, D.out_cnt, M.gu};
-                EpiDeltaTagged epid{M.cdelta, M.d, Dd.out_cnt};
-                const bool okg = glu_run<WD>(S, Sd, ring, xs, stg, lacc, (u32)kFusedWaves * (u32)(D.layer + 1),
-                                             kChunkUnitsOf<WD> * WTraits<WD>::EPU / M.gu.nw, lane, epig, epid);
-                if (!okg) {
-                    if (lane == 0) atomicCAS(M.status, 0, -57 - 10 * ph);
-                    return;
-                }
-                if (wv && lane == 0) as_global(wv)[PH_DOWN] = wall_clock64();
-                glu_done = true;
+        if (glu_off >= 0 && D.kind == PH_GU) {
+            // gate/up, SwiGLU and down projection as one stream, the down projection's input
+            // staged chunk by chunk on the way (glu_run); the DOWN phase below is skipped
+            const PhaseDesc Dd = phase_desc(M, tokens, tag_base, sl, ph + 1, lm_in_kernel, phase_state(M, ph + 1));
+            const Stream<WD, B> Sd = Stream<WD, B>::make(Dd.W, 0, gwave, n_gwaves);
+            const int pd = (int)n_gwaves.div((u32)(M.d / 2) + n_gwaves.n - 1u);   // most down-projection row pairs a wave owns
+            float* lacc = (float*)(lds + kLdsActBytes + kLdsAuxBytes) - (size_t)(kFusedWaves - wave) * pd * 128;
+            GluStager<WD> stg{M.ch, sl + (u32)D.layer, M.F, Sd.nup, Sd.cpr, (float4*)(lds + glu_off), glu_counters_of(xs)};
+            EpiSwiGLUTagged epig{M.ch, M.F, D.out_cnt, M.gu};
+            EpiDeltaTagged epid{M.cdelta, M.d, Dd.out_cnt};
+            const bool okg = glu_run<WD>(S, Sd, ring, xs, stg, lacc, (u32)kFusedWaves * (u32)(D.layer + 1),
+                                         kChunkUnitsOf<WD> * WTraits<WD>::EPU / M.gu.nw, lane, epig, epid);
+            if (!okg) {
+                if (lane == 0) atomicCAS(M.status, 0, -57 - 10 * ph);
+                return;
             }
+            if (wv && lane == 0) as_global(wv)[PH_DOWN] = wall_clock64();
+            glu_done = true;
         }
         if (glu_done) { /* both projections are finished */ }
-        else if constexpr (kQuad) gemv_run_quad<WD, B>(S, ring, xs, myacc, batch, lane, epi);
         else gemv_run<WD, B>(S, ring, xs, myacc, batch, lane, epi);
-        asm volatile("" ::"s"(warm));   // keeps the touch alive
         if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_RUN_DONE, lane);
         if (wv && lane == 0) as_global(wv)[D.kind] = wall_clock64();
         // next iteration: further K segment of the same projection, or the next projection
@@ -338,9 +313,9 @@ struct KernelSetup {
         return err;
     }
 };
-template <int WD, int B, int HD, int G>
+template <int WD, int HD, int G>
 inline hipError_t launch_fused_instance(const FusedLaunch& a, const char** what) {
-    auto kern = fused_decode_kernel<WD, B, HD, G>;
+    auto kern = fused_decode_kernel<WD, HD, G>;
     static KernelSetup setup;
     if (hipError_t e = setup.run((const void*)kern, kFusedThreads, a.lds_bytes)) { *what = setup.what; return e; }
     kern<<<a.n_cta, kFusedThreads, a.lds_bytes, a.stream>>>(a.M, a.KV, a.tokens, a.pos, a.logits, a.batch, a.lm_in_kernel, a.n_cta, a.mute_wg, a.switches, a.glu_off);
@@ -360,13 +335,11 @@ template <int WD, int HD, int G>
 inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
     // (the host decides whether a pass is wide, and sizes the buffers for it; up to eight sequences share an operand tile with their remainders)
     if (a.wide) return a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
-    if (a.batch == 1) return launch_fused_instance<WD, 1, HD, G>(a, what);
-    if (a.batch == 2) return launch_fused_instance<WD, 2, HD, G>(a, what);
-    if (a.batch > kMaxBatch) {
-        *what = "more than four sequences per pass without the wide kernel";
+    if (a.batch != 1) {
+        *what = "several sequences on the single-sequence kernel";
         return hipErrorInvalidValue;
     }
-    return launch_fused_instance<WD, 4, HD, G>(a, what);
+    return launch_fused_instance<WD, HD, G>(a, what);
 }
 // One definition per (weight type, head geometry), each in its own translation unit.
 #define FF_FUSED_FAMILIES(X) \

@@ -38,10 +38,6 @@ template <int WD> constexpr int kChunkUnitsOf = 64 * kUnrOf<WD>;   // units of o
 #define FF_REFILL_PARTS_I4 1
 #endif
 template <int WD, int B> constexpr int kRefillPartsOf = B != 1 ? 1 : WD == W_INT4 ? FF_REFILL_PARTS_I4 : (kUnrOf<WD> % FF_REFILL_PARTS == 0 ? FF_REFILL_PARTS : 1);
-#ifndef FF_REFILL_PARTS_QUAD
-#define FF_REFILL_PARTS_QUAD 2
-#endif
-template <int WD> constexpr int kQuadRefillPartsOf = WD == W_INT4 ? 1 : FF_REFILL_PARTS_QUAD;   // the same for the matrix-core streams of 2-4 sequences
 template <int U0, int U1> struct StageUnits { static constexpr int u0 = U0, u1 = U1; };   // units [U0, U1) of a stage
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -50,21 +46,13 @@ __device__ __forceinline__ void static_for(F&& f) {
         static_for<I + 1, N>(f);
     }
 }
-// With two or more sequences per pass the projections run on the matrix cores in groups of four
-// rows (gemv_run_quad below) instead of row pairs on the vector ALUs.
-template <int WD, int B> constexpr bool kQuadOf = B > 1;
-template <int WD> constexpr int kQuadLoadsOf = WD == W_INT4 ? 4 : 8;       // 16-byte loads per lane and stage in that mode ...
-template <int WD> constexpr int kQuadChunkUnitsOf = 16 * kQuadLoadsOf<WD>; // ... = units of one row covered by one stage of one wave
-constexpr int kAccFloatsPerWave = (kLdsAuxBytes - kLdsXsumBytes) / 4 / kWaves;   // partial sums a wave can carry between K segments
-// Per-unit input sums of the int4 matrix-core path live at the end of the aux region (xs = start of LDS).
-__device__ __forceinline__ float* xsum_of(const float4* xs) { return (float*)((uint8_t*)xs + kLdsActBytes + kLdsAuxBytes - kLdsXsumBytes); }
-// Mailboxes of the wave pairs (0,1) and (2,3) of a workgroup: [pair][side][16 x 8 floats], then one flag word per pair.
+constexpr int kAccFloatsPerWave = (kLdsAuxBytes - kLdsAuxTailBytes) / 4 / kWaves;   // partial sums a wave can carry between K segments
+// Arrival counters of the staged h chunks (glu_run).
 typedef __attribute__((address_space(3))) float lds_float;
 typedef __attribute__((address_space(3))) u32 lds_u32;
-__device__ __forceinline__ lds_float* pairbox_of(const float4* xs) {
-    return (lds_float*)((uint8_t*)xs + kLdsActBytes + kLdsAuxBytes + kLdsRopeBytes + kLdsMiscBytes);
+__device__ __forceinline__ lds_u32* glu_counters_of(const float4* xs) {
+    return (lds_u32*)((uint8_t*)xs + kLdsActBytes + kLdsAuxBytes + kLdsRopeBytes + kLdsMiscBytes);
 }
-constexpr int kPairBoxFloats = 32;   // per (pair, side): 4 rows x 8 sequences
 
 // ---------------------------------------------------------------- reductions
 // Sum over the 64 lanes with DPP row operations; the result is wave-uniform.
@@ -268,15 +256,13 @@ struct Stream {
     size_t rowb;
     int N, K, ng;
     int nseg, seg, j0, nunits, cpr, nup;
-    int p0, c0, n_it;   // first row pair (or group) and first chunk of it, iterations
+    int p0, n_it;   // first row pair, iterations
 
     static constexpr int EPU = WTraits<WD>::EPU;
     static constexpr int kChunkUnits = kChunkUnitsOf<WD>;
     static constexpr int seg_units = (kLdsActBytes / (B * EPU * 4)) / kChunkUnits * kChunkUnits;
 
-    // quad: rows are dealt out in groups of four (p0 counts groups) and a stage covers
-    // kQuadChunkUnitsOf units of each of the four rows instead of kChunkUnits units of two rows.
-    __device__ __forceinline__ static Stream make(const PMat& M, int seg, int gwave, const UDiv& n_gwaves, bool quad = false) {
+    __device__ __forceinline__ static Stream make(const PMat& M, int seg, int gwave, const UDiv& n_gwaves) {
         Stream S;
         S.w = M.w; S.s = M.s; S.z = M.z; S.N = M.n; S.K = M.k; S.ng = M.k / 128;
         S.rowb = WD == W_BF16 ? (size_t)M.k * 2 : WD == W_INT8 ? (size_t)M.k : (size_t)M.k / 2;
@@ -286,23 +272,11 @@ struct Stream {
         S.j0 = seg * seg_units;
         S.nunits = min(seg_units, total_units - S.j0);
         S.nup = (S.nunits + kChunkUnits - 1) / kChunkUnits * kChunkUnits;
-        S.cpr = S.nup / (quad ? kQuadChunkUnitsOf<WD> : kChunkUnits);
-        // row pairs (groups) [p0, p1) of this wave; the products fit 32 bits (rows * waves < 2^32)
-        const u32 npairs = quad ? (u32)(M.n + 3) / 4 : (u32)(M.n + 1) / 2;
+        S.cpr = S.nup / kChunkUnits;
+        // row pairs [p0, p1) of this wave; the products fit 32 bits (rows * waves < 2^32)
+        const u32 npairs = (u32)(M.n + 1) / 2;
         S.p0 = (int)n_gwaves.div(npairs * (u32)gwave);
-        S.c0 = 0;
         S.n_it = ((int)n_gwaves.div(npairs * (u32)(gwave + 1)) - S.p0) * S.cpr;
-        // Groups of four rows that come out as an odd number of HALF groups per wave (the 8B QKV
-        // projection: 1.5) are dealt out in halves along K instead: the wave's work is the flat
-        // range [gwave * h, (gwave + 1) * h) of (group, chunk) iterations, h = chunks per wave, so
-        // an odd wave starts in the middle of the group its even neighbour (same workgroup)
-        // began; the two exchange their partial sums through LDS (gemv_run_quad).
-        if (quad && S.nseg == 1 && (S.cpr & 1) == 0 && n_gwaves.mod(2 * npairs) == 0 && (n_gwaves.div(2 * npairs) & 1)) {
-            const int h = (int)n_gwaves.div(2 * npairs) * (S.cpr / 2);
-            S.p0 = gwave * h / S.cpr;
-            S.c0 = gwave * h % S.cpr;
-            S.n_it = h;
-        }
         return S;
     }
 };
@@ -335,28 +309,6 @@ __device__ __forceinline__ void load_stage(const Stream<WD, B>& S, int pair, int
     }
 }
 
-// The same for a group of four rows: lane (blk = lane / 4, r = lane % 4) loads unit blk of row r of
-// each of the stage's 16-unit slices, i.e. a wave load covers 256 contiguous bytes of four rows.
-template <int WD, int B, int U0 = 0, int U1 = kQuadLoadsOf<WD>>
-__device__ __forceinline__ void load_stage_quad(const Stream<WD, B>& S, int grp, int chunk, Stage<WD>& st, int lane) {
-    constexpr int NL = kQuadLoadsOf<WD>, kUnr = kUnrOf<WD>;
-    const int row = min(4 * grp + (lane & 3), S.N - 1);
-    const uint8_t* rp = S.w + (size_t)row * S.rowb + (size_t)S.j0 * 16;
-#pragma unroll
-    for (int u = U0; u < U1; u++) {
-        const int j = min((chunk * NL + u) * 16 + (lane >> 2), S.nunits - 1);
-        st.w[u / kUnr][u % kUnr] = ldg_stream(rp + (size_t)j * 16);
-        if constexpr (WD == W_INT4) {
-            const size_t gi = (size_t)row * S.ng + (S.j0 + j) / 4;
-            st.s[u / kUnr][u % kUnr] = as_global(S.s)[gi];
-            st.z[u / kUnr][u % kUnr] = as_global(S.z)[gi];
-        }
-    }
-    if constexpr (WD == W_INT8 && U1 == NL) {
-        st.rs[0] = as_global(S.s)[row];   // this lane's row (every stage: a wave may end in the middle of a group)
-    }
-}
-
 // Issue iterations [s0, min(s1, n_it)) of a stream into ring slots of the same index (by default the
 // whole ring: the first min(kDepth, n_it) iterations).
 // FF_PREFETCH_STAGES: how many of them the fused kernel requests BEFORE it waits for a projection's
@@ -366,16 +318,13 @@ __device__ __forceinline__ void load_stage_quad(const Stream<WD, B>& S, int grp,
 #define FF_PREFETCH_STAGES FF_DEPTH
 #endif
 template <int WD> constexpr int kPrefetchOf = (WD == W_INT4 ? 2 : 1) * (FF_PREFETCH_STAGES < FF_DEPTH ? FF_PREFETCH_STAGES : FF_DEPTH);
-template <bool QUAD, int WD, int B>
+template <int WD, int B>
 __device__ __forceinline__ void prefetch_stream(const Stream<WD, B>& S, Stage<WD> (&ring)[kDepthOf<WD>], int lane, int s0 = 0, int s1 = kDepthOf<WD>) {
     constexpr int kDepth = kDepthOf<WD>;
-    int pair = S.p0, chunk = S.c0;
+    int pair = S.p0, chunk = 0;
 #pragma unroll
     for (int s = 0; s < kDepth; s++) {
-        if (s >= s0 && s < s1 && s < S.n_it) {
-            if constexpr (QUAD) load_stage_quad(S, pair, chunk, ring[s], lane);
-            else load_stage(S, pair, chunk, ring[s], lane);
-        }
+        if (s >= s0 && s < s1 && s < S.n_it) load_stage(S, pair, chunk, ring[s], lane);
         if (++chunk == S.cpr) { chunk = 0; ++pair; }
     }
 }
@@ -483,8 +432,8 @@ __device__ __forceinline__ void stage_fma_x(const Stage<WD>& st, const float4 (&
 
 // Weight-streaming GEMV over one stream for up to B batch rows (paper Section 4.2: batch-one
 // projections are matrix-vector products with the input cached on chip and each workgroup owning
-// some rows of W; Section 5.2: at batch 2-4 the weights are still read exactly once and the inputs
-// replicated).  On entry ring[s] holds iteration s (s < min(kDepth, n_it)); iteration i+kDepth is
+// some rows of W; Section 5.2: for a few rows the weights are still read exactly once and the inputs
+// replicated, which the per-operation path does).  On entry ring[s] holds iteration s (s < min(kDepth, n_it)); iteration i+kDepth is
 // issued into the slot iteration i has just freed, so 2*kDepth*kUnr 16-byte non-temporal loads
 // per lane stay in flight across row boundaries.  epi(pair, b, v0, v1) runs on lane 0 with the two
 // finished dot products of rows (2*pair, 2*pair+1); partial sums of earlier K segments are carried
@@ -566,249 +515,7 @@ __device__ __forceinline__ void gemv_run(const Stream<WD, B>& S, Stage<WD> (&rin
     }
 }
 
-// ---------------------------------------------------------------- matrix-core variant (bf16, batch >= 2)
-// The same stream for groups of FOUR rows on v_mfma_f32_4x4x4_16b_bf16, which multiplies sixteen
-// independent 4x4x4 blocks per wave: in block blk = lane / 4, lane r = lane % 4 supplies row r of
-// A (four k values) and column r of B, and receives column r of the 4x4 result (register i = row
-// i).  Here A = the four weight rows over four consecutive k (half of the lane's 16-byte unit) and
-// B = the staged inputs of sequences 0..3 over the same k, so one instruction does the 64
-// multiply-adds that cost 16 vector FMAs plus conversions in gemv_run, and the cost no longer
-// grows with the batch (paper Section 5.2 keeps the weights read once at batch 2-4; this keeps the
-// arithmetic from becoming the limit there).  The inputs stay fp32-accurate: staging splits every
-// value into a bf16 head and a bf16 remainder (two planes per sequence, see stage_store), and both
-// are multiplied.  Unit j of sequence b sits at index (j ^ ((b & 3) << 2)) of its plane, which spreads
-// the four lanes of a block over different LDS banks.  More than four sequences take one
-// accumulator pair per set of four (the weights in registers are reused).
-// Value of lane I of every aligned group of four lanes (DPP quad permute).
-template <int I>
-__device__ __forceinline__ float quad_bcast(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), I * 0x55, 0xF, 0xF, true));
-}
 typedef short mfma_s4 __attribute__((ext_vector_type(4)));
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
-
-template <int WD, int B, class Epi>
-__device__ __forceinline__ void gemv_run_quad(const Stream<WD, B>& S, Stage<WD> (&ring)[kDepthOf<WD>], const float4* xs,
-                                              float* myacc, int batch, int lane, Epi& epi) {
-    static_assert(WD == W_BF16 || B <= 4, "more than one set of four sequences: bf16 only");
-    constexpr int kDepth = kDepthOf<WD>;
-    constexpr int NL = kQuadLoadsOf<WD>, kUnr = kUnrOf<WD>;
-    constexpr int NC = (B + 3) / 4;   // sets of four sequences (one accumulator pair each)
-    const int nup = S.nup;
-    const int r4 = lane & 3;
-    const u32x4* xh[NC];
-#pragma unroll
-    for (int c = 0; c < NC; c++) {
-        const int bl = min(4 * c + r4, B - 1);   // sequence whose inputs this lane feeds (columns >= B are never read back)
-        if constexpr (WD == W_BF16) xh[c] = (const u32x4*)xs + (size_t)(2 * bl) * nup + ((lane >> 2) ^ ((bl & 3) << 2));
-        else if constexpr (WD == W_INT8) xh[c] = (const u32x4*)xs + ((size_t)(2 * bl) * nup + ((lane >> 2) ^ ((bl & 2) << 1))) * 2;
-        else xh[c] = (const u32x4*)xs + ((size_t)(2 * bl) * nup + (lane >> 2)) * 4;
-    }
-    const int bl0 = min(r4, B - 1);
-    const float* xsum = xsum_of(xs) + (size_t)bl0 * nup + (lane >> 2);   // int4 only
-    mfma_f4 acc0[NC], acc1[NC];
-#pragma unroll
-    for (int c = 0; c < NC; c++) { acc0[c] = mfma_f4{0.f, 0.f, 0.f, 0.f}; acc1[c] = mfma_f4{0.f, 0.f, 0.f, 0.f}; }
-    int pc = S.p0, cc = S.c0;       // (group, chunk) of the next compute
-    int pl = S.p0, cl = S.c0;       // (group, chunk) of the next load = iteration kDepth
-    for (int s = 0; s < kDepth; s++) if (++cl == S.cpr) { cl = 0; ++pl; }
-
-    auto half = [](u32 a, u32 b) { u32x2 v{a, b}; return __builtin_bit_cast(mfma_s4, v); };
-    constexpr int kParts = kQuadRefillPartsOf<WD>;
-    auto compute = [&](const Stage<WD>& st, bool last, auto units) {   // units: the StageUnits range of the stage's loads multiplied by this call; the last one finishes the iteration
-        constexpr int U0 = decltype(units)::u0, U1 = decltype(units)::u1;
-        // int4: the staged inputs of unit u+1 are requested from LDS before unit u is multiplied
-        // (with one wave per SIMD nothing else hides the LDS latency, and a unit needs nine reads)
-        u32x4 hx[2][4], lx[2][4];
-        float Xs[2];
-        auto fetch = [&](int u, int slot) {
-            const size_t off = (size_t)(cc * NL + u) * 16;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                hx[slot][q] = xh[0][off * 4 + (q ^ r4)];
-                lx[slot][q] = xh[0][((size_t)nup + off) * 4 + (q ^ r4)];
-            }
-            Xs[slot] = xsum[off];
-        };
-        if constexpr (WD == W_INT4) fetch(0, 0);
-#pragma unroll
-        for (int u = U0; u < U1; u++) {
-            const int off = (cc * NL + u) * 16;
-            const u32x4 w = st.w[u / kUnr][u % kUnr];
-            if constexpr (WD == W_INT4) {
-                if (u + 1 < NL) fetch(u + 1, (u + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (WD == W_BF16) {
-#pragma unroll
-                for (int c = 0; c < NC; c++) {
-                    const u32x4 h = xh[c][off], l = xh[c][off + nup];
-                    acc0[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(w.x, w.y), half(h.x, h.y), acc0[c], 0, 0, 0);
-                    acc1[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(w.x, w.y), half(l.x, l.y), acc1[c], 0, 0, 0);
-                    acc0[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(w.z, w.w), half(h.z, h.w), acc0[c], 0, 0, 0);
-                    acc1[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(w.z, w.w), half(l.z, l.w), acc1[c], 0, 0, 0);
-                }
-            } else if constexpr (WD == W_INT8) {
-                // int8 per-channel: a signed byte is exact in bf16 (8 significant bits), so the
-                // unit's 16 codes are converted (sign-extending byte conversion, then the upper
-                // halves of two floats packed into one register) and multiplied like bf16
-                // weights; the row scale is applied to the finished sums.
-                const u32 ww[4] = {w.x, w.y, w.z, w.w};
-                auto pack = [](float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); };
-#pragma unroll
-                for (int q = 0; q < 2; q++) {   // 8 codes = one 16-byte chunk of heads and one of remainders
-                    const int qq = q ^ (bl0 & 1);
-                    const u32x4 h = xh[0][(size_t)off * 2 + qq], l = xh[0][((size_t)nup + off) * 2 + qq];
-                    const u32 wa = ww[2 * q], wb = ww[2 * q + 1];
-                    const u32 a0 = pack((float)(int)(int8_t)wa, (float)(int)(int8_t)(wa >> 8));
-                    const u32 a1 = pack((float)(int)(int8_t)(wa >> 16), (float)((int)wa >> 24));
-                    const u32 a2 = pack((float)(int)(int8_t)wb, (float)(int)(int8_t)(wb >> 8));
-                    const u32 a3 = pack((float)(int)(int8_t)(wb >> 16), (float)((int)wb >> 24));
-                    acc0[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a0, a1), half(h.x, h.y), acc0[0], 0, 0, 0);
-                    acc1[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a0, a1), half(l.x, l.y), acc1[0], 0, 0, 0);
-                    acc0[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a2, a3), half(h.z, h.w), acc0[0], 0, 0, 0);
-                    acc1[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a2, a3), half(l.z, l.w), acc1[0], 0, 0, 0);
-                }
-            } else {
-                // int4 group-128: the unit's 32 codes n become the bf16 numbers 128 + n by bit
-                // operations alone (0x4300 | n: exponent 2^7, n in the mantissa), so the blocks
-                // deliver d = sum (128 + n) x, and with X = sum of the unit's x (staged beside it)
-                //   sum s (n - z) x  =  s (d - (128 + z) X).
-                // Scale s and zero z belong to the ROW, which the lanes of a block hold one each:
-                // they are passed round the four lanes with quad permutes.
-                const u32 ww[4] = {w.x, w.y, w.z, w.w};
-                mfma_f4 dh = {0.f, 0.f, 0.f, 0.f}, dl = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int q = 0; q < 4; q++) {   // 8 codes = one 16-byte chunk of heads and one of remainders
-                    const u32x4 h = hx[u & 1][q], l = lx[u & 1][q];
-                    const u32 e = ww[q] & 0x0F0F0F0Fu, o = (ww[q] >> 4) & 0x0F0F0F0Fu;   // codes 0,2,4,6 / 1,3,5,7 as bytes
-                    const u32 a0 = __builtin_amdgcn_perm(o, e, 0x0c040c00u) | 0x43004300u;   // codes 0, 1
-                    const u32 a1 = __builtin_amdgcn_perm(o, e, 0x0c050c01u) | 0x43004300u;   // codes 2, 3
-                    const u32 a2 = __builtin_amdgcn_perm(o, e, 0x0c060c02u) | 0x43004300u;   // codes 4, 5
-                    const u32 a3 = __builtin_amdgcn_perm(o, e, 0x0c070c03u) | 0x43004300u;   // codes 6, 7
-                    dh = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a0, a1), half(h.x, h.y), dh, 0, 0, 0);
-                    dl = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a0, a1), half(l.x, l.y), dl, 0, 0, 0);
-                    dh = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a2, a3), half(h.z, h.w), dh, 0, 0, 0);
-                    dl = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(half(a2, a3), half(l.z, l.w), dl, 0, 0, 0);
-                }
-                const float X = Xs[u & 1];
-                const float sc = f16_to_f((f16_t)st.s[u / kUnr][u % kUnr]);
-                const float zp = 128.f + f16_to_f((f16_t)st.z[u / kUnr][u % kUnr]);
-                // row i of the block: scale and zero held by lane i of the quad
-                acc0[0][0] = fmaf(quad_bcast<0>(sc), fmaf(-quad_bcast<0>(zp), X, dh[0] + dl[0]), acc0[0][0]);
-                acc0[0][1] = fmaf(quad_bcast<1>(sc), fmaf(-quad_bcast<1>(zp), X, dh[1] + dl[1]), acc0[0][1]);
-                acc0[0][2] = fmaf(quad_bcast<2>(sc), fmaf(-quad_bcast<2>(zp), X, dh[2] + dl[2]), acc0[0][2]);
-                acc0[0][3] = fmaf(quad_bcast<3>(sc), fmaf(-quad_bcast<3>(zp), X, dh[3] + dl[3]), acc0[0][3]);
-            }
-        }
-        if constexpr (U1 < NL) return;
-        if (cc == S.cpr - 1 || last) {   // group finished (for this K segment, or this wave's part of it): add up the sixteen blocks
-            float t[NC][4];
-#pragma unroll
-            for (int c = 0; c < NC; c++) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    float v = acc0[c][i] + acc1[c][i];
-                    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));   // row_ror:8
-                    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xF, 0xF, true));   // row_ror:4
-                    v += __shfl_xor(v, 16);
-                    v += __shfl_xor(v, 32);
-                    t[c][i] = v;   // row 4*group + i, sequence 4*c + lane % 4
-                }
-                if constexpr (WD == W_INT8) {   // row scales: lane r of a quad holds that of row r
-                    const float rs = f16_to_f((f16_t)st.rs[0]);
-                    t[c][0] *= quad_bcast<0>(rs); t[c][1] *= quad_bcast<1>(rs); t[c][2] *= quad_bcast<2>(rs); t[c][3] *= quad_bcast<3>(rs);
-                }
-                acc0[c] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-                acc1[c] = mfma_f4{0.f, 0.f, 0.f, 0.f};
-            }
-            // A group shared with the neighbouring wave (see Stream::make): each of the two drops
-            // its sums into its side of the pair's mailbox and then bumps the pair's flag; the
-            // one that finds the flag already bumped adds the other's sums and finishes the rows.
-            // LDS executes a wave's operations in order, so the sums are in place before the flag
-            // moves; nobody waits for anybody.
-            const bool ended_early = cc != S.cpr - 1, started_late = pc == S.p0 && S.c0 != 0;
-            bool finish = true;
-            if (ended_early || started_late) {
-                const int pair = (int)(threadIdx.x >> 7), side = ended_early ? 0 : 1;
-                lds_float* box = pairbox_of(xs);
-                lds_u32* flag = (lds_u32*)(box + 4 * kPairBoxFloats) + pair;
-                lds_float* mine = box + (pair * 2 + side) * kPairBoxFloats;
-                lds_float* other = box + (pair * 2 + (1 - side)) * kPairBoxFloats;
-                if (lane < 4) {
-#pragma unroll
-                    for (int c = 0; c < NC; c++)
-#pragma unroll
-                        for (int i = 0; i < 4; i++) mine[(c * 4 + lane) * 4 + i] = t[c][i];
-                }
-                asm volatile("" ::: "memory");
-                u32 seen = 0;
-                if (lane == 0) seen = __hip_atomic_fetch_add(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                seen = (u32)__builtin_amdgcn_readfirstlane((int)seen);
-                asm volatile("" ::: "memory");
-                finish = seen != 0;
-                if (finish) {
-                    if (lane < 4) {
-#pragma unroll
-                        for (int c = 0; c < NC; c++)
-#pragma unroll
-                            for (int i = 0; i < 4; i++) t[c][i] += other[(c * 4 + lane) * 4 + i];
-                    }
-                    if (lane == 0) *flag = 0u;   // next use: a later projection, behind workgroup barriers
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < NC; c++) {
-                const int b = 4 * c + lane;
-                if (finish && lane < 4 && b < batch) {   // lanes 0..3 finish one sequence each
-                    if (S.nseg > 1) {
-                        float* a = myacc + ((size_t)(pc - S.p0) * B + b) * 4;
-#pragma unroll
-                        for (int i = 0; i < 4; i++) {
-                            if (S.seg > 0) t[c][i] += a[i];
-                            if (S.seg < S.nseg - 1) a[i] = t[c][i];
-                        }
-                    }
-                    if (S.seg == S.nseg - 1) {
-                        epi(2 * pc, b, t[c][0], t[c][1]);
-                        if (4 * pc + 2 < S.N) epi(2 * pc + 1, b, t[c][2], t[c][3]);
-                    }
-                }
-            }
-        }
-        if (++cc == S.cpr) { cc = 0; ++pc; }
-    };
-    auto load = [&](Stage<WD>& st, auto units) {
-        constexpr int U0 = decltype(units)::u0, U1 = decltype(units)::u1;
-        load_stage_quad<WD, B, U0, U1>(S, pl, cl, st, lane);
-        if constexpr (U1 < NL) return;
-        if (++cl == S.cpr) { cl = 0; ++pl; }
-    };
-    int it = 0;
-    for (; it + 2 * kDepth <= S.n_it; it += kDepth) {
-#pragma unroll
-        for (int s = 0; s < kDepth; s++) {
-            static_for<0, kParts>([&](auto part) {
-                constexpr int P = decltype(part)::u0;
-                typedef StageUnits<P * NL / kParts, (P + 1) * NL / kParts> Units;
-                compute(ring[s], false, Units{});
-                __builtin_amdgcn_sched_barrier(0);
-                load(ring[s], Units{});
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        }
-    }
-    for (; it < S.n_it; it += kDepth) {
-#pragma unroll
-        for (int s = 0; s < kDepth; s++) {
-            if (it + s < S.n_it) {
-                compute(ring[s], it + s == S.n_it - 1, StageUnits<0, NL>{});
-                __builtin_amdgcn_sched_barrier(0);
-                if (it + s + kDepth < S.n_it) load(ring[s], StageUnits<0, NL>{});
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-}
 
 }  // namespace ff

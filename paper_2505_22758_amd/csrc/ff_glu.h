@@ -65,7 +65,7 @@ struct GluStager {
             const int qi = staged * kChunkQuads + tid + u * kThreads;
             float4 t = make_float4(cvalue(v[u].x), cvalue(v[u].y), cvalue(v[u].z), cvalue(v[u].w));
             if (qi * 4 >= F) t = make_float4(0.f, 0.f, 0.f, 0.f);   // padding behind a ragged last chunk
-            if (qi < nup * (EPU / 4)) stage_store<EPU, false>(hs, nup, 0, qi, t);
+            if (qi < nup * (EPU / 4)) stage_store<EPU>(hs, nup, 0, qi, t);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_fetch_add(flags + staged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -33,9 +33,9 @@ __global__ void __launch_bounds__(kThreads) op_rmsnorm(const float* x, const bf1
 // x = residual + last sublayer output, from the fused kernel's tagged buffers (finishes the residual
 // stream when the LM head is launched separately after the fused kernel)
 // Re-initialises rows [row0, row1) of the compact exchange vectors so that their counter bits are
-// the ones just BEFORE each vector's first write of the next step: rows a smaller batch has left
-// untouched for a while could otherwise carry, by chance, the bits a later reader waits for.
-// The decision is taken on the device (rows [stepctr[1], batch) are scrubbed, usually none), so the
+// the ones just BEFORE each vector's first write of the next step: scratch with other contents
+// could otherwise carry, by chance, the bits a later reader waits for.
+// The decision is taken on the device (rows [stepctr[1], batch) are scrubbed), so the
 // launch itself carries no host-side state and may be recorded into a HIP graph.
 __global__ void __launch_bounds__(kThreads) k_scrub_rows(DevModel M, int batch) {
     const int row0 = (int)as_global(M.stepctr)[1], row1 = batch;
@@ -78,7 +78,7 @@ __device__ __forceinline__ void op_gemv_body(const PMat& W, const ActSrc& src, i
     const int nseg = S.nseg;
     for (int seg = 0; seg < nseg; seg++) {
         if (seg > 0) { S = Stream<WD, B>::make(W, seg, gwave, n_gwaves); __syncthreads(); }
-        prefetch_stream<false>(S, ring, lane);   // weights do not depend on the input: issue them first
+        prefetch_stream(S, ring, lane);   // weights do not depend on the input: issue them first
         stage_act<EPU, PlainIO, kThreads>(src, batch, S.K, S.j0 * EPU, S.nunits, S.nup, xs, red, threadIdx.x);
         __syncthreads();
         gemv_run<WD, B>(S, ring, xs, myacc, batch, lane, epi);
@@ -191,34 +191,6 @@ __global__ void __launch_bounds__(kThreads) op_gemv_tiled(PMat W, const float* i
         }
         __syncthreads();
     }
-}
-// Debug: the matrix-core GEMV of the fused kernel (gemv_run_quad on the split-bf16 staged input) as
-// a kernel of its own on plain fp32 input rows; out[b][row] in packed row order.  The projection
-// must fit one K segment.
-template <int WD, int B>
-__global__ void __launch_bounds__(kThreads) k_debug_gemv_quad(PMat W, const float* in, int in_stride, float* out, int batch) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    constexpr int EPU = WTraits<WD>::EPU;
-    float4* xs = (float4*)lds;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gwave = blockIdx.x * kWaves + wave;
-    const UDiv n_gwaves = UDiv::of(gridDim.x * kWaves);
-    float* myacc = (float*)(lds + kLdsActBytes) + (size_t)wave * kAccFloatsPerWave;
-    if (threadIdx.x < 2) ((lds_u32*)(pairbox_of(xs) + 4 * kPairBoxFloats))[threadIdx.x] = 0u;
-    const Stream<WD, B> S = Stream<WD, B>::make(W, 0, gwave, n_gwaves, true);
-    Stage<WD> ring[kDepthOf<WD>];
-    prefetch_stream<true>(S, ring, lane);
-    const int padquads = S.nup * (EPU / 4), nquads = S.nunits * (EPU / 4);
-    for (int b = 0; b < batch; b++)
-        for (int q0 = 0; q0 < padquads; q0 += kThreads) {   // whole waves call together (see stage_store)
-            const int qi = q0 + (int)threadIdx.x;
-            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (qi < nquads) t = PlainIO::ld4(in + (size_t)b * in_stride, qi * 4);
-            if (qi < padquads) stage_store<EPU, true>(xs, S.nup, b, qi, t);
-        }
-    __syncthreads();
-    EpiStore epi{out, W.n};
-    gemv_run_quad<WD, B>(S, ring, xs, myacc, batch, lane, epi);
 }
 // Debug: one projection of the wide pass on its own, out[n][row] in packed row order (rows of out: M.V = W.n floats), input image in img.
 template <int WD, int NC>

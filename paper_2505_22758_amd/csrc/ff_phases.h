@@ -121,7 +121,6 @@ struct TSrc {
     cword_t* wb = nullptr; size_t wb_stride = 0; u32 wb_tag = 0;           // optional: publish the sum (residual stream)
     const bf16_t* gain = nullptr; float eps = 0.f;                         // optional: RMSNorm
     UDiv ncta = {1, 0};                                                    // workgroups in the grid (each publishes 1/ncta of wb)
-    bool eager = false;   // re-read the whole vector while waiting instead of polling samples (see stage_tagged_onepass)
 };
 
 // Waits (bounded) until kPollLanes sampled elements of the source vector(s) carry their tags: a
@@ -173,54 +172,11 @@ struct WideImg {
     }
 };
 
-// Writes quad qi (elements 4*qi .. 4*qi+3) of sequence b into the staged vector.  Plain form: the
-// quad-planar fp32 layout of stage_act.  SPLIT form (input of gemv_run_quad): every value v is
-// stored as bf16 head h = v rounded to nearest and bf16 remainder = v - h rounded to nearest (the
-// pair carries 17 significant bits), heads in plane 2b and remainders in plane 2b+1, element order as in a weight unit.
-//   bf16 weights (8 elements = 16 bytes per unit and plane): unit j at index j ^ ((b & 3) << 2);
-//   int8 weights (16 elements = two 16-byte chunks): chunk q of unit j at index
-//   2 (j ^ ((b & 2) << 1)) + (q ^ (b & 1));
-//   int4 weights (32 elements = four 16-byte chunks per unit and plane): chunk q of unit j at
-//   index 4 j + (q ^ (b & 3)), and the sum of the unit's 32 values in xsum_of(xs)[b * nup + j].
-// Either way the four lanes of a matrix-core block (same j, sequences 0..3) hit different banks.
-// All lanes of a unit must call together (int4: eight consecutive quads = eight consecutive lanes).
-template <int EPU, bool SPLIT>
+// Writes quad qi (elements 4*qi .. 4*qi+3) of sequence b into the staged vector: the quad-planar fp32 layout of stage_act.
+template <int EPU>
 __device__ __forceinline__ void stage_store(float4* xs, int nup, int b, int qi, const float4& t) {
     constexpr int NQ = EPU / 4;
-    if constexpr (!SPLIT) {
-        xs[((size_t)b * NQ + qi % NQ) * nup + qi / NQ] = t;
-    } else {
-        static_assert(EPU == 8 || EPU == 16 || EPU == 32, "bf16, int8 or int4 weights");
-        // heads and remainders with the packed conversion (two values per instruction, round to
-        // nearest even): |error| <= 2^-18 |v|
-        u32 h01, l01, h23, l23;
-        split_bf16x2(t.x, t.y, h01, l01);
-        split_bf16x2(t.z, t.w, h23, l23);
-        const u32 h[4] = {h01 << 16, h01 & 0xFFFF0000u, h23 << 16, h23 & 0xFFFF0000u};   // (only the int4 unit sums below look at these)
-        const u32 l[4] = {l01 << 16, l01 & 0xFFFF0000u, l23 << 16, l23 & 0xFFFF0000u};
-        u32x2 *ph, *pl;
-        if constexpr (EPU == 8) {
-            const int j = (qi >> 1) ^ ((b & 3) << 2);
-            ph = (u32x2*)(xs + (size_t)(2 * b) * nup + j) + (qi & 1);
-            pl = (u32x2*)(xs + (size_t)(2 * b + 1) * nup + j) + (qi & 1);
-        } else if constexpr (EPU == 16) {
-            const int j = (qi >> 2) ^ ((b & 2) << 1), q = ((qi >> 1) & 1) ^ (b & 1);
-            ph = (u32x2*)(xs + ((size_t)(2 * b) * nup + j) * 2 + q) + (qi & 1);
-            pl = (u32x2*)(xs + ((size_t)(2 * b + 1) * nup + j) * 2 + q) + (qi & 1);
-        } else {
-            const int j = qi >> 3, q = ((qi >> 1) & 3) ^ (b & 3);
-            ph = (u32x2*)(xs + ((size_t)(2 * b) * nup + j) * 4 + q) + (qi & 1);
-            pl = (u32x2*)(xs + ((size_t)(2 * b + 1) * nup + j) * 4 + q) + (qi & 1);
-            // the sum of the values as the matrix cores will see them (head + stored remainder)
-            float hv[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) hv[e] = __uint_as_float(h[e]) + __uint_as_float(l[e]);
-            const float us = group_sum<8>((hv[0] + hv[1]) + (hv[2] + hv[3]));
-            if ((qi & 7) == 0) xsum_of(xs)[(size_t)b * nup + j] = us;
-        }
-        *ph = u32x2{h01, h23};
-        *pl = u32x2{l01, l23};
-    }
+    xs[((size_t)b * NQ + qi % NQ) * nup + qi / NQ] = t;
 }
 
 // Several-pass form (vectors longer than one pass of stage_tagged_onepass; one row at a time).
@@ -234,7 +190,7 @@ __device__ __forceinline__ void stage_store(float4* xs, int nup, int b, int qi, 
 // QB = quads per thread and pass (2 8-byte loads per quad and source, all in flight at once; their
 // 4*QB destination registers per source must fit beside the wave's prefetched weight tiles, or the
 // compiler parks those tiles elsewhere and has to wait for them first).
-template <int EPU, bool HAS_ADD, bool HAS_GAIN, int NT, int QB, bool SPLIT>
+template <int EPU, bool HAS_ADD, bool HAS_GAIN, int NT, int QB>
 __device__ __forceinline__ bool stage_tagged_multipass(const TSrc& S, int batch, int K, int k0, int nunits, int nup, float4* xs, float* red, int tid, WgVote& vote, u64* ev) {
     constexpr int NQ = EPU / 4;
     if (ev && tid == 0) { as_global(ev)[0] = wall_clock64(); as_global(ev)[2] = 0; as_global(ev)[5] = 0; }
@@ -313,12 +269,11 @@ __device__ __forceinline__ bool stage_tagged_multipass(const TSrc& S, int batch,
                             t.x *= bf_lo(g[u].x); t.y *= bf_hi(g[u].x); t.z *= bf_lo(g[u].y); t.w *= bf_hi(g[u].y);
                         }
                     }
-                    stage_store<EPU, SPLIT>(xs, nup, b, qi, t);
+                    stage_store<EPU>(xs, nup, b, qi, t);
                 }
             }
         }
         if constexpr (HAS_GAIN) {
-            static_assert(!SPLIT, "the rescaling pass below works on the fp32 layout");
             ss = wave_sum_uniform(ss);
             if (lane == 0) red[tid >> 6] = ss;
             __syncthreads();
@@ -341,11 +296,9 @@ __device__ __forceinline__ bool stage_tagged_multipass(const TSrc& S, int batch,
 
 // The common case, where one pass of QB quads per thread covers the whole vector (nup * EPU / 4 <=
 // NT * QB): every thread keeps its quads in registers from the load to the LDS write, and the sums
-// of squares of the normalisation travel with the freshness vote, so a group of RB batch rows costs
-// a single workgroup barrier and the staged vectors are written once, already scaled.  The loads
-// of all RB rows are in flight together: behind a wave's weight prefetch a round trip takes
-// microseconds, and one per row would make the hand-over grow with the batch.
-template <int EPU, bool HAS_ADD, bool HAS_GAIN, int NT, int QB, bool SPLIT, int RB>
+// of squares of the normalisation travel with the freshness vote, so a row costs a single workgroup
+// barrier and the staged vector is written once, already scaled.
+template <int EPU, bool HAS_ADD, bool HAS_GAIN, int NT, int QB>
 __device__ __forceinline__ bool stage_tagged_onepass(const TSrc& S, int batch, int K, int k0, int nunits, int nup, float4* xs, int tid, WgVote& vote, u64* ev) {
     constexpr int NQ = EPU / 4;
     if (ev && tid == 0) { as_global(ev)[0] = wall_clock64(); as_global(ev)[2] = 0; as_global(ev)[5] = 0; }
@@ -353,101 +306,75 @@ __device__ __forceinline__ bool stage_tagged_onepass(const TSrc& S, int batch, i
     const int nquads = nunits * NQ;
     const int padquads = nup * NQ;
     const u32 wb_lo = S.ncta.div((u32)nquads * blockIdx.x), wb_hi = S.ncta.div((u32)nquads * (blockIdx.x + 1));
-    for (int b0 = 0; b0 < batch; b0 += RB) {
-        // rows b0 .. b0+RB-1; a row past the batch repeats the last one (loaded and checked, never written)
-        const cword_t* src[RB];
-        const cword_t* add[RB];
-        const bf16_t* erow[RB];   // embedding rows only come through the (no add, gain) instance
-#pragma unroll
-        for (int r = 0; r < RB; r++) {
-            const int b = min(b0 + r, batch - 1);
-            src[r] = S.base + (size_t)b * S.stride;
-            add[r] = HAS_ADD ? S.add + (size_t)b * S.add_stride : nullptr;
-            erow[r] = nullptr;
-            if constexpr (!HAS_ADD && HAS_GAIN) erow[r] = S.tokens ? S.embed + (size_t)max(as_global(S.tokens)[b], 0) * K : nullptr;
-        }
-        u32x4 v[RB][QB], a[HAS_ADD ? RB : 1][HAS_ADD ? QB : 1];   // four compact words per quad and source
+    for (int b = 0; b < batch; b++) {
+        const cword_t* src = S.base + (size_t)b * S.stride;
+        const cword_t* add = HAS_ADD ? S.add + (size_t)b * S.add_stride : nullptr;
+        const bf16_t* erow = nullptr;   // embedding rows only come through the (no add, gain) instance
+        if constexpr (!HAS_ADD && HAS_GAIN) erow = S.tokens ? S.embed + (size_t)max(as_global(S.tokens)[b], 0) * K : nullptr;
+        u32x4 v[QB], a[HAS_ADD ? QB : 1];   // four compact words per quad and source
         u32x2 g[HAS_GAIN ? QB : 1];
         bool all_ok = false;
-        float tot[RB];
-        u32 stale[RB];   // quads (bit u) of row r this lane still has to (re)load
-#pragma unroll
-        for (int r = 0; r < RB; r++) { stale[r] = (1u << QB) - 1; tot[r] = 0.f; }
+        float tot[1] = {0.f};
+        u32 stale = (1u << QB) - 1;   // quads (bit u) this lane still has to (re)load
         // first every quad of every lane, unconditionally (no per-lane branches on the way to the
         // first request); after a failed vote only what came back stale, so a vector that was
         // mostly complete is not fetched twice
         auto load_quads = [&](auto ALL) {
             constexpr bool kAll = decltype(ALL)::value;
 #pragma unroll
-            for (int r = 0; r < RB; r++) {
-#pragma unroll
-                for (int u = 0; u < QB; u++) {
-                    const int k = k0 + min(tid + u * NT, nquads - 1) * 4;   // clamped: every load is issued
-                    if (kAll || ((stale[r] >> u) & 1)) {
-                        if (erow[r]) {   // bf16 values are exact in the compact format: mark them fresh
-                            u32x2 w = *as_global((const u32x2*)(erow[r] + k));
-                            const u32 t = S.tag & kCntMask;
-                            v[r][u] = u32x4{(w.x << 16) | t, (w.x & 0xFFFF0000u) | t, (w.y << 16) | t, (w.y & 0xFFFF0000u) | t};
-                        } else {
-                            const u32x2 lo = cld2(src[r], k), hi = cld2(src[r], k + 2);
-                            v[r][u] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                        }
-                        if constexpr (HAS_ADD) {
-                            const u32x2 lo = cld2(add[r], k), hi = cld2(add[r], k + 2);
-                            a[r][u] = u32x4{lo.x, lo.y, hi.x, hi.y};
-                        }
+            for (int u = 0; u < QB; u++) {
+                const int k = k0 + min(tid + u * NT, nquads - 1) * 4;   // clamped: every load is issued
+                if (kAll || ((stale >> u) & 1)) {
+                    if (erow) {   // bf16 values are exact in the compact format: mark them fresh
+                        u32x2 w = *as_global((const u32x2*)(erow + k));
+                        const u32 t = S.tag & kCntMask;
+                        v[u] = u32x4{(w.x << 16) | t, (w.x & 0xFFFF0000u) | t, (w.y << 16) | t, (w.y & 0xFFFF0000u) | t};
+                    } else {
+                        const u32x2 lo = cld2(src, k), hi = cld2(src, k + 2);
+                        v[u] = u32x4{lo.x, lo.y, hi.x, hi.y};
                     }
-                    if constexpr (HAS_GAIN && kAll) { if (r == 0) g[u] = *as_global((const u32x2*)(S.gain + k)); }
+                    if constexpr (HAS_ADD) {
+                        const u32x2 lo = cld2(add, k), hi = cld2(add, k + 2);
+                        a[u] = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    }
                 }
+                if constexpr (HAS_GAIN && kAll) { g[u] = *as_global((const u32x2*)(S.gain + k)); }
             }
         };
         load_quads(std::true_type{});
         for (int spins = 0; spins < kSpinLimit && !all_ok; spins++) {
-            float ss[RB];   // only meaningful if the vote passes
-            bool mine = true;
-            // With a single row in flight the lane first ORs the counter mismatches of all its
-            // words together (one operation per word) and looks at single quads only if something
-            // is stale; with several rows that form needs more registers than there are beside
-            // the weight tiles (it spills), so they test quad by quad.
+            float ss[1] = {0.f};   // only meaningful if the vote passes
+            // The lane first ORs the counter mismatches of all its words together (one operation per
+            // word) and looks at single quads only if something is stale.
             u32 dirty = 0;
-            if constexpr (RB == 1) {
 #pragma unroll
-                for (int u = 0; u < QB; u++) {
-                    dirty |= (v[0][u].x ^ S.tag) | (v[0][u].y ^ S.tag) | (v[0][u].z ^ S.tag) | (v[0][u].w ^ S.tag);
-                    if constexpr (HAS_ADD) dirty |= (a[0][u].x ^ S.add_tag) | (a[0][u].y ^ S.add_tag) | (a[0][u].z ^ S.add_tag) | (a[0][u].w ^ S.add_tag);
-                }
-                dirty &= kCntMask;
+            for (int u = 0; u < QB; u++) {
+                dirty |= (v[u].x ^ S.tag) | (v[u].y ^ S.tag) | (v[u].z ^ S.tag) | (v[u].w ^ S.tag);
+                if constexpr (HAS_ADD) dirty |= (a[u].x ^ S.add_tag) | (a[u].y ^ S.add_tag) | (a[u].z ^ S.add_tag) | (a[u].w ^ S.add_tag);
             }
+            dirty &= kCntMask;
+            stale = 0;
 #pragma unroll
-            for (int r = 0; r < RB; r++) {
-                stale[r] = 0;
-                ss[r] = 0.f;
-#pragma unroll
-                for (int u = 0; u < QB; u++) {
-                    if (RB > 1 || dirty) {
-                        bool ok = cfresh(v[r][u].x, S.tag) && cfresh(v[r][u].y, S.tag) && cfresh(v[r][u].z, S.tag) && cfresh(v[r][u].w, S.tag);
-                        if constexpr (HAS_ADD)
-                            ok = ok && cfresh(a[r][u].x, S.add_tag) && cfresh(a[r][u].y, S.add_tag) && cfresh(a[r][u].z, S.add_tag) && cfresh(a[r][u].w, S.add_tag);
-                        if (!ok) stale[r] |= 1u << u;
-                    }
-                    if constexpr (HAS_GAIN) {
-                        float4 t = make_float4(cvalue(v[r][u].x), cvalue(v[r][u].y), cvalue(v[r][u].z), cvalue(v[r][u].w));
-                        if constexpr (HAS_ADD) { t.x += cvalue(a[r][u].x); t.y += cvalue(a[r][u].y); t.z += cvalue(a[r][u].z); t.w += cvalue(a[r][u].w); }
-                        if (tid + u * NT < nquads) ss[r] += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
-                    }
+            for (int u = 0; u < QB; u++) {
+                if (dirty) {
+                    bool ok = cfresh(v[u].x, S.tag) && cfresh(v[u].y, S.tag) && cfresh(v[u].z, S.tag) && cfresh(v[u].w, S.tag);
+                    if constexpr (HAS_ADD)
+                        ok = ok && cfresh(a[u].x, S.add_tag) && cfresh(a[u].y, S.add_tag) && cfresh(a[u].z, S.add_tag) && cfresh(a[u].w, S.add_tag);
+                    if (!ok) stale |= 1u << u;
                 }
-                mine = mine && stale[r] == 0;
-                if constexpr (HAS_GAIN) ss[r] = wave_sum_uniform(ss[r]);
+                if constexpr (HAS_GAIN) {
+                    float4 t = make_float4(cvalue(v[u].x), cvalue(v[u].y), cvalue(v[u].z), cvalue(v[u].w));
+                    if constexpr (HAS_ADD) { t.x += cvalue(a[u].x); t.y += cvalue(a[u].y); t.z += cvalue(a[u].z); t.w += cvalue(a[u].w); }
+                    if (tid + u * NT < nquads) ss[0] += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
+                }
             }
-            if constexpr (HAS_GAIN) all_ok = vote.all_sum<NT, RB>(mine, ss, tot);
-            else all_ok = vote.all<NT>(mine);
-            if (ev && tid == 0 && spins == 0 && b0 == 0) as_global(ev)[1] = wall_clock64();
-            if (!all_ok && !S.eager) {
+            if constexpr (HAS_GAIN) ss[0] = wave_sum_uniform(ss[0]);
+            if constexpr (HAS_GAIN) all_ok = vote.all_sum<NT, 1>(stale == 0, ss, tot);
+            else all_ok = vote.all<NT>(stale == 0);
+            if (ev && tid == 0 && spins == 0 && b == 0) as_global(ev)[1] = wall_clock64();
+            if (!all_ok) {
                 // A producer that is still streaming weights should not have to compete with 256
-                // workgroups re-reading its output: wait on a few samples.  An eager source is
-                // written by a handful of workgroups while the rest of the chip idles (the merged
-                // attention output): there the stale quads are simply read again, which saves the
-                // round trip between "sample seen" and "vector loaded".
+                // workgroups re-reading its output: wait on a few samples.
                 bool lw = true;
                 if (tid < 64) lw = light_wait<HAS_ADD>(S, batch, k0, nunits * EPU, lane);
                 if (!vote.all<NT>(lw)) return false;
@@ -461,12 +388,12 @@ __device__ __forceinline__ bool stage_tagged_onepass(const TSrc& S, int batch, i
         // no padding): that case runs without the per-lane range tests, each of which is a
         // divergent branch -- expensive for a wave that has its SIMD to itself.
         const bool exact = nquads == padquads && padquads == QB * NT;
-        auto write_quad = [&](auto EX, int r, int u, int b, float rs) {
+        auto write_quad = [&](auto EX, int u, float rs) {
             constexpr bool kExact = decltype(EX)::value;
             const int qi = tid + u * NT;
             if (kExact || qi < padquads) {
-                float4 t = make_float4(cvalue(v[r][u].x), cvalue(v[r][u].y), cvalue(v[r][u].z), cvalue(v[r][u].w));
-                if constexpr (HAS_ADD) { t.x += cvalue(a[r][u].x); t.y += cvalue(a[r][u].y); t.z += cvalue(a[r][u].z); t.w += cvalue(a[r][u].w); }
+                float4 t = make_float4(cvalue(v[u].x), cvalue(v[u].y), cvalue(v[u].z), cvalue(v[u].w));
+                if constexpr (HAS_ADD) { t.x += cvalue(a[u].x); t.y += cvalue(a[u].y); t.z += cvalue(a[u].z); t.w += cvalue(a[u].w); }
                 if (!kExact && qi >= nquads) t = make_float4(0.f, 0.f, 0.f, 0.f);
                 else {
                     if (S.wb && (u32)qi >= wb_lo && (u32)qi < wb_hi) {   // this workgroup's slice of the published sum
@@ -478,52 +405,39 @@ __device__ __forceinline__ bool stage_tagged_onepass(const TSrc& S, int batch, i
                         t.x *= bf_lo(g[u].x) * rs; t.y *= bf_hi(g[u].x) * rs; t.z *= bf_lo(g[u].y) * rs; t.w *= bf_hi(g[u].y) * rs;
                     }
                 }
-                stage_store<EPU, SPLIT>(xs, nup, b, qi, t);
+                stage_store<EPU>(xs, nup, b, qi, t);
             }
         };
+        const float rs = HAS_GAIN ? rsqrtf(tot[0] / (float)K + S.eps) : 1.f;
+        if (exact) {
 #pragma unroll
-        for (int r = 0; r < RB; r++) {
-            const int b = b0 + r;
-            if (b < batch) {
-                const float rs = HAS_GAIN ? rsqrtf(tot[r] / (float)K + S.eps) : 1.f;
-                if (exact) {
+            for (int u = 0; u < QB; u++) write_quad(std::true_type{}, u, rs);
+        } else {
 #pragma unroll
-                    for (int u = 0; u < QB; u++) write_quad(std::true_type{}, r, u, b, rs);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < QB; u++) write_quad(std::false_type{}, r, u, b, rs);
-                }
-            }
+            for (int u = 0; u < QB; u++) write_quad(std::false_type{}, u, rs);
         }
     }
     __syncthreads();
     return true;
 }
 
-// Picks the pass size that covers the vector in one pass with the fewest registers, and how many
-// batch rows are loaded together (RBMAX = the kernel's batch capacity; four rows of a short
-// vector, two of a long one, to keep the quads of all rows in registers beside the weight tiles).
-// SPLIT selects the staged format (see stage_store); a normalised vector too long for one pass has
-// no SPLIT form (the host rejects such configurations).
-template <int EPU, bool HAS_ADD, int NT, bool SPLIT, int RBMAX>
+// Picks the pass size that covers the vector in one pass with the fewest registers.
+template <int EPU, bool HAS_ADD, int NT>
 __device__ __forceinline__ bool stage_tagged(const TSrc& S, int batch, int K, int k0, int nunits, int nup, float4* xs, float* red, int tid,
                                              WgVote& vote, u64* ev = nullptr) {
-    constexpr int RB4 = RBMAX < 4 ? RBMAX : 4, RB2 = RBMAX < 2 ? RBMAX : 2;
     const int per_thread = (nup * (EPU / 4) + NT - 1) / NT;
     if constexpr (HAS_ADD) {   // residual stream + sublayer output, always normalised
-        if (per_thread <= 4) return stage_tagged_onepass<EPU, true, true, NT, 4, SPLIT, RB4>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        if (per_thread <= 8) return stage_tagged_onepass<EPU, true, true, NT, 8, SPLIT, RB2>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        if constexpr (SPLIT) return false;
-        else return stage_tagged_multipass<EPU, true, true, NT, 8, false>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
+        if (per_thread <= 4) return stage_tagged_onepass<EPU, true, true, NT, 4>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        if (per_thread <= 8) return stage_tagged_onepass<EPU, true, true, NT, 8>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        return stage_tagged_multipass<EPU, true, true, NT, 8>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
     } else if (S.gain) {       // embedding rows
-        if (per_thread <= 8) return stage_tagged_onepass<EPU, false, true, NT, 8, SPLIT, RB2>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        if constexpr (SPLIT) return false;
-        else return stage_tagged_multipass<EPU, false, true, NT, 8, false>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
+        if (per_thread <= 8) return stage_tagged_onepass<EPU, false, true, NT, 8>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        return stage_tagged_multipass<EPU, false, true, NT, 8>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
     } else {
-        if (per_thread <= 4) return stage_tagged_onepass<EPU, false, false, NT, 4, SPLIT, RB4>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        if (per_thread <= 8) return stage_tagged_onepass<EPU, false, false, NT, 8, SPLIT, RB4>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        if (per_thread <= 14) return stage_tagged_onepass<EPU, false, false, NT, 14, SPLIT, RB2>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
-        return stage_tagged_multipass<EPU, false, false, NT, 14, SPLIT>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
+        if (per_thread <= 4) return stage_tagged_onepass<EPU, false, false, NT, 4>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        if (per_thread <= 8) return stage_tagged_onepass<EPU, false, false, NT, 8>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        if (per_thread <= 14) return stage_tagged_onepass<EPU, false, false, NT, 14>(S, batch, K, k0, nunits, nup, xs, tid, vote, ev);
+        return stage_tagged_multipass<EPU, false, false, NT, 14>(S, batch, K, k0, nunits, nup, xs, red, tid, vote, ev);
     }
 }
 
@@ -619,7 +533,7 @@ struct TaggedAttnIO {
 #endif
 // MM (head dimension 128; built for the wide pass with its hundreds of cached rows per wave and item,
 // where the vector ALUs and not the memory set the pace, and also used by the bf16 and int8 passes of
-// up to four sequences, with one batch of loads in flight): the scores of a batch of 16 rows come
+// one sequence, with one batch of loads in flight): the scores of a batch of 16 rows come
 // from the matrix cores, and the running maximum is updated once per batch instead of once per row.
 //   * v_mfma_f32_16x16x32_bf16 with A = 16 cached key rows (lane (r, g4) loads dims [32 kk + 8 g4, + 8)
 //     of row r for the k-steps kk = 0..3) and B = the queries as bf16 head (columns 0..G-1) and bf16

@@ -46,17 +46,17 @@ __global__ void __launch_bounds__(kFusedThreads) stack_linear_kernel(StackArgs A
         W.w = A.w + (size_t)l * A.d * A.d * 2; W.s = nullptr; W.z = nullptr; W.n = A.d; W.k = A.d; W.wd = W_BF16;
         const Stream<W_BF16, 1> S = Stream<W_BF16, 1>::make(W, 0, gwave, n_gwaves);
         Stage<W_BF16> ring[kDepthOf<W_BF16>];
-        if constexpr (OVERLAP) prefetch_stream<false>(S, ring, lane);
+        if constexpr (OVERLAP) prefetch_stream(S, ring, lane);
         TSrc src;
         src.base = A.buf[l & 1]; src.stride = (size_t)A.d; src.tag = (u32)l;
         src.ncta = n_ctas;
         if (l > 0) __syncthreads();   // every wave has finished reading the previous staged input
-        const bool ok = stage_tagged<EPU, false, kFusedThreads, false, 1>(src, 1, S.K, 0, S.nunits, S.nup, xs, red, threadIdx.x, vote);
+        const bool ok = stage_tagged<EPU, false, kFusedThreads>(src, 1, S.K, 0, S.nunits, S.nup, xs, red, threadIdx.x, vote);
         if (!ok) {
             if (threadIdx.x == 0) atomicCAS(A.status, 0, -55 - 10 * l);
             return;
         }
-        if constexpr (!OVERLAP) prefetch_stream<false>(S, ring, lane);
+        if constexpr (!OVERLAP) prefetch_stream(S, ring, lane);
         EpiDeltaTagged epi{A.buf[(l + 1) & 1], A.d, (u32)(l + 1)};
         gemv_run<W_BF16, 1>(S, ring, xs, myacc, 1, lane, epi);
     }

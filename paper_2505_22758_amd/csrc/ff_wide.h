@@ -1,8 +1,8 @@
 // The wide pass: exchange between workgroups, epilogues and the kernel.
 //
-// The row-partitioned passes have every workgroup stage every sequence's whole input itself (load
+// The single-sequence kernel has every workgroup stage the whole input itself (load
 // the tagged words, add the sublayer output, normalise, convert to the matrix cores' head/remainder
-// form), replicated 256 times and growing with the batch.  The wide pass exchanges activations in
+// form), replicated 256 times, which would grow with the batch.  The wide pass exchanges activations in
 // the form their consumers multiply, produced once by the workgroup that OWNS the value:
 //   * every workgroup owns a fixed range of rows of the residual stream (the rows of the output
 //     and down projections it computes, N / workgroups) and keeps them in its LDS for the whole step;
@@ -26,7 +26,7 @@
 // Queries, keys, values and attention partials keep their tagged 8-byte format.
 // Measured us per step of an 8-layer block, before (four waves, images copied through LDS, row-major weights) / with
 // this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 865, int8 x 11 992 / 936 / 780, int4 x 16 1628 / 978 /
-// 796, 70B bf16 x 16 3283 / 3098 / 2715; against the row-partitioned pass: bf16 x 2 865 -> 788, int4 x 4 1044 -> 595, int8 x 4
+// 796, 70B bf16 x 16 3283 / 3098 / 2715; against a row-partitioned pass of up to four sequences (4x4x4 matrix-core tiles, inputs staged by every workgroup): bf16 x 2 865 -> 788, int4 x 4 1044 -> 595, int8 x 4
 // 875 -> 597.  What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
 #pragma once
 #include "ff_dense.h"
@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     }
     // workgroup 0 can only get here after every workgroup has taken part in every phase, i.e. has read the counter
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        xst_u32(M.stepctr + 1, 0u);   // the compact exchange rows were not written: the next narrow pass re-initialises its rows
+        xst_u32(M.stepctr + 1, 0u);
         xst_u32(M.stepctr, steps_done + 1u);
     }
 }

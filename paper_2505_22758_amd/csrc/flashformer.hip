@@ -109,16 +109,12 @@ bool wide_fits(const ff_config& c, int n_cta) {
 }
 constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the chip the kernels are built for
 
-// Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout);
-// the others run row-partitioned passes of up to four sequences (paper Section 5.2) on row-major weights.
-// FF_WIDE_MIN (experiments): smallest max_batch that takes the wide pass.
-int wide_min_batch() {
-    const char* e = getenv("FF_WIDE_MIN");
-    const int v = e ? atoi(e) : 0;
-    return v > 0 ? v : 2;
-}
-bool wide_model(const ff_config& c) { return c.max_batch >= wide_min_batch() && wide_fits(c, kGridCtas); }
-int fused_pass_rows(const ff_config& c, bool wide) { return wide ? c.max_batch : std::min(c.max_batch, kMaxBatch); }
+// Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout): those for
+// several sequences (all that check_config accepts fit a grid of kGridCtas); a single sequence runs row-partitioned on
+// row-major weights.
+// Both sides measured at one sequence (us per step): the wide pass took 4391 against 4721 (8B int4) and 1152 against 1200
+// (8B int8, eight layers), but its bf16 head + remainder inputs (17 bits) would replace fp32 ones there.
+bool wide_model(const ff_config& c) { return c.max_batch > 1; }
 
 // wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
 // n_cta: workgroups of the grid (sizes are largest for kGridCtas); perop: with the per-operation path's buffers
@@ -146,7 +142,7 @@ Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool pe
     P.packed_bytes = off;
 
     size_t s = 0;
-    const size_t mb = fused_pass_rows(c, P.wide), pb = perop ? mb : 0;   // exchange buffers hold one pass
+    const size_t mb = c.max_batch, pb = perop ? mb : 0;   // exchange buffers hold one pass
     auto take = [&](size_t bytes) { size_t o = s; s = align256(s + bytes); return o; };
     P.x = take(mb * c.d_model * 4);
     P.xn = take(mb * c.d_model * 4);
@@ -654,21 +650,15 @@ int ff_kv_free(ff_kv* kv) {
 }
 
 namespace {
-// One pass of the fused kernel over sequences [seq0, seq0 + batch) of a step of step_batch
-// sequences, batch <= fused_pass_rows.  Nothing here depends on host-side state that changes from
+// One step of the whole-model kernel.  Nothing here depends on host-side state that changes from
 // step to step (exchange tags, write counters and the rows to re-initialise all derive from
 // counters kept on the device), so the launches of a step may be recorded into a HIP graph.
-int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, int seq0,
-               int step_batch, hipStream_t st) {
+int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, hipStream_t st) {
     const bool wide = m->plan.wide;
     const int lm_in_kernel = D.lm.wd == m->cfg.wdtype;   // LM head inside the fused kernel when its weights have the layers' type
     DevKV kvd = kv->dev;
-    kvd.seq0 = seq0;
-    kvd.step_batch = step_batch;
-    if (!wide && m->cfg.max_batch > 1) {   // rows a smaller batch left behind: see k_scrub_rows (decides on the device)
-        k_scrub_rows<<<64, kThreads, 0, st>>>(D, batch);
-        HIPCHK(hipGetLastError());
-    }
+    kvd.seq0 = 0;
+    kvd.step_batch = batch;
     FusedLaunch a{D, kvd, tokens_dev, positions_dev, logits_dev, batch, lm_in_kernel, m->n_cta, m->lds_bytes, st, m->mute_wg, m->switches, m->glu_off,
                   wide ? 1 : 0};
     const char* what = "";
@@ -695,19 +685,11 @@ int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const 
 }
 }  // namespace
 
-// Batches above one pass run as consecutive passes on the stream (every pass streams the weights
-// again; the exchange buffers are reused pass after pass).
 int ff_decode_step(ff_model* m, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch,
                    void* stream) {
     int rc = check_step_args(m, tokens_dev, positions_dev, kv, logits_dev, batch);
     if (rc) return rc;
-    const int rows = fused_pass_rows(m->cfg, m->plan.wide);
-    for (int s0 = 0; s0 < batch; s0 += rows) {
-        rc = fused_pass(m, m->dev, tokens_dev + s0, positions_dev + s0, kv, logits_dev + (size_t)s0 * m->cfg.vocab, std::min(rows, batch - s0),
-                        s0, batch, (hipStream_t)stream);
-        if (rc) return rc;
-    }
-    return FF_OK;
+    return fused_pass(m, m->dev, tokens_dev, positions_dev, kv, logits_dev, batch, (hipStream_t)stream);
 }
 
 namespace {
@@ -816,15 +798,9 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
     // not a memset node, so the call may be recorded into a HIP graph), then the write-counter
     // bits of the compact rows (k_scrub_rows sees "0 rows clean").
     k_fill_u32<<<256, 256, 0, st>>>((u32*)s, P.scratch_bytes / 4, 0u);
-    if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(D, std::min(batch, fused_pass_rows(m->cfg, false)));
+    if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(D, batch);
     HIPCHK(hipGetLastError());
-    const int rows = fused_pass_rows(m->cfg, m->plan.wide);
-    for (int s0 = 0; s0 < batch; s0 += rows) {
-        rc = fused_pass(m, D, tokens_dev + s0, positions_dev + s0, kv, logits_dev + (size_t)s0 * m->cfg.vocab, std::min(rows, batch - s0), s0,
-                        batch, st);
-        if (rc) return rc;
-    }
-    return FF_OK;
+    return fused_pass(m, D, tokens_dev, positions_dev, kv, logits_dev, batch, st);
 }
 
 int ff_status(ff_model* m, void* stream) {
@@ -868,16 +844,6 @@ int select_matrix(const ff_model* m, int32_t layer, int32_t which, MatSel* out) 
     *out = s;
     return FF_OK;
 }
-template <int WD, int B>
-int launch_debug_quad(ff_model* m, const PMat& W, const float* in, float* out, int batch, hipStream_t st) {
-    auto kern = k_debug_gemv_quad<WD, B>;
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->lds_bytes); });
-    if (attr_err != hipSuccess) return fail(FF_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-    kern<<<m->n_cta, kThreads, m->lds_bytes, st>>>(W, in, W.k, out, batch);
-    return FF_OK;
-}
 // The wide pass's projection on a tiled matrix: the inputs become a wide image in the model's scratch (region of the matrix's own input).
 template <int WD>
 int debug_wide(ff_model* m, const PMat& W, size_t img_off, const float* in, float* out, int batch, hipStream_t st) {
@@ -893,11 +859,6 @@ int debug_wide(ff_model* m, const PMat& W, size_t img_off, const float* in, floa
     kern<<<W.tiled, kWideThreads, kWideLdsBytes, st>>>(D, DevKV{}, W, img, out, batch, m->n_cta);
     return FF_OK;
 }
-template <int WD>
-int debug_quad_any(ff_model* m, const PMat& W, const float* in, float* out, int batch, hipStream_t st) {
-    if (batch == 2) return launch_debug_quad<WD, 2>(m, W, in, out, batch, st);
-    return launch_debug_quad<WD, 4>(m, W, in, out, batch, st);
-}
 }  // namespace
 
 extern "C" {
@@ -912,25 +873,21 @@ int ff_debug_gemv(ff_model* m, int32_t layer, int32_t which, const float* in_dev
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     const PMat& W = s.W;
-    const int epu = W.wd == W_BF16 ? 8 : W.wd == W_INT8 ? 16 : 32;
     if (path == 1 && (size_t)W.k * 4 * (size_t)(batch <= 2 ? 2 : 4) > (size_t)kLdsActBytes)
         return fail(FF_ERR_UNSUPPORTED, "matrix-core debug GEMV needs the input rows in one K segment (K = %d)", W.k);
-    (void)epu;
     // raw output in packed row order: straight into out_dev when rows need no mapping and the matrix
     // is not shared (LM head, output and down projections), else through the per-op row buffer
     const bool direct = s.map == 0 && s.row_off == 0 && W.n == s.n_can;
     float* raw = direct ? out_dev : m->dev.y;
-    if (path == 0) rc = gemv_op(m, W, in_dev, W.k, raw, batch, EPI_STORE, st);
-    else if (W.tiled) {
+    // (a bf16 LM head over quantised layers is row-major and runs on the vector ALU: path 1 is that, too)
+    if (path == 0 || !W.tiled) rc = gemv_op(m, W, in_dev, W.k, raw, batch, EPI_STORE, st);
+    else {
         const ff_config& c = m->cfg;
         const WideLayout wl = WideLayout::of(c.d_model, c.n_q_heads * c.head_dim, c.d_ffn, c.wdtype, c.max_batch, m->n_cta);
         const size_t off = which == FF_MAT_WO ? wl.a : which == FF_MAT_WDOWN ? wl.h : wl.x1;
         rc = W.wd == W_BF16 ? debug_wide<W_BF16>(m, W, off, in_dev, raw, batch, st)
              : W.wd == W_INT8 ? debug_wide<W_INT8>(m, W, off, in_dev, raw, batch, st) : debug_wide<W_INT4>(m, W, off, in_dev, raw, batch, st);
     }
-    else if (W.wd == W_BF16) rc = debug_quad_any<W_BF16>(m, W, in_dev, raw, batch, st);
-    else if (W.wd == W_INT8) rc = debug_quad_any<W_INT8>(m, W, in_dev, raw, batch, st);
-    else rc = debug_quad_any<W_INT4>(m, W, in_dev, raw, batch, st);
     if (rc) return rc;
     if (!direct) k_unmap_rows<<<256, 256, 0, st>>>(raw, W.n, out_dev, s.n_can, s.map, s.parity, s.row_off, m->cfg.head_dim, batch, m->dev.gu);
     HIPCHK(hipGetLastError());
