@@ -917,3 +917,42 @@ def test_wide_pass_of_up_to_16_sequences_small_model():
     S = synth.TINY.replace(name="wide", n_layers=2, d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ffn=6144, vocab=3000)
     _run_teacher_forced(S, 0x250522790, synth.WDTYPE_BF16, batch=16, T0=[40, 0, 1, 130, 64, 63, 65, 9, 300, 17, 128, 5, 77, 256, 2, 33], steps=2)
     _run_teacher_forced(S, 0x250522791, synth.WDTYPE_BF16, batch=11, T0=[7, 70, 0, 129, 31, 64, 200, 1, 90, 12, 55], steps=2)
+
+
+# Sizes at which the tiled weight layout and the panels of a model for several sequences can go wrong: rows that are no
+# whole tiles (vocab), widths that are no whole iterations (1376 columns), the operand form changing between eight and
+# nine sequences, int4 rows too long for their scales to be held on chip (139264 columns), one tile and many per workgroup.
+TILED_EDGES = [
+    ("bf16-odd", synth.TINY.replace(name="tiled-odd", n_layers=2, vocab=4099), synth.WDTYPE_BF16, (1, 2, 8, 9)),
+    ("int8-odd", synth.TINY.replace(name="tiled-odd", n_layers=2, d_ffn=1376, vocab=1021), synth.WDTYPE_INT8, (1, 8, 9, 16)),
+    ("int4-groups", synth.TINY.replace(name="tiled-groups", n_layers=2, d_ffn=1408, vocab=4102), synth.WDTYPE_INT4, (2, 5, 8, 16)),
+    ("int4-long-rows", synth.TINY.replace(name="tiled-long", n_layers=1, d_model=256, n_q_heads=4, n_kv_heads=1, d_ffn=139264, vocab=515),
+     synth.WDTYPE_INT4, (3, 9)),
+]
+
+
+@pytest.mark.parametrize("shape,wdtype,batches", [c[1:] for c in TILED_EDGES], ids=[c[0] for c in TILED_EDGES])
+def test_tiled_weights_and_panels_at_the_edges(shape, wdtype, batches):
+    """Every packed matrix read back bit for bit from the tiled layout (same values as the oracle's
+    dequantisation), then steps of several batch sizes against the oracle at the bounds of the other steps."""
+    from paper_2505_22758_amd import binding
+    from oracle import oracle
+    dec = binding.Decoder(shape, wdtype, max_batch=2)
+    layers = [synth.make_layer(shape, 91, l, wdtype, "cuda:0") for l in range(shape.n_layers)]
+    head = synth.make_head(shape, 91, wdtype, "cuda:0")
+    for l, lw in enumerate(layers):
+        dec.load_layer(l, lw)
+    dec.load_head(head)
+    mats = [(l, w, layers[l][w]) for l in range(shape.n_layers) for w in synth.LAYER_MATS] + [(0, "lm_head", head["lm_head"])]
+    for l, which, m in mats:
+        ref = oracle.dequant_matrix({k: v.cpu() for k, v in m.items()})
+        out = torch.empty(*ref.shape, dtype=torch.float32, device="cuda:0")
+        binding.ff_debug_dequant(dec.model, l, which, out)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.view(np.uint32)), (l, which)
+    dec.close()
+    # at least 512 appended cache words per sequence, so that a single word rounded the other way (a rate of
+    # 1/512) stays below the floor of the bound on differing words (helpers.KV_RATE_FLOOR = 0.002)
+    words = 2 * shape.n_layers * shape.n_kv_heads * shape.head_dim
+    steps = max(2, -(-512 // words))
+    for batch in batches:
+        _run_teacher_forced(shape, 0x91 + batch, wdtype, batch=batch, T0=[(37 * b + 5) % 140 for b in range(batch)], steps=steps)
