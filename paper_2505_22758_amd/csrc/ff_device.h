@@ -45,7 +45,8 @@ enum { W_BF16 = 0, W_INT8 = 1, W_INT4 = 2 };
 //   16-byte units column by column: unit 0 of all rows, unit 1 of all rows, ...  A matrix-core operand (16
 //   rows x 4 units) is then one contiguous kilobyte and a wave's whole share of a tile one stream.  Rows
 //   are padded with zero units to whole iterations of the wide pass.  int4 words hold code 2 p in
-//   nibble p and code 2 p + 1 in nibble p + 4, so that one mask yields two codes in the halves of a word.
+//   nibble p and code 2 p + 1 in nibble p + 4, so that one mask yields two codes in the halves of a word, and are
+//   rotated left by three, which puts a code where the mantissa of a bf16 number wants it (i4_to_bf16).
 // Scales and zeros are row-major either way.
 struct PMat {
     const uint8_t* w;
@@ -83,10 +84,12 @@ __host__ __device__ inline u32 i4_tiled_word(u32 w) {
     u32 e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
     e = (e | (e >> 4)) & 0x00FF00FFu; o = (o | (o >> 4)) & 0x00FF00FFu;
     e = (e | (e >> 8)) & 0xFFFFu; o = (o | (o >> 8)) & 0xFFFFu;
-    return e | (o << 16);
+    const u32 t = e | (o << 16);
+    return (t << 3) | (t >> 29);
 }
 __host__ __device__ inline u32 i4_canonical_word(u32 w) {
     u32 r = 0;
+    w = (w >> 3) | (w << 29);
     for (int p = 0; p < 4; p++) r |= ((w >> (4 * p)) & 15u) << (8 * p) | ((w >> (16 + 4 * p)) & 15u) << (8 * p + 4);
     return r;
 }

@@ -42,9 +42,10 @@ def oracle_side(shape, seed, wdtype, batch, T0, max_ctx, quant_lm_head=True):
     return M, kv
 
 
-def hip_side(shape, seed, wdtype, batch, T0, max_ctx, n_caches=1, quant_lm_head=True, device="cuda:0"):
+def hip_side(shape, seed, wdtype, batch, T0, max_ctx, n_caches=1, quant_lm_head=True, device="cuda:0", max_batch=None):
+    """batch: sequences of the caches; max_batch: sequences the model is created for (default: the same)."""
     from paper_2505_22758_amd import binding
-    dec = binding.Decoder(shape, wdtype, max_batch=batch, quant_lm_head=quant_lm_head, device=device)
+    dec = binding.Decoder(shape, wdtype, max_batch=max_batch or batch, quant_lm_head=quant_lm_head, device=device)
     for l in range(shape.n_layers):
         lw = synth.make_layer(shape, seed, l, wdtype, device)
         dec.load_layer(l, lw)

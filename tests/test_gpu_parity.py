@@ -956,3 +956,39 @@ def test_tiled_weights_and_panels_at_the_edges(shape, wdtype, batches):
     steps = max(2, -(-512 // words))
     for batch in batches:
         _run_teacher_forced(shape, 0x91 + batch, wdtype, batch=batch, T0=[(37 * b + 5) % 140 for b in range(batch)], steps=steps)
+
+
+def _median_step_error(shape, seed, wdtype, batch, T0, n, max_batch=None):
+    """Median over sequences and n teacher-forced steps of the logits' relative L2 error against the oracle."""
+    from paper_2505_22758_amd import binding
+    M, okv = helpers.oracle_side(shape, seed, wdtype, batch, T0, T0 + n)
+    dec, caches = helpers.hip_side(shape, seed, wdtype, batch, T0, T0 + n, max_batch=max_batch)
+    toks = synth.make_tokens(shape, seed, n, batch)
+    lg = torch.zeros(batch, shape.vocab, device="cuda:0")
+    errs = []
+    for s in range(n):
+        pos = np.full((batch,), T0 + s, dtype=np.int32)
+        ref = M.decode_step(toks[s].numpy(), pos, okv)
+        binding.ff_decode_step(dec.model, toks[s].to("cuda:0"), torch.from_numpy(pos).to("cuda:0"), caches[0][0], lg, batch)
+        binding.ff_status(dec.model)
+        got = lg.cpu().numpy()
+        errs += [helpers.compare_logits(got[b:b + 1], ref[b:b + 1])[1] for b in range(batch)]
+    dec.close()
+    return float(np.median(errs))
+
+
+# One layer, so that a cache element stored on the other bf16 neighbour (on either side) reaches the logits through one
+# of the attention's rows only, and medians.
+EXACT = synth.TINY.replace(name="exact", n_layers=1, d_model=1024, d_ffn=2816, vocab=2048)
+
+
+@pytest.mark.parametrize("batch", (2, 8, 16))
+def test_int4_steps_are_as_exact_as_bf16_ones(batch):
+    """Inputs of 17 bits are what limits a step of several sequences, with int4 weights as with bf16 ones: the constant
+    that int4 codes carry through the matrix cores (and that is taken off the finished sums) must not add to that.
+    Rounding of the sums by a constant c adds about c / 2^24 relative per sum against 2^-18 of the inputs;
+    bound: one and a half times the bf16 error."""
+    S = EXACT.replace(n_q_heads=8, n_kv_heads=2, head_dim=128)
+    err = {wd: _median_step_error(S, 0x2505227d1, wd, batch, 70, 5) for wd in (synth.WDTYPE_BF16, synth.WDTYPE_INT4)}
+    print(f"batch {batch}: median relative L2 error bf16 {err[synth.WDTYPE_BF16]:.2e}, int4 {err[synth.WDTYPE_INT4]:.2e}")
+    assert err[synth.WDTYPE_INT4] <= 1.5 * err[synth.WDTYPE_BF16], err
