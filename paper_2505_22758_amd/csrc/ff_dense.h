@@ -24,7 +24,8 @@
 // Inputs are bf16 head + bf16 remainder (17 significant bits).  NC = 16: heads and remainders are
 // separate operands, 16 sequences per tile.  NC = 8: rows 0..7 of the operand are the heads and rows
 // 8..15 the remainders of 8 sequences, i.e. one multiplication and half the input bytes per k-step;
-// the two halves of the result are added when the waves' partial tiles meet.
+// the two halves of the result are added when the waves' partial tiles meet.  NC = 1: one sequence,
+// whose inputs keep the 24 bits of fp32 (as on the vector ALU): head, remainder and third part are rows 0, 1, 2.
 #pragma once
 #include "ff_kernels.h"
 
@@ -41,13 +42,15 @@ typedef __bf16 mfma_bf8 __attribute__((ext_vector_type(8)));
 template <int WD> constexpr int kWLoads = WD == W_BF16 ? 2 : 1;
 template <int WD> constexpr int kWSteps = WD == W_INT4 ? 4 : 2;
 template <int WD> constexpr int kWCols = 32 * kWSteps<WD>;
+template <int NC> constexpr int kXOps = NC == 16 ? 2 : 1;   // input operands per k-step
 // Ring depth in iterations: about 14 weight loads (14 KB) per wave in flight, i.e. 112 KB per compute unit, as far
 // as the registers go.  Twice as many measured slower everywhere (8B bf16 x 2, x 8, 70B x 16, us a pass: 14 loads 1541,
 // 1729, 5396; 28 loads 1693, 1914, 5735; 8 loads 1563, 1775, 5464): requests that wait for the memory pipe block the
-// younger wave of a SIMD, which then finishes alone, and stand in front of the next hand-over.
+// younger wave of a SIMD, which then finishes alone, and stand in front of the next hand-over.  (One sequence, 8B bf16, eight
+// layers, us per step: 8, 10, 14, 20, 28 loads 766, 762, 749, 775, 763.)
 template <int WD, int NC, int T> constexpr int kWDepth = [] {
     const int want = (14 + T * kWLoads<WD> - 1) / (T * kWLoads<WD>);
-    const int regs = 4 * (T * kWLoads<WD> + kWSteps<WD> * (NC / 8)), fit = (WD == W_INT4 ? 112 : 144) / regs;
+    const int regs = 4 * (T * kWLoads<WD> + kWSteps<WD> * kXOps<NC>), fit = (WD == W_INT4 ? 112 : 144) / regs;
     const int d = want < fit ? want : fit;
     return d < 1 ? 1 : d > 6 ? 6 : d;
 }();
@@ -92,14 +95,14 @@ struct PanelImg {
     __device__ __forceinline__ static PanelImg make(const uint8_t* img, int K, int batch, int lane) {
         const int r = lane & 15, g = lane >> 4, step = wide_step_bytes(batch);
         const int steps = (K + kWCols<WD> - 1) / kWCols<WD> * kWSteps<WD>;
-        const int piece = NC == 8 ? (2 * g + (r >> 3)) * batch + min(r & 7, batch - 1) : g * batch + min(r, batch - 1);
+        const int piece = NC == 1 ? 4 * g + min(r, 2) : NC == 8 ? (2 * g + (r >> 3)) * batch + min(r & 7, batch - 1) : g * batch + min(r, batch - 1);
         return PanelImg{__builtin_amdgcn_make_buffer_rsrc((void*)img, 0, steps * step, 0x00020000), step, piece * 16};
     }
 };
 
 template <int WD, int NC, int T>
 struct PanelRing {
-    static constexpr int D = kWDepth<WD, NC, T>, DX = D < 2 ? 2 : D, L = kWLoads<WD>, NB = kWSteps<WD> * (NC / 8);
+    static constexpr int D = kWDepth<WD, NC, T>, DX = D < 2 ? 2 : D, L = kWLoads<WD>, NP = kXOps<NC>, NB = kWSteps<WD> * NP;
     u32x4 w[D][T][L];
     u32x4 x[DX][NB];
     // Weights of iteration it.
@@ -117,8 +120,8 @@ struct PanelRing {
 #pragma unroll
         for (int k = 0; k < kWSteps<WD>; k++)
 #pragma unroll
-            for (int h = 0; h < NC / 8; h++)
-                x[slot][k * (NC / 8) + h] =
+            for (int h = 0; h < NP; h++)
+                x[slot][k * NP + h] =
                     __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(I.base, I.lane_off, (it * kWSteps<WD> + k) * I.step + h * (I.step >> 1), 0));
     }
 };
@@ -153,7 +156,7 @@ struct PanelSz {
 };
 template <int WD, int NC, int T, class Refill>
 __device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, int slot, int xslot, int it, const PanelSz& sz, int lane, mfma_f4 (&acc)[T], Refill&& refill) {
-    constexpr int NP = NC / 8;
+    constexpr int NP = kXOps<NC>;
     mfma_f4 X = {0.f, 0.f, 0.f, 0.f};
     const lds_u32* szp = nullptr;
     if constexpr (WD == W_INT4) {
@@ -292,24 +295,27 @@ __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC
     }
 }
 
-// A wave's partial tiles into LDS: [wave][tile][sequence % 4][lane].
-template <int T>
+// A wave's partial tiles into LDS: [wave][tile][sequence % 4][lane] (NC = 1: the three parts in place of four sequences).
+template <int T, int NC>
 __device__ __forceinline__ void panel_put(lds_float* red, const mfma_f4 (&acc)[T], int wave, int lane) {
+    if (NC == 1 && lane >= 16) return;
 #pragma unroll
     for (int t = 0; t < T; t++)
 #pragma unroll
-        for (int i = 0; i < 4; i++) red[((wave * T + t) * 4 + i) * 64 + lane] = acc[t][i];
+        for (int i = 0; i < (NC == 1 ? 3 : 4); i++) red[((wave * T + t) * 4 + i) * 64 + lane] = acc[t][i];
 }
-// Rows 4 q .. 4 q + 3 of tile t for sequence n, summed over the waves (and over heads and remainders).
+// Rows 4 q .. 4 q + 3 of tile t for sequence n, summed over the waves (and over the parts of the inputs).
 template <int NC, int T>
 __device__ __forceinline__ f32x4 panel_get(const lds_float* red, int t, int q, int n) {
     typedef __attribute__((address_space(3))) f32x4 lds_f4;
+    if constexpr (NC == 1) n = 0;
     const lds_f4* p = (const lds_f4*)(red + ((size_t)t * 4 + (n & 3)) * 64 + (n >> 2) * 16 + 4 * q);
     f32x4 v[kWideWaves];
 #pragma unroll
     for (int w = 0; w < kWideWaves; w++) {
         v[w] = p[w * T * 64];
         if constexpr (NC == 8) v[w] += p[w * T * 64 + 8];   // sequence n's remainders: operand row n + 8
+        if constexpr (NC == 1) v[w] += p[w * T * 64 + 16] + p[w * T * 64 + 32];   // operand rows 1 and 2
     }
     return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
 }

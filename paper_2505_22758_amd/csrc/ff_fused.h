@@ -134,18 +134,6 @@ __device__ __forceinline__ PhaseDesc phase_desc(const DevModel& M, const int* to
     return D;
 }
 
-// Attention form of the single-sequence kernel (see attn_item): 0 = row by row on the vector
-// ALU, 1 = scores of 16 cached rows at a time on the matrix cores (head dimension 128 only).  With
-// eight query heads per KV head the row-wise form is bound by the vector ALU (the 70B shape at batch
-// 1: 23.8 -> 23.3 ms per step with form 1); with four, form 1 is ahead by 0.2 % (8B bf16, batch 1,
-// context 1024) to 1.1 % (context 6144).  FF_ATTN_MODE / FF_ATTN_MODE_I4 override at build time.
-#ifndef FF_ATTN_MODE
-#define FF_ATTN_MODE 1
-#endif
-#ifndef FF_ATTN_MODE_I4
-#define FF_ATTN_MODE_I4 0   // int4 instances: form 1 was not faster
-#endif
-template <int WD> constexpr int kAttnModeOf = WD == W_INT4 ? FF_ATTN_MODE_I4 : FF_ATTN_MODE;
 template <int WD, int HD, int G>
 __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M, DevKV KV, const int* __restrict__ tokens,
                                                                      const int* __restrict__ pos, float* __restrict__ logits,
@@ -334,7 +322,7 @@ inline hipError_t launch_wide_instance(const FusedLaunch& a, const char** what) 
 template <int WD, int HD, int G>
 inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
     // (the host decides whether a pass is wide, and sizes the buffers for it; up to eight sequences share an operand tile with their remainders)
-    if (a.wide) return a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
+    if (a.wide) return a.batch == 1 ? launch_wide_instance<WD, 1, HD, G>(a, what) : a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
     if (a.batch != 1) {
         *what = "several sequences on the single-sequence kernel";
         return hipErrorInvalidValue;

@@ -83,6 +83,19 @@ __device__ __forceinline__ int attn_share_of(const int* tokens, const int* pos, 
     return 1 + (int)((u32)((u64)budget * mine / tot) / (u32)Hkv);
 }
 
+// Attention form of the single-sequence kernel (see attn_item): 0 = row by row on the vector
+// ALU, 1 = scores of 16 cached rows at a time on the matrix cores (head dimension 128 only).  With
+// eight query heads per KV head the row-wise form is bound by the vector ALU (the 70B shape at batch
+// 1: 23.8 -> 23.3 ms per step with form 1); with four, form 1 is ahead by 0.2 % (8B bf16, batch 1,
+// context 1024) to 1.1 % (context 6144).  FF_ATTN_MODE / FF_ATTN_MODE_I4 override at build time.
+#ifndef FF_ATTN_MODE
+#define FF_ATTN_MODE 1
+#endif
+#ifndef FF_ATTN_MODE_I4
+#define FF_ATTN_MODE_I4 0   // int4 instances: form 1 was not faster
+#endif
+template <int WD> constexpr int kAttnModeOf = WD == W_INT4 ? FF_ATTN_MODE_I4 : FF_ATTN_MODE;
+
 // share: workgroups per kv head of each sequence (attn_share_of), staged in LDS like the positions.
 template <int NW, int HD, int G, int MODE = 0>
 __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const DevKV& KV, const int* pos, const int* share, int batch, int layer,

@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_gemv_kernel(DevModel M, Dev
     if (threadIdx.x < kMaxBatchWide) pos_lds[threadIdx.x] = 0;
     const UDiv n_ctas = UDiv::of((u32)ncta);
     WideSync sync{nullptr, ncta, false, nullptr, 0u};
-    const WideCtx C{M, KV, pos_lds, nullptr, out, batch, 0, PH_LM, 0u, WideImg{nullptr, 0, 1, false}, nullptr, nullptr, RowRange{0, 0}};
+    const WideCtx C{M, KV, pos_lds, nullptr, out, batch, 0, PH_LM, 0u, WideImg{nullptr, 0, 1, NC}, nullptr, nullptr, RowRange{0, 0}};
     wide_project_any<WD, NC>(W, img, nullptr, nullptr, 0u, sync, C, lds, n_ctas, wave, lane, 0);
 }
 // Its input: rows of fp32 [img.batch][K] as a wide image of cols columns (those behind K: zero).

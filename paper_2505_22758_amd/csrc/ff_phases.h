@@ -155,20 +155,45 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, u32& hi, u32& lo)
     hi = pack_bf16(a, b);
     lo = pack_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
+// The same in three parts: head, remainder and the remainder's remainder, |error| <= 2^-27 |v| (both subtractions are exact).
+__device__ __forceinline__ void split3_bf16x2(float a, float b, u32& hi, u32& mid, u32& lo) {
+    hi = pack_bf16(a, b);
+    const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xFFFF0000u);
+    split_bf16x2(ra, rb, mid, lo);
+}
 // Wide pass (see ff_wide.h): a global image of a projection's inputs in the matrix cores' operand order,
 // for `batch` sequences.  A k-step (32 columns) takes wide_step_bytes(batch): 16-byte pieces (8 columns of one
-// sequence) for each of the operand's four lane groups g.  Up to eight sequences (half): group by group the
-// heads of all sequences, then their remainders (operand rows 0..7 and 8..15); more: the heads of all
-// groups, then the remainders of all groups (an operand each).
+// sequence) for each of the operand's four lane groups g.  Its form depends on nc, the sequences an operand holds:
+//   1: one sequence in three parts (operand rows 0, 1, 2), group by group, with room for a fourth piece, so that a
+//      step is 256 bytes and no load straddles a line;
+//   8: group by group the heads of all sequences, then their remainders (operand rows 0..7 and 8..15);
+//   16: the heads of all groups, then the remainders of all groups (an operand each).
 // Which 8 columns lane group g multiplies in a k-step follows from the weights it loads, 16 bytes per lane:
 // 8 << e columns (e = 0 bf16, 1 int8, 2 int4) used up in 1 << e k-steps.
-__host__ __device__ __forceinline__ int wide_step_bytes(int batch) { return 128 * batch; }
+__host__ __device__ __forceinline__ int wide_step_bytes(int batch) { return batch == 1 ? 256 : 128 * batch; }
 struct WideImg {
-    uint8_t* p; int e; int batch; bool half;
+    uint8_t* p; int e; int batch; int nc;
+    __device__ __forceinline__ int planes() const { return nc == 1 ? 3 : 2; }
     __device__ __forceinline__ uint8_t* at(int n, int plane, int col) const {
         const int j = col >> 3, unit = j >> e, step = ((unit >> 2) << e) + (j & ((1 << e) - 1)), g = unit & 3;
-        const int piece = half ? (2 * g + plane) * batch + n : (4 * plane + g) * batch + n;
+        const int piece = nc == 1 ? 4 * g + plane : nc == 8 ? (2 * g + plane) * batch + n : (4 * plane + g) * batch + n;
         return p + (size_t)step * wide_step_bytes(batch) + (piece * 16 + (col & 7) * 2);
+    }
+    // Columns col, col + 1 (col even) of sequence n.
+    __device__ __forceinline__ void put2(int n, int col, float a, float b) const {
+        u32 v[3];
+        if (nc == 1) split3_bf16x2(a, b, v[0], v[1], v[2]);
+        else split_bf16x2(a, b, v[0], v[1]);
+#pragma unroll
+        for (int pl = 0; pl < 3; pl++) if (pl < planes()) xst_u32((u32*)at(n, pl, col), v[pl]);
+    }
+    // Columns col .. col + 3 (col a multiple of four).
+    __device__ __forceinline__ void put4(int n, int col, float a, float b, float c, float d) const {
+        u32 v[3], w[3];
+        if (nc == 1) { split3_bf16x2(a, b, v[0], v[1], v[2]); split3_bf16x2(c, d, w[0], w[1], w[2]); }
+        else { split_bf16x2(a, b, v[0], v[1]); split_bf16x2(c, d, w[0], w[1]); }
+#pragma unroll
+        for (int pl = 0; pl < 3; pl++) if (pl < planes()) xst2((float*)at(n, pl, col), __uint_as_float(v[pl]), __uint_as_float(w[pl]));
     }
 };
 
@@ -805,8 +830,7 @@ __device__ void attn_merge(const DevModel& M, int b, int j, int nsplit, float* l
 // The same merge on tagged partials (fused kernel): the workgroup that computed the LAST split of
 // (b, j) gathers all splits, re-reading until every partial carries this layer's attention tag,
 // and publishes attn_o with the same tag.  Returns false on a time-out.
-// img (wide pass): the merged output goes into the output projection's input image as bf16 head +
-// remainder instead of the compact vector.
+// img (wide pass): the merged output goes into the output projection's input image instead of the compact vector.
 template <int HD, int G, int NT>
 __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, int b, int j, int nsplit, u32 tag, u32 out_cnt, float* lds, WgVote& vote, u64* ev = nullptr,
                                                   const WideImg* img = nullptr) {
@@ -889,13 +913,8 @@ __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, int b, int 
                 a1 = fmaf(__uint_as_float(r[u].z), w, a1);
             }
         }
-        if (img) {
-            u32 hi, lo;
-            split_bf16x2(a0, a1, hi, lo);
-            const int col = (j * G + g) * HD + d2;
-            xst_u32((u32*)img->at(b, 0, col), hi);
-            xst_u32((u32*)img->at(b, 1, col), lo);
-        } else {
+        if (img) img->put2(b, (j * G + g) * HD + d2, a0, a1);
+        else {
             cst2(M.cattn_o + ((size_t)b * M.Hq + (j * G + g)) * HD + d2, a0, a1, out_cnt);
         }
     }

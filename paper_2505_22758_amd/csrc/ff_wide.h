@@ -129,20 +129,13 @@ __device__ __forceinline__ float wide_residual(const WideCtx& C, int row, int n,
     f32x4 x = *(const f32x4*)xp;
     x += c;
     *(f32x4*)xp = x;
-    u32 h0, l0, h1, l1;
-    split_bf16x2(x.x * bf_lo(gw.x), x.y * bf_hi(gw.x), h0, l0);
-    split_bf16x2(x.z * bf_lo(gw.y), x.w * bf_hi(gw.y), h1, l1);
-    xst2((float*)C.out.at(n, 0, row), __uint_as_float(h0), __uint_as_float(h1));
-    xst2((float*)C.out.at(n, 1, row), __uint_as_float(l0), __uint_as_float(l1));
+    C.out.put4(n, row, x.x * bf_lo(gw.x), x.y * bf_hi(gw.x), x.z * bf_lo(gw.y), x.w * bf_hi(gw.y));
     return (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
 }
 // Packed pair q of a tiled gate/up matrix is FFN unit q; a quad of rows gives the neighbouring units f, f + 1 (f even).
 __device__ __forceinline__ void wide_swiglu(const WideCtx& C, int f, int n, const f32x4& c, bool two) {
     const float h0 = c.x / (1.0f + expf(-c.x)) * c.y, h1 = two ? c.z / (1.0f + expf(-c.z)) * c.w : 0.f;
-    u32 hi, lo;
-    split_bf16x2(h0, h1, hi, lo);
-    xst_u32((u32*)C.out.at(n, 0, f), hi);   // (a missing second unit is padding, zero in the image)
-    xst_u32((u32*)C.out.at(n, 1, f), lo);
+    C.out.put2(n, f, h0, h1);   // (a missing second unit is padding, zero in the image)
 }
 __device__ __forceinline__ void wide_epilogue(const WideCtx& C, int row, int n, const f32x4& c, int nv) {
     const int pair = row >> 1;
@@ -244,7 +237,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
             if (lane < kMaxBatchWide) rms[wave * kMaxBatchWide + lane] = t;
         }
         if (p > 0) __syncthreads();   // the previous panel's partial tiles have been read
-        panel_put<T>(red, acc, wave, lane);
+        panel_put<T, NC>(red, acc, wave, lane);
         const u32x2 rowscale = pre;
         const bool more = p + 1 < npanels;
         if (more) prefetch(p + 1);   // the next panel's first weights, while this one is finished
@@ -285,13 +278,20 @@ __device__ __forceinline__ bool wide_project_any(const PMat& W, const uint8_t* i
     return false;
 }
 
+// Attention form (see attn_item).  One sequence takes the form of the single-sequence kernel (8B bf16, eight layers, context
+// 1024 / 4096, us per step: form 0 746 / 773, 1 749 / 767, 2 755 / 782), int4 steps of up to eight sequences its row-wise
+// form, which keeps the queries' 24 bits and is ahead as well (8B int4 x 2 context 1024, x 4 context 2048: 519, 567; form 2 538, 597).
+template <int WD, int NC> constexpr int kWideAttnModeOf = NC == 1 ? kAttnModeOf<WD> : WD == W_INT4 && NC == 8 ? 0 : 2;
+
 // ---------------------------------------------------------------- the kernel
-// One launch = one step of up to NC sequences (phases as in fused_decode_kernel).
+// One launch = one step of up to NC sequences (phases as in fused_decode_kernel).  One sequence has an instance of its own:
+// its step on a model for several sequences is as exact as on a model for one.
 // n_lm: 1 = the LM head runs here, 0 = launched separately.
 template <int WD, int NC, int HD, int G>
 __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, DevKV KV, const int* __restrict__ tokens, const int* __restrict__ pos,
-                                                                   float* __restrict__ logits, int batch, int lm_in_kernel, int ncta, int mute_wg, int switches) {
+                                                                   float* __restrict__ logits, int n_seq, int lm_in_kernel, int ncta, int mute_wg, int switches) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int batch = NC == 1 ? 1 : n_seq;
     if (!inputs_ok(M, KV, tokens, pos)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicExch(M.status, kStatusRange);
         return;
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     constexpr int kImgE = WD == W_BF16 ? 0 : WD == W_INT8 ? 1 : 2;
     const RowRange own = wide_rows(M.d, n_ctas);
     auto block = [&](int l) { return M.wimg + (size_t)(M.wring == 1 ? 0 : l) * WL.bytes; };
-    auto image = [&](uint8_t* p) { return WideImg{p, kImgE, batch, NC == 8}; };
+    auto image = [&](uint8_t* p) { return WideImg{p, kImgE, batch, NC}; };
     auto timed = [&](int ph, int ev) { if (M.dbg && blockIdx.x == 0 && threadIdx.x == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64(); };
     __syncthreads();
     WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own};
@@ -348,8 +348,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             for (int i = 0; i < 4; i++) {
                 const int pad = wide_img_cols(widths[i], WD) - widths[i];   // (even)
                 const WideImg im = image(M.wimg + (size_t)l * WL.bytes + offs[i]);
-                for (int e = threadIdx.x; e < pad * batch; e += kWideThreads)   // (batch x pad / 2 pairs of columns x 2 planes)
-                    xst_u32((u32*)im.at(e % batch, (e / batch) & 1, widths[i] + 2 * (e / batch >> 1)), 0u);
+                for (int e = threadIdx.x; e < pad / 2 * batch; e += kWideThreads) im.put2(e % batch, widths[i] + 2 * (e / batch), 0.f, 0.f);
             }
     }
     sync.arrive(ebase, lane);
@@ -373,7 +372,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             const WideImg ai = image(blk + WL.a);
             u64* aev = M.dbg && l == 1 ? M.dbg + (size_t)(4 * M.L + 1) * kEvSlots + (size_t)ncta * 32 + ((size_t)blockIdx.x * 5 + 4) * 8 : nullptr;
             if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
-            if (!attention_phase_tagged<kWideWaves, HD, G, 2>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
+            if (!attention_phase_tagged<kWideWaves, HD, G, kWideAttnModeOf<WD, NC>>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
                                                               n_ctas, vote, aev, &ai)) return;
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
             sync.arrive(e0 + 1u, lane);

@@ -112,8 +112,9 @@ constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the
 // Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout): those for
 // several sequences (all that check_config accepts fit a grid of kGridCtas); a single sequence runs row-partitioned on
 // row-major weights.
-// Both sides measured at one sequence (us per step): the wide pass took 4391 against 4721 (8B int4) and 1152 against 1200
-// (8B int8, eight layers), but its bf16 head + remainder inputs (17 bits) would replace fp32 ones there.
+// Both sides measured at one sequence, which keeps its inputs' 24 bits on either (8B, eight layers, context 1024, us per step,
+// row-partitioned / wide): bf16 737 / 749, int8 556 / 548, int4 580 / 503; the quantised models for one sequence stay where
+// their results are what they were.
 bool wide_model(const ff_config& c) { return c.max_batch > 1; }
 
 // wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
@@ -853,7 +854,7 @@ int debug_wide(ff_model* m, const PMat& W, size_t img_off, const float* in, floa
     std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kWideLdsBytes); });
     if (attr_err != hipSuccess) return fail(FF_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
     uint8_t* img = m->dev.wimg + img_off;
-    wide_image_kernel<<<256, 256, 0, st>>>(WideImg{img, WD == W_BF16 ? 0 : WD == W_INT8 ? 1 : 2, batch, true}, in, W.k, wide_img_cols(W.k, WD));
+    wide_image_kernel<<<256, 256, 0, st>>>(WideImg{img, WD == W_BF16 ? 0 : WD == W_INT8 ? 1 : 2, batch, 8}, in, W.k, wide_img_cols(W.k, WD));
     DevModel D = m->dev;
     D.V = W.n;   // rows of the output
     kern<<<W.tiled, kWideThreads, kWideLdsBytes, st>>>(D, DevKV{}, W, img, out, batch, m->n_cta);

@@ -79,7 +79,7 @@ def compare_logits(got: np.ndarray, ref: np.ndarray):
     return max_abs, rel_l2, same
 
 
-def both_sides_gpu_generated(shape, seed, wdtype, batch, T0, max_ctx, n_caches=1, quant_lm_head=True, device="cuda:0"):
+def both_sides_gpu_generated(shape, seed, wdtype, batch, T0, max_ctx, n_caches=1, quant_lm_head=True, device="cuda:0", max_batch=None):
     """Full-size set-up: every tensor is produced once by the seeded generators on the GPU (fast),
     handed to the HIP loader, and copied to the host for the oracle.  The generators are
     bit-identical on both devices, so this equals generating twice."""
@@ -89,7 +89,7 @@ def both_sides_gpu_generated(shape, seed, wdtype, batch, T0, max_ctx, n_caches=1
     def to_cpu(obj):
         return {k: to_cpu(v) for k, v in obj.items()} if isinstance(obj, dict) else obj.cpu()
 
-    dec = binding.Decoder(shape, wdtype, max_batch=batch, quant_lm_head=quant_lm_head, device=device)
+    dec = binding.Decoder(shape, wdtype, max_batch=max_batch or batch, quant_lm_head=quant_lm_head, device=device)
     cpu_layers = []
     for l in range(shape.n_layers):
         lw = synth.make_layer(shape, seed, l, wdtype, device)

@@ -91,19 +91,20 @@ def oracle_bits_to_f64(a):
 
 
 def _run_teacher_forced(shape, seed, wdtype, batch, T0, steps, check_kv=True, gpu_generated=False, quant_lm_head=True, perop_steps=None,
-                        capsys=None, attention_by_length=True):
+                        capsys=None, attention_by_length=True, max_batch=None):
     """Teacher-forced decoding on both sides; every logit of every step is compared.  perop_steps
     limits how many steps the per-operation path runs as well (it shares no kernels' schedule with
-    the fused one; long runs check it on their first steps only)."""
+    the fused one; long runs check it on their first steps only).  max_batch: sequences the model is
+    created for (default: those of the step)."""
     from paper_2505_22758_amd import binding
     T0s = helpers.prefill_lengths(T0, batch)   # one prefill length for all sequences, or one each
     max_ctx = max(T0s) + steps + 3
     perop_steps = steps if perop_steps is None else perop_steps
     if gpu_generated:
-        M, okv, dec, caches = helpers.both_sides_gpu_generated(shape, seed, wdtype, batch, T0, max_ctx, n_caches=2, quant_lm_head=quant_lm_head)
+        M, okv, dec, caches = helpers.both_sides_gpu_generated(shape, seed, wdtype, batch, T0, max_ctx, n_caches=2, quant_lm_head=quant_lm_head, max_batch=max_batch)
     else:
         M, okv = helpers.oracle_side(shape, seed, wdtype, batch, T0, max_ctx, quant_lm_head=quant_lm_head)
-        dec, caches = helpers.hip_side(shape, seed, wdtype, batch, T0, max_ctx, n_caches=2, quant_lm_head=quant_lm_head)
+        dec, caches = helpers.hip_side(shape, seed, wdtype, batch, T0, max_ctx, n_caches=2, quant_lm_head=quant_lm_head, max_batch=max_batch)
     if not attention_by_length:
         binding.ff_debug_set_attention_balance(dec.model, False)
     toks = synth.make_tokens(shape, seed, steps, batch)
@@ -459,7 +460,7 @@ def test_two_models_interleaved_on_a_side_stream():
 def _run_changing_batches(nseq, sizes, wdtype=synth.WDTYPE_BF16):
     from paper_2505_22758_amd import binding
     from oracle import oracle
-    shape, seed, T0 = synth.TINY, 0x77, 20
+    shape, seed, T0 = (synth.TINY.replace(d_ffn=1408) if wdtype == synth.WDTYPE_INT4 else synth.TINY), 0x77, 20   # (whole int4 groups)
     max_ctx = T0 + len(sizes) + 2
     layers = [synth.make_layer(shape, seed, l, wdtype, "cpu") for l in range(shape.n_layers)]
     M = oracle.OracleModel(shape, layers, synth.make_head(shape, seed, wdtype, "cpu"))
@@ -496,13 +497,13 @@ def test_batch_size_changing_from_step_to_step():
     _run_changing_batches(4, [4, 1, 1, 1, 1, 4, 2, 2, 2, 2, 3, 1, 4, 4, 1, 1, 1, 1, 1, 1, 1, 1, 2])
 
 
-def test_wide_and_row_partitioned_steps_alternate_on_one_model():
-    """A model created for 16 sequences stepped with batches on both sides of the wide pass's
-    threshold: wide steps leave the compact exchange rows of the other paths untouched (those are
-    re-initialised before the next small batch), small steps leave the wide pass's epochs alone."""
+def test_steps_of_all_operand_forms_alternate_on_one_model():
+    """A model created for 16 sequences stepped with batches on both sides of the changes of operand form
+    (one sequence, up to eight, up to sixteen), whose images are laid out differently in the same place: a
+    step must not be served what another form left there.  All weight formats."""
     _run_changing_batches(16, [6, 1, 16, 4, 9, 2, 5, 5, 1, 1, 12, 3, 16])
-    # int8: the wide pass from four sequences on
     _run_changing_batches(16, [5, 1, 4, 3, 16, 2, 4, 1, 9, 3], wdtype=synth.WDTYPE_INT8)
+    _run_changing_batches(16, [8, 9, 1, 8, 16, 1, 2, 9], wdtype=synth.WDTYPE_INT4)
 
 
 def _run_sequences_stopping_early(nseq, stops, steps, wdtype=synth.WDTYPE_BF16, quant_lm_head=True, perop=False):
@@ -920,21 +921,22 @@ def test_wide_pass_of_up_to_16_sequences_small_model():
 
 
 # Sizes at which the tiled weight layout and the panels of a model for several sequences can go wrong: rows that are no
-# whole tiles (vocab), widths that are no whole iterations (1376 columns), the operand form changing between eight and
-# nine sequences, int4 rows too long for their scales to be held on chip (139264 columns), one tile and many per workgroup.
+# whole tiles (vocab), widths that are no whole iterations (1376 columns), the operand form changing between one, two and
+# eight and nine sequences, int4 rows too long for their scales to be held on chip (139264 columns), one tile and many per workgroup.
 TILED_EDGES = [
     ("bf16-odd", synth.TINY.replace(name="tiled-odd", n_layers=2, vocab=4099), synth.WDTYPE_BF16, (1, 2, 8, 9)),
     ("int8-odd", synth.TINY.replace(name="tiled-odd", n_layers=2, d_ffn=1376, vocab=1021), synth.WDTYPE_INT8, (1, 8, 9, 16)),
-    ("int4-groups", synth.TINY.replace(name="tiled-groups", n_layers=2, d_ffn=1408, vocab=4102), synth.WDTYPE_INT4, (2, 5, 8, 16)),
+    ("int4-groups", synth.TINY.replace(name="tiled-groups", n_layers=2, d_ffn=1408, vocab=4102), synth.WDTYPE_INT4, (1, 2, 5, 8, 16)),
     ("int4-long-rows", synth.TINY.replace(name="tiled-long", n_layers=1, d_model=256, n_q_heads=4, n_kv_heads=1, d_ffn=139264, vocab=515),
-     synth.WDTYPE_INT4, (3, 9)),
+     synth.WDTYPE_INT4, (1, 3, 9)),
 ]
 
 
 @pytest.mark.parametrize("shape,wdtype,batches", [c[1:] for c in TILED_EDGES], ids=[c[0] for c in TILED_EDGES])
 def test_tiled_weights_and_panels_at_the_edges(shape, wdtype, batches):
     """Every packed matrix read back bit for bit from the tiled layout (same values as the oracle's
-    dequantisation), then steps of several batch sizes against the oracle at the bounds of the other steps."""
+    dequantisation), then steps of several batch sizes, each on a model created for 16 sequences, against the
+    oracle at the bounds of the other steps."""
     from paper_2505_22758_amd import binding
     from oracle import oracle
     dec = binding.Decoder(shape, wdtype, max_batch=2)
@@ -955,7 +957,7 @@ def test_tiled_weights_and_panels_at_the_edges(shape, wdtype, batches):
     words = 2 * shape.n_layers * shape.n_kv_heads * shape.head_dim
     steps = max(2, -(-512 // words))
     for batch in batches:
-        _run_teacher_forced(shape, 0x91 + batch, wdtype, batch=batch, T0=[(37 * b + 5) % 140 for b in range(batch)], steps=steps)
+        _run_teacher_forced(shape, 0x91 + batch, wdtype, batch=batch, T0=[(37 * b + 5) % 140 for b in range(batch)], steps=steps, max_batch=16)
 
 
 def _median_step_error(shape, seed, wdtype, batch, T0, n, max_batch=None):
@@ -992,3 +994,17 @@ def test_int4_steps_are_as_exact_as_bf16_ones(batch):
     err = {wd: _median_step_error(S, 0x2505227d1, wd, batch, 70, 5) for wd in (synth.WDTYPE_BF16, synth.WDTYPE_INT4)}
     print(f"batch {batch}: median relative L2 error bf16 {err[synth.WDTYPE_BF16]:.2e}, int4 {err[synth.WDTYPE_INT4]:.2e}")
     assert err[synth.WDTYPE_INT4] <= 1.5 * err[synth.WDTYPE_BF16], err
+
+
+@pytest.mark.parametrize("wdtype", (synth.WDTYPE_BF16, synth.WDTYPE_INT8, synth.WDTYPE_INT4), ids=("bf16", "int8", "int4"))
+@pytest.mark.parametrize("heads", ((8, 2, 64), (8, 2, 128), (8, 1, 128)), ids=("hd64-g4", "hd128-g4", "hd128-g8"))
+def test_one_sequence_is_as_exact_on_a_model_for_several(heads, wdtype):
+    """A step of one sequence keeps fp32 inputs (24 bits, and the queries of the models for one sequence) whatever
+    number of sequences its model was created for.  Inputs of 17 bits (bf16 head + remainder) are off by up to 2^-18
+    each, three times and more the error of the models for one sequence, whose exchange words carry 22 mantissa bits;
+    bound: one and a half times that error."""
+    hq, hkv, hd = heads
+    S = EXACT.replace(n_q_heads=hq, n_kv_heads=hkv, head_dim=hd)
+    err = {mb: _median_step_error(S, 0x2505227d0, wdtype, 1, 70, 9, max_batch=mb) for mb in (1, 16)}
+    print(f"heads {heads} wd={wdtype}: median relative L2 error, max_batch 1: {err[1]:.2e}, 16: {err[16]:.2e}")
+    assert err[16] <= 1.5 * err[1], err
