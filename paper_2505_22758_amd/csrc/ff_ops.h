@@ -101,95 +101,222 @@ __global__ void __launch_bounds__(kThreads) op_gemv(PMat W, const float* in, int
         op_gemv_body<WD, B>(W, src, batch, lds, epi);
     }
 }
-// The same on a tiled matrix (models for several sequences): a workgroup multiplies the tiles of its own
-// rows, its four waves taking every fourth block of four units; lane (r, g) works on unit g of row r on the
-// vector ALU, the inputs come from LDS (as much of K at a time as fits), the lanes g and the waves are added at the end.
-constexpr int kOpTileBlocks = 4;   // 1 KB blocks a wave has in flight
-template <int WD, int B>
-__global__ void __launch_bounds__(kThreads) op_gemv_tiled(PMat W, const float* in, int in_stride, float* out, int batch, int epi_kind, const int* skip_tokens) {
+// The same on a tiled matrix (models for several sequences), fp32 inputs on the vector ALU.  A workgroup works on its own rows
+// in panels of T tiles; its eight waves take every eighth 1 KB block (four units of a tile's rows) of all tiles of the panel,
+// lane (r, g) multiplying unit g of row r; the lanes g and the waves are added at the end.
+//   * a wave keeps D blocks per tile in flight, requested before the inputs are staged and again behind their products;
+//   * as much of K as fits is staged at a time; the tiles' sums stay in registers from segment to segment, so
+//     an input that needs several segments is staged once per panel;
+//   * a group of eight staged columns is read once for all tiles of the panel, four neighbouring lanes' worth per 64 bytes;
+//   * RUNS (int4, rows of whole runs of four groups): a wave takes runs of four blocks, whose scales are one 8-byte load
+//     per row; loads of single scales touch 16 cache lines per kilobyte of weights.
+// What bounds it: at one and two sequences the stream and the launches, at four the LDS reads and the conversions.  Against the
+// form that waited for four blocks at a time and staged the inputs anew for every tile, and against row-major op_gemv
+// (us per step, 8B, eight layers, context 1024, before / now / row-major):
+//   bf16 x 1 2530 / 987 / 975, x 2 2827 / 1044 / 1078, x 4 3762 / 1146 / 1401; int8 x 1 1673 / 749 / 758, x 2 2067 / 817 / 910,
+//   x 4 2757 / 1008 / 1269; int4 x 1 1454 / 784 / 763, x 2 1732 / 867 / 945, x 4 2430 / 1054 / 1333.
+template <int WD, int T> constexpr int kOpDepth = T == 4 ? 4 : 8;
+template <int WD, int B, int T, bool RUNS>
+__global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const float* in, int in_stride, float* out, int batch, int epi_kind, const int* skip_tokens) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    constexpr int EPU = WTraits<WD>::EPU, COLS = 4 * EPU;   // columns of a block
-    float* xs = (float*)lds;                                // [B][seg]
-    float* red = (float*)(lds + kLdsActBytes);              // [wave][16 rows][B]
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4;
-    const int padk = (int)(W.row_bytes() / 16) * EPU;
-    const int seg = min(padk, kLdsActBytes / 4 / B / COLS * COLS), nseg = (padk + seg - 1) / seg;
-    const PMat::Rows rr = W.cta_rows(blockIdx.x);
-    for (int t0 = rr.r0; t0 < rr.r1; t0 += 16) {
-        const int nt = min(rr.r1 - t0, 16), row = t0 + min(lane & 15, nt - 1);
-        size_t stride;
-        const uint8_t* wp = W.w + W.row_off(row, &stride);
-        float acc[B];
+    constexpr int EPU = WTraits<WD>::EPU, COLS = 4 * EPU, D = kOpDepth<WD, T>;
+    constexpr int kSegIters = kLdsActBytes / 4 / (kWideWaves * COLS * B) / D * D;   // blocks of a wave per segment
+    constexpr int kSegCols = kSegIters * kWideWaves * COLS;
+    static_assert(kSegIters >= D, "a segment holds a whole ring");
+    f32x4* xs = (f32x4*)lds;                     // [B][segment's blocks][quad of a unit][g]
+    float* red = (float*)(lds + kLdsActBytes);   // [wave][tile][16 rows][B]
+    float* xsum = red + kWideWaves * T * 16 * B;  // int4: [B][segment's blocks][g], sums of the units' inputs
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, g = lane >> 4;
+    const int nblk = (int)(W.row_bytes() / 64), nseg = (nblk * COLS + kSegCols - 1) / kSegCols;
+    PMat::Rows rr = W.cta_rows(blockIdx.x);
+    rr.r0 = __builtin_amdgcn_readfirstlane(rr.r0);   // (the 64-bit division leaves them in vector registers, and a load
+    rr.r1 = __builtin_amdgcn_readfirstlane(rr.r1);   //  whose scalar offset depends on one becomes a loop over the lanes)
+    const int np = (rr.r1 - rr.r0 + 16 * T - 1) / (16 * T);   // (0: no rows)
+    const WaveIters I = WaveIters::of(nblk, wave);
+    PanelSrc<T> S;
+    u32x4 w[D][T];
+    // scales and zeros of the slots: one by one, or (RUNS) of four slots at a time, 8 bytes each, with the last of the four
+    constexpr bool I4 = WD == W_INT4;
+    constexpr int NS = !I4 ? 1 : RUNS ? D / 2 : D, NT = I4 ? T : 1;
+    u32 sc[NS][NT], zp[NS][NT];
+    int row[T];
+    const int ng = W.k / 128;
+    const int n_it = RUNS ? 4 * ((ng / 4 - wave + kWideWaves - 1) / kWideWaves) : I.n;   // this wave's blocks
+    auto block = [&](int i) {   // (past the end: the last run or block again, for a wave that has none one in range)
+        if constexpr (RUNS) return min((((max(min(i, n_it - 4 + (i & 3)), i & 3) >> 2) * kWideWaves + wave) << 2) + (i & 3), ng - 4 + (i & 3));
+        else return I.at(i);
+    };
+    auto load = [&](int slot, int i) {
+        const int it = block(i);
 #pragma unroll
-        for (int b = 0; b < B; b++) acc[b] = 0.f;
-        for (int s = 0; s < nseg; s++) {
-            const int k0 = s * seg, nk = min(seg, padk - k0);
-            if (nseg > 1 || t0 == rr.r0) {
-                __syncthreads();
-                for (int b = 0; b < batch; b++)
-                    for (int i = threadIdx.x; i < nk; i += kThreads) xs[b * seg + i] = k0 + i < W.k ? as_global(in)[(size_t)b * in_stride + k0 + i] : 0.f;
-                __syncthreads();
+        for (int t = 0; t < T; t++) {
+            w[slot][t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S.base, S.lane_off[t], S.tile[t] + (u32)it * S.step[t], 2));
+            if constexpr (I4 && !RUNS) {
+                const size_t e = (size_t)row[t] * ng + it;
+                sc[slot][t] = as_global(W.s)[e]; zp[slot][t] = as_global(W.z)[e];
+            } else if constexpr (RUNS) if (slot % 4 == 3) {
+                const size_t e = (size_t)row[t] * ng + (it - 3);
+                const u32x2 a = *as_global((const u32x2*)(W.s + e)), z = *as_global((const u32x2*)(W.z + e));
+                sc[slot / 4 * 2][t] = a.x; sc[slot / 4 * 2 + 1][t] = a.y; zp[slot / 4 * 2][t] = z.x; zp[slot / 4 * 2 + 1][t] = z.y;
             }
-            const int j0 = k0 / COLS, nj = nk / COLS;
-            for (int j = wave; j < nj; j += kWaves * kOpTileBlocks) {
-                u32x4 w[kOpTileBlocks];
+        }
+    };
+    auto scale_of = [&](const u32 (&v)[NS][NT], int slot, int t) { return f16_to_f((f16_t)(RUNS ? v[slot / 2][t] >> (16 * (slot & 1)) : v[slot][t])); };
+    auto prefetch = [&](int p) {
+        const int p0 = rr.r0 + 16 * T * p;
+        S = PanelSrc<T>::make(W, p0, rr.r1, lane);
 #pragma unroll
-                for (int u = 0; u < kOpTileBlocks; u++) w[u] = ldg_stream(wp + (size_t)(4 * (j0 + min(j + u * kWaves, nj - 1)) + g) * stride);
+        for (int t = 0; t < T; t++) {   // (rows as PanelSrc repeats them)
+            const int t0 = p0 + 16 * t < rr.r1 ? p0 + 16 * t : p0;
+            row[t] = t0 + min(r, min(rr.r1 - t0, 16) - 1);
+        }
 #pragma unroll
-                for (int u = 0; u < kOpTileBlocks; u++) {
-                    const int jj = j + u * kWaves;
-                    if (jj >= nj) break;
-                    float sc = 1.f, zp = 0.f;
-                    if constexpr (WD == W_INT4) {
-                        const size_t e = (size_t)row * (W.k / 128) + j0 + jj;
-                        sc = f16_to_f(as_global(W.s)[e]); zp = f16_to_f(as_global(W.z)[e]);
-                    }
+        for (int j = 0; j < D; j++) load(j, j);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto stage = [&](int seg) {   // ends with a barrier
+        const int k0 = seg * kSegCols, nq = min(kSegCols, nblk * COLS - k0) / 4;   // quads of a row
+        for (int b = 0; b < batch; b++) {
+            const float* src = in + (size_t)b * in_stride + k0;
+            for (int q0 = threadIdx.x; q0 < nq; q0 += kWideThreads * 4) {
+                f32x4 v[4];
 #pragma unroll
-                    for (int b = 0; b < B; b++) {
-                        const float4* x = (const float4*)(xs + min(b, batch - 1) * seg + jj * COLS + g * EPU);
-                        if constexpr (WD == W_BF16) acc[b] = dot_bf16(w[u], x[0], x[1], acc[b]);
-                        else if constexpr (WD == W_INT8)
-                            acc[b] = dot_i8x4(w[u].w, x[3], dot_i8x4(w[u].z, x[2], dot_i8x4(w[u].y, x[1], dot_i8x4(w[u].x, x[0], acc[b]))));
-                        else {   // (code - zero is exact; the sum of the group's share is scaled)
-                            const u32 ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
-                            float t = 0.f;
+                for (int u = 0; u < 4; u++) {
+                    const int c = 4 * (q0 + u * kWideThreads);
+                    v[u] = f32x4{0.f, 0.f, 0.f, 0.f};   // (columns behind the row's end)
+                    if (k0 + c < W.k && c < 4 * nq) v[u] = *as_global((const f32x4*)(src + c));
+                }
 #pragma unroll
-                            for (int q = 0; q < 4; q++) {
-                                const u32 c = i4_canonical_word(ww[q]);
-                                const float4 x0 = x[2 * q], x1 = x[2 * q + 1];
-                                t = fmaf((float)(c & 15u) - zp, x0.x, t); t = fmaf((float)((c >> 4) & 15u) - zp, x0.y, t);
-                                t = fmaf((float)((c >> 8) & 15u) - zp, x0.z, t); t = fmaf((float)((c >> 12) & 15u) - zp, x0.w, t);
-                                t = fmaf((float)((c >> 16) & 15u) - zp, x1.x, t); t = fmaf((float)((c >> 20) & 15u) - zp, x1.y, t);
-                                t = fmaf((float)((c >> 24) & 15u) - zp, x1.z, t); t = fmaf((float)(c >> 28) - zp, x1.w, t);
-                            }
-                            acc[b] = fmaf(sc, t, acc[b]);
-                        }
-                    }
+                for (int u = 0; u < 4; u++) {
+                    const int c = 4 * (q0 + u * kWideThreads);
+                    if (c < 4 * nq) xs[(size_t)b * (kSegCols / 4) + c / COLS * (COLS / 4) + c % EPU / 4 * 4 + c % COLS / EPU] = v[u];
                 }
             }
         }
-        if constexpr (WD == W_INT8) {
-            const float rs = f16_to_f(as_global(W.s)[row]);
-#pragma unroll
-            for (int b = 0; b < B; b++) acc[b] *= rs;
-        }
-#pragma unroll
-        for (int b = 0; b < B; b++) {
-            acc[b] += __shfl_xor(acc[b], 16);
-            acc[b] += __shfl_xor(acc[b], 32);
-            if (lane < 16) red[(wave * 16 + lane) * B + b] = acc[b];
-        }
         __syncthreads();
-        for (int i = threadIdx.x; i < nt * batch; i += kThreads) {
-            const int r = i % nt, b = i / nt;
+        if constexpr (WD == W_INT4) {
+            const int nu = 4 * nq / EPU;   // units of a row
+            for (int i = threadIdx.x; i < nu * batch; i += kWideThreads) {
+                const int b = i / nu, u = i - b * nu;
+                const f32x4* q = xs + (size_t)b * (kSegCols / 4) + u / 4 * (COLS / 4) + u % 4;
+                f32x4 v = q[0];
+#pragma unroll
+                for (int k = 1; k < EPU / 4; k++) v += q[4 * k];
+                xsum[b * (kSegCols / EPU) + u] = (v.x + v.y) + (v.z + v.w);
+            }
+            __syncthreads();
+        }
+    };
+    float acc[T][B];
+    // Block of ring slot `slot`, which is block `blk` of the staged segment.
+    auto multiply = [&](int slot, int blk) {
+        const f32x4* xb = xs + (size_t)blk * (COLS / 4) + g;
+        float part[T][B];   // int4: sum of code x input
+        if constexpr (WD == W_INT4) {
+#pragma unroll
+            for (int t = 0; t < T; t++)
+#pragma unroll
+                for (int b = 0; b < B; b++) part[t][b] = 0.f;
+        }
+#pragma unroll
+        for (int c8 = 0; c8 < EPU / 8; c8++) {
+            f32x4 x[B][2];
+#pragma unroll
+            for (int b = 0; b < B; b++)
+#pragma unroll
+                for (int h = 0; h < 2; h++) x[b][h] = xb[(size_t)min(b, batch - 1) * (kSegCols / 4) + (2 * c8 + h) * 4];
+#pragma unroll
+            for (int t = 0; t < T; t++) {
+                float f[8];
+                if constexpr (WD == W_BF16) {
+#pragma unroll
+                    for (int i = 0; i < 4; i++) { f[2 * i] = bf_lo(w[slot][t][i]); f[2 * i + 1] = bf_hi(w[slot][t][i]); }
+                } else if constexpr (WD == W_INT8) {
+#pragma unroll
+                    for (int i = 0; i < 8; i++) f[i] = (float)(int)(int8_t)(w[slot][t][2 * c8 + i / 4] >> (8 * (i & 3)));
+                } else {
+                    const u32 v = __builtin_amdgcn_alignbit(w[slot][t][c8], w[slot][t][c8], 3);
+                    const u32 e = v & 0x0F0F0F0Fu, o = (v >> 4) & 0x0F0F0F0Fu;   // bytes: codes 0, 4, 1, 5 and 2, 6, 3, 7
+                    f[0] = (float)(e & 0xFFu); f[4] = (float)((e >> 8) & 0xFFu); f[1] = (float)((e >> 16) & 0xFFu); f[5] = (float)(e >> 24);
+                    f[2] = (float)(o & 0xFFu); f[6] = (float)((o >> 8) & 0xFFu); f[3] = (float)((o >> 16) & 0xFFu); f[7] = (float)(o >> 24);
+                }
+#pragma unroll
+                for (int b = 0; b < B; b++)
+#pragma unroll
+                    for (int i = 0; i < 8; i++) {
+                        float& a = WD == W_INT4 ? part[t][b] : acc[t][b];
+                        a = fmaf(f[i], x[b][i >> 2][i & 3], a);
+                    }
+            }
+        }
+        if constexpr (WD == W_INT4) {   // sum s (n - z) x of the unit, as in stage_fma
+#pragma unroll
+            for (int b = 0; b < B; b++) {
+                const float xu = xsum[min(b, batch - 1) * (kSegCols / EPU) + 4 * blk + g];
+#pragma unroll
+                for (int t = 0; t < T; t++)
+                    acc[t][b] = fmaf(scale_of(sc, slot, t), fmaf(-scale_of(zp, slot, t), xu, part[t][b]), acc[t][b]);
+            }
+        }
+        // (pinned here: nothing else keeps a block's products from being sunk behind the refills, with all their inputs live)
+#pragma unroll
+        for (int t = 0; t < T; t++)
+#pragma unroll
+            for (int b = 0; b < B; b++) asm volatile("" : "+v"(acc[t][b]));
+    };
+    if (np > 0) prefetch(0);
+    for (int p = 0; p < np; p++) {
+        const int p0 = rr.r0 + 16 * T * p;
+#pragma unroll
+        for (int t = 0; t < T; t++)
+#pragma unroll
+            for (int b = 0; b < B; b++) acc[t][b] = 0.f;
+        for (int seg = 0; seg < nseg; seg++) {
+            if (nseg > 1 || p == 0) {
+                if (seg + p > 0) __syncthreads();   // the previous segment has been multiplied
+                stage(seg);
+            }
+            const int i0 = seg * kSegIters, i1 = min(i0 + kSegIters, n_it), b0 = i0 * kWideWaves;   // (b0: the segment's first block)
+            int i = i0;
+            for (; i + D <= i1; i += D) {
+#pragma unroll
+                for (int j = 0; j < D; j++) {
+                    multiply(j, block(i + j) - b0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load(j, i + j + D);   // (past the end: the last one again)
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < D - 1; j++)   // (the end of the rows; whole rings before it)
+                if (i + j < i1) {
+                    multiply(j, block(i + j) - b0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
+        if (p > 0) __syncthreads();   // the previous panel's sums have been read
+#pragma unroll
+        for (int t = 0; t < T; t++)
+#pragma unroll
+            for (int b = 0; b < B; b++) {
+                float v = acc[t][b];
+                v += __shfl_xor(v, 16);
+                v += __shfl_xor(v, 32);
+                if (lane < 16) red[((wave * T + t) * 16 + r) * B + b] = v;
+            }
+        if (p + 1 < np) prefetch(p + 1);
+        __syncthreads();
+        const int nr = min(16 * T, rr.r1 - p0);
+        for (int i = threadIdx.x; i < nr * batch; i += kWideThreads) {
+            const int q = i % nr, b = i / nr;
             float v = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; w++) v += red[(w * 16 + r) * B + b];
-            float* o = out + (size_t)b * W.n + t0 + r;
+            for (int k = 0; k < kWideWaves; k++) v += red[(k * T * 16 + q) * B + b];
+            if constexpr (WD == W_INT8) v *= f16_to_f(as_global(W.s)[p0 + q]);
+            FF_GLOBAL float* o = as_global(out + (size_t)b * W.n + p0 + q);
             if (epi_kind == EPI_RESIDUAL) *o += v;
             else if (!skip_tokens || skip_tokens[b] != kTokenSkip) *o = v;
         }
-        __syncthreads();
     }
 }
 // Debug: one projection of the wide pass on its own, out[n][row] in packed row order (rows of out: M.V = W.n floats), input image in img.

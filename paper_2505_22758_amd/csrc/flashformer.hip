@@ -268,23 +268,36 @@ int launch_gemv(ff_model* m, const PMat& W, const float* in, int in_stride, floa
     kern<<<m->n_cta, kThreads, m->lds_bytes, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
     return FF_OK;
 }
-template <int WD, int B>
-int launch_gemv_tiled(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
-    auto kern = op_gemv_tiled<WD, B>;
-    constexpr size_t lds = kLdsActBytes + (size_t)kWaves * 16 * B * 4;
+template <int WD, int B, int T, bool RUNS>
+int launch_gemv_tiled_form(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
+    auto kern = op_gemv_tiled<WD, B, T, RUNS>;
+    constexpr size_t lds = kLdsActBytes + (size_t)kWideWaves * T * 16 * B * 4 + (WD == W_INT4 ? kLdsActBytes / 32 : 0);
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); });
     if (attr_err != hipSuccess) return fail(FF_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-    kern<<<W.tiled, kThreads, lds, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
+    kern<<<W.tiled, kWideThreads, lds, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
     return FF_OK;
+}
+template <int WD, int B, int T>
+int launch_gemv_tiled(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
+    if (WD == W_INT4 && W.k % 512 == 0) return launch_gemv_tiled_form<WD, B, T, WD == W_INT4>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    return launch_gemv_tiled_form<WD, B, T, false>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+}
+// Panels of one or two tiles where a workgroup has no more rows, else of four (the staged inputs are read once per panel).
+template <int WD, int B>
+int gemv_tiled(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
+    const int rows = 4 * (((W.n + 3) / 4 + W.tiled - 1) / W.tiled);   // of the workgroup that has most
+    if (rows <= 16) return launch_gemv_tiled<WD, B, 1>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    if (rows <= 32) return launch_gemv_tiled<WD, B, 2>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    return launch_gemv_tiled<WD, B, 4>(W, in, in_stride, out, batch, epi, st, skip_tokens);
 }
 template <int B>
 int gemv_any(ff_model* m, const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
     if (W.tiled) switch (W.wd) {
-        case W_BF16: return launch_gemv_tiled<W_BF16, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
-        case W_INT8: return launch_gemv_tiled<W_INT8, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
-        default: return launch_gemv_tiled<W_INT4, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        case W_BF16: return gemv_tiled<W_BF16, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        case W_INT8: return gemv_tiled<W_INT8, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        default: return gemv_tiled<W_INT4, B>(W, in, in_stride, out, batch, epi, st, skip_tokens);
     }
     switch (W.wd) {
         case W_BF16: return launch_gemv<W_BF16, B>(m, W, in, in_stride, out, batch, epi, st, skip_tokens);
