@@ -155,8 +155,13 @@ int ff_kv_free(ff_kv *kv);
  * A model created for more than one sequence runs every step, of 1 to max_batch sequences, as ONE
  * "wide" pass (paper Section 5.2 reads the weights once up to batch 4 and stops there): weights packed
  * as matrix-core operand tiles, projections on 16x16x32 tiles (int8 and int4 codes converted to bf16 in
- * registers), activations exchanged in operand order by the workgroups that own them.  Models for one
- * sequence run the row-partitioned pass on row-major weights. */
+ * registers), activations exchanged in operand order by the workgroups that own them.  The inputs of its
+ * projections carry 24 bits at one sequence and 17 (bf16 head + remainder) at more, everything else fp32.
+ * Models for one sequence run the row-partitioned pass on row-major weights (exchanged values carry 22
+ * mantissa bits).  The wide pass needs a grid of at most 256 workgroups (one per compute unit) that leaves
+ * at most 32 rows of d_model to each, which every supported d_model does on a whole MI355X; on a partition
+ * that does not, a model for several sequences keeps row-major weights and a step runs its sequences one
+ * after another on the row-partitioned pass, each streaming the weights again. */
 int ff_decode_step(ff_model *m, const int32_t *tokens_dev, const int32_t *positions_dev, ff_kv *kv,
                    float *logits_dev, int32_t batch, void *stream);
 

@@ -89,8 +89,7 @@ int check_config(const ff_config* c) {
     // the row partition among waves is computed in 32 bits: (rows / 2) * (waves in the grid) < 2^32
     if (c->vocab > (1 << 21) || c->d_ffn > (1 << 20) || c->d_model > (1 << 20) || qd > (1 << 20))
         return fail(FF_ERR_UNSUPPORTED, "matrix with more than 2^21 rows");
-    // with two or more sequences per pass (matrix-core projections) a row is normalised in a
-    // single staging pass (8 quads per thread)
+    // several sequences: 32 residual rows per workgroup of a full grid (wide_fits)
     if (c->max_batch > 1 && c->d_model > 8192)
         return fail(FF_ERR_UNSUPPORTED, "d_model %d > 8192 with max_batch > 1 is not supported", c->d_model);
     if ((size_t)c->d_model * 4 * std::min(c->max_batch, kMaxBatch) > (size_t)kLdsActBytes)
@@ -111,17 +110,19 @@ constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the
 
 // Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout): those for
 // several sequences (all that check_config accepts fit a grid of kGridCtas); a single sequence runs row-partitioned on
-// row-major weights.
+// row-major weights, and so do, one sequence after the other, models for several on a grid that the wide pass does not fit.
 // Both sides measured at one sequence, which keeps its inputs' 24 bits on either (8B, eight layers, context 1024, us per step,
 // row-partitioned / wide): bf16 737 / 749, int8 556 / 548, int4 580 / 503; the quantised models for one sequence stay where
 // their results are what they were.
 bool wide_model(const ff_config& c) { return c.max_batch > 1; }
 
 // wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
-// n_cta: workgroups of the grid (sizes are largest for kGridCtas); perop: with the per-operation path's buffers
+// n_cta: workgroups of the grid (sizes are largest for kGridCtas; a grid that the wide pass does not fit needs fewer bytes
+// than that: rows without padding, the compact exchange rows of one sequence in place of two and more image sets);
+// perop: with the per-operation path's buffers
 Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool perop = true) {
     Plan P;
-    P.wide = wide_model(c);
+    P.wide = wide_model(c) && wide_fits(c, n_cta);
     const int tiled = P.wide ? n_cta : 0;
     size_t off = 0;
     P.layers_tab = off; off = align256(off + sizeof(PLayer) * c.n_layers);
@@ -143,7 +144,7 @@ Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool pe
     P.packed_bytes = off;
 
     size_t s = 0;
-    const size_t mb = c.max_batch, pb = perop ? mb : 0;   // exchange buffers hold one pass
+    const size_t mb = c.max_batch, pb = perop ? mb : 0;
     auto take = [&](size_t bytes) { size_t o = s; s = align256(s + bytes); return o; };
     P.x = take(mb * c.d_model * 4);
     P.xn = take(mb * c.d_model * 4);
@@ -156,7 +157,7 @@ Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool pe
     P.part_m = take(pb * c.n_q_heads * kMaxSplits * 4);
     P.part_l = take(pb * c.n_q_heads * kMaxSplits * 4);
     P.part_o = take(pb * c.n_q_heads * kMaxSplits * c.head_dim * 4);
-    const size_t cb = P.wide ? 0 : mb;   // compact exchange rows: row-partitioned passes only
+    const size_t cb = P.wide ? 0 : 1;   // compact exchange rows: row-partitioned passes, of one sequence each
     P.cx = take(cb * c.d_model * 4);
     P.cx2 = take(cb * c.d_model * 4);
     P.cdelta = take(cb * c.d_model * 4);
@@ -353,15 +354,13 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
     m->layer_loaded.assign(cfg->n_layers, 0);
     m->head_loaded = false;
     m->n_cta = prop.multiProcessorCount;
+    if (const char* g = getenv("FF_GRID")) {   // fewer workgroups than compute units (what a smaller partition of the chip has)
+        const int n = atoi(g);
+        if (n >= 1 && n < m->n_cta) m->n_cta = n;
+    }
     m->lds_bytes = kLdsFusedBytes;
     if ((size_t)prop.sharedMemPerBlock < m->lds_bytes + 256) { delete m; return fail(FF_ERR_UNSUPPORTED, "device LDS per workgroup too small"); }
-    if (P.wide) {
-        if (!wide_fits(*cfg, m->n_cta)) {
-            delete m;
-            return fail(FF_ERR_UNSUPPORTED, "max_batch %d needs the wide pass, which does not fit a grid of %d workgroups", cfg->max_batch, prop.multiProcessorCount);
-        }
-        m->plan = P = make_plan(*cfg, m->n_cta);
-    }
+    if (m->n_cta != kGridCtas) m->plan = P = make_plan(*cfg, m->n_cta);
 
     DevModel& D = m->dev;
     D.L = cfg->n_layers; D.d = cfg->d_model; D.Hq = cfg->n_q_heads; D.Hkv = cfg->n_kv_heads; D.hd = cfg->head_dim;
@@ -416,9 +415,8 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
     hipError_t e = hipMemcpyAsync(m->packed + P.layers_tab, m->host_layers.data(), sizeof(PLayer) * cfg->n_layers, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) {
         k_fill_u32<<<256, 256, 0, st>>>((u32*)m->scratch, P.scratch_bytes / 4, 0u);
-        // a model for single sequences never sees its batch grow: its one row is initialised here
-        // and ff_decode_step launches no k_scrub_rows
-        if (cfg->max_batch == 1 && !P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(m->dev, 1);
+        // (passes of one sequence: their one row is initialised here, and ff_decode_step launches no k_scrub_rows)
+        if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(m->dev, 1);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);   // host_layers is pageable: finish the copy before returning
@@ -664,15 +662,16 @@ int ff_kv_free(ff_kv* kv) {
 }
 
 namespace {
-// One step of the whole-model kernel.  Nothing here depends on host-side state that changes from
+// One launch of the whole-model kernel: sequences [seq0, seq0 + batch) of a step of step_batch.  Nothing here depends on host-side state that changes from
 // step to step (exchange tags, write counters and the rows to re-initialise all derive from
 // counters kept on the device), so the launches of a step may be recorded into a HIP graph.
-int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, hipStream_t st) {
+int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, int seq0,
+               int step_batch, hipStream_t st) {
     const bool wide = m->plan.wide;
     const int lm_in_kernel = D.lm.wd == m->cfg.wdtype;   // LM head inside the fused kernel when its weights have the layers' type
     DevKV kvd = kv->dev;
-    kvd.seq0 = 0;
-    kvd.step_batch = batch;
+    kvd.seq0 = seq0;
+    kvd.step_batch = step_batch;
     FusedLaunch a{D, kvd, tokens_dev, positions_dev, logits_dev, batch, lm_in_kernel, m->n_cta, m->lds_bytes, st, m->mute_wg, m->switches, m->glu_off,
                   wide ? 1 : 0};
     const char* what = "";
@@ -697,13 +696,20 @@ int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const 
     }
     return FF_OK;
 }
+// A whole step: one wide pass, or one pass per sequence (every pass checks the whole step's inputs).
+int fused_step(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch, hipStream_t st) {
+    const int n = m->plan.wide ? batch : 1;
+    for (int s0 = 0; s0 < batch; s0 += n)
+        if (int rc = fused_pass(m, D, tokens_dev + s0, positions_dev + s0, kv, logits_dev + (size_t)s0 * m->cfg.vocab, n, s0, batch, st)) return rc;
+    return FF_OK;
+}
 }  // namespace
 
 int ff_decode_step(ff_model* m, const int32_t* tokens_dev, const int32_t* positions_dev, ff_kv* kv, float* logits_dev, int32_t batch,
                    void* stream) {
     int rc = check_step_args(m, tokens_dev, positions_dev, kv, logits_dev, batch);
     if (rc) return rc;
-    return fused_pass(m, m->dev, tokens_dev, positions_dev, kv, logits_dev, batch, (hipStream_t)stream);
+    return fused_step(m, m->dev, tokens_dev, positions_dev, kv, logits_dev, batch, (hipStream_t)stream);
 }
 
 namespace {
@@ -812,9 +818,9 @@ int ff_decode_step_static(ff_model* m, const int32_t* tokens_dev, const int32_t*
     // not a memset node, so the call may be recorded into a HIP graph), then the write-counter
     // bits of the compact rows (k_scrub_rows sees "0 rows clean").
     k_fill_u32<<<256, 256, 0, st>>>((u32*)s, P.scratch_bytes / 4, 0u);
-    if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(D, batch);
+    if (!P.wide) k_scrub_rows<<<64, kThreads, 0, st>>>(D, 1);
     HIPCHK(hipGetLastError());
-    return fused_pass(m, D, tokens_dev, positions_dev, kv, logits_dev, batch, st);
+    return fused_step(m, D, tokens_dev, positions_dev, kv, logits_dev, batch, st);
 }
 
 int ff_status(ff_model* m, void* stream) {

@@ -1042,3 +1042,40 @@ def test_per_operation_step_on_tiled_weights_keeps_up_with_row_major_ones(wdtype
         dec.close()
     print(f"wd={wdtype}: per-operation step, model for 1: {best[1]:.0f} us, for 16: {best[16]:.0f} us")
     assert best[16] <= 1.3 * best[1], best
+
+
+@pytest.mark.parametrize("grid,d_model", ((64, 4096), (200, 512)), ids=("no-wide-pass", "wide-pass"))
+def test_models_for_several_sequences_on_a_smaller_grid(monkeypatch, grid, d_model):
+    """A partition of the chip has fewer compute units (FF_GRID: workgroups of the grid, read when a model is
+    created).  64 workgroups leave 64 rows of d_model 4096 to each, more than the wide pass holds: the model is accepted
+    all the same and steps its sequences one after another; 200 workgroups (no power of two) run the wide pass.
+    Steps, a stopped sequence, the skipped step of a bad position and the static-scratch step, all weight formats."""
+    from paper_2505_22758_amd import binding
+    monkeypatch.setenv("FF_GRID", str(grid))
+    S = synth.TINY.replace(name="grid", n_layers=2, d_model=d_model, d_ffn=1408, vocab=1003)
+    _run_teacher_forced(S, 0x2505227e0, synth.WDTYPE_BF16, batch=4, T0=[30, 0, 77, 5], steps=2)
+    _run_teacher_forced(S, 0x2505227e1, synth.WDTYPE_INT8, batch=3, T0=[9, 70, 2], steps=2, quant_lm_head=False)
+    _run_teacher_forced(S, 0x2505227e2, synth.WDTYPE_INT4, batch=6, T0=20, steps=2)
+    B, T0 = 3, 12
+    dec, caches = helpers.hip_side(S, 7, synth.WDTYPE_INT8, B, T0, max_ctx=T0 + 4, n_caches=3)
+    assert binding.ff_fused_schedule(dec.model)[1] == grid
+    tok = torch.tensor([5, 6, 7], dtype=torch.int32, device="cuda:0")
+    pos = torch.full((B,), T0, dtype=torch.int32, device="cuda:0")
+    want, got, stat = (torch.full((B, S.vocab), 7.5, device="cuda:0") for _ in range(3))
+    bad = pos.clone()
+    bad[2] = T0 + 4
+    before = caches[0][1].clone()
+    binding.ff_decode_step(dec.model, tok, bad, caches[0][0], want, B)
+    with pytest.raises(binding.FFError) as e:
+        binding.ff_status(dec.model)
+    assert e.value.code == binding.FF_ERR_RANGE
+    assert bool((want == 7.5).all()) and torch.equal(before, caches[0][1]), "a skipped step left something behind"
+    binding.ff_decode_step(dec.model, tok, pos, caches[0][0], want, B)
+    binding.ff_decode_step_static(dec.model, tok, pos, caches[1][0], stat, B)
+    skip = tok.clone()
+    skip[1] = binding.FF_TOKEN_SKIP
+    binding.ff_decode_step(dec.model, skip, pos, caches[2][0], got, B)
+    binding.ff_status(dec.model)
+    assert torch.equal(want, stat) and torch.equal(caches[0][1], caches[1][1])
+    assert torch.equal(got[[0, 2]], want[[0, 2]]) and bool((got[1] == 7.5).all())
+    dec.close()
