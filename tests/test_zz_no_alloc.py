@@ -49,3 +49,34 @@ def test_static_scratch_step_equals_the_workspace_step_twice_in_a_row():
     dec.close()
     for dec, _ in models.values():
         dec.close()
+
+
+# (layers, batch): images of one set per layer alone exceed the array, one set fits
+@pytest.mark.parametrize("wdtype,layers,batch", ((synth.WDTYPE_BF16, 60, 16), (synth.WDTYPE_INT8, 400, 2), (synth.WDTYPE_INT4, 400, 1)),
+                         ids=("bf16-x16", "int8-x2", "int4-x1"))
+def test_static_scratch_with_one_set_of_images_for_all_layers(wdtype, layers, batch):
+    """Where the exchange images of every layer do not fit the static array, the wide pass reuses one set: readers drop
+    their cached copies with an acquire fence, and the epochs order a set's next writes behind its last reads.  Several steps
+    in a row, each bit for bit the step with images of its own per layer.  Models for 16, 2 and 2 sequences: every operand form."""
+    from paper_2505_22758_amd import binding
+    S, T0, steps, max_batch = synth.TINY.replace(name="deep", n_layers=layers, d_ffn=1408, vocab=1000), 21, 3, max(batch, 2)
+    image_set = 4 * max_batch * (2 * S.d_model + S.n_q_heads * S.head_dim + S.d_ffn)   # bytes: 2 x bf16 per element
+    static = 8 << 20   # FF_STATIC_SCRATCH_BYTES
+    assert layers * image_set > static > 8 * image_set
+    dec = binding.Decoder.synthetic(S, 0x5ca8, wdtype, max_batch)
+    bufs = [torch.zeros(binding.ff_kv_bytes(dec.model, batch, T0 + steps), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    kvs = [binding.ff_kv_alloc(dec.model, batch, T0 + steps, b) for b in bufs]
+    for kv in kvs:
+        binding.ff_kv_fill_synthetic(kv, 0x5ca8, T0)
+    toks = synth.make_tokens(S, 0x5ca8, steps, batch).to("cuda:0")
+    want, got = torch.zeros(batch, S.vocab, device="cuda:0"), torch.full((batch, S.vocab), -3.0, device="cuda:0")
+    for s in range(steps):
+        pos = torch.full((batch,), T0 + s, dtype=torch.int32, device="cuda:0")
+        binding.ff_decode_step(dec.model, toks[s], pos, kvs[0], want, batch)
+        binding.ff_decode_step_static(dec.model, toks[s], pos, kvs[1], got, batch)
+        binding.ff_status(dec.model)
+        assert bool(torch.isfinite(want).all()) and torch.equal(got, want), (s, float((got - want).abs().max()))
+    assert torch.equal(bufs[0], bufs[1]), "appended cache rows differ"
+    for kv in kvs:
+        binding.ff_kv_free(kv)
+    dec.close()
