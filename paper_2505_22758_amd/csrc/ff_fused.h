@@ -59,12 +59,11 @@ __device__ __forceinline__ u64* dbg_stage_slots(const DevModel& M, int n_phases,
 struct EpiFused {
     int kind; u32 tag; u32 cnt;   // tag: 32-bit tag of q / k,v; cnt: write counter of the compact output vector
     const DevModel& M; const DevKV& KV; const int* pos; int layer; const float2* rope; float* logits;
-    int pair0 = 0;   // LM head in row blocks (wide pass): first row pair of the block
     __device__ __forceinline__ void operator()(int pair, int b, float v0, float v1) const {
         switch (kind) {
             case PH_QKV: EpiQKVTagged{M, KV, pos, layer, rope, tag}(pair, b, v0, v1); break;
             case PH_GU: EpiSwiGLUTagged{M.ch, M.F, cnt, M.gu}(pair, b, v0, v1); break;
-            case PH_LM: if (pos[b] >= 0) EpiStore{logits, M.V}(pair + pair0, b, v0, v1); break;   // (no logits for a sequence that sits the step out)
+            case PH_LM: if (pos[b] >= 0) EpiStore{logits, M.V}(pair, b, v0, v1); break;   // (no logits for a sequence that sits the step out)
             default: EpiDeltaTagged{M.cdelta, M.d, cnt}(pair, b, v0, v1); break;
         }
     }
