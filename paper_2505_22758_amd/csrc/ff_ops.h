@@ -397,29 +397,7 @@ __global__ void __launch_bounds__(kThreads) op_swiglu(DevModel M, int batch) {
 }
 
 // ---------------------------------------------------------------- loaders and utilities
-// dst row r  <-  source row per mode.  row_bytes is a multiple of 2.
-__global__ void __launch_bounds__(kThreads) k_repack_rows(uint8_t* dst, const uint8_t* src_a, const uint8_t* src_b, int n_rows,
-                                                         size_t row_bytes, int mode, int hd, GuPerm perm) {
-    for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
-        const uint8_t* src;
-        if (mode == REPACK_ROPE) {
-            int head = r / hd, within = r % hd;
-            src = src_a + (size_t)(head * hd + within / 2 + (within & 1) * (hd / 2)) * row_bytes;
-        } else if (mode == REPACK_INTERLEAVE) {
-            src = ((r & 1) ? src_b : src_a) + (size_t)perm.unit_of_pair(r / 2) * row_bytes;
-        } else {
-            src = src_a + (size_t)r * row_bytes;
-        }
-        uint8_t* d = dst + (size_t)r * row_bytes;
-        if (row_bytes % 16 == 0) {
-            for (size_t i = threadIdx.x; i < row_bytes / 16; i += kThreads) ((u32x4*)d)[i] = ((const u32x4*)src)[i];
-        } else {
-            for (size_t i = threadIdx.x; i < row_bytes / 2; i += kThreads) ((uint16_t*)d)[i] = ((const uint16_t*)src)[i];
-        }
-    }
-}
-// Weight rows of part [row0, row0 + n_rows) of a tiled matrix (see PMat), one tile per block (grid: workgroups
-// of the decode grid x tiles): unit u of packed row r comes from the source row of r - row0 by the same maps.
+// Where packed rows come from.
 struct RowMap {
     int mode, hd; GuPerm perm;
     // canonical row of packed row r of a part; *second: it is a row of the second source (interleaved mode)
@@ -430,6 +408,23 @@ struct RowMap {
         return r;
     }
 };
+// dst row r  <-  source row by the map.  row_bytes is a multiple of 2.
+__global__ void __launch_bounds__(kThreads) k_repack_rows(uint8_t* dst, const uint8_t* src_a, const uint8_t* src_b, int n_rows,
+                                                         size_t row_bytes, RowMap map) {
+    for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
+        bool second;
+        const int sr = map.source(r, &second);
+        const uint8_t* src = (second ? src_b : src_a) + (size_t)sr * row_bytes;
+        uint8_t* d = dst + (size_t)r * row_bytes;
+        if (row_bytes % 16 == 0) {
+            for (size_t i = threadIdx.x; i < row_bytes / 16; i += kThreads) ((u32x4*)d)[i] = ((const u32x4*)src)[i];
+        } else {
+            for (size_t i = threadIdx.x; i < row_bytes / 2; i += kThreads) ((uint16_t*)d)[i] = ((const uint16_t*)src)[i];
+        }
+    }
+}
+// Weight rows of part [row0, row0 + n_rows) of a tiled matrix (see PMat), one tile per block (grid: workgroups
+// of the decode grid x tiles): unit u of packed row r comes from the source row of r - row0 by the same maps.
 template <class F>
 __device__ __forceinline__ void for_tile_units(const PMat& W, int row0, int n_rows, F&& f) {   // f(r - row0, unit, destination)
     const PMat::Rows rr = W.cta_rows(blockIdx.x);
@@ -572,23 +567,15 @@ struct SynthMat {   // one canonical matrix [n][k] of the seeded recipe
     int k;
     float c_scale;   // int8: 0.02 / 73.6, int4: 0.02 / 6.5 (fp32)
 };
-// Fills packed rows [0, n_rows) of a matrix part: packed row r holds canonical row src(r) of A (or,
-// interleaved mode, of A / B alternately), same row maps as k_repack_rows.  dst_w rows of row_bytes;
+// Fills packed rows [0, n_rows) of a matrix part: packed row r holds the map's canonical row of A (or,
+// interleaved mode, of A / B alternately).  dst_w rows of row_bytes;
 // dst_s / dst_z rows of one fp16 (int8) or k/128 fp16 (int4).
 __global__ void __launch_bounds__(kThreads) k_synth_rows(uint8_t* dst_w, f16_t* dst_s, f16_t* dst_z, int n_rows, int wd, SynthMat A, SynthMat B,
-                                                        int mode, int hd, float w_scale, GuPerm perm) {
+                                                        RowMap map, float w_scale) {
     for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
-        int sr;
-        const SynthMat* Mt = &A;
-        if (mode == REPACK_ROPE) {
-            int head = r / hd, within = r % hd;
-            sr = head * hd + within / 2 + (within & 1) * (hd / 2);
-        } else if (mode == REPACK_INTERLEAVE) {
-            sr = perm.unit_of_pair(r / 2);
-            if (r & 1) Mt = &B;
-        } else {
-            sr = r;
-        }
+        bool second;
+        const int sr = map.source(r, &second);
+        const SynthMat* Mt = second ? &B : &A;
         const int k = Mt->k;
         const u64 e0 = (u64)sr * (u64)k;
         if (wd == W_BF16) {

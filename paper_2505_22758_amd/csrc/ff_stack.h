@@ -43,7 +43,7 @@ __global__ void __launch_bounds__(kFusedThreads) stack_linear_kernel(StackArgs A
     const UDiv n_gwaves = UDiv::of((u32)ncta * kFusedWaves), n_ctas = UDiv::of((u32)ncta);
     for (int l = 0; l < A.n_layers; l++) {
         PMat W;
-        W.w = A.w + (size_t)l * A.d * A.d * 2; W.s = nullptr; W.z = nullptr; W.n = A.d; W.k = A.d; W.wd = W_BF16;
+        W.w = A.w + (size_t)l * A.d * A.d * 2; W.s = nullptr; W.z = nullptr; W.n = A.d; W.k = A.d; W.wd = W_BF16; W.tiled = 0;
         const Stream<W_BF16, 1> S = Stream<W_BF16, 1>::make(W, 0, gwave, n_gwaves);
         Stage<W_BF16> ring[kDepthOf<W_BF16>];
         if constexpr (OVERLAP) prefetch_stream(S, ring, lane);

@@ -222,20 +222,21 @@ int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const f
     if (!a.w || (b && !b->w)) return fail(FF_ERR_ARG, "matrix pointer is null");
     size_t rb = PMat::row_bytes_of(dst.k, dst.wd, 0);
     int grid = std::min(n_rows, 4096);
+    const RowMap map{mode, hd, perm};
     if (dst.tiled)
-        k_repack_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr, RowMap{mode, hd, perm});
+        k_repack_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr, map);
     else
         k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.w + (size_t)dst_row * rb, (const uint8_t*)a.w, b ? (const uint8_t*)b->w : nullptr,
-                                             n_rows, rb, mode, hd, perm);
+                                             n_rows, rb, map);
     if (dst.wd != W_BF16) {
         if (!a.s || (b && !b->s)) return fail(FF_ERR_ARG, "scale pointer is null for a quantised matrix");
         size_t sb = dst.wd == W_INT8 ? 2 : (size_t)(dst.k / 128) * 2;
         k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.s + (size_t)dst_row * sb, (const uint8_t*)a.s, b ? (const uint8_t*)b->s : nullptr,
-                                                 n_rows, sb, mode, hd, perm);
+                                                 n_rows, sb, map);
         if (dst.wd == W_INT4) {
             if (!a.z || (b && !b->z)) return fail(FF_ERR_ARG, "zero-point pointer is null for an int4 matrix");
             k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.z + (size_t)dst_row * sb, (const uint8_t*)a.z,
-                                                     b ? (const uint8_t*)b->z : nullptr, n_rows, sb, mode, hd, perm);
+                                                     b ? (const uint8_t*)b->z : nullptr, n_rows, sb, map);
         }
     }
     HIPCHK(hipGetLastError());
@@ -511,8 +512,8 @@ int synth_part(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, con
                const GuPerm& perm, hipStream_t st) {
     const size_t rb = PMat::row_bytes_of(dst.k, dst.wd, 0);
     const size_t sb = dst.wd == W_INT8 ? 2 : (size_t)(dst.k / 128) * 2;
+    const RowMap map{mode, hd, perm};
     if (dst.tiled) {
-        const RowMap map{mode, hd, perm};
         k_synth_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, a, b, map, (float)(0.02 / kIh4Std));
         if (dst.wd != W_BF16)
             k_synth_scales<<<std::min(n_rows, 8192), kThreads, 0, st>>>((f16_t*)(packed + dst.s + (size_t)dst_row * sb), (f16_t*)(packed + dst.z + (size_t)dst_row * sb),
@@ -521,8 +522,8 @@ int synth_part(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, con
         return FF_OK;
     }
     k_synth_rows<<<std::min(n_rows, 8192), kThreads, 0, st>>>(packed + dst.w + (size_t)dst_row * rb, (f16_t*)(packed + dst.s + (size_t)dst_row * sb),
-                                                             (f16_t*)(packed + dst.z + (size_t)dst_row * sb), n_rows, dst.wd, a, b, mode, hd,
-                                                             (float)(0.02 / kIh4Std), perm);
+                                                             (f16_t*)(packed + dst.z + (size_t)dst_row * sb), n_rows, dst.wd, a, b, map,
+                                                             (float)(0.02 / kIh4Std));
     HIPCHK(hipGetLastError());
     return FF_OK;
 }
@@ -977,7 +978,7 @@ int ff_debug_stack_linear(const void* w_dev, int32_t d, int32_t n_layers, const 
         shim.n_cta = n_cta; shim.lds_bytes = kLdsFusedBytes;
         for (int l = 0; l < n_layers; l++) {
             PMat W;
-            W.w = (const uint8_t*)w_dev + (size_t)l * d * d * 2; W.s = nullptr; W.z = nullptr; W.n = d; W.k = d; W.wd = W_BF16;
+            W.w = (const uint8_t*)w_dev + (size_t)l * d * d * 2; W.s = nullptr; W.z = nullptr; W.n = d; W.k = d; W.wd = W_BF16; W.tiled = 0;
             int rc = launch_gemv<W_BF16, 1>(&shim, W, (l & 1) ? b1 : b0, d, (l & 1) ? b0 : b1, 1, EPI_STORE, st);
             if (rc) return rc;
         }
