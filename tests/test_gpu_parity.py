@@ -180,7 +180,7 @@ def test_sequences_of_different_lengths_in_one_batch():
 
 def test_attention_work_list_follows_the_lengths():
     """One long sequence among short ones: the step's attention work list gives it most of the grid
-    (16 slices where equal shares allow 8, resp. 2 in the wide pass); both forms of the list against
+    (16 slices where equal shares allow 8, resp. 2 with twelve sequences); both forms of the list against
     the oracle, on a model with 8 kv heads (32 / 96 head groups on 256 workgroups)."""
     S = synth.TINY.replace(name="kv8", n_layers=2, n_q_heads=32, n_kv_heads=8)
     for by_length in (True, False):
@@ -190,8 +190,8 @@ def test_attention_work_list_follows_the_lengths():
 
 
 def test_tiny_batches_above_one_pass():
-    """Batches 5..16: with bf16 weights one wide pass each (a single K segment at this width, workgroups
-    that own one row group or none), with int8 weights passes of four (6 = a full and a ragged pass)."""
+    """Batches 5..16, one wide pass each (workgroups that own one row group or none): both operand forms for several
+    sequences, bf16 and int8 weights; the per-operation path runs them as passes of four (7: a full and a ragged one)."""
     for b in (5, 7, 8, 16):
         _run_teacher_forced(synth.TINY, 40 + b, synth.WDTYPE_BF16, batch=b, T0=24, steps=2)
     _run_teacher_forced(synth.TINY.replace(d_ffn=1408), 61, synth.WDTYPE_INT8, batch=6, T0=24, steps=2)
@@ -373,17 +373,15 @@ def test_llama70b_shaped_one_layer_int4_and_int8():
 
 
 def test_llama8b_shaped_one_layer_batch8_single_pass():
-    """Eight sequences in ONE (wide) pass at the 8B width (one layer): one or two tiles of 16 rows per
-    workgroup (seven for gate/up), inputs copied in two K segments (seven for the down projection),
-    sequences of different lengths."""
+    """Eight sequences in one wide pass at the 8B width (one layer): one or two tiles of 16 rows per
+    workgroup (seven for gate/up), sequences of different lengths."""
     _run_teacher_forced(synth.LLAMA_8B.replace(n_layers=1), 0x250522766, synth.WDTYPE_BF16, batch=8, T0=[96, 1, 300, 64, 63, 65, 0, 200], steps=2,
                         gpu_generated=True)
 
 
 def test_llama8b_shaped_one_layer_quantised_batches():
-    """The matrix-core projections for int8 and int4 weights at the 8B width (one layer): the down
-    projection's 14336-column input staged in one long pass (batch 2) and in two K segments
-    (batch 4), several chunks per row group."""
+    """The matrix-core projections for int8 and int4 weights at the 8B width (one layer); on the per-operation
+    path the down projection's 14336-column input is staged in one K segment (batch 2) and in two (batch 4)."""
     S = synth.LLAMA_8B.replace(n_layers=1)
     _run_teacher_forced(S, 0x250522767, synth.WDTYPE_INT8, batch=2, T0=80, steps=1, gpu_generated=True)
     _run_teacher_forced(S, 0x250522768, synth.WDTYPE_INT8, batch=4, T0=70, steps=1, gpu_generated=True)
@@ -400,8 +398,7 @@ def test_wide_model_staged_in_several_passes():
 
 def test_eight_query_heads_per_kv_head_small_model_all_formats():
     """The (head_dim 128, 8 query heads per kv head) kernel family on a small model, in the batch
-    classes the 70B-shaped tests do not reach: eight sequences in one wide pass (bf16), and the int8
-    and int4 matrix-core projections at batch 4 and 3."""
+    classes the 70B-shaped tests do not reach: eight and six sequences (bf16), int8 at batch 4, int4 at 3 and 1."""
     S = synth.TINY.replace(name="g8", n_layers=2, d_model=1024, n_q_heads=8, n_kv_heads=1, head_dim=128, d_ffn=1536, vocab=1500)
     _run_teacher_forced(S, 0x25052276b, synth.WDTYPE_BF16, batch=8, T0=70, steps=2)
     # (wide pass, ragged: its attention takes the scores of 16 rows at a time from the matrix cores)
@@ -412,9 +409,8 @@ def test_eight_query_heads_per_kv_head_small_model_all_formats():
 
 
 def test_half_a_row_group_per_wave():
-    """d_model 2048 at batch 2: the output and down projections have 512 four-row groups for the
-    1024 waves of the grid, so every wave multiplies half of a group (split along K) and every
-    group is finished through the wave pair's mailbox; bf16 and int4."""
+    """d_model 2048 at batch 2 and 4: eight rows of the output and down projections per workgroup, half a
+    tile, two row groups of four; bf16 and int4."""
     S = synth.TINY.replace(name="half", n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, d_ffn=2048, vocab=3000)
     _run_teacher_forced(S, 0x25052276f, synth.WDTYPE_BF16, batch=2, T0=50, steps=2)
     _run_teacher_forced(S, 0x250522770, synth.WDTYPE_INT4, batch=4, T0=20, steps=2)
@@ -490,10 +486,8 @@ def _run_changing_batches(nseq, sizes, wdtype=synth.WDTYPE_BF16):
 
 
 def test_batch_size_changing_from_step_to_step():
-    """Steps of different batch sizes on one model and one cache: a sequence that sits out some steps
-    (the exchange vectors' 2-bit write counters come round every step of this 4-layer model, so any
-    number of skipped steps leaves the counter bits a reader would accept) must not be served values
-    its exchange rows kept from its last step."""
+    """Steps of different batch sizes on one model and one cache: the exchange images are laid out for the step's batch,
+    so a step finds what other batches left in its place, and must not be served any of it."""
     _run_changing_batches(4, [4, 1, 1, 1, 1, 4, 2, 2, 2, 2, 3, 1, 4, 4, 1, 1, 1, 1, 1, 1, 1, 1, 2])
 
 
@@ -569,15 +563,14 @@ def _run_sequences_stopping_early(nseq, stops, steps, wdtype=synth.WDTYPE_BF16, 
 
 def test_sequences_that_stop_early_in_a_batch():
     """Early stop inside a batch (beyond the lock-step batches of the paper's Section 5.2): on the
-    row-partitioned pass of up to four sequences, the wide pass, consecutive passes with the LM head
-    as separate launches, the quantised formats and the per-operation path; also a step in which
-    nobody takes part."""
+    single-sequence kernel, the wide pass in its operand forms, the LM head as separate launches, the quantised
+    formats and the per-operation path; also a step in which nobody takes part."""
     _run_sequences_stopping_early(4, [6, 0, 3, 6], 6)
     _run_sequences_stopping_early(2, [2, 3], 4)                                   # last step: nobody
     _run_sequences_stopping_early(1, [1], 2)
     _run_sequences_stopping_early(7, [5, 0, 5, 2, 5, 1, 3], 5)                     # one wide pass
     _run_sequences_stopping_early(16, [3] * 5 + [0] + [1] * 9 + [3], 3)
-    _run_sequences_stopping_early(6, [4, 0, 2, 4, 1, 4], 4, wdtype=synth.WDTYPE_INT8, quant_lm_head=False)   # passes of four and two, bf16 LM head
+    _run_sequences_stopping_early(6, [4, 0, 2, 4, 1, 4], 4, wdtype=synth.WDTYPE_INT8, quant_lm_head=False)   # bf16 LM head as separate launches
     _run_sequences_stopping_early(6, [4, 0, 2, 4, 1, 4], 4, wdtype=synth.WDTYPE_INT8)                        # int8 wide pass
     _run_sequences_stopping_early(3, [3, 0, 1], 3, wdtype=synth.WDTYPE_INT4)
     _run_sequences_stopping_early(5, [3, 0, 1, 3, 2], 3, perop=True)
@@ -652,8 +645,8 @@ def test_hot_path_dequantisation_is_bit_exact_on_unit_vectors():
 
 
 def test_bad_position_in_a_later_pass_skips_the_whole_step():
-    """Batch 6 with int8 weights runs as a pass of four and a pass of two.  A position == max_ctx in
-    the SECOND pass must skip the first pass too: no row is appended, the logits buffer is left
+    """Batch 6 runs as one wide pass, and on the per-operation path as a pass of four and a pass of two.  A position
+    == max_ctx in the SECOND pass must skip the first pass too: no row is appended, the logits buffer is left
     alone, ff_status reports FF_ERR_RANGE, and the next good step matches a model that never saw
     the bad one."""
     from paper_2505_22758_amd import binding
@@ -687,8 +680,8 @@ def test_fused_step_replayed_from_a_hip_graph():
     """ff_decode_step carries no host-side per-step state, so a captured step can be replayed: tokens
     and positions live in fixed device tensors that are updated between replays (with the program's
     own eager work and synchronisations in between), and every replay must equal the eager result
-    of the same step on a second cache; batch 1, batch 3 (with the row re-initialisation launch) and
-    batch 6 (wide pass: embedding launch + fused kernel, epochs derived from the device-side counter)."""
+    of the same step on a second cache; batch 1 (single-sequence kernel), 3 and 6 (wide pass, epochs derived from
+    the device-side counter)."""
     from paper_2505_22758_amd import binding
     S, seed, T0, steps = synth.TINY, 97, 30, 6
     for B in (1, 3, 6):
@@ -721,11 +714,10 @@ def test_fused_step_replayed_from_a_hip_graph():
 
 
 def test_wide_pass_with_int8_weights():
-    """The wide pass with int8 per-channel weights (five or more sequences, int8 LM head): the codes are
-    converted to bf16 in registers (exact) and multiplied on the same 16x16x32 tiles, one ring stage of 512
-    columns per tile and K segment, row scales on the finished sums.  A small model with an odd and an even
-    number of tiles per workgroup (16 and 11 sequences, ragged lengths), the model whose output and down
-    projections are split along K, and one layer at the 8B width."""
+    """The wide pass with int8 per-channel weights: the codes are converted to bf16 in registers (exact) and
+    multiplied on the same 16x16x32 tiles, row scales on the finished sums.  A small model with an odd and an even
+    number of tiles per workgroup (16 and 11 sequences, ragged lengths), a model with 8192-column output and down
+    projections, and one layer at the 8B width."""
     S = synth.TINY.replace(name="wide8", n_layers=2, d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ffn=6144, vocab=3000)
     _run_teacher_forced(S, 0x2505227b0, synth.WDTYPE_INT8, batch=16, T0=[40, 0, 1, 130, 64, 63, 65, 9, 300, 17, 128, 5, 77, 256, 2, 33], steps=2)
     _run_teacher_forced(S, 0x2505227b1, synth.WDTYPE_INT8, batch=11, T0=[7, 70, 0, 129, 31, 64, 200, 1, 90, 12, 55], steps=2)
@@ -735,11 +727,10 @@ def test_wide_pass_with_int8_weights():
 
 
 def test_wide_pass_with_int4_weights():
-    """The wide pass with int4 group-128 weights (input widths multiples of 512, int4 LM head): codes as bf16
-    128 + n on the 16x16x32 tiles, one ring stage per pair of tiles, group sums of the inputs from a ones operand,
-    scales and zeros fetched across lanes into the accumulator layout.  A small model with odd and even numbers
-    of tile pairs (16 and 11 sequences, ragged lengths), the model whose output and down projections are split
-    along K, and one layer at the 8B width."""
+    """The wide pass with int4 group-128 weights: codes as bf16 16 + n on the 16x16x32 tiles, group sums of the
+    inputs from a ones operand, scales and zeros of a panel in LDS.  A small model with odd and even numbers
+    of tiles (16 and 11 sequences, ragged lengths), a model with 8192-column output and down projections, and
+    one layer at the 8B width."""
     S = synth.TINY.replace(name="wide4", n_layers=2, d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ffn=6144, vocab=3000)
     _run_teacher_forced(S, 0x2505227c0, synth.WDTYPE_INT4, batch=16, T0=[40, 0, 1, 130, 64, 63, 65, 9, 300, 17, 128, 5, 77, 256, 2, 33], steps=2)
     _run_teacher_forced(S, 0x2505227c1, synth.WDTYPE_INT4, batch=11, T0=[7, 70, 0, 129, 31, 64, 200, 1, 90, 12, 55], steps=2)
@@ -752,9 +743,8 @@ KSPLIT = synth.TINY.replace(name="ksplit", n_layers=2, d_model=1024, n_q_heads=6
 
 
 def test_wide_pass_output_and_down_projection_split_along_k():
-    """Wide pass on a model whose output and down projections have four K segments each (8192 input
-    columns): the workgroups of a pair multiply the rows of both over half of the segments and hand each
-    other the partial sums of the partner's rows.  Eight query heads per KV head, ragged lengths (the
+    """Wide pass on a model whose output and down projections have many more columns than rows (8192 to 1024: the eight
+    waves of a workgroup split K of four rows).  Eight query heads per KV head, ragged lengths (the
     matrix-core attention form), a full pass of 16 and a pass of 7, two layers."""
     _run_teacher_forced(KSPLIT, 0x2505227a0, synth.WDTYPE_BF16, batch=16, T0=[40, 0, 1, 130, 64, 63, 65, 9, 300, 17, 128, 5, 77, 256, 2, 33], steps=2)
     _run_teacher_forced(KSPLIT, 0x2505227a1, synth.WDTYPE_BF16, batch=7, T0=[7, 70, 0, 129, 31, 64, 200], steps=2)
@@ -767,7 +757,7 @@ def test_a_silent_workgroup_ends_in_a_timeout_not_a_hang():
     import time
     from paper_2505_22758_amd import binding
     seed, T0 = 99, 20
-    # 6: wide pass (waits on epochs instead of per-word counters); KSPLIT: the muted workgroup's partner waits for its partial sums
+    # 2 and 6: wide pass (waits on epochs instead of per-word counters)
     for S, B in ((synth.TINY, 1), (synth.TINY, 2), (synth.TINY, 6), (KSPLIT, 6)):
         dec, caches = helpers.hip_side(S, seed, synth.WDTYPE_BF16, B, T0, max_ctx=T0 + 4)
         tok = torch.arange(3, 3 + B, dtype=torch.int32, device="cuda:0")
@@ -899,8 +889,8 @@ def test_overlap_switch_changes_timing_not_results():
 def test_glu_as_one_stream_small_model_all_formats(monkeypatch):
     """Single-sequence steps of a small model whose FFN is a whole number of gate/up pairs per wave
     (d_ffn 8192 over 1024 waves), so gate/up + down run as one stream with the down projection's input
-    staged chunk by chunk (four chunks with bf16 weights, two with int8 / int4); the same models at
-    batch 2 and 3 use the interleaved gate/up row order with the ordinary phase sequence."""
+    staged chunk by chunk (four chunks with bf16 weights, two with int8 / int4); the same shape for two and three
+    sequences runs the wide pass, with the gate/up rows in plain order."""
     S = synth.TINY.replace(name="glu", n_layers=3, d_model=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, d_ffn=8192, vocab=3000)
     monkeypatch.setenv("FF_GLU_PIPE", "all")   # int8 weights take the one-stream form only on request (read when a model is created)
     for wd in (synth.WDTYPE_BF16, synth.WDTYPE_INT8, synth.WDTYPE_INT4):
@@ -910,11 +900,10 @@ def test_glu_as_one_stream_small_model_all_formats(monkeypatch):
 
 
 def test_wide_pass_of_up_to_16_sequences_small_model():
-    """More than four sequences (bf16 weights) run as ONE wide pass: projections on 16x16x32 matrix-core
-    tiles, inputs copied one K segment of 2048 columns at a time (d_model 4096 = 2 segments, d_ffn 6144
-    = 3) from images written by the workgroups that own the values, the RMSNorm factor applied to the
-    projection outputs, the LM head in row blocks: a full pass of 16 and a ragged one of 11, sequences
-    of different lengths, two layers so that the residual rows are carried from layer to layer."""
+    """Several sequences run as ONE wide pass: projections on 16x16x32 matrix-core tiles, inputs from images
+    written by the workgroups that own the values, the RMSNorm factor applied to the projection outputs, the
+    LM head in panels: a full pass of 16 and a ragged one of 11, sequences of different lengths, two layers so
+    that the residual rows are carried from layer to layer."""
     S = synth.TINY.replace(name="wide", n_layers=2, d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ffn=6144, vocab=3000)
     _run_teacher_forced(S, 0x250522790, synth.WDTYPE_BF16, batch=16, T0=[40, 0, 1, 130, 64, 63, 65, 9, 300, 17, 128, 5, 77, 256, 2, 33], steps=2)
     _run_teacher_forced(S, 0x250522791, synth.WDTYPE_BF16, batch=11, T0=[7, 70, 0, 129, 31, 64, 200, 1, 90, 12, 55], steps=2)
