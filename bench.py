@@ -23,12 +23,11 @@ HBM_PEAK_GBS = 8000.0
 # a plain copy of known size); the summary under profiles/ gives the commands and the raw figures.
 def measured_traffic(workload):
     """traffic_bytes_per_launch of the workload's committed rocprofv3 summary, if it has one."""
-    path = os.path.join(ROOT, "profiles", f"fused_decode_kernel_{workload}.md")
-    if not os.path.isfile(path):
-        return None
-    for line in open(path):
-        if line.startswith("traffic_bytes_per_launch="):
-            return float(line.split("=", 1)[1])
+    for kernel in ("fused", "wide"):
+        path = os.path.join(ROOT, "profiles", f"{kernel}_decode_kernel_{workload}.md")
+        for line in open(path) if os.path.isfile(path) else ():
+            if line.startswith("traffic_bytes_per_launch="):
+                return float(line.split("=", 1)[1])
     return None
 
 WORKLOADS = {
@@ -283,9 +282,8 @@ def main():
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
         "dtype": {0: "bf16", 1: "int8", 2: "int4"}[wdtype] + " weights, f32 accumulate; "
-                 + ("activations exchanged between phases and multiplied as bf16 head + bf16 remainder (17 bits), residual stream f32" if batch > 4
-                    else "activations exchanged between phases as f32 rounded to 22 mantissa bits"
-                         + ("" if batch == 1 else ", staged projection inputs as bf16 head + bf16 remainder (17 bits)")),
+                 + ("activations exchanged between phases and multiplied as bf16 head + bf16 remainder (17 bits), residual stream f32" if batch > 1
+                    else "activations exchanged between phases as f32 rounded to 22 mantissa bits"),
         "data": "synthetic",
         "config": {"workload": args.workload if not (args.batch or args.ctx or args.ctx_list) else f"{args.workload} with batch {batch}, ctx {ctx}",
                    "batch": batch, "kv_context": ctx if not args.ctx_list else ctxs,
@@ -295,7 +293,7 @@ def main():
         "latency_us_p10_p50_p90": [float(np.percentile(per_step_ms, q)) * 1e3 for q in (10, 50, 90)],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None if (args.batch or args.ctx or args.ctx_list) else measured_traffic(args.workload),
-                     "kernel": "fused_decode_kernel", "kernel_ms": kern_ms, "algorithmic_bytes": alg_bytes,
+                     "kernel": "wide_decode_kernel" if batch > 1 else "fused_decode_kernel", "kernel_ms": kern_ms, "algorithmic_bytes": alg_bytes,
                      "ceiling_gbs": ceiling_gbs, "frac_of_ceiling": None if ceiling_gbs is None else achieved / ceiling_gbs},
     }
 

@@ -85,7 +85,9 @@ typedef struct {
 const char *ff_last_error(void);
 
 /* Bytes the caller must provide for the repacked parameters and for the activation-exchange /
- * synchronisation scratch of a model with this configuration. */
+ * synchronisation scratch of a model with this configuration.  With max_batch > 1 the scratch holds
+ * exchange images of every layer, 4 bytes per sequence and input column (8B shape x 16: about 55 MB,
+ * 70B x 16: about 280 MB), which ff_model_create clears. */
 int ff_model_bytes(const ff_config *cfg, size_t *packed_bytes, size_t *scratch_bytes);
 
 /* Creates a model over caller-owned device buffers (contents of packed_dev undefined until the
@@ -171,7 +173,7 @@ int ff_decode_step(ff_model *m, const int32_t *tokens_dev, const int32_t *positi
  * library's device code (one copy per GPU, held until the process ends) instead of the model's
  * scratch_dev; only the model's status word is still used.  Calls no allocating routine.  The
  * array is shared by every model and call on the GPU and is re-initialised on `stream` at the
- * start of each call (two small extra launches), so calls need not follow each other on the same
+ * start of each call (one or two small extra launches), so calls need not follow each other on the same
  * model -- but two calls that overlap in time on one GPU race on it and give undefined results.
  * FF_ERR_NOMEM if the configuration's scratch (ff_model_bytes) exceeds the array: it holds the tiny
  * shape at any batch, the 8B shape up to max_batch 2 and the 70B shape at max_batch 1. */
@@ -218,7 +220,13 @@ int ff_debug_gemv(ff_model *m, int32_t layer, int32_t which, const float *in_dev
  *   [12P+32W, +40W)   layer 1, per workgroup: 8 per projection (input staging entered, first load
  *                     checked, last light wait done, all fresh, staged, number of stale passes),
  *                     then 8 about its attention work (start, queries seen, rows done, partial
- *                     stored, split maxima seen and merged output stored if it merges, end) */
+ *                     stored, split maxima seen and merged output stored if it merges, end)
+ * That is the row-partitioned kernel; a wide pass fills the same buffer with
+ *   [0, 12P)          workgroup 0: 12 slots per phase (0 input published, 1 projection done, 2 first weights
+ *                     requested, 3 phase starts, 4 / 5 first panel multiplied / partial tiles exchanged, 7
+ *                     attention end, 8 / 9 as 4 / 5 for the last further panel)
+ *   [12P, 12P+32W)    layer 1, 4 per wave of its 8: first panel of QKV/O/GU/DOWN multiplied
+ *   [12P+32W, +40W)   layer 1, per workgroup: the last 8 words, about its attention work, as above */
 int ff_debug_timeline(ff_model *m, void *buf_dev);
 
 /* Measurement aid: one launch that reads `bytes` of buf_dev once with the access pattern of the

@@ -18,7 +18,7 @@
 //     refilled tile by tile behind its products, unconditionally; the last iterations are peeled off the
 //     loop (where code paths that issued different numbers of loads meet, the compiler waits for all);
 //   * the waves' partial tiles meet in LDS, wave t adds and finishes tile t.
-// Two waves per SIMD: the eight waves' rings hold up to 128 KB per compute unit in flight, and one
+// Two waves per SIMD: the eight waves' rings hold up to 112 KB per compute unit in flight, and one
 // wave's conversions overlap the other's matrix-core work.
 //
 // Inputs are bf16 head + bf16 remainder (17 significant bits).  NC = 16: heads and remainders are
@@ -44,7 +44,7 @@ template <int WD> constexpr int kWSteps = WD == W_INT4 ? 4 : 2;
 template <int WD> constexpr int kWCols = 32 * kWSteps<WD>;
 template <int NC> constexpr int kXOps = NC == 16 ? 2 : 1;   // input operands per k-step
 // Ring depth in iterations: about 14 weight loads (14 KB) per wave in flight, i.e. 112 KB per compute unit, as far
-// as the registers go.  Twice as many measured slower everywhere (8B bf16 x 2, x 8, 70B x 16, us a pass: 14 loads 1541,
+// as the registers and six iterations go (panels of one tile: int8 6 loads, int4 5, at 16 sequences 3).  Twice as many measured slower everywhere (8B bf16 x 2, x 8, 70B x 16, us a pass: 14 loads 1541,
 // 1729, 5396; 28 loads 1693, 1914, 5735; 8 loads 1563, 1775, 5464): requests that wait for the memory pipe block the
 // younger wave of a SIMD, which then finishes alone, and stand in front of the next hand-over.  (One sequence, 8B bf16, eight
 // layers, us per step: 8, 10, 14, 20, 28 loads 766, 762, 749, 775, 763.)
@@ -210,7 +210,7 @@ template <int T>
 struct PanelScales {
     u32x2 s[kSzItems], z[kSzItems];
     __device__ __forceinline__ static int items(const PMat& M, int nrows) { return nrows * ((M.k / 128 + 3) / 4); }
-    // (row, first group) of item i; a row's last item starts four groups from its end, so that it never reads past it
+    // (item i: four groups of row i / q; only rows of whole items, others go word by word in store)
     __device__ __forceinline__ void load(const PMat& M, int tid, int p0, int nrows, int i0) {
         const int ng = M.k / 128, q = (ng + 3) / 4, n = nrows * q;
         if (ng & 3) return;   // (not whole 8-byte pieces: see store)

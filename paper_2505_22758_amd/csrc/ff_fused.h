@@ -267,8 +267,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     }
     // this step has been executed: the next one uses the next write counters (workgroup 0 can only
     // get here after every workgroup has taken part in every phase, i.e. has read the counter)
-    // Word 1 of the counter block: sequences whose compact exchange rows this launch has written
-    // (k_scrub_rows re-initialises further rows before a larger batch runs).
+    // Word 1 of the counter block: rows of the compact exchange vectors that k_scrub_rows need not initialise.
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         xst_u32(M.stepctr + 1, (u32)batch);
         xst_u32(M.stepctr, steps_done + 1u);

@@ -30,8 +30,6 @@ __global__ void __launch_bounds__(kThreads) op_rmsnorm(const float* x, const bf1
     float r = 1.0f / sqrtf(tot / (float)d + eps);
     for (int i = threadIdx.x; i < d; i += kThreads) out[(size_t)blockIdx.x * d + i] = xr[i] * bf_to_f(gain[i]) * r;
 }
-// x = residual + last sublayer output, from the fused kernel's tagged buffers (finishes the residual
-// stream when the LM head is launched separately after the fused kernel)
 // Re-initialises rows [row0, row1) of the compact exchange vectors so that their counter bits are
 // the ones just BEFORE each vector's first write of the next step: scratch with other contents
 // could otherwise carry, by chance, the bits a later reader waits for.
@@ -58,6 +56,8 @@ __global__ void __launch_bounds__(kThreads) k_scrub_rows(DevModel M, int batch) 
     }
 }
 
+// x = residual + last sublayer output, from the fused kernel's tagged buffers (finishes the residual
+// stream when the LM head is launched separately after the fused kernel)
 __global__ void __launch_bounds__(kThreads) op_final_x(float* x, const u32* tx, const u32* tdelta, int n) {
     for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads)
         x[i] = __uint_as_float(tx[i] & ~kCntMask) + __uint_as_float(tdelta[i] & ~kCntMask);

@@ -7,7 +7,7 @@
 //   * every workgroup owns a fixed range of rows of the residual stream (the rows of the output
 //     and down projections it computes, N / workgroups) and keeps them in its LDS for the whole step;
 //     the epilogue of those two projections adds the projection output to its rows, and writes
-//     (gain of the next normalised projection) x (new value) as bf16 head + bf16 remainder straight
+//     (gain of the next normalised projection) x (new value) as bf16 head + bf16 remainder (one sequence: three parts) straight
 //     into a global IMAGE in the matrix cores' operand order, plus the workgroup's share of every
 //     sequence's sum of squares (the 1/rms factor is applied by the consumer to its finished sums:
 //     a scalar per sequence that commutes with the projection);
@@ -25,9 +25,11 @@
 // reader of the old contents published after its last read).
 // Queries, keys, values and attention partials keep their tagged 8-byte format.
 // Measured us per step of an 8-layer block, before (four waves, images copied through LDS, row-major weights) / with
-// this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 865, int8 x 11 992 / 936 / 780, int4 x 16 1628 / 978 /
-// 796, 70B bf16 x 16 3283 / 3098 / 2715; against a row-partitioned pass of up to four sequences (4x4x4 matrix-core tiles, inputs staged by every workgroup): bf16 x 2 865 -> 788, int4 x 4 1044 -> 595, int8 x 4
-// 875 -> 597.  What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
+// this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 834, int8 x 11 992 / 936 / 770, int4 x 16 1628 /
+// 978 / 783, 70B bf16 x 16 3283 / 3098 / 2619; against a row-partitioned pass of up to four sequences (4x4x4 matrix-core
+// tiles, inputs staged by every workgroup): bf16 x 2 858 / 769, int4 x 4 1038 / 570, int8 x 4 879 / 581; one sequence, on a
+// model for several, against the single-sequence kernel: bf16 737 / 749, int8 556 / 548, int4 580 / 503.
+// What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
 #pragma once
 #include "ff_dense.h"
 
