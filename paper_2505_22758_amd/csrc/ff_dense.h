@@ -93,7 +93,7 @@ struct PanelImg {
     int lane_off;
     template <int WD, int NC>
     __device__ __forceinline__ static PanelImg make(const uint8_t* img, int K, int batch, int lane) {
-        const int r = lane & 15, g = lane >> 4, step = wide_step_bytes(batch);
+        const int r = lane & 15, g = lane >> 4, step = wide_step_bytes(NC, batch);
         const int steps = (K + kWCols<WD> - 1) / kWCols<WD> * kWSteps<WD>;
         const int piece = NC == 1 ? 4 * g + min(r, 2) : NC == 8 ? (2 * g + (r >> 3)) * batch + min(r & 7, batch - 1) : g * batch + min(r, batch - 1);
         return PanelImg{__builtin_amdgcn_make_buffer_rsrc((void*)img, 0, steps * step, 0x00020000), step, piece * 16};

@@ -162,7 +162,7 @@ __device__ __forceinline__ void split3_bf16x2(float a, float b, u32& hi, u32& mi
     split_bf16x2(ra, rb, mid, lo);
 }
 // Wide pass (see ff_wide.h): a global image of a projection's inputs in the matrix cores' operand order,
-// for `batch` sequences.  A k-step (32 columns) takes wide_step_bytes(batch): 16-byte pieces (8 columns of one
+// for `batch` sequences.  A k-step (32 columns) takes wide_step_bytes(nc, batch): 16-byte pieces (8 columns of one
 // sequence) for each of the operand's four lane groups g.  Its form depends on nc, the sequences an operand holds:
 //   1: one sequence in three parts (operand rows 0, 1, 2), group by group, with room for a fourth piece, so that a
 //      step is 256 bytes and no load straddles a line;
@@ -170,14 +170,14 @@ __device__ __forceinline__ void split3_bf16x2(float a, float b, u32& hi, u32& mi
 //   16: the heads of all groups, then the remainders of all groups (an operand each).
 // Which 8 columns lane group g multiplies in a k-step follows from the weights it loads, 16 bytes per lane:
 // 8 << e columns (e = 0 bf16, 1 int8, 2 int4) used up in 1 << e k-steps.
-__host__ __device__ __forceinline__ int wide_step_bytes(int batch) { return batch == 1 ? 256 : 128 * batch; }
+__host__ __device__ __forceinline__ int wide_step_bytes(int nc, int batch) { return nc == 1 ? 256 : 128 * batch; }
 struct WideImg {
     uint8_t* p; int e; int batch; int nc;
     __device__ __forceinline__ int planes() const { return nc == 1 ? 3 : 2; }
     __device__ __forceinline__ uint8_t* at(int n, int plane, int col) const {
         const int j = col >> 3, unit = j >> e, step = ((unit >> 2) << e) + (j & ((1 << e) - 1)), g = unit & 3;
         const int piece = nc == 1 ? 4 * g + plane : nc == 8 ? (2 * g + plane) * batch + n : (4 * plane + g) * batch + n;
-        return p + (size_t)step * wide_step_bytes(batch) + (piece * 16 + (col & 7) * 2);
+        return p + (size_t)step * wide_step_bytes(nc, batch) + (piece * 16 + (col & 7) * 2);
     }
     // Columns col, col + 1 (col even) of sequence n.
     __device__ __forceinline__ void put2(int n, int col, float a, float b) const {

@@ -98,7 +98,7 @@ __host__ __device__ inline int wide_img_cols(int K, int wd) {   // whole iterati
     const int cols = wd == W_INT4 ? 128 : 64;
     return (K + cols - 1) / cols * cols;
 }
-__host__ __device__ inline size_t wide_img_bytes(int K, int wd, int max_batch) { return (size_t)wide_img_cols(K, wd) / 32 * wide_step_bytes(max_batch); }
+__host__ __device__ inline size_t wide_img_bytes(int K, int wd, int max_batch) { return (size_t)wide_img_cols(K, wd) / 32 * wide_step_bytes(max_batch == 1 ? 1 : kMaxBatchWide, max_batch); }   // (two sequences take what one does)
 struct WideLayout {
     size_t x1, x2, a, h, ss1, ss2, bytes;
     __host__ __device__ static WideLayout of(int d, int qd, int F, int wd, int max_batch, int ncta) {
