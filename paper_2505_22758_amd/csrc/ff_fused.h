@@ -44,7 +44,7 @@ __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory")
 //                        its input: 0 entered, 1 first load checked, 2 last light wait done,
 //                        3 all tags fresh, 4 staged, 5 number of stale passes; then 8 words about
 //                        its attention work: 0 start, 1 queries seen, 2 rows done, 3 partial stored,
-//                        4 (merging workgroups) split maxima seen, 5 merged output stored, 6 end
+//                        5 its share of the merged output stored, 6 end
 __device__ __forceinline__ void dbg_event(const DevModel& M, int ph, int ev, int lane) {
     if (M.dbg && blockIdx.x == 0 && lane == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64();
 }
@@ -58,10 +58,10 @@ __device__ __forceinline__ u64* dbg_stage_slots(const DevModel& M, int n_phases,
 
 struct EpiFused {
     int kind; u32 tag; u32 cnt;   // tag: 32-bit tag of q / k,v; cnt: write counter of the compact output vector
-    const DevModel& M; const DevKV& KV; const int* pos; int layer; const float2* rope; float* logits;
+    const DevModel& M; const DevKV& KV; const int* pos; int layer; const float2* rope; float* logits; int hd;
     __device__ __forceinline__ void operator()(int pair, int b, float v0, float v1) const {
         switch (kind) {
-            case PH_QKV: EpiQKVTagged{M, KV, pos, layer, rope, tag}(pair, b, v0, v1); break;
+            case PH_QKV: EpiQKVTagged{M, KV, pos, layer, rope, tag, hd}(pair, b, v0, v1); break;
             case PH_GU: EpiSwiGLUTagged{M.ch, M.F, cnt, M.gu}(pair, b, v0, v1); break;
             case PH_LM: if (pos[b] >= 0) EpiStore{logits, M.V}(pair, b, v0, v1); break;   // (no logits for a sequence that sits the step out)
             default: EpiDeltaTagged{M.cdelta, M.d, cnt}(pair, b, v0, v1); break;
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
     int ph = 0, seg = 0;
     for (;;) {
         const PhaseDesc D = phase_desc(M, tokens, tag_base, sl, ph, lm_in_kernel, phase_state(M, ph));
-        EpiFused epi{D.kind, D.out_tag, D.out_cnt, M, KV, pos_lds, D.layer, rope_lds, logits};
+        EpiFused epi{D.kind, D.out_tag, D.out_cnt, M, KV, pos_lds, D.layer, rope_lds, logits, HD};
         const Stream<WD, B> S = Stream<WD, B>::make(D.W, seg, gwave, n_gwaves);
         // The wave's first tiles of this projection are requested before anything it has to wait
         // for (its input vector; for the output projection the whole attention), so the memory

@@ -49,16 +49,16 @@ __device__ void attention_phase_plain(const DevModel& M, const DevKV& KV, const 
             int j = it / ns, s = it % ns;
             int t0 = (int)((long)T * s / ns), t1 = (int)((long)T * (s + 1) / ns);
             bool cur = s == ns - 1;
-            if (M.hd == 64 && G == 4) attn_item<64, 4, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, lds);
-            else if (M.hd == 128 && G == 4) attn_item<128, 4, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, lds);
-            else if (M.hd == 128 && G == 8) attn_item<128, 8, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, lds);
+            if (M.hd == 64 && G == 4) attn_item<64, 4, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, ns, lds);
+            else if (M.hd == 128 && G == 4) attn_item<128, 4, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, ns, lds);
+            else if (M.hd == 128 && G == 8) attn_item<128, 8, NW>(M, KV, xio, layer, b, j, t0, t1, cur, s, ns, lds);
         }
         base = (base + nitems) % (int)gridDim.x;
     }
 }
 
-// Fused kernel: queries / current k,v are awaited through their tags; the workgroup that owns the
-// last split of (b, j) also merges all splits of that head group (paper Section 4.2: the reduction
+// Fused kernel: queries / current k,v are awaited through their tags; the workgroups of a
+// head group's splits share out the merge of its outputs (paper Section 4.2: the reduction
 // is fused into the attention pass instead of a separate kernel).  The head geometry is a template
 // parameter here (one kernel instance per geometry) to keep the register footprint of the fused
 // kernel down to what the model at hand needs.  `pos` points to the positions staged in LDS and
@@ -105,7 +105,8 @@ __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const 
     const int ncta = (int)nc.n;
     int base = 0;
     bool ok = true;
-    TaggedAttnIO xio{in_tag, out_tag, &vote};
+    TaggedAttnIO xio{in_tag, out_tag, out_cnt, merged_img, &vote};
+    bool mine = true;   // of this wave
     for (int b = 0; b < batch; b++) {
         const int T = max(pos[b], 0);   // (-1: the sequence sits this step out and is carried as a placeholder with an empty cache)
         const int ns = attn_nsplit(T, share[b]);
@@ -117,12 +118,15 @@ __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const 
             const int j = (int)((u32)it / (u32)ns), s = it - j * ns;
             const int t0 = (int)((u32)T * (u32)s / (u32)ns), t1 = (int)((u32)T * (u32)(s + 1) / (u32)ns);   // T * 64 < 2^32
             bool cur = s == ns - 1;
-            ok = attn_item<HD, G, NW, TaggedAttnIO, MODE>(M, KV, xio, layer, b, j, t0, t1, cur, s, lds, ev) && ok;
-            if (cur) ok = attn_merge_tagged<HD, G, NT>(M, b, j, ns, out_tag, out_cnt, (float*)lds, vote, ev, merged_img) && ok;
+            ok = attn_item<HD, G, NW, TaggedAttnIO, MODE>(M, KV, xio, layer, b, j, t0, t1, cur, s, ns, lds, ev) && ok;
+            if (ns > 1 && ok) {
+                mine = attn_merge_tagged<HD, G, NT>(M, xio, b, j, s, ns) && mine;
+                if (ev && threadIdx.x == 0) as_global(ev)[5] = wall_clock64();
+            }
         }
         base = (int)nc.mod((u32)base + (u32)nitems);
     }
-    return ok;
+    return vote.all<NT>(ok && mine);
 }
 
 }  // namespace ff

@@ -501,15 +501,19 @@ struct PlainAttnIO {
         __syncthreads();
         return true;
     }
+    // Four neighbouring output dims of query head h: the slice's unnormalised output, its maximum and denominator.
     template <int HD>
-    __device__ __forceinline__ void store_partial(const DevModel& M, size_t hs, int dim, float ot, float mx, float lt) const {
-        PlainIO::st(M.part_o + hs * HD + dim, ot);
+    __device__ __forceinline__ void put(const DevModel& M, int b, int h, int split, int nsplit, int dim, const f32x4& o, float mx, float lt) const {
+        const size_t hs = ((size_t)b * M.Hq + h) * kMaxSplits + split;
+        PlainIO::st4(M.part_o + hs * HD + dim, make_float4(o.x, o.y, o.z, o.w));
         if (dim == 0) { PlainIO::st(M.part_m + hs, mx); PlainIO::st(M.part_l + hs, lt); }
     }
 };
 struct TaggedAttnIO {
     u32 in_tag;    // tag of q / kvcur (this layer's QKV projection)
-    u32 out_tag;   // tag of the partials and of attn_o (this layer's attention)
+    u32 out_tag;   // tag of the partials (this layer's attention)
+    u32 out_cnt;   // write counter of the merged output's compact vector ...
+    const WideImg* img;   // ... or (wide pass) the output projection's input image, which takes its place
     WgVote* vote;
     // Workgroup-collective, same contract as PlainAttnIO::stage_inputs.  The whole input of an
     // item is a few kilobytes (one or two 16-byte pairs per thread), so the workgroup simply
@@ -546,12 +550,56 @@ struct TaggedAttnIO {
         __syncthreads();
         return true;
     }
+    __device__ __forceinline__ void put_merged(const DevModel& M, int b, int h, int hd, int dim, float a, float c) const {   // two neighbouring dims
+        if (img) img->put2(b, h * hd + dim, a, c);
+        else cst2(M.cattn_o + ((size_t)b * M.Hq + h) * hd + dim, a, c, out_cnt);
+    }
     template <int HD>
-    __device__ __forceinline__ void store_partial(const DevModel& M, size_t hs, int dim, float ot, float mx, float lt) const {
-        tst(M.tpart_o + hs * HD + dim, ot, out_tag);
+    __device__ __forceinline__ void put(const DevModel& M, int b, int h, int split, int nsplit, int dim, const f32x4& o, float mx, float lt) const {
+        if (nsplit == 1) {   // the only slice: nothing to merge it with
+            const float inv = 1.0f / lt;
+            put_merged(M, b, h, HD, dim, o.x * inv, o.y * inv);
+            put_merged(M, b, h, HD, dim + 2, o.z * inv, o.w * inv);
+            return;
+        }
+        const size_t hs = ((size_t)b * M.Hq + h) * kMaxSplits + split;
         if (dim == 0) { tst(M.tpart_m + hs, mx, out_tag); tst(M.tpart_l + hs, lt, out_tag); }
+        tst2(M.tpart_o + hs * HD + dim, o.x, o.y, out_tag);
+        tst2(M.tpart_o + hs * HD + dim + 2, o.z, o.w, out_tag);
     }
 };
+
+// ---- row groups of a wave (attn_item) meeting in registers ----
+// Lanes l and l ^ D exchange: the lane whose bit D is clear gets (own a, other's a), the other one (other's b, own b).
+// D = 32, 16: one permlane swap; D = 8: a rotation within the row of 16 lanes.
+template <int D>
+__device__ __forceinline__ void lane_exchange(float& a, float& b, int lane) {
+    if constexpr (D == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+    } else if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        a = __uint_as_float(r[0]); b = __uint_as_float(r[1]);
+    } else {
+        static_assert(D == 8, "exchange distance");
+        const bool up = (lane & 8) != 0;
+        const float give = up ? a : b, keep = up ? b : a;
+        a = keep;
+        b = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), 0x128, 0xF, 0xF, true));   // row_ror:8
+    }
+}
+template <int D> __device__ __forceinline__ float lane_pair_max(float v, int lane) { float a = v, b = v; lane_exchange<D>(a, b, lane); return fmaxf(a, b); }
+template <int D> __device__ __forceinline__ float lane_pair_sum(float v, int lane) { float a = v, b = v; lane_exchange<D>(a, b, lane); return a + b; }
+// v[0..N) summed over lanes l and l ^ D; the lane keeps the half of the sums that its bit D names, in v[0..N/2).
+template <int D, int N, int M>
+__device__ __forceinline__ void lane_halve(float (&v)[M], int lane) {
+#pragma unroll
+    for (int i = 0; i < N / 2; i++) {
+        float a = v[i], b = v[i + N / 2];
+        lane_exchange<D>(a, b, lane);
+        v[i] = a + b;
+    }
+}
 
 #ifndef FF_ATTN_BATCH
 #define FF_ATTN_BATCH 4   // wave loads of K and of V in flight per wave (can be overridden at build time for sweeps; 8 measured no faster)
@@ -572,14 +620,15 @@ struct TaggedAttnIO {
 // last row they repeat that row), like the refills of the weight ring: where code paths that issued
 // different numbers of loads meet, the compiler waits for all.
 typedef __bf16 attn_bf8 __attribute__((ext_vector_type(8)));
+// LDS of attn_item: the waves' states, then the staged queries and the step's own key and value, then the waves' score exchange.
+template <int HD, int G, int NW> constexpr int kAttnStateFloats = NW * G * HD + 2 * NW * G;
 template <int HD, int G, int NW, class XIO, int MODE = 0>   // 0: row-wise; 1: MM, one batch of loads in flight; 2: MM, two
 __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, const XIO& xio, int layer, int b, int j, int t0, int t1, bool with_cur,
-                          int split, uint8_t* lds, u64* ev = nullptr) {
+                          int split, int nsplit, uint8_t* lds, u64* ev = nullptr) {
     constexpr bool MM = MODE > 0 && HD == 128 && G <= 8;
     constexpr bool PIPE = MODE == 2;
     constexpr int LPR = HD / 8;        // lanes per cache row
     constexpr int RPW = 64 / LPR;      // rows per wave load
-    constexpr int NS = NW * RPW;       // partial states per workgroup
     constexpr int NT = NW * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / LPR, sub = lane % LPR;
@@ -649,7 +698,7 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
     }
     // queries of the G heads and this step's own k, v: staged once per workgroup behind the state
     // merge area, then read by every lane from LDS
-    float* xin = (float*)lds + 2 * NS * G + (size_t)NS * G * HD;
+    float* xin = (float*)lds + kAttnStateFloats<HD, G, NW>;
     const bool ok = xio.template stage_inputs<HD, G, NT>(M, b, j, with_cur, xin);
     if (ev && threadIdx.x == 0) as_global(ev)[1] = wall_clock64();
     if (!ok) return false;   // uniform
@@ -752,32 +801,63 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
         for (int e = 0; e < 8; e++) { kf[e] = kc[e]; vf[e] = vc[e]; }
         update(kf, vf, grp == 0);   // scores reduce over the lanes of one row group: only group 0 is valid
     }
-    // ---- merge the NS states of this workgroup ----
-    float* sm = (float*)lds;              // [NS][G]
-    float* sl = sm + NS * G;              // [NS][G]
-    float* so = sl + NS * G;              // [NS][G][HD]
-    const int si = wave * RPW + grp;
-    if (ev && threadIdx.x == 0) as_global(ev)[2] = wall_clock64();
-    __syncthreads();
+    // ---- the row groups of a wave merge in registers, the waves' states through LDS ----
+    // Every wave first brings its groups to one maximum per head, then the sums over groups are formed by
+    // exchanging halves: of a lane's G * 8 values (head g, element e of its eight dims) it keeps those that
+    // the group bits of its lane number select, so the wave's state ends up spread over all lanes and is
+    // written and read once, in a fourth of the LDS (HD 64: an eighth) that the groups' states took.  (From the queries to the
+    // stored partial, 8B, groups' states through LDS / this: bf16 x 2 3.9 / 3.5 us, int4 x 4 7.0 / 6.8, int4 x 16 19.2 / 19.0.)
+    constexpr int NV = G * 8 / RPW;   // values a lane keeps
+    static_assert((RPW == 4 && LPR == 16) || (RPW == 8 && LPR == 8 && G == 4), "group bits of the lane number");
+    float st[G * 8];
 #pragma unroll
     for (int g = 0; g < G; g++) {
-        if (sub == 0) { sm[si * G + g] = m[g]; sl[si * G + g] = l[g]; }
+        float mw = lane_pair_max<32>(m[g], lane);
+        mw = lane_pair_max<16>(mw, lane);
+        if constexpr (RPW == 8) mw = lane_pair_max<8>(mw, lane);
+        const float f = exp2_hw(m[g] - (mw == -INFINITY ? 0.f : mw));   // groups (or waves) without a row: weight 0
+        l[g] = lane_pair_sum<16>(lane_pair_sum<32>(l[g] * f, lane), lane);
+        if constexpr (RPW == 8) l[g] = lane_pair_sum<8>(l[g], lane);
+        m[g] = mw;
 #pragma unroll
-        for (int e = 0; e < 8; e++) so[((size_t)si * G + g) * HD + sub * 8 + e] = o[g][e];
+        for (int e = 0; e < 8; e++) st[g * 8 + e] = o[g][e] * f;
+    }
+    lane_halve<32, G * 8>(st, lane);
+    lane_halve<16, G * 4>(st, lane);
+    if constexpr (RPW == 8) lane_halve<8, G * 2>(st, lane);
+    // quad c (of NV / 4) of the lane: values 4 c .. 4 c + 3; planes of 64 float4, so that neither side has bank conflicts
+    f32x4* so = (f32x4*)lds;                                            // [wave][NV / 4][64]
+    float2* sml = (float2*)((float*)lds + (size_t)NW * G * HD);         // [wave][G] (maximum, denominator)
+    if (ev && threadIdx.x == 0) as_global(ev)[2] = wall_clock64();
+#pragma unroll
+    for (int c = 0; c < NV / 4; c++) so[(wave * (NV / 4) + c) * 64 + lane] = f32x4{st[4 * c], st[4 * c + 1], st[4 * c + 2], st[4 * c + 3]};
+    if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; g++) sml[wave * G + g] = make_float2(m[g], l[g]);
     }
     __syncthreads();
-    for (int idx = threadIdx.x; idx < G * HD; idx += NT) {
-        int g = idx / HD, dim = idx % HD;
-        float mx = -INFINITY;
-        for (int s = 0; s < NS; s++) mx = fmaxf(mx, sm[s * G + g]);
-        float lt = 0.f, ot = 0.f;
-        for (int s = 0; s < NS; s++) {
-            float w = exp2_hw(sm[s * G + g] - mx);   // empty states have m = -inf -> weight 0
-            lt = fmaf(sl[s * G + g], w, lt);
-            ot = fmaf(so[((size_t)s * G + g) * HD + dim], w, ot);
+    for (int i = threadIdx.x; i < NV / 4 * 64; i += NT) {
+        const int c = i >> 6, n = i & 63;
+        // the value 4 c of lane n: its group bits select halves of the list (head, element) from the top down
+        const int first = (RPW == 8 ? 16 * (n >> 5) + 8 * ((n >> 4) & 1) + 4 * ((n >> 3) & 1) : G * 2 * (n >> 4)) + 4 * c;
+        const int g = first >> 3, dim = (n % LPR) * 8 + (first & 7);
+        float2 ml[NW];
+        f32x4 v[NW];
+#pragma unroll
+        for (int w = 0; w < NW; w++) { ml[w] = sml[w * G + g]; v[w] = so[(w * (NV / 4) + c) * 64 + n]; }
+        float mx = ml[0].x;
+#pragma unroll
+        for (int w = 1; w < NW; w++) mx = fmaxf(mx, ml[w].x);
+        float lt = 0.f;
+        f32x4 ot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            const float f = exp2_hw(ml[w].x - mx);   // empty states have m = -inf -> weight 0
+            lt = fmaf(ml[w].y, f, lt);
+#pragma unroll
+            for (int e = 0; e < 4; e++) ot[e] = fmaf(v[w][e], f, ot[e]);
         }
-        size_t hs = ((size_t)b * M.Hq + (j * G + g)) * kMaxSplits + split;
-        xio.template store_partial<HD>(M, hs, dim, ot, mx, lt);
+        xio.template put<HD>(M, b, j * G + g, split, nsplit, dim, ot, mx, lt);
     }
     if (ev && threadIdx.x == 0) as_global(ev)[3] = wall_clock64();
     return ok;
@@ -827,99 +907,80 @@ __device__ void attn_merge(const DevModel& M, int b, int j, int nsplit, float* l
     }
 }
 
-// The same merge on tagged partials (fused kernel): the workgroup that computed the LAST split of
-// (b, j) gathers all splits, re-reading until every partial carries this layer's attention tag,
-// and publishes attn_o with the same tag.  Returns false on a time-out.
-// img (wide pass): the merged output goes into the output projection's input image instead of the compact vector.
+// The same merge on tagged partials (fused kernel), shared out: each of the nsplit workgroups of the head
+// group merges its share of the output dims, in pairs, out of all slices' partials.  Nothing goes through
+// LDS and no wave waits for another: a lane requests the partial outputs, maxima and denominators it needs
+// in one round and repeats that until all of them carry this layer's attention tag.  Up to four slices: a
+// lane has a pair to itself; more: sixteen lanes share a pair, each taking every sixteenth slice, and add up with
+// row operations.  What bounds it is the hop from the stores to the loads.  (The workgroup of the last slice alone
+// gathering all partials, which first waited for the maxima and then re-read what was stale: from the stored partials to the
+// merged output 7.7 us at 8B int4 x 1, context 2048, 5.7 at x 4 and 4.7 at x 16; shared out 3.2, 2.6 and 2.1.)
+// A workgroup whose item has several slices has no other item (attn_share_of), so the waits are never circular.
+// Returns false (per wave) on a time-out.
 template <int HD, int G, int NT>
-__device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, int b, int j, int nsplit, u32 tag, u32 out_cnt, float* lds, WgVote& vote, u64* ev = nullptr,
-                                                  const WideImg* img = nullptr) {
-    float* ms = lds;
-    float* ls = lds + G * kMaxSplits;
-    constexpr int kSB = 16;   // splits gathered per batch of loads
-    constexpr u32 kAll = (1u << kSB) - 1;
-    // (re)loads the partial outputs of splits s0.. (bit u of mask = split s0+u) for output pair d2
-    auto issue = [&](u32x4 (&r)[kSB], int hs, int d2, int s0, u32 mask) {
-#pragma unroll
-        for (int u = 0; u < kSB; u++)
-            if ((mask >> u) & 1) r[u] = tld2(M.tpart_o, (hs + min(s0 + u, nsplit - 1)) * HD + d2);
-    };
-    auto stale_of = [&](const u32x4 (&r)[kSB]) {
-        u32 m = 0;
-#pragma unroll
-        for (int u = 0; u < kSB; u++) if (!(r[u].y == tag && r[u].w == tag)) m |= 1u << u;
-        return m;
-    };
-    // The first batch of partial outputs is requested before the maxima and denominators are
-    // waited for: all partials of a head group arrive in one round trip, and whatever is still
-    // stale (the last split's rows, typically) is re-read selectively.
-    u32x4 r[kSB];
-    const bool pre = (int)threadIdx.x < G * HD / 2;
-    if (pre) issue(r, (b * M.Hq + (j * G + (int)threadIdx.x / (HD / 2))) * kMaxSplits, ((int)threadIdx.x % (HD / 2)) * 2, 0, kAll);
-    __syncthreads();
-    bool done = false;
-    for (int spins = 0; spins < kSpinLimit && !done; spins++) {
-        bool ok = true;
-        for (int idx = threadIdx.x; idx < G * nsplit; idx += NT) {
-            int g = idx / nsplit, s = idx % nsplit;
-            int hs = (b * M.Hq + (j * G + g)) * kMaxSplits + s;
-            u32x2 pm = tld1(M.tpart_m, hs), pl = tld1(M.tpart_l, hs);
-            ok = ok && pm.y == tag && pl.y == tag;
-            ms[g * kMaxSplits + s] = __uint_as_float(pm.x);
-            ls[g * kMaxSplits + s] = __uint_as_float(pl.x);
-        }
-        done = vote.all<NT>(ok);
-        if (!done) __builtin_amdgcn_s_sleep(2);
-    }
-    if (!done) { atomicCAS(M.status, 0, -53); return false; }
-    if (ev && threadIdx.x == 0) as_global(ev)[4] = wall_clock64();
+__device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, const TaggedAttnIO& xio, int b, int j, int split, int nsplit) {
+    constexpr int E = G * HD / 2;   // pairs of the head group
+    const u32 tag = xio.out_tag;
+    const int e0 = (int)((u32)(E * split) / (u32)nsplit), e1 = (int)((u32)(E * (split + 1)) / (u32)nsplit);
+    const int h0 = b * M.Hq + j * G;
     bool all_ok = true;
-    for (int idx = threadIdx.x; idx < G * HD / 2; idx += NT) {
-        int g = idx / (HD / 2), d2 = (idx % (HD / 2)) * 2;
-        int hs = (b * M.Hq + (j * G + g)) * kMaxSplits;
-        // every thread reduces the maxima and denominators of its head itself (independent LDS
-        // reads; no serial section, no further barrier)
-        float mx = -INFINITY;
-        for (int s0 = 0; s0 < nsplit; s0 += kSB) {
+    // N partials per lane: slices s, s + STEP, ... (the last one again behind the end, with weight 0)
+    auto gather = [&](auto N_, auto STEP_, int e, int s, float& a0, float& a1) {
+        constexpr int N = decltype(N_)::value, STEP = decltype(STEP_)::value;
+        const int hs = (h0 + e / (HD / 2)) * kMaxSplits, d2 = (e % (HD / 2)) * 2;
+        u32x4 o[N];
+        u32x2 pm[N], pl[N];
+        bool ok = false;
+        for (int spins = 0; spins < kSpinLimit && !ok; spins++) {
+            bool mine = true;
 #pragma unroll
-            for (int u = 0; u < kSB; u++) mx = fmaxf(mx, ms[g * kMaxSplits + min(s0 + u, nsplit - 1)]);   // batched LDS reads
+            for (int u = 0; u < N; u++) {
+                const int k = hs + min(s + STEP * u, nsplit - 1);
+                o[u] = tld2(M.tpart_o, k * HD + d2);
+                pm[u] = tld1(M.tpart_m, k);
+                pl[u] = tld1(M.tpart_l, k);
+            }
+#pragma unroll
+            for (int u = 0; u < N; u++) mine = mine && o[u].y == tag && o[u].w == tag && pm[u].y == tag && pl[u].y == tag;
+            ok = __all(mine);
+            if (!ok) __builtin_amdgcn_s_sleep(1);
         }
+        if (!ok) { atomicCAS(M.status, 0, -53); all_ok = false; return; }
+        float mx = __uint_as_float(pm[0].x);
+#pragma unroll
+        for (int u = 1; u < N; u++) mx = fmaxf(mx, __uint_as_float(pm[u].x));
+        if constexpr (STEP > 1) mx = group_max16(mx);
         float lt = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += kSB) {
+        a0 = a1 = 0.f;
 #pragma unroll
-            for (int u = 0; u < kSB; u++) {
-                const int s = min(s0 + u, nsplit - 1);
-                const float w = exp2_hw(ms[g * kMaxSplits + s] - mx);
-                lt = fmaf(ls[g * kMaxSplits + s], s0 + u < nsplit ? w : 0.f, lt);
-            }
+        for (int u = 0; u < N; u++) {
+            const float w = s + STEP * u < nsplit ? exp2_hw(__uint_as_float(pm[u].x) - mx) : 0.f;
+            lt = fmaf(__uint_as_float(pl[u].x), w, lt);
+            a0 = fmaf(__uint_as_float(o[u].x), w, a0);
+            a1 = fmaf(__uint_as_float(o[u].z), w, a1);
         }
+        if constexpr (STEP > 1) { lt = group_sum<16>(lt); a0 = group_sum<16>(a0); a1 = group_sum<16>(a1); }
         const float inv = 1.0f / lt;
-        float a0 = 0.f, a1 = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += kSB) {
-            u32 need = (idx == (int)threadIdx.x && s0 == 0) ? 0u : kAll;   // the first batch is already in flight
-            bool ok = false;
-            for (int spins = 0; spins < kSpinLimit && !ok; spins++) {
-                issue(r, hs, d2, s0, need);
-                need = stale_of(r);
-                ok = need == 0;
-            }
-            all_ok = all_ok && ok;
-            if (!ok) atomicCAS(M.status, 0, -54);
-#pragma unroll
-            for (int u = 0; u < kSB; u++) {
-                const float mu = ms[g * kMaxSplits + min(s0 + u, nsplit - 1)];
-                const float w = s0 + u < nsplit ? exp2_hw(mu - mx) * inv : 0.f;
-                a0 = fmaf(__uint_as_float(r[u].x), w, a0);
-                a1 = fmaf(__uint_as_float(r[u].z), w, a1);
-            }
+        a0 *= inv; a1 *= inv;
+    };
+    typedef std::integral_constant<int, 1> One;
+    if (nsplit <= 4) {
+        for (int e = e0 + (int)threadIdx.x; e < e1; e += NT) {   // (a wave's lanes past the end do not vote)
+            float a0, a1;
+            gather(std::integral_constant<int, 4>{}, One{}, e, 0, a0, a1);
+            if (all_ok) xio.put_merged(M, b, j * G + e / (HD / 2), HD, (e % (HD / 2)) * 2, a0, a1);
         }
-        if (img) img->put2(b, (j * G + g) * HD + d2, a0, a1);
-        else {
-            cst2(M.cattn_o + ((size_t)b * M.Hq + (j * G + g)) * HD + d2, a0, a1, out_cnt);
-        }
+        return all_ok;
     }
-    if (ev && threadIdx.x == 0) as_global(ev)[5] = wall_clock64();
-    return vote.all<NT>(all_ok);
+    const int s = (int)threadIdx.x & 15;
+    for (int e = e0 + ((int)threadIdx.x >> 4); e < e1; e += NT / 16) {
+        float a0, a1;
+        typedef std::integral_constant<int, 16> Row;
+        if (nsplit <= 16) gather(One{}, Row{}, e, s, a0, a1);
+        else gather(std::integral_constant<int, kMaxSplits / 16>{}, Row{}, e, s, a0, a1);
+        if (all_ok && s == 0) xio.put_merged(M, b, j * G + e / (HD / 2), HD, (e % (HD / 2)) * 2, a0, a1);
+    }
+    return all_ok;
 }
 
 // Number of KV splits for a sequence with `ncache` cached rows when `share` workgroups are
@@ -999,9 +1060,9 @@ struct EpiSwiGLU {
 };
 // ---- fused-kernel epilogues: outputs go to the tagged exchange buffers ----
 struct EpiQKVTagged {   // pos: positions of this step, staged in LDS (-1: the sequence sits the step out, its cache is not touched)
-    const DevModel& M; const DevKV& KV; const int* pos; int layer; const float2* rope; u32 tag;
+    const DevModel& M; const DevKV& KV; const int* pos; int layer; const float2* rope; u32 tag; int hd;   // hd: a constant of the kernel instance, so that the row arithmetic is shifts
     __device__ __forceinline__ void operator()(int pair, int b, float v0, float v1) const {
-        const int half = M.hd / 2;
+        const int half = hd / 2;
         const int nq = M.Hq * half, nk = M.Hkv * half;
         const int p = pos[b];
         if (pair < nq + nk) {
@@ -1012,22 +1073,22 @@ struct EpiQKVTagged {   // pos: positions of this step, staged in LDS (-1: the s
             float a = v0 * cs.x - v1 * cs.y;
             float c = v1 * cs.x + v0 * cs.y;
             if (isq) {
-                tagged_t* qp = M.tq + ((size_t)b * M.Hq + head) * M.hd;
+                tagged_t* qp = M.tq + ((size_t)b * M.Hq + head) * hd;
                 tst(qp + i, a, tag); tst(qp + i + half, c, tag);
             } else {
                 bf16_t ab = f_to_bf(a), cb = f_to_bf(c);
-                bf16_t* row = KV.plane(M, layer, b, head, 0) + (size_t)p * M.hd;
+                bf16_t* row = KV.plane(M, layer, b, head, 0) + (size_t)p * hd;
                 if (p >= 0) { as_global(row)[i] = ab; as_global(row)[i + half] = cb; }
-                tagged_t* kc = M.tkvcur + ((size_t)b * 2 + 0) * M.Hkv * M.hd + (size_t)head * M.hd;
+                tagged_t* kc = M.tkvcur + ((size_t)b * 2 + 0) * M.Hkv * hd + (size_t)head * hd;
                 tst(kc + i, bf_to_f(ab), tag); tst(kc + i + half, bf_to_f(cb), tag);
             }
         } else {
             int pp = pair - nq - nk;
             int head = pp / half, i = (pp % half) * 2;
             bf16_t ab = f_to_bf(v0), cb = f_to_bf(v1);
-            bf16_t* row = KV.plane(M, layer, b, head, 1) + (size_t)p * M.hd;
+            bf16_t* row = KV.plane(M, layer, b, head, 1) + (size_t)p * hd;
             if (p >= 0) *as_global((u32*)(row + i)) = (u32)ab | ((u32)cb << 16);
-            tagged_t* vc = M.tkvcur + ((size_t)b * 2 + 1) * M.Hkv * M.hd + (size_t)head * M.hd;
+            tagged_t* vc = M.tkvcur + ((size_t)b * 2 + 1) * M.Hkv * hd + (size_t)head * hd;
             tst2(vc + i, bf_to_f(ab), bf_to_f(cb), tag);
         }
     }

@@ -36,7 +36,7 @@
 namespace ff {
 
 // ---------------------------------------------------------------- LDS
-constexpr int kWideAttnBytes = 142592;   // attention state of eight waves at head dimension 128 with eight query heads (attn_item); the projections' regions lie inside
+constexpr int kWideAttnBytes = kWideRedBytes + kWideSzBytes;   // the projections' regions; the attention's (attn_item) lies inside
 constexpr int kWideRopeOff = kWideAttnBytes;
 constexpr int kWideResOff = kWideRopeOff + kMaxBatchWide * 64 * 8;     // residual rows of the workgroup: [sequence][kWideResRows]
 constexpr int kWideResRows = 32;
@@ -44,8 +44,8 @@ constexpr int kWideRmsOff = kWideResOff + kMaxBatchWide * kWideResRows * 4;   //
 constexpr int kWideIntOff = kWideRmsOff + kWideWaves * kMaxBatchWide * 4;     // positions, attention shares, epoch verdicts, arrival counter, vote slots
 constexpr int kWideMaxCtas = 256;   // workgroups whose sums of squares a consumer gathers in one round (wide_project)
 constexpr int kWideLdsBytes = kWideIntOff + 1024;
-static_assert(kWideRedBytes + kWideSzBytes <= kWideAttnBytes && kWideLdsBytes <= 160 * 1024, "LDS layout of the wide pass");
-static_assert((2 * 32 * 8 + 32 * 8 * 128 + (8 + 2) * 128 + kWideWaves * 128) * 4 <= kWideAttnBytes, "attention state");
+static_assert(kWideLdsBytes <= 160 * 1024, "LDS layout of the wide pass");
+static_assert((kAttnStateFloats<128, 8, kWideWaves> + (8 + 2) * 128 + kWideWaves * 128) * 4 <= kWideAttnBytes, "attention state");
 
 // ---------------------------------------------------------------- epochs
 struct WideSync {
@@ -124,6 +124,7 @@ struct WideCtx {
     float* ss;             // sums of squares beside it (residual)
     float* xres;           // LDS: residual rows of this workgroup
     RowRange own;
+    int hd;                // head dimension (a constant of the kernel instance: the row arithmetic of q, k, v is shifts)
 };
 // Rows row .. row + 3 (nv of them real) for sequence n with the finished sums c; gw: the next norm's gains of these rows.
 __device__ __forceinline__ float wide_residual(const WideCtx& C, int row, int n, const f32x4& c, const u32x2& gw) {
@@ -139,12 +140,44 @@ __device__ __forceinline__ void wide_swiglu(const WideCtx& C, int f, int n, cons
     const float h0 = c.x / (1.0f + expf(-c.x)) * c.y, h1 = two ? c.z / (1.0f + expf(-c.z)) * c.w : 0.f;
     C.out.put2(n, f, h0, h1);   // (a missing second unit is padding, zero in the image)
 }
+// Four rows of the QKV projection (row a multiple of four, all of one head): two RoPE pairs (i, i + hd / 2) and
+// (i + 1, i + 1 + hd / 2) of a query or key head, or four value rows.
+__device__ __forceinline__ void wide_qkv(const WideCtx& C, int row, int n, const f32x4& c) {
+    const DevModel& M = C.M;
+    const int hd = C.hd, half = hd / 2, nq = M.Hq * hd, nk = M.Hkv * hd, p = C.pos[n];   // (p < 0: the sequence sits the step out, its cache is not touched)
+    if (row < nq + nk) {
+        const bool isq = row < nq;
+        const int r = isq ? row : row - nq, head = r / hd, i = (r % hd) / 2;
+        const float4 cs = *(const float4*)(C.rope + n * half + i);
+        const float a0 = c.x * cs.x - c.y * cs.y, b0 = c.y * cs.x + c.x * cs.y, a1 = c.z * cs.z - c.w * cs.w, b1 = c.w * cs.z + c.z * cs.w;
+        if (isq) {
+            tagged_t* q = M.tq + ((size_t)n * M.Hq + head) * hd + i;
+            tst2(q, a0, a1, C.tag);
+            tst2(q + half, b0, b1, C.tag);
+        } else {
+            const u32 a = (u32)f_to_bf(a0) | ((u32)f_to_bf(a1) << 16), b = (u32)f_to_bf(b0) | ((u32)f_to_bf(b1) << 16);
+            tagged_t* k = M.tkvcur + ((size_t)(n * 2) * M.Hkv + head) * hd + i;
+            tst2(k, bf_lo(a), bf_hi(a), C.tag);
+            tst2(k + half, bf_lo(b), bf_hi(b), C.tag);
+            if (p >= 0) {
+                bf16_t* kr = C.KV.plane(M, C.layer, n, head, 0) + (size_t)p * hd + i;
+                *as_global((u32*)kr) = a;
+                *as_global((u32*)(kr + half)) = b;
+            }
+        }
+    } else {
+        const int r = row - nq - nk, head = r / hd, i = r % hd;
+        const u32 a = (u32)f_to_bf(c.x) | ((u32)f_to_bf(c.y) << 16), b = (u32)f_to_bf(c.z) | ((u32)f_to_bf(c.w) << 16);
+        tagged_t* v = M.tkvcur + ((size_t)(n * 2 + 1) * M.Hkv + head) * hd + i;
+        tst2(v, bf_lo(a), bf_hi(a), C.tag);
+        tst2(v + 2, bf_lo(b), bf_hi(b), C.tag);
+        if (p >= 0) *as_global((u32x2*)(C.KV.plane(M, C.layer, n, head, 1) + (size_t)p * hd + i)) = u32x2{a, b};
+    }
+}
 __device__ __forceinline__ void wide_epilogue(const WideCtx& C, int row, int n, const f32x4& c, int nv) {
     const int pair = row >> 1;
     if (C.kind == PH_QKV) {
-        EpiQKVTagged e{C.M, C.KV, C.pos, C.layer, C.rope, C.tag};
-        e(pair, n, c.x, c.y);
-        if (nv > 2) e(pair + 1, n, c.z, c.w);
+        wide_qkv(C, row, n, c);   // (the number of rows is a multiple of the head dimension: all four are there)
     } else if (C.kind == PH_GU) {
         wide_swiglu(C, pair, n, c, nv > 2);
     } else if (C.pos[n] >= 0) {   // LM head (no logits for a sequence that sits the step out)
@@ -328,7 +361,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     auto image = [&](uint8_t* p) { return WideImg{p, kImgE, batch, NC}; };
     auto timed = [&](int ph, int ev) { if (M.dbg && blockIdx.x == 0 && threadIdx.x == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64(); };
     __syncthreads();
-    WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own};
+    WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own, HD};
     // the step's embedding rows enter like the output of a projection onto zero
     if (16 * wave < kWideResRows) {
         const int row = own.r0 + 16 * wave + 4 * (lane >> 4), seq = lane & 15;
@@ -379,7 +412,6 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
             sync.arrive(e0 + 1u, lane);
             timed(ph, EV_ATT_END);
-            __syncthreads();   // LDS goes back to the projections
             W = FF_PMAT_FIELDS(Lp->o);
             epoch = e0 + 1u; img = blk + WL.a; gain = Lp->g2;
             C.out = image(blk + WL.x2); C.ss = (float*)(blk + WL.ss2);

@@ -1068,3 +1068,16 @@ def test_models_for_several_sequences_on_a_smaller_grid(monkeypatch, grid, d_mod
     assert torch.equal(want, stat) and torch.equal(caches[0][1], caches[1][1])
     assert torch.equal(got[[0, 2]], want[[0, 2]]) and bool((got[1] == 7.5).all())
     dec.close()
+
+
+@pytest.mark.parametrize("max_batch", (1, 2), ids=("model-for-one", "model-for-two"))
+@pytest.mark.parametrize("heads", ((8, 2, 64), (8, 2, 128), (8, 1, 128)), ids=("hd64-g4", "hd128-g4", "hd128-g8"))
+def test_merge_of_every_number_of_slices(heads, max_batch):
+    """A head group's slices share out the merge of their partial outputs: one slice (no merge), two to four (a lane
+    holds all slices of its outputs), five and more (sixteen lanes share an output; the shares are uneven for numbers that
+    do not divide the outputs), and two to four rounds of sixteen.  Model widths that leave most workgroups without a slice.
+    max_batch 2: a second sequence with one slice sits beside the first one."""
+    hq, hkv, hd = heads
+    S = synth.TINY.replace(name="slices", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, vocab=512)
+    for T0 in (63, 128, 255, 256, 320, 1023, 4200, 8300, 12300):   # 1, 2, 3, 4, 5, 15, 32, 48, 64 slices
+        _run_teacher_forced(S, 0x2505227e0 + T0, synth.WDTYPE_BF16, batch=max_batch, T0=[T0, 17][:max_batch], steps=1, check_kv=False)
