@@ -159,11 +159,12 @@ int ff_kv_free(ff_kv *kv);
  * as matrix-core operand tiles, projections on 16x16x32 tiles (int8 and int4 codes converted to bf16 in
  * registers), activations exchanged in operand order by the workgroups that own them.  The inputs of its
  * projections carry 24 bits at one sequence and 17 (bf16 head + remainder) at more, everything else fp32.
- * Models for one sequence run the row-partitioned pass on row-major weights (exchanged values carry 22
- * mantissa bits).  The wide pass needs a grid of at most 256 workgroups (one per compute unit) that leaves
- * at most 32 rows of d_model to each, which every supported d_model does on a whole MI355X; on a partition
- * that does not, a model for several sequences keeps row-major weights and a step runs its sequences one
- * after another on the row-partitioned pass, each streaming the weights again. */
+ * Models for one sequence run a kernel of their own on the same weight tiles (exchanged values carry 22
+ * mantissa bits, projections multiply them exactly, sums are fp32).  Both need a grid of at most 256
+ * workgroups (one per compute unit) that leaves at most 32 rows of d_model to each, which d_model <= 8192
+ * does on a whole MI355X; wider models for one sequence, and models on a partition of the chip that does not,
+ * keep row-major weights and a step runs its sequences one after another on the row-partitioned kernel,
+ * each streaming the weights again. */
 int ff_decode_step(ff_model *m, const int32_t *tokens_dev, const int32_t *positions_dev, ff_kv *kv,
                    float *logits_dev, int32_t batch, void *stream);
 
@@ -200,8 +201,8 @@ int ff_debug_dequant(const ff_model *m, int32_t layer, int32_t which, float *out
 
 /* Runs the decode kernels' own projection code on caller input: out_dev[b][n] = sum_k W[n][k] *
  * in_dev[b][k] for matrix `which` of `layer`, fp32 in_dev [batch][K], fp32 out_dev [batch][N] with
- * rows in canonical order.  path 0: the vector-ALU GEMV (batch 1..4) used at batch 1 and
- * by the per-operation baseline; path 1: the matrix-core projection of models for several sequences
+ * rows in canonical order.  path 0: the vector-ALU GEMV (batch 1..4) of the row-partitioned kernel and
+ * the per-operation baseline; path 1: the matrix-core projection of models for several sequences
  * (batch 2..4, inputs as bf16 head + remainder; K * 4 bytes * batch at most 128 KiB; a bf16 LM head
  * over quantised layers stays on the vector ALU).  Fed with
  * unit vectors it returns the columns of W exactly as the hot path dequantises them (the int8 row
@@ -220,10 +221,10 @@ int ff_debug_gemv(ff_model *m, int32_t layer, int32_t which, const float *in_dev
  *   [12P+32W, +40W)   layer 1, per workgroup: 8 per projection (input staging entered, first load
  *                     checked, last light wait done, all fresh, staged, number of stale passes),
  *                     then 8 about its attention work (start, queries seen, rows done, partial
- *                     stored, split maxima seen and merged output stored if it merges, end)
- * That is the row-partitioned kernel; a wide pass fills the same buffer with
+ *                     stored, unused, share of the merged output stored, end)
+ * That is the row-partitioned kernel; the others fill the same buffer with
  *   [0, 12P)          workgroup 0: 12 slots per phase (0 input published, 1 projection done, 2 first weights
- *                     requested, 3 phase starts, 4 / 5 first panel multiplied / partial tiles exchanged, 7
+ *                     requested (wide pass only), 3 phase starts, 4 / 5 first panel multiplied / partial tiles exchanged, 7
  *                     attention end, 8 / 9 as 4 / 5 for the last further panel)
  *   [12P, 12P+32W)    layer 1, 4 per wave of its 8: first panel of QKV/O/GU/DOWN multiplied
  *   [12P+32W, +40W)   layer 1, per workgroup: the last 8 words, about its attention work, as above */
@@ -270,7 +271,7 @@ int ff_debug_mute_workgroup(ff_model *m, int32_t workgroup);
 
 /* Number of device-wide barriers one fused step executes (0: phases are ordered by tagged dataflow;
  * kept for tests of the schedule), and the number of
- * workgroups / threads per workgroup the row-partitioned kernel launches with (a wide pass: the same
+ * workgroups / threads per workgroup the row-partitioned kernel launches with (the others: the same
  * workgroups, twice the threads). */
 int ff_fused_schedule(const ff_model *m, int32_t *barriers_per_step, int32_t *n_workgroups,
                       int32_t *threads_per_workgroup);

@@ -6,7 +6,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflashformer.so")
-SOURCES = ["flashformer.hip"] + [f"ff_fused_{w}_hd{h}_g{g}.hip" for w in ("bf16", "int8", "int4")
+SOURCES = ["flashformer.hip"] + [f"ff_{k}_{w}_hd{h}_g{g}.hip" for k in ("fused", "solo") for w in ("bf16", "int8", "int4")
                                for h, g in ((64, 4), (128, 4), (128, 8))]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

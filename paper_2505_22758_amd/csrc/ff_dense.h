@@ -139,9 +139,8 @@ __device__ __forceinline__ u32x4 i8_to_bf16(u32 wa, u32 wb) {
 // (With 128 + n what is subtracted again is six times as large: relative error of the logits against 64 bits, one layer,
 // 16 sequences: 2.5e-5 with 128 + n, 7.2e-6 with 16 + n, bf16 weights 6.1e-6; 8B x 16, eight layers 681 / 679 us per step.)
 constexpr float kI4Offset = 16.f;
-__device__ __forceinline__ u32x4 i4_to_bf16(u32 w) {
-    return u32x4{(w & 0x00780078u) | 0x41804180u, ((w >> 4) & 0x00780078u) | 0x41804180u, ((w >> 8) & 0x00780078u) | 0x41804180u,
-                 (__builtin_amdgcn_alignbit(w, w, 12) & 0x00780078u) | 0x41804180u};
+__device__ __forceinline__ u32x4 i4_to_bf16(u32 w, u32 mask = 0x00780078u, u32 offs = 0x41804180u) {
+    return u32x4{(w & mask) | offs, ((w >> 4) & mask) | offs, ((w >> 8) & mask) | offs, (__builtin_amdgcn_alignbit(w, w, 12) & mask) | offs};
 }
 
 // acc[t] += (inputs of iteration it) x (weights of tile t).

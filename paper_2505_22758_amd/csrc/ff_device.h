@@ -55,6 +55,8 @@ struct PMat {
     int n, k;           // rows (outputs), columns (inputs)
     int wd;
     int tiled;
+    int panels;         // tiled: tiles of a panel of the one-sequence step (ff_solo.h)
+    const u32* sz;      // int4, one-sequence step: (scale | zero << 16), in the tiles' order: [tile][group][row of the tile]
     __host__ __device__ static size_t row_bytes_of(int k, int wd, int tiled) {
         if (!tiled) return wd == W_BF16 ? (size_t)k * 2 : wd == W_INT8 ? (size_t)k : (size_t)k / 2;
         const size_t cols = wd == W_INT4 ? 128 : 64, pad = (k + cols - 1) / cols * cols;
@@ -68,17 +70,22 @@ struct PMat {
         const int r1 = 4 * (int)(g * (u64)(c + 1) / (u64)tiled);
         return Rows{4 * (int)(g * (u64)c / (u64)tiled), r1 < n ? r1 : n};
     }
+    // The tile that holds a row (tiled layout): rows [r0, r1).
+    __host__ __device__ Rows tile_rows(int row) const {
+        const u64 g = (u64)(n + 3) / 4;
+        const Rows r = cta_rows((int)(((u64)(row / 4 + 1) * (u64)tiled - 1) / g));
+        const int t0 = r.r0 + (row - r.r0) / 16 * 16;
+        return Rows{t0, r.r1 - t0 < 16 ? r.r1 : t0 + 16};
+    }
     // Byte offset of unit 0 of a row; consecutive units of the row are `stride` bytes apart.
     __host__ __device__ size_t row_off(int row, size_t* stride) const {
         if (!tiled) { *stride = 16; return (size_t)row * row_bytes(); }
-        const u64 g = (u64)(n + 3) / 4;
-        const Rows r = cta_rows((int)(((u64)(row / 4 + 1) * (u64)tiled - 1) / g));
-        const int t0 = r.r0 + (row - r.r0) / 16 * 16, nt = r.r1 - t0 < 16 ? r.r1 - t0 : 16;
-        *stride = (size_t)nt * 16;
-        return (size_t)t0 * row_bytes() + (size_t)(row - t0) * 16;
+        const Rows t = tile_rows(row);
+        *stride = (size_t)(t.r1 - t.r0) * 16;
+        return (size_t)t.r0 * row_bytes() + (size_t)(row - t.r0) * 16;
     }
 };
-#define FF_PMAT_FIELDS(p) PMat{(p).w, (p).s, (p).z, (p).n, (p).k, (p).wd, (p).tiled}
+#define FF_PMAT_FIELDS(p) PMat{(p).w, (p).s, (p).z, (p).n, (p).k, (p).wd, (p).tiled, (p).panels, (p).sz}
 // int4 codes of a canonical word (nibble i = code i) in the tiled layout's order.
 __host__ __device__ inline u32 i4_tiled_word(u32 w) {
     u32 e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
@@ -119,7 +126,8 @@ struct DevModel {
     int L, d, Hq, Hkv, hd, F, V;
     GuPerm gu;               // gate/up pair order of the packed copy
     float eps;
-    const PLayer* layers;    // device array [L]
+    const PLayer* layers;    // device array [L + 1]; the last entry's g1 and qkv are the final gain and the LM head
+    size_t layer_stride;     // bytes from a layer's matrices and gains to the next one's
     const bf16_t* embed;
     const bf16_t* gf;
     PMat lm;
@@ -144,7 +152,7 @@ struct DevModel {
     // wide pass (ff_wide.h): exchange images and sums of squares, wring blocks (one per layer and one for the LM head,
     // or 1: reused by every layer); one epoch word per workgroup
     uint8_t* wimg;  u32* wflag;  int wring, wbatch;   // wbatch: sequences the images have room for
-    u32* stepctr;    // [0] fused launches executed so far on these buffers (skipped steps do not count); [1] sequences the last one served
+    u32* stepctr;    // [0] fused launches executed so far on these buffers (skipped steps do not count); [1] sequences the last one served; [2] one-sequence step: workgroups that have read [0]
     u32x2* tpart_m;  u32x2* tpart_l;  u32x2* tpart_o;
     int* status;
     u64* dbg;        // optional timeline buffer (null unless enabled through the debug entry point)

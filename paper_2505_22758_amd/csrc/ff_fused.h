@@ -1,7 +1,7 @@
 // The fused whole-model decode kernel (one persistent launch per decode step).
 #pragma once
 #include <mutex>
-#include "ff_wide.h"
+#include "ff_solo.h"
 
 namespace ff {
 
@@ -214,8 +214,10 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
             if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_ATT_START, lane);
             u64* aev = dbg_stage_slots(M, n_phases, ncta, D.layer, 4);
             if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
-            const bool ok = attention_phase_tagged<kFusedWaves, HD, G, kAttnModeOf<WD>>(M, KV, pos_lds, share_lds, batch, D.layer, lds, tag_of(tag_base, D.layer, TAG_QKV),
-                                                                tag_of(tag_base, D.layer, TAG_ATT), sl + D.layer, n_ctas, vote, aev);
+            bool mine = true;
+            bool ok = attention_phase_tagged<kFusedWaves, HD, G, kAttnModeOf<WD>, false>(M, KV, pos_lds, share_lds, batch, D.layer, lds, tag_of(tag_base, D.layer, TAG_QKV),
+                                                                tag_of(tag_base, D.layer, TAG_ATT), sl + D.layer, n_ctas, vote, mine, aev);
+            ok = vote.all<kFusedThreads>(ok && mine);
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
             if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_ATT_END, lane);
             if (!ok) return;
@@ -318,6 +320,15 @@ inline hipError_t launch_wide_instance(const FusedLaunch& a, const char** what) 
     return hipGetLastError();
 }
 template <int WD, int HD, int G>
+inline hipError_t launch_solo_instance(const FusedLaunch& a, const char** what) {
+    auto kern = solo_decode_kernel<WD, HD, G>;
+    static KernelSetup setup;
+    if (hipError_t e = setup.run((const void*)kern, kSoloThreads, SoloLds<WD>::kBytes)) { *what = setup.what; return e; }
+    kern<<<a.n_cta, kSoloThreads, SoloLds<WD>::kBytes, a.stream>>>(a.M, a.KV, a.tokens, a.pos, a.logits, a.lm_in_kernel, a.n_cta, a.mute_wg, a.switches);
+    *what = "one-sequence kernel launch";
+    return hipGetLastError();
+}
+template <int WD, int HD, int G>
 inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
     // (the host decides whether a pass is wide, and sizes the buffers for it; up to eight sequences share an operand tile with their remainders)
     if (a.wide) return a.batch == 1 ? launch_wide_instance<WD, 1, HD, G>(a, what) : a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
@@ -332,7 +343,9 @@ inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
     X(bf16, W_BF16, 64, 4) X(bf16, W_BF16, 128, 4) X(bf16, W_BF16, 128, 8) \
     X(int8, W_INT8, 64, 4) X(int8, W_INT8, 128, 4) X(int8, W_INT8, 128, 8) \
     X(int4, W_INT4, 64, 4) X(int4, W_INT4, 128, 4) X(int4, W_INT4, 128, 8)
-#define FF_DECLARE_FAMILY(name, wd, hd, g) hipError_t launch_fused_##name##_hd##hd##_g##g(const FusedLaunch& a, const char** what);
+#define FF_DECLARE_FAMILY(name, wd, hd, g) \
+    hipError_t launch_fused_##name##_hd##hd##_g##g(const FusedLaunch& a, const char** what); \
+    hipError_t launch_solo_##name##_hd##hd##_g##g(const FusedLaunch& a, const char** what);
 FF_FUSED_FAMILIES(FF_DECLARE_FAMILY)
 #undef FF_DECLARE_FAMILY
 

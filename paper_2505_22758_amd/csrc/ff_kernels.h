@@ -97,16 +97,17 @@ __device__ __forceinline__ int attn_share_of(const int* tokens, const int* pos, 
 template <int WD> constexpr int kAttnModeOf = WD == W_INT4 ? FF_ATTN_MODE_I4 : FF_ATTN_MODE;
 
 // share: workgroups per kv head of each sequence (attn_share_of), staged in LDS like the positions.
-template <int NW, int HD, int G, int MODE = 0>
+// Returns false (uniformly) if the queries did not come; mine: whether this wave's part of the merge did.
+// REUSE: the caller's waves write to lds as soon as they return.
+template <int NW, int HD, int G, int MODE, bool REUSE>
 __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const DevKV& KV, const int* pos, const int* share, int batch, int layer,
-                                                       uint8_t* lds, u32 in_tag, u32 out_tag, u32 out_cnt, const UDiv& nc, WgVote& vote, u64* ev = nullptr,
+                                                       uint8_t* lds, u32 in_tag, u32 out_tag, u32 out_cnt, const UDiv& nc, WgVote& vote, bool& mine, u64* ev = nullptr,
                                                        const WideImg* merged_img = nullptr) {
     constexpr int NT = NW * 64;
     const int ncta = (int)nc.n;
     int base = 0;
     bool ok = true;
     TaggedAttnIO xio{in_tag, out_tag, out_cnt, merged_img, &vote};
-    bool mine = true;   // of this wave
     for (int b = 0; b < batch; b++) {
         const int T = max(pos[b], 0);   // (-1: the sequence sits this step out and is carried as a placeholder with an empty cache)
         const int ns = attn_nsplit(T, share[b]);
@@ -119,6 +120,7 @@ __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const 
             const int t0 = (int)((u32)T * (u32)s / (u32)ns), t1 = (int)((u32)T * (u32)(s + 1) / (u32)ns);   // T * 64 < 2^32
             bool cur = s == ns - 1;
             ok = attn_item<HD, G, NW, TaggedAttnIO, MODE>(M, KV, xio, layer, b, j, t0, t1, cur, s, ns, lds, ev) && ok;
+            if constexpr (REUSE) __syncthreads();   // the waves' states have been read
             if (ns > 1 && ok) {
                 mine = attn_merge_tagged<HD, G, NT>(M, xio, b, j, s, ns) && mine;
                 if (ev && threadIdx.x == 0) as_global(ev)[5] = wall_clock64();
@@ -126,7 +128,7 @@ __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const 
         }
         base = (int)nc.mod((u32)base + (u32)nitems);
     }
-    return vote.all<NT>(ok && mine);
+    return ok;
 }
 
 }  // namespace ff

@@ -437,6 +437,15 @@ __device__ __forceinline__ void for_tile_units(const PMat& W, int row0, int n_ro
         if (r >= 0 && r < n_rows) f(r, u, dst + i);
     }
 }
+// Scales and zeros of rows [row0, row0 + n_rows) in the tiles' order (PMat::sz).
+__global__ void __launch_bounds__(kThreads) k_tile_scales(PMat W, u32* sz, int row0, int n_rows) {
+    const int ng = W.k / 128;
+    for (int r = row0 + blockIdx.x; r < row0 + n_rows; r += gridDim.x) {
+        const PMat::Rows t = W.tile_rows(r);
+        for (int g = threadIdx.x; g < ng; g += kThreads)
+            sz[(size_t)t.r0 * ng + (size_t)g * (t.r1 - t.r0) + (r - t.r0)] = (u32)W.s[(size_t)r * ng + g] | ((u32)W.z[(size_t)r * ng + g] << 16);
+    }
+}
 // (A wave copies 8 units x 8 rows at a time: whole 128-byte lines on both sides.)
 __global__ void __launch_bounds__(kThreads) k_repack_tiles(PMat W, int row0, int n_rows, const uint8_t* src_a, const uint8_t* src_b, RowMap map) {
     const size_t rb = PMat::row_bytes_of(W.k, W.wd, 0);

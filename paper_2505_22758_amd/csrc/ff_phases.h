@@ -634,32 +634,34 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
     const int grp = lane / LPR, sub = lane % LPR;
     const float sc = 1.4426950408889634f / sqrtf((float)HD);   // alpha * log2(e)
 
-    float m[G], l[G], o[G][8];
+    float m[G], l[G], o[G * 8];
 #pragma unroll
     for (int g = 0; g < G; g++) {
         m[g] = -INFINITY; l[g] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; e++) o[g][e] = 0.f;
+        for (int e = 0; e < 8; e++) o[g * 8 + e] = 0.f;
     }
     const bf16_t* Kp = KV.plane(M, layer, b, j, 0);
     const bf16_t* Vp = KV.plane(M, layer, b, j, 1);
-    float qr[G][8];
-    auto update = [&](const float (&kf)[8], const float (&vf)[8], bool valid) {
-#pragma unroll
-        for (int g = 0; g < G; g++) {
+    float qr[MM ? 1 : G][8];
+    // one row (keys kf, values vf of the lane's eight dims) into head g's state; q: the head's query
+    auto update_head = [&](int g, const float (&q)[8], const float (&kf)[8], const float (&vf)[8], bool valid) {
             float s = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; e++) s = fmaf(qr[g][e], kf[e], s);
+            for (int e = 0; e < 8; e++) s = fmaf(q[e], kf[e], s);
             s = group_sum<LPR>(s) * sc;
             if (valid) {
                 float mn = fmaxf(m[g], s);
                 float corr = exp2_hw(m[g] - mn), p = exp2_hw(s - mn);
                 l[g] = l[g] * corr + p;
 #pragma unroll
-                for (int e = 0; e < 8; e++) o[g][e] = fmaf(p, vf[e], o[g][e] * corr);
+                for (int e = 0; e < 8; e++) o[g * 8 + e] = fmaf(p, vf[e], o[g * 8 + e] * corr);
                 m[g] = mn;
             }
-        }
+    };
+    auto update = [&](const float (&kf)[8], const float (&vf)[8], bool valid) {
+#pragma unroll
+        for (int g = 0; g < G; g++) update_head(g, qr[MM ? 0 : g], kf, vf, valid);
     };
     // Cached rows do not depend on this step: the first kAttnBatch wave-loads are issued BEFORE the
     // queries are waited for, so the wait for the QKV projection overlaps them.
@@ -702,13 +704,10 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
     const bool ok = xio.template stage_inputs<HD, G, NT>(M, b, j, with_cur, xin);
     if (ev && threadIdx.x == 0) as_global(ev)[1] = wall_clock64();
     if (!ok) return false;   // uniform
-    auto load_qr = [&]() {
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-            const float4 q0 = *(const float4*)(xin + g * HD + sub * 8), q1 = *(const float4*)(xin + g * HD + sub * 8 + 4);
-            qr[g][0] = q0.x; qr[g][1] = q0.y; qr[g][2] = q0.z; qr[g][3] = q0.w;
-            qr[g][4] = q1.x; qr[g][5] = q1.y; qr[g][6] = q1.z; qr[g][7] = q1.w;
-        }
+    auto load_q = [&](int g, float (&q)[8]) {
+        const float4 q0 = *(const float4*)(xin + g * HD + sub * 8), q1 = *(const float4*)(xin + g * HD + sub * 8 + 4);
+        q[0] = q0.x; q[1] = q0.y; q[2] = q0.z; q[3] = q0.w;
+        q[4] = q1.x; q[5] = q1.y; q[6] = q1.z; q[7] = q1.w;
     };
     if constexpr (MM) {
         // queries as matrix-core B operand: column n = head n % 8, bf16 head (n < 8) or remainder (n >= 8)
@@ -759,7 +758,7 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
                 l[g] = fmaf(l[g], corr, (p0 + p1) + (p2 + p3));
 #pragma unroll
                 for (int e = 0; e < 8; e++)
-                    o[g][e] = fmaf(p3, vf[3][e], fmaf(p2, vf[2][e], fmaf(p1, vf[1][e], fmaf(p0, vf[0][e], o[g][e] * corr))));
+                    o[g * 8 + e] = fmaf(p3, vf[3][e], fmaf(p2, vf[2][e], fmaf(p1, vf[1][e], fmaf(p0, vf[0][e], o[g * 8 + e] * corr))));
                 m[g] = mn;
             }
         };
@@ -780,7 +779,8 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        load_qr();
+#pragma unroll
+        for (int g = 0; g < G; g++) load_q(g, qr[g]);
         for (bool first = true; tb0 < t1; tb0 += kStride, first = false) {
             if (!first) issue(tb0);
 #pragma unroll
@@ -792,14 +792,21 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
             }
         }
     }
-    if constexpr (MM) { if (with_cur && wave == 0) load_qr(); }   // (the row-wise update below needs the queries per lane)
     if (with_cur && wave == 0) {   // this step's own key/value (uniform branch per wave)
         float kf[8], vf[8];
         const float* kc = xin + G * HD + sub * 8;
         const float* vc = kc + HD;
 #pragma unroll
         for (int e = 0; e < 8; e++) { kf[e] = kc[e]; vf[e] = vc[e]; }
-        update(kf, vf, grp == 0);   // scores reduce over the lanes of one row group: only group 0 is valid
+        if constexpr (MM) {   // (one head's queries at a time: they are not kept in registers)
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                float q[8];
+                load_q(g, q);
+                update_head(g, q, kf, vf, grp == 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else update(kf, vf, grp == 0);   // scores reduce over the lanes of one row group: only group 0 is valid
     }
     // ---- the row groups of a wave merge in registers, the waves' states through LDS ----
     // Every wave first brings its groups to one maximum per head, then the sums over groups are formed by
@@ -809,7 +816,6 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
     // stored partial, 8B, groups' states through LDS / this: bf16 x 2 3.9 / 3.5 us, int4 x 4 7.0 / 6.8, int4 x 16 19.2 / 19.0.)
     constexpr int NV = G * 8 / RPW;   // values a lane keeps
     static_assert((RPW == 4 && LPR == 16) || (RPW == 8 && LPR == 8 && G == 4), "group bits of the lane number");
-    float st[G * 8];
 #pragma unroll
     for (int g = 0; g < G; g++) {
         float mw = lane_pair_max<32>(m[g], lane);
@@ -820,17 +826,17 @@ __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, co
         if constexpr (RPW == 8) l[g] = lane_pair_sum<8>(l[g], lane);
         m[g] = mw;
 #pragma unroll
-        for (int e = 0; e < 8; e++) st[g * 8 + e] = o[g][e] * f;
+        for (int e = 0; e < 8; e++) o[g * 8 + e] *= f;
     }
-    lane_halve<32, G * 8>(st, lane);
-    lane_halve<16, G * 4>(st, lane);
-    if constexpr (RPW == 8) lane_halve<8, G * 2>(st, lane);
+    lane_halve<32, G * 8>(o, lane);
+    lane_halve<16, G * 4>(o, lane);
+    if constexpr (RPW == 8) lane_halve<8, G * 2>(o, lane);
     // quad c (of NV / 4) of the lane: values 4 c .. 4 c + 3; planes of 64 float4, so that neither side has bank conflicts
     f32x4* so = (f32x4*)lds;                                            // [wave][NV / 4][64]
     float2* sml = (float2*)((float*)lds + (size_t)NW * G * HD);         // [wave][G] (maximum, denominator)
     if (ev && threadIdx.x == 0) as_global(ev)[2] = wall_clock64();
 #pragma unroll
-    for (int c = 0; c < NV / 4; c++) so[(wave * (NV / 4) + c) * 64 + lane] = f32x4{st[4 * c], st[4 * c + 1], st[4 * c + 2], st[4 * c + 3]};
+    for (int c = 0; c < NV / 4; c++) so[(wave * (NV / 4) + c) * 64 + lane] = f32x4{o[4 * c], o[4 * c + 1], o[4 * c + 2], o[4 * c + 3]};
     if (lane == 0) {
 #pragma unroll
         for (int g = 0; g < G; g++) sml[wave * G + g] = make_float2(m[g], l[g]);

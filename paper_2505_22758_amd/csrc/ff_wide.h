@@ -407,9 +407,11 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
             const WideImg ai = image(blk + WL.a);
             u64* aev = M.dbg && l == 1 ? M.dbg + (size_t)(4 * M.L + 1) * kEvSlots + (size_t)ncta * 32 + ((size_t)blockIdx.x * 5 + 4) * 8 : nullptr;
             if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
-            if (!attention_phase_tagged<kWideWaves, HD, G, kWideAttnModeOf<WD, NC>>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
-                                                              n_ctas, vote, aev, &ai)) return;
+            bool mine = true;
+            if (!attention_phase_tagged<kWideWaves, HD, G, kWideAttnModeOf<WD, NC>, false>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
+                                                              n_ctas, vote, mine, aev, &ai)) return;
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
+            if (!vote.all<kWideThreads>(mine)) return;
             sync.arrive(e0 + 1u, lane);
             timed(ph, EV_ATT_END);
             W = FF_PMAT_FIELDS(Lp->o);

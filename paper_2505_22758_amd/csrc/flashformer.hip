@@ -44,7 +44,7 @@ int fail(int code, const char* fmt, ...) {
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-struct MatPlan { size_t w, s, z; int n, k, wd, tiled; };   // byte offsets into packed_dev
+struct MatPlan { size_t w, s, z, sz, sz_bytes; int n, k, wd, tiled; };   // byte offsets into packed_dev
 struct LayerPlan { size_t g1, g2; MatPlan qkv, o, gu, down; };
 struct Plan {
     size_t layers_tab;
@@ -57,17 +57,18 @@ struct Plan {
     size_t cx, cx2, cdelta, tq, tkvcur, cattn_o, ch, stepctr, tpart_m, tpart_l, tpart_o;
     size_t wimg, wflag;   // wide pass only (zero bytes otherwise)
     int wring;
-    bool wide;
+    bool wide, solo;   // kernel of the steps: wide pass (ff_wide.h), one-sequence step (ff_solo.h), neither: the row-partitioned one (ff_fused.h)
 };
 
 size_t mat_s_bytes(int n, int k, int wd) { return wd == W_INT8 ? (size_t)n * 2 : wd == W_INT4 ? (size_t)n * (k / 128) * 2 : 0; }
 
-// tiled: workgroups of the grid the wide pass's layout is cut for, 0 = row-major
-MatPlan plan_mat(size_t& off, int n, int k, int wd, int tiled) {
-    MatPlan p{0, 0, 0, n, k, wd, tiled};
+// tiled: workgroups of the grid the tiled layout is cut for, 0 = row-major; solo: for the one-sequence step
+MatPlan plan_mat(size_t& off, int n, int k, int wd, int tiled, bool solo) {
+    MatPlan p{0, 0, 0, 0, wd == W_INT4 && tiled && solo ? 2 * mat_s_bytes(n, k, wd) : 0, n, k, wd, tiled};
     p.w = off; off = align256(off + (size_t)n * PMat::row_bytes_of(k, wd, tiled));
     p.s = off; off = align256(off + mat_s_bytes(n, k, wd));
     p.z = off; off = align256(off + (wd == W_INT4 ? mat_s_bytes(n, k, wd) : 0));
+    p.sz = off; off = align256(off + p.sz_bytes);
     return p;
 }
 
@@ -108,13 +109,12 @@ bool wide_fits(const ff_config& c, int n_cta) {
 }
 constexpr int kGridCtas = 256;   // workgroups of the fused kernel's grid on the chip the kernels are built for
 
-// Models whose steps run on the wide pass (any batch up to max_batch in one pass, weights in the tiled layout): those for
-// several sequences (all that check_config accepts fit a grid of kGridCtas); a single sequence runs row-partitioned on
-// row-major weights, and so do, one sequence after the other, models for several on a grid that the wide pass does not fit.
-// Both sides measured at one sequence, which keeps its inputs' 24 bits on either (8B, eight layers, context 1024, us per step,
-// row-partitioned / wide): bf16 737 / 749, int8 556 / 548, int4 580 / 503; the quantised models for one sequence stay where
-// their results are what they were.
-bool wide_model(const ff_config& c) { return c.max_batch > 1; }
+// Steps of a model for several sequences run on the wide pass (any batch up to max_batch in one pass), those of a model for one on
+// the one-sequence kernel; both read weights in the tiled layout.  Where the grid or the width does not fit them (check_config
+// accepts nothing that several sequences could not run on a grid of kGridCtas; a model for one sequence may be wider than 8192) the
+// weights stay row-major and a step runs its sequences one after the other on the row-partitioned kernel.
+// (Figures of both: ff_solo.h.)
+bool solo_fits(const ff_config& c, int n_cta) { return c.d_model <= 8192 && wide_fits(c, n_cta); }
 
 // wring: blocks of the wide pass's exchange images, 0 = one per layer and one for the LM head (see ff_wide.h)
 // n_cta: workgroups of the grid (sizes are largest for kGridCtas; a grid that the wide pass does not fit needs fewer bytes
@@ -122,25 +122,26 @@ bool wide_model(const ff_config& c) { return c.max_batch > 1; }
 // perop: with the per-operation path's buffers
 Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool perop = true) {
     Plan P;
-    P.wide = wide_model(c) && wide_fits(c, n_cta);
-    const int tiled = P.wide ? n_cta : 0;
+    P.wide = c.max_batch > 1 && wide_fits(c, n_cta);
+    P.solo = c.max_batch == 1 && solo_fits(c, n_cta);
+    const int tiled = P.wide || P.solo ? n_cta : 0;
     size_t off = 0;
-    P.layers_tab = off; off = align256(off + sizeof(PLayer) * c.n_layers);
+    P.layers_tab = off; off = align256(off + sizeof(PLayer) * (c.n_layers + 1));
     int qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, qd = c.n_q_heads * c.head_dim;
     for (int l = 0; l < c.n_layers; l++) {
         LayerPlan L;
         L.g1 = off; off = align256(off + (size_t)c.d_model * 2);
         L.g2 = off; off = align256(off + (size_t)c.d_model * 2);
-        L.qkv = plan_mat(off, qkv_rows, c.d_model, c.wdtype, tiled);
-        L.o = plan_mat(off, c.d_model, qd, c.wdtype, tiled);
-        L.gu = plan_mat(off, 2 * c.d_ffn, c.d_model, c.wdtype, tiled);
-        L.down = plan_mat(off, c.d_model, c.d_ffn, c.wdtype, tiled);
+        L.qkv = plan_mat(off, qkv_rows, c.d_model, c.wdtype, tiled, P.solo);
+        L.o = plan_mat(off, c.d_model, qd, c.wdtype, tiled, P.solo);
+        L.gu = plan_mat(off, 2 * c.d_ffn, c.d_model, c.wdtype, tiled, P.solo);
+        L.down = plan_mat(off, c.d_model, c.d_ffn, c.wdtype, tiled, P.solo);
         P.layers.push_back(L);
     }
     P.embed = off; off = align256(off + (size_t)c.vocab * c.d_model * 2);
     P.gf = off; off = align256(off + (size_t)c.d_model * 2);
     const int lm_wd = c.quant_lm_head ? c.wdtype : W_BF16;
-    P.lm = plan_mat(off, c.vocab, c.d_model, lm_wd, lm_wd == c.wdtype ? tiled : 0);   // (a head of another type runs as separate launches)
+    P.lm = plan_mat(off, c.vocab, c.d_model, lm_wd, lm_wd == c.wdtype ? tiled : 0, P.solo);   // (a head of another type runs as separate launches)
     P.packed_bytes = off;
 
     size_t s = 0;
@@ -157,7 +158,7 @@ Plan make_plan(const ff_config& c, int n_cta = kGridCtas, int wring = 0, bool pe
     P.part_m = take(pb * c.n_q_heads * kMaxSplits * 4);
     P.part_l = take(pb * c.n_q_heads * kMaxSplits * 4);
     P.part_o = take(pb * c.n_q_heads * kMaxSplits * c.head_dim * 4);
-    const size_t cb = P.wide ? 0 : 1;   // compact exchange rows: row-partitioned passes, of one sequence each
+    const size_t cb = P.wide ? 0 : 1;   // compact exchange rows, of one sequence
     P.cx = take(cb * c.d_model * 4);
     P.cx2 = take(cb * c.d_model * 4);
     P.cdelta = take(cb * c.d_model * 4);
@@ -208,6 +209,12 @@ PMat to_pmat(const MatPlan& p, uint8_t* base) {
     m.s = (const f16_t*)(base + p.s);
     m.z = (const f16_t*)(base + p.z);
     m.n = p.n; m.k = p.k; m.wd = p.wd; m.tiled = p.tiled;
+    m.sz = (const u32*)(base + p.sz);
+    m.panels = 0;
+    if (p.tiled) {   // as few panels as possible, of equal size (by the workgroup that has most rows)
+        const int tiles = (4 * (((p.n + 3) / 4 + p.tiled - 1) / p.tiled) + 15) / 16, np = (tiles + kPanelTiles - 1) / kPanelTiles;
+        m.panels = (tiles + np - 1) / np;
+    }
     return m;
 }
 
@@ -215,6 +222,10 @@ PMat to_pmat(const MatPlan& p, uint8_t* base) {
 dim3 tile_grid(const MatPlan& p) {
     const int rows = 4 * (((p.n + 3) / 4 + p.tiled - 1) / p.tiled);
     return dim3((unsigned)p.tiled, (unsigned)((rows + 15) / 16));
+}
+// int4, one-sequence step: scales and zeros of packed rows [dst_row, dst_row + n_rows) once more, in the tiles' order
+void tile_scales(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, hipStream_t st) {
+    if (dst.sz_bytes) k_tile_scales<<<std::min(n_rows, 4096), kThreads, 0, st>>>(to_pmat(dst, packed), (u32*)(packed + dst.sz), dst_row, n_rows);
 }
 // copy canonical rows [n_rows] of `src` into packed rows starting at dst_row, with row mapping
 int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const ff_matrix& a, const ff_matrix* b, int mode, int hd,
@@ -237,6 +248,7 @@ int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const f
             if (!a.z || (b && !b->z)) return fail(FF_ERR_ARG, "zero-point pointer is null for an int4 matrix");
             k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.z + (size_t)dst_row * sb, (const uint8_t*)a.z,
                                                      b ? (const uint8_t*)b->z : nullptr, n_rows, sb, map);
+            tile_scales(dst, packed, dst_row, n_rows, st);
         }
     }
     HIPCHK(hipGetLastError());
@@ -375,7 +387,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
         // is only 14 stages long there, too few to stage the four chunks of h behind it) and is off by default
         const char* pipe = getenv("FF_GLU_PIPE");
         const bool pipe_off = pipe && pipe[0] == '0', pipe_all = pipe && pipe[0] == 'a';
-        const bool ok = !P.wide && cfg->d_ffn % nw == 0 && chunk_elems % nw == 0 && !pipe_off;
+        const bool ok = !P.wide && !P.solo && cfg->d_ffn % nw == 0 && chunk_elems % nw == 0 && !pipe_off;
         D.gu = ok ? GuPerm{cfg->d_ffn / nw, nw} : GuPerm{0, 0};
         // glu_run (single-sequence passes) needs the staged h beside the staged projection input, the
         // per-lane partial sums of a wave's down-projection rows at the end of the aux region, at most
@@ -390,6 +402,7 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
         m->glu_off = ok && fits && (cfg->wdtype != W_INT8 || pipe_all) ? in_off : -1;
     }
     D.layers = (const PLayer*)(m->packed + P.layers_tab);
+    D.layer_stride = cfg->n_layers > 1 ? P.layers[1].g1 - P.layers[0].g1 : 0;
     D.embed = (const bf16_t*)(m->packed + P.embed);
     D.gf = (const bf16_t*)(m->packed + P.gf);
     D.lm = to_pmat(P.lm, m->packed);
@@ -413,7 +426,12 @@ int ff_model_create(const ff_config* cfg, void* packed_dev, size_t packed_bytes,
         pl.gu = to_pmat(L.gu, m->packed); pl.down = to_pmat(L.down, m->packed);
         m->host_layers.push_back(pl);
     }
-    hipError_t e = hipMemcpyAsync(m->packed + P.layers_tab, m->host_layers.data(), sizeof(PLayer) * cfg->n_layers, hipMemcpyHostToDevice, st);
+    {
+        PLayer head{};   // (see DevModel::layers)
+        head.g1 = D.gf; head.qkv = D.lm;
+        m->host_layers.push_back(head);
+    }
+    hipError_t e = hipMemcpyAsync(m->packed + P.layers_tab, m->host_layers.data(), sizeof(PLayer) * m->host_layers.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) {
         k_fill_u32<<<256, 256, 0, st>>>((u32*)m->scratch, P.scratch_bytes / 4, 0u);
         // (passes of one sequence: their one row is initialised here, and ff_decode_step launches no k_scrub_rows)
@@ -518,6 +536,7 @@ int synth_part(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, con
         if (dst.wd != W_BF16)
             k_synth_scales<<<std::min(n_rows, 8192), kThreads, 0, st>>>((f16_t*)(packed + dst.s + (size_t)dst_row * sb), (f16_t*)(packed + dst.z + (size_t)dst_row * sb),
                                                                        n_rows, dst.wd, a, b, map);
+        tile_scales(dst, packed, dst_row, n_rows, st);
         HIPCHK(hipGetLastError());
         return FF_OK;
     }
@@ -680,13 +699,13 @@ int fused_pass(ff_model* m, const DevModel& D, const int32_t* tokens_dev, const 
     hipError_t e = hipErrorInvalidValue;
     what = "no fused kernel instance for this configuration";
 #define FF_TRY_FAMILY(name, wd, hd, g) \
-    if (m->cfg.wdtype == wd && m->cfg.head_dim == hd && G == g) e = launch_fused_##name##_hd##hd##_g##g(a, &what);
+    if (m->cfg.wdtype == wd && m->cfg.head_dim == hd && G == g) e = m->plan.solo ? launch_solo_##name##_hd##hd##_g##g(a, &what) : launch_fused_##name##_hd##hd##_g##g(a, &what);
     FF_FUSED_FAMILIES(FF_TRY_FAMILY)
 #undef FF_TRY_FAMILY
     if (e != hipSuccess) return fail(e == hipErrorLaunchOutOfResources ? FF_ERR_UNSUPPORTED : FF_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
     if (!lm_in_kernel) {   // LM head of a different weight type than the layers: separate launches
         const ff_config& c = m->cfg;
-        if (!wide) op_final_x<<<16, kThreads, 0, st>>>(D.x, D.cx, D.cdelta, batch * c.d_model);   // (the wide kernel leaves the final rows in x)
+        if (!wide && !m->plan.solo) op_final_x<<<16, kThreads, 0, st>>>(D.x, D.cx, D.cdelta, batch * c.d_model);   // (the other kernels leave the final rows in x)
         op_rmsnorm<<<batch, kThreads, 0, st>>>(D.x, D.gf, D.xn, c.d_model, c.rms_eps);
         for (int b0 = 0; b0 < batch; b0 += kMaxBatch) {
             int rc = gemv_op(m, D.lm, D.xn + (size_t)b0 * c.d_model, c.d_model, logits_dev + (size_t)b0 * c.vocab, std::min(kMaxBatch, batch - b0), EPI_STORE, st,

@@ -1081,3 +1081,27 @@ def test_merge_of_every_number_of_slices(heads, max_batch):
     S = synth.TINY.replace(name="slices", n_layers=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, vocab=512)
     for T0 in (63, 128, 255, 256, 320, 1023, 4200, 8300, 12300):   # 1, 2, 3, 4, 5, 15, 32, 48, 64 slices
         _run_teacher_forced(S, 0x2505227e0 + T0, synth.WDTYPE_BF16, batch=max_batch, T0=[T0, 17][:max_batch], steps=1, check_kv=False)
+
+
+# The one-sequence step's edges: rows that are no whole tiles, more panels than one, waves without columns, widths that are no
+# whole iterations or an odd number of them (half a ring unit), inputs of three passes and of many (words sent ahead of their pass).
+SOLO_EDGES = [
+    ("bf16-odd", synth.TINY.replace(name="solo-odd", n_layers=2, vocab=4099), synth.WDTYPE_BF16),
+    ("bf16-panels", synth.TINY.replace(name="solo-panels", n_layers=1, d_ffn=17416, vocab=40001), synth.WDTYPE_BF16),
+    ("int8-odd", synth.TINY.replace(name="solo-odd", n_layers=2, d_ffn=1344, vocab=1021), synth.WDTYPE_INT8),
+    ("int8-passes", synth.TINY.replace(name="solo-passes", n_layers=1, d_ffn=20544, vocab=515), synth.WDTYPE_INT8),
+    ("int4-odd", synth.TINY.replace(name="solo-odd", n_layers=2, d_ffn=1408, vocab=4102), synth.WDTYPE_INT4),
+    ("int4-passes", synth.TINY.replace(name="solo-passes", n_layers=1, d_ffn=20608, vocab=515), synth.WDTYPE_INT4),
+    ("int4-long-rows", synth.TINY.replace(name="solo-long", n_layers=1, d_model=256, n_q_heads=4, n_kv_heads=1, d_ffn=139264, vocab=515), synth.WDTYPE_INT4),
+]
+
+
+@pytest.mark.parametrize("shape,wdtype", [c[1:] for c in SOLO_EDGES], ids=[c[0] for c in SOLO_EDGES])
+def test_one_sequence_step_at_the_edges(shape, wdtype):
+    """Steps of models for one sequence against the oracle, at the bounds of the other steps and, where one layer keeps flipped
+    cache elements out of it, at 22-bit inputs' own: their relative error is 2^-23 each, about 4e-7 in the logits with fp32
+    sums (1e-6 where a constant is taken off the sums of int4 codes); bound 3e-6, half of what 17-bit inputs would show."""
+    words = 2 * shape.n_layers * shape.n_kv_heads * shape.head_dim
+    worst = _run_teacher_forced(shape, 0xe0, wdtype, batch=1, T0=37, steps=max(2, -(-1536 // words)), check_kv=True)
+    if shape.n_layers == 1:
+        assert _median_step_error(shape, 0xe1, wdtype, 1, 37, 5) < 3e-6, worst
