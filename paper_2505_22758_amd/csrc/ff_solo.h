@@ -103,8 +103,6 @@ struct SoloMat {
 };
 static_assert(sizeof(SoloMat) == 64, "size in LDS");
 typedef __attribute__((address_space(3))) SoloMat lds_mat;
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ u64 uni(u64 v) { return (u64)(u32)uni((int)(u32)v) | ((u64)(u32)uni((int)(u32)(v >> 32)) << 32); }
 template <int WD>
 __device__ __forceinline__ void solo_table(lds_mat* tab, const DevModel& M, const UDiv& n_ctas, int kind, bool lm) {   // entry `kind`, by one thread
     const PLayer* L = M.layers + (kind == PH_LM ? M.L : 0);
@@ -451,7 +449,7 @@ __global__ void __launch_bounds__(kSoloThreads) solo_decode_kernel(DevModel M, D
             timed(ph, EV_ATT_START);
             u64* aev = M.dbg && l == 1 ? M.dbg + (size_t)(4 * M.L + 1) * kEvSlots + (size_t)ncta * 32 + ((size_t)blockIdx.x * 5 + 4) * 8 : nullptr;
             if (aev && tid == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
-            if (!attention_phase_tagged<kSoloWaves, HD, G, kWideAttnModeOf<WD, 1>, true>(M, KV, pos_lds, share_lds, 1, l, lds + Lds::kImg, tag_of(tag_base, l, TAG_QKV),
+            if (!attention_phase_tagged<kSoloWaves, HD, G, kAttnModeOf<WD>, true>(M, KV, pos_lds, share_lds, 1, l, lds + Lds::kImg, tag_of(tag_base, l, TAG_QKV),
                                                                                          tag_of(tag_base, l, TAG_ATT), sl + (u32)l, n_ctas, vote, ok, aev)) {
                 leave();
                 return;

@@ -42,10 +42,39 @@ constexpr int kWideResOff = kWideRopeOff + kMaxBatchWide * 64 * 8;     // residu
 constexpr int kWideResRows = 32;
 constexpr int kWideRmsOff = kWideResOff + kMaxBatchWide * kWideResRows * 4;   // sums of squares: [wave][sequence]
 constexpr int kWideIntOff = kWideRmsOff + kWideWaves * kMaxBatchWide * 4;     // positions, attention shares, epoch verdicts, arrival counter, vote slots
+constexpr int kWideTabOff = kWideIntOff + 512;   // WideMat of the five projections
 constexpr int kWideMaxCtas = 256;   // workgroups whose sums of squares a consumer gathers in one round (wide_project)
 constexpr int kWideLdsBytes = kWideIntOff + 1024;
 static_assert(kWideLdsBytes <= 160 * 1024, "LDS layout of the wide pass");
 static_assert((kAttnStateFloats<128, 8, kWideWaves> + (8 + 2) * 128 + kWideWaves * 128) * 4 <= kWideAttnBytes, "attention state");
+
+// A projection as its phases find it in LDS (kinds PH_QKV .. PH_LM): pointers of layer 0, advanced by the layers' stride, and the gains of the norm
+// behind it.  (Read out of the layer table where they are needed, the descriptors of a layer that nobody has touched yet are
+// misses all the way to memory between one projection and the next: 8B, eight layers, us per step, bf16 x 2 740 -> 735, x 8 784 -> 779,
+// int8 x 4 540 -> 534, int4 x 16 731 -> 723, int4 x 4 525 -> 529.)
+struct WideMat { u64 w, s, z, gain; int n, k; };
+typedef __attribute__((address_space(3))) WideMat lds_wmat;
+static_assert(5 * sizeof(WideMat) <= 512, "descriptors in LDS");
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ u64 uni(u64 v) { return (u64)(u32)uni((int)(u32)v) | ((u64)(u32)uni((int)(u32)(v >> 32)) << 32); }
+__device__ __forceinline__ void wide_table(lds_wmat* tab, const DevModel& M, int kind) {   // entry `kind`, by one thread
+    const PLayer* L = M.layers + (kind == PH_LM ? M.L : 0);
+    const PMat* W = &L->qkv + (kind & 3);
+    tab[kind].w = (u64)W->w; tab[kind].s = (u64)W->s; tab[kind].z = (u64)W->z;
+    tab[kind].n = W->n; tab[kind].k = W->k;
+    tab[kind].gain = kind == PH_O ? (u64)L->g2 : kind == PH_DOWN ? (u64)L->g1 : 0;   // (the gains behind a down projection: the next layer's)
+}
+template <int WD>
+__device__ __forceinline__ PMat wide_mat(const lds_wmat* tab, const DevModel& M, int kind, int l) {
+    const lds_wmat* e = tab + kind;
+    const size_t off = kind == PH_LM ? 0 : (size_t)l * M.layer_stride;
+    PMat W{};
+    W.w = (const uint8_t*)(uni(e->w) + off);
+    W.s = (const f16_t*)(uni(e->s) + off); W.z = (const f16_t*)(uni(e->z) + off);
+    W.n = uni(e->n); W.k = uni(e->k);
+    W.wd = WD; W.tiled = 1;   // (tiled: not zero)
+    return W;
+}
 
 // ---------------------------------------------------------------- epochs
 struct WideSync {
@@ -313,10 +342,13 @@ __device__ __forceinline__ bool wide_project_any(const PMat& W, const uint8_t* i
     return false;
 }
 
-// Attention form (see attn_item).  One sequence takes the form of the single-sequence kernel (8B bf16, eight layers, context
+// Attention form (see attn_item).  One sequence takes the form of the models for one (8B bf16, eight layers, context
 // 1024 / 4096, us per step: form 0 746 / 773, 1 749 / 767, 2 755 / 782), int4 steps of up to eight sequences its row-wise
-// form, which keeps the queries' 24 bits and is ahead as well (8B int4 x 2 context 1024, x 4 context 2048: 519, 567; form 2 538, 597).
-template <int WD, int NC> constexpr int kWideAttnModeOf = NC == 1 ? kAttnModeOf<WD> : WD == W_INT4 && NC == 8 ? 0 : 2;
+// form, which keeps the queries' 24 bits and is ahead as well (8B int4 x 4 context 2048: 529; form 1 541).  Otherwise form 1 (forms 0, 1, 2, 8B: bf16 x 2
+// context 1024 758, 760, 766, x 8 context 1024 785, 778, 789 and 4200 941, 905, 909, int8 x 4 context 1500 553, 552, 556, int8 x 16 context 4200 1029, 1046, 1051,
+// int4 x 16 context 512 590, 600, 608, 2048 739, 722, 745 and 4200 932, 891, 912), and with eight query heads form 2 (70B x 16 context
+// 2048 2012, 1928, 1927, 4200 2281, 2090, 2072).
+template <int WD, int NC, int G> constexpr int kWideAttnModeOf = NC == 1 ? kAttnModeOf<WD> : WD == W_INT4 && NC == 8 ? 0 : G == 8 ? 2 : 1;
 
 // ---------------------------------------------------------------- the kernel
 // One launch = one step of up to NC sequences (phases as in fused_decode_kernel).  One sequence has an instance of its own:
@@ -348,6 +380,8 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         share_lds[threadIdx.x] = attn_share_of(tokens, pos, batch, threadIdx.x, ncta, M.Hkv, (switches & kSwUniformShares) != 0);
     }
     if (threadIdx.x < 4) slots[threadIdx.x] = 0u;
+    lds_wmat* tab = (lds_wmat*)(lds + kWideTabOff);
+    if (threadIdx.x < 5) wide_table(tab, M, threadIdx.x);
     const u32 steps_done = (u32)__builtin_amdgcn_readfirstlane(xld_u32(M.stepctr));
     const u32 tag_base = steps_done * (u32)(kTagsPerLayer * M.L + 1);
     const u32 ebase = steps_done * (u32)(4 * M.L + 1) + 1u;   // epochs of this step: ebase: embedding rows; + 4 l + {1: attention, 2: output, 3: gate/up, 4: down projection}
@@ -390,10 +424,8 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     const int n_phases = 4 * M.L + lm_in_kernel;
     for (int ph = 0; ph < n_phases; ph++) {
         const int l = ph >> 2;
-        const FF_CONST PLayer* Lp = as_const(M.layers) + min(l, M.L - 1);
         const u32 e0 = ebase + 4u * (u32)l;
         uint8_t* blk = block(l);
-        PMat W;
         u32 epoch = e0;
         const uint8_t* img;
         const float* ssin = nullptr;
@@ -401,32 +433,30 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         C.layer = l;
         C.kind = ph == 4 * M.L ? PH_LM : (ph & 3);
         C.tag = tag_of(tag_base, l, TAG_QKV);
-        if (C.kind == PH_QKV) { W = FF_PMAT_FIELDS(Lp->qkv); img = blk + WL.x1; ssin = (const float*)(blk + WL.ss1); }
+        if (C.kind == PH_QKV) { img = blk + WL.x1; ssin = (const float*)(blk + WL.ss1); }
         else if (C.kind == PH_O) {
             __syncthreads();   // the QKV epilogues have read their sums out of LDS
             const WideImg ai = image(blk + WL.a);
             u64* aev = M.dbg && l == 1 ? M.dbg + (size_t)(4 * M.L + 1) * kEvSlots + (size_t)ncta * 32 + ((size_t)blockIdx.x * 5 + 4) * 8 : nullptr;
             if (aev && threadIdx.x == 0) { as_global(aev)[0] = wall_clock64(); as_global(aev)[4] = 0; as_global(aev)[5] = 0; }
             bool mine = true;
-            if (!attention_phase_tagged<kWideWaves, HD, G, kWideAttnModeOf<WD, NC>, false>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
+            if (!attention_phase_tagged<kWideWaves, HD, G, kWideAttnModeOf<WD, NC, G>, false>(M, KV, pos_lds, share_lds, batch, l, lds, tag_of(tag_base, l, TAG_QKV), tag_of(tag_base, l, TAG_ATT), 0u,
                                                               n_ctas, vote, mine, aev, &ai)) return;
             if (aev && threadIdx.x == 0) as_global(aev)[6] = wall_clock64();
             if (!vote.all<kWideThreads>(mine)) return;
             sync.arrive(e0 + 1u, lane);
             timed(ph, EV_ATT_END);
-            W = FF_PMAT_FIELDS(Lp->o);
-            epoch = e0 + 1u; img = blk + WL.a; gain = Lp->g2;
+            epoch = e0 + 1u; img = blk + WL.a; gain = (const bf16_t*)(uni(tab[PH_O].gain) + (size_t)l * M.layer_stride);
             C.out = image(blk + WL.x2); C.ss = (float*)(blk + WL.ss2);
         } else if (C.kind == PH_GU) {
-            W = FF_PMAT_FIELDS(Lp->gu);
             epoch = e0 + 2u; img = blk + WL.x2; ssin = (const float*)(blk + WL.ss2);
             C.out = image(blk + WL.h);
         } else if (C.kind == PH_DOWN) {
-            W = FF_PMAT_FIELDS(Lp->down);
-            epoch = e0 + 3u; img = blk + WL.h; gain = l + 1 < M.L ? (as_const(M.layers) + l + 1)->g1 : M.gf;
+            epoch = e0 + 3u; img = blk + WL.h; gain = l + 1 < M.L ? (const bf16_t*)(uni(tab[PH_DOWN].gain) + (size_t)(l + 1) * M.layer_stride) : M.gf;
             uint8_t* nb = block(l + 1);
             C.out = image(nb + WL.x1); C.ss = (float*)(nb + WL.ss1);
-        } else { W = FF_PMAT_FIELDS(M.lm); img = blk + WL.x1; ssin = (const float*)(blk + WL.ss1); }
+        } else { img = blk + WL.x1; ssin = (const float*)(blk + WL.ss1); }
+        const PMat W = wide_mat<WD>(tab, M, C.kind, l);
         timed(ph, EV_H_START);
         const bool ok = wide_project_any<WD, NC>(W, img, ssin, gain, epoch, sync, C, lds, n_ctas, wave, lane, ph);
         timed(ph, EV_RUN_DONE);
