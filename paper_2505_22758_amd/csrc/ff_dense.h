@@ -15,8 +15,8 @@
 //     The accumulators of lane (r, g) hold row r for sequences 4 g .. 4 g + 3, so what belongs to a
 //     weight row (int4 scales and zeros) belongs to the lane that loaded the row;
 //   * a wave keeps D iterations of weights (and of the inputs they meet) in flight in a register ring,
-//     refilled tile by tile behind its products, unconditionally; the last iterations are peeled off the
-//     loop (where code paths that issued different numbers of loads meet, the compiler waits for all);
+//     refilled tile by tile behind its products, unconditionally (where code paths that issued different
+//     numbers of loads meet, the compiler waits for all);
 //   * the waves' partial tiles meet in LDS, wave t adds and finishes tile t.
 // Two waves per SIMD: the eight waves' rings hold up to 112 KB per compute unit in flight, and one
 // wave's conversions overlap the other's matrix-core work.
@@ -105,24 +105,25 @@ struct PanelRing {
     static constexpr int D = kWDepth<WD, NC, T>, DX = D < 2 ? 2 : D, L = kWLoads<WD>, NP = kXOps<NC>, NB = kWSteps<WD> * NP;
     u32x4 w[D][T][L];
     u32x4 x[DX][NB];
-    // Weights of iteration it.
-    __device__ __forceinline__ void load_w(const PanelSrc<T>& S, int slot, int it) {
+    static constexpr u32 kNowhere = 0x7FFFFFF0u;   // an offset behind every buffer: answered with zeros, without an access
+    // Weights of iteration it (zeros unless `real`).
+    __device__ __forceinline__ void load_w(const PanelSrc<T>& S, int slot, int it, bool real) {
 #pragma unroll
-        for (int t = 0; t < T; t++) load_wt(S, slot, it, t);
+        for (int t = 0; t < T; t++) load_wt(S, slot, it, t, real);
     }
-    __device__ __forceinline__ void load_wt(const PanelSrc<T>& S, int slot, int it, int t) {
+    __device__ __forceinline__ void load_wt(const PanelSrc<T>& S, int slot, int it, int t, bool real) {
 #pragma unroll
         for (int l = 0; l < L; l++)
-                w[slot][t][l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S.base, S.lane_off[t], S.tile[t] + (u32)(it * L + l) * S.step[t], 2))   /* streaming */;
+                w[slot][t][l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S.base, real ? S.lane_off[t] : kNowhere, S.tile[t] + (u32)(it * L + l) * S.step[t], 2))   /* streaming */;
     }
     // Inputs of iteration it.  (Buffer loads: base and iteration are scalar operands, the lane's offset one register.)
-    __device__ __forceinline__ void load_x(const PanelImg& I, int slot, int it) {
+    __device__ __forceinline__ void load_x(const PanelImg& I, int slot, int it, bool real) {
 #pragma unroll
         for (int k = 0; k < kWSteps<WD>; k++)
 #pragma unroll
             for (int h = 0; h < NP; h++)
                 x[slot][k * NP + h] =
-                    __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(I.base, I.lane_off, (it * kWSteps<WD> + k) * I.step + h * (I.step >> 1), 0));
+                    __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(I.base, real ? I.lane_off : (int)kNowhere, (it * kWSteps<WD> + k) * I.step + h * (I.step >> 1), 0));
     }
 };
 
@@ -258,13 +259,34 @@ struct WaveIters {
     __device__ __forceinline__ int at(int i) const { return max(min(i, n - 1), 0) * kWideWaves + first; }
 };
 
-// The wave's iterations of a panel; the first D slots of weights and DX of inputs have been requested
-// (slots past the end hold repeats).
+// The wave's iterations of a panel; the first D slots of weights and DX of inputs have been requested (slots past the end hold repeats).
+// int4 up to eight sequences: requests past the end read nothing, so that the loop has no tail of its own to be unrolled, a copy of the long
+// product per slot and step (a layer uses three or four panel widths, and the instruction cache holds 64 KB: kernel 272 -> 184 KB, spilled
+// registers 56 -> 16, 8B x 4, eight layers, 529 -> 516 us per step).  The others are ahead with the last iterations peeled off the loop (735 /
+// 770 bf16 x 2, 534 / 555 int8 x 4, 779 / 811 bf16 x 8, 724 / 737 int4 x 16).
 template <int WD, int NC, int T>
 __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC, T>& R, const PanelImg& img, const WaveIters& I, const PanelSz& sz, int lane,
                                           mfma_f4 (&acc)[T]) {
     constexpr int D = PanelRing<WD, NC, T>::D, DX = PanelRing<WD, NC, T>::DX;
     static_assert(DX % D == 0, "slots");
+    if constexpr (WD == W_INT4 && NC <= 8) {
+        for (int i = 0; i < I.n; i += DX) {
+#pragma unroll
+            for (int j = 0; j < DX; j++) {
+                if (j > 0 && i + j >= I.n) break;
+                const int nw = i + j + D, nx = i + j + DX;
+                // a tile's weights are requested again right behind its products
+                panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz, lane, acc, [&](int t) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    R.load_wt(S, j % D, I.at(nw), t, nw < I.n);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                R.load_x(img, j, I.at(nx), nx < I.n);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        return;
+    }
     const auto keep = [](int) {};
     int i = 0;
     for (; i + DX + D <= I.n; i += DX) {
@@ -274,10 +296,10 @@ __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC
             // a tile's weights are requested again right behind its products
             panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz, lane, acc, [&](int t) {
                 __builtin_amdgcn_sched_barrier(0);
-                R.load_wt(S, j % D, nw, t);
+                R.load_wt(S, j % D, nw, t, true);
                 __builtin_amdgcn_sched_barrier(0);
             });
-            R.load_x(img, j, nx);   // (past the end: the last one again)
+            R.load_x(img, j, nx, true);   // (past the end: the last one again)
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -287,8 +309,8 @@ __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC
         if (i + j < I.n) {
             panel_multiply<WD, NC, T>(R, j % D, j % DX, I.at(i + j), sz, lane, acc, keep);
             __builtin_amdgcn_sched_barrier(0);
-            if (i + j + D < I.n) R.load_w(S, j % D, I.at(i + j + D));
-            if (i + j + DX < I.n) R.load_x(img, j % DX, I.at(i + j + DX));
+            if (i + j + D < I.n) R.load_w(S, j % D, I.at(i + j + D), true);
+            if (i + j + DX < I.n) R.load_x(img, j % DX, I.at(i + j + DX), true);
             __builtin_amdgcn_sched_barrier(0);
         }
     }

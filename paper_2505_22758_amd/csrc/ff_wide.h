@@ -261,7 +261,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         __builtin_amdgcn_sched_barrier(0);
         S = PanelSrc<T>::make(W, p0, max(rr.r1, p0 + 1), lane);
 #pragma unroll
-        for (int j = 0; j < D; j++) R.load_w(S, j, I.at(j));
+        for (int j = 0; j < D; j++) R.load_w(S, j, I.at(j), WD != W_INT4 || NC > 8 || j < I.n);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (WD == W_INT4) if (sz_fits) {
             lds_u32* szp = sz + (p & 1) * kSzStride;
@@ -283,7 +283,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
 #pragma unroll
         for (int t = 0; t < T; t++) acc[t] = mfma_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < PanelRing<WD, NC, T>::DX; j++) R.load_x(X, j, I.at(j));
+        for (int j = 0; j < PanelRing<WD, NC, T>::DX; j++) R.load_x(X, j, I.at(j), WD != W_INT4 || NC > 8 || j < I.n);
         __builtin_amdgcn_sched_barrier(0);
         panel_run<WD, NC, T>(S, R, X, I, PanelSz{sz_fits ? sz + (p & 1) * kSzStride : (const lds_u32*)nullptr, &W, min(rr.r0 + 16 * T * p, W.n - 1), rr.r1}, lane, acc);
         timed(p == 0 ? 4 : 8);
