@@ -39,15 +39,15 @@ constexpr int kSpinLimit = 1 << 16;
 enum { W_BF16 = 0, W_INT8 = 1, W_INT4 = 2 };
 
 // A projection matrix in packed (device-private) row order.  Two layouts of the weights:
-//   row-major (tiled == 0), streamed row by row by the single-sequence kernel and the per-operation path;
-//   tiled for the wide pass (tiled == workgroups of the grid): every workgroup's rows (whole groups of
+//   row-major (tiled == 0), streamed row by row by the row-partitioned kernel and the per-operation path;
+//   tiled for the wide pass and the one-sequence kernel (tiled == workgroups of the grid): every workgroup's rows (whole groups of
 //   four, see cta_rows) are cut into tiles of 16 (the last one may be shorter), and a tile holds its rows'
 //   16-byte units column by column: unit 0 of all rows, unit 1 of all rows, ...  A matrix-core operand (16
 //   rows x 4 units) is then one contiguous kilobyte and a wave's whole share of a tile one stream.  Rows
-//   are padded with zero units to whole iterations of the wide pass.  int4 words hold code 2 p in
+//   are padded with zero units to whole iterations.  int4 words hold code 2 p in
 //   nibble p and code 2 p + 1 in nibble p + 4, so that one mask yields two codes in the halves of a word, and are
 //   rotated left by three, which puts a code where the mantissa of a bf16 number wants it (i4_to_bf16).
-// Scales and zeros are row-major either way.
+// Scales and zeros are row-major either way, but for the int4 matrices of the one-sequence step: there they are words of their own tiles (sz).
 struct PMat {
     const uint8_t* w;
     const f16_t* s;     // int8: [n]; int4: [n][k/128]
@@ -56,7 +56,7 @@ struct PMat {
     int wd;
     int tiled;
     int panels;         // tiled: tiles of a panel of the one-sequence step (ff_solo.h)
-    const u32* sz;      // int4, one-sequence step: (scale | zero << 16), in the tiles' order: [tile][group][row of the tile]
+    const u32* sz;      // int4, one-sequence step, in place of s and z: (scale | zero << 16), in the tiles' order: [tile][group][row of the tile]
     __host__ __device__ static size_t row_bytes_of(int k, int wd, int tiled) {
         if (!tiled) return wd == W_BF16 ? (size_t)k * 2 : wd == W_INT8 ? (size_t)k : (size_t)k / 2;
         const size_t cols = wd == W_INT4 ? 128 : 64, pad = (k + cols - 1) / cols * cols;
@@ -76,6 +76,12 @@ struct PMat {
         const Rows r = cta_rows((int)(((u64)(row / 4 + 1) * (u64)tiled - 1) / g));
         const int t0 = r.r0 + (row - r.r0) / 16 * 16;
         return Rows{t0, r.r1 - t0 < 16 ? r.r1 : t0 + 16};
+    }
+    // Word of group 0 of a row in sz; consecutive groups of the row are `stride` words apart.
+    __host__ __device__ size_t sz_at(int row, int* stride) const {
+        const Rows t = tile_rows(row);
+        *stride = t.r1 - t.r0;
+        return (size_t)t.r0 * (k / 128) + (size_t)(row - t.r0);
     }
     // Byte offset of unit 0 of a row; consecutive units of the row are `stride` bytes apart.
     __host__ __device__ size_t row_off(int row, size_t* stride) const {

@@ -109,14 +109,16 @@ __global__ void __launch_bounds__(kThreads) op_gemv(PMat W, const float* in, int
 //     an input that needs several segments is staged once per panel;
 //   * a group of eight staged columns is read once for all tiles of the panel, four neighbouring lanes' worth per 64 bytes;
 //   * RUNS (int4, rows of whole runs of four groups): a wave takes runs of four blocks, whose scales are one 8-byte load
-//     per row; loads of single scales touch 16 cache lines per kilobyte of weights.
+//     per row; loads of single scales touch 16 cache lines per kilobyte of weights;
+//   * TILES (int4 models for one sequence): scale and zero are one word beside those of the tile's other rows.
 // What bounds it: at one and two sequences the stream and the launches, at four the LDS reads and the conversions.  Against the
 // form that waited for four blocks at a time and staged the inputs anew for every tile, and against row-major op_gemv
 // (us per step, 8B, eight layers, context 1024, before / now / row-major):
 //   bf16 x 1 2530 / 987 / 975, x 2 2827 / 1044 / 1078, x 4 3762 / 1146 / 1401; int8 x 1 1673 / 749 / 758, x 2 2067 / 817 / 910,
 //   x 4 2757 / 1008 / 1269; int4 x 1 1454 / 784 / 763, x 2 1732 / 867 / 945, x 4 2430 / 1054 / 1333.
 template <int WD, int T> constexpr int kOpDepth = T == 4 ? 4 : 8;
-template <int WD, int B, int T, bool RUNS>
+enum { SCALES_EACH = 0, SCALES_RUNS = 1, SCALES_TILES = 2 };
+template <int WD, int B, int T, int SCALES>
 __global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const float* in, int in_stride, float* out, int batch, int epi_kind, const int* skip_tokens) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int EPU = WTraits<WD>::EPU, COLS = 4 * EPU, D = kOpDepth<WD, T>;
@@ -136,10 +138,10 @@ __global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const floa
     PanelSrc<T> S;
     u32x4 w[D][T];
     // scales and zeros of the slots: one by one, or (RUNS) of four slots at a time, 8 bytes each, with the last of the four
-    constexpr bool I4 = WD == W_INT4;
+    constexpr bool I4 = WD == W_INT4, RUNS = I4 && SCALES == SCALES_RUNS, TILES = I4 && SCALES == SCALES_TILES;
     constexpr int NS = !I4 ? 1 : RUNS ? D / 2 : D, NT = I4 ? T : 1;
-    u32 sc[NS][NT], zp[NS][NT];
-    int row[T];
+    u32 sc[NS][NT], zp[NS][NT];   // (TILES: both in sc)
+    int row[T], nrow[T];          // (nrow: rows of the tile)
     const int ng = W.k / 128;
     const int n_it = RUNS ? 4 * ((ng / 4 - wave + kWideWaves - 1) / kWideWaves) : I.n;   // this wave's blocks
     auto block = [&](int i) {   // (past the end: the last run or block again, for a wave that has none one in range)
@@ -151,7 +153,8 @@ __global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const floa
 #pragma unroll
         for (int t = 0; t < T; t++) {
             w[slot][t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(S.base, S.lane_off[t], S.tile[t] + (u32)it * S.step[t], 2));
-            if constexpr (I4 && !RUNS) {
+            if constexpr (TILES) sc[slot][t] = as_global(W.sz)[(size_t)(u32)row[t] + (size_t)(u32)(it * nrow[t])];
+            else if constexpr (I4 && !RUNS) {
                 const size_t e = (size_t)row[t] * ng + it;
                 sc[slot][t] = as_global(W.s)[e]; zp[slot][t] = as_global(W.z)[e];
             } else if constexpr (RUNS) if (slot % 4 == 3) {
@@ -162,13 +165,16 @@ __global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const floa
         }
     };
     auto scale_of = [&](const u32 (&v)[NS][NT], int slot, int t) { return f16_to_f((f16_t)(RUNS ? v[slot / 2][t] >> (16 * (slot & 1)) : v[slot][t])); };
+    auto zero_of = [&](int slot, int t) { return TILES ? f16_to_f((f16_t)(sc[slot][t] >> 16)) : scale_of(zp, slot, t); };
     auto prefetch = [&](int p) {
         const int p0 = rr.r0 + 16 * T * p;
         S = PanelSrc<T>::make(W, p0, rr.r1, lane);
 #pragma unroll
         for (int t = 0; t < T; t++) {   // (rows as PanelSrc repeats them)
             const int t0 = p0 + 16 * t < rr.r1 ? p0 + 16 * t : p0;
-            row[t] = t0 + min(r, min(rr.r1 - t0, 16) - 1);
+            nrow[t] = min(rr.r1 - t0, 16);
+            row[t] = t0 + min(r, nrow[t] - 1);
+            if constexpr (TILES) row[t] = t0 * ng + min(r, nrow[t] - 1);   // (its word of group 0)
         }
 #pragma unroll
         for (int j = 0; j < D; j++) load(j, j);
@@ -255,7 +261,7 @@ __global__ void __launch_bounds__(kWideThreads) op_gemv_tiled(PMat W, const floa
                 const float xu = xsum[min(b, batch - 1) * (kSegCols / EPU) + 4 * blk + g];
 #pragma unroll
                 for (int t = 0; t < T; t++)
-                    acc[t][b] = fmaf(scale_of(sc, slot, t), fmaf(-scale_of(zp, slot, t), xu, part[t][b]), acc[t][b]);
+                    acc[t][b] = fmaf(scale_of(sc, slot, t), fmaf(-zero_of(slot, t), xu, part[t][b]), acc[t][b]);
             }
         }
         // (pinned here: nothing else keeps a block's products from being sunk behind the refills, with all their inputs live)
@@ -437,13 +443,16 @@ __device__ __forceinline__ void for_tile_units(const PMat& W, int row0, int n_ro
         if (r >= 0 && r < n_rows) f(r, u, dst + i);
     }
 }
-// Scales and zeros of rows [row0, row0 + n_rows) in the tiles' order (PMat::sz).
-__global__ void __launch_bounds__(kThreads) k_tile_scales(PMat W, u32* sz, int row0, int n_rows) {
+// Scales and zeros of rows [row0, row0 + n_rows) in the tiles' order (PMat::sz); source rows by the same maps.
+__global__ void __launch_bounds__(kThreads) k_tile_scales(PMat W, int row0, int n_rows, const f16_t* sa, const f16_t* sb, const f16_t* za, const f16_t* zb, RowMap map) {
     const int ng = W.k / 128;
-    for (int r = row0 + blockIdx.x; r < row0 + n_rows; r += gridDim.x) {
-        const PMat::Rows t = W.tile_rows(r);
-        for (int g = threadIdx.x; g < ng; g += kThreads)
-            sz[(size_t)t.r0 * ng + (size_t)g * (t.r1 - t.r0) + (r - t.r0)] = (u32)W.s[(size_t)r * ng + g] | ((u32)W.z[(size_t)r * ng + g] << 16);
+    for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
+        bool second;
+        const size_t src = (size_t)map.source(r, &second) * ng;
+        const f16_t *s = (second ? sb : sa) + src, *z = (second ? zb : za) + src;
+        int stride;
+        u32* dst = (u32*)W.sz + W.sz_at(row0 + r, &stride);
+        for (int g = threadIdx.x; g < ng; g += kThreads) dst[(size_t)g * stride] = (u32)s[g] | ((u32)z[g] << 16);
     }
 }
 // (A wave copies 8 units x 8 rows at a time: whole 128-byte lines on both sides.)
@@ -530,7 +539,14 @@ __global__ void k_dequant(PMat W, float* out, int n_can, int map, int parity, in
             int ng = W.k / 128;
             const u32 word = ((const u32*)unit)[e / 8];
             const int code = (int)((W.tiled ? i4_canonical_word(word) : word) >> (4 * (e % 8))) & 15;
-            v = ((float)code - f16_to_f(W.z[(size_t)pr * ng + c / 128])) * f16_to_f(W.s[(size_t)pr * ng + c / 128]);
+            f16_t s, z;
+            if (W.sz) {
+                int step;
+                const size_t at = W.sz_at(pr, &step);
+                const u32 both = W.sz[at + (size_t)(c / 128) * step];
+                s = (f16_t)(both & 0xFFFFu); z = (f16_t)(both >> 16);
+            } else { s = W.s[(size_t)pr * ng + c / 128]; z = W.z[(size_t)pr * ng + c / 128]; }
+            v = ((float)code - f16_to_f(z)) * f16_to_f(s);
         }
         out[i] = v;
     }
@@ -632,20 +648,26 @@ __global__ void __launch_bounds__(kThreads) k_synth_tiles(PMat W, int row0, int 
         *dst = u32x4{v[0], v[1], v[2], v[3]};
     });
 }
-// ... and the scales and zeros of rows [0, n_rows) of a part (row-major in either layout).
-__global__ void __launch_bounds__(kThreads) k_synth_scales(f16_t* dst_s, f16_t* dst_z, int n_rows, int wd, SynthMat A, SynthMat B, RowMap map) {
+// ... and the scales and zeros of its rows [row0, row0 + n_rows).
+__global__ void __launch_bounds__(kThreads) k_synth_scales(PMat W, int row0, int n_rows, SynthMat A, SynthMat B, RowMap map) {
     for (int r = blockIdx.x; r < n_rows; r += gridDim.x) {
         bool second;
         const int sr = map.source(r, &second);
         const SynthMat& Mt = second ? B : A;
-        const int ng = wd == W_INT4 ? Mt.k / 128 : 1;
+        const int ng = W.wd == W_INT4 ? Mt.k / 128 : 1;
+        int stride = 0;
+        const size_t at = W.sz ? W.sz_at(row0 + r, &stride) : (size_t)(row0 + r) * ng;
         for (int g = threadIdx.x; g < ng; g += kThreads) {
-            dst_s[(size_t)r * ng + g] = synth_scale_f16(Mt.key_s, (u64)sr * ng + g, Mt.c_scale);
-            if (wd == W_INT4) {
+            const f16_t s = synth_scale_f16(Mt.key_s, (u64)sr * ng + g, Mt.c_scale);
+            f16_t zb = 0;
+            if (W.wd == W_INT4) {
                 const _Float16 z = (_Float16)(float)synth_uniform_int(Mt.key_z, (u64)sr * ng + g, 0, 15);
-                f16_t zb;
                 __builtin_memcpy(&zb, &z, 2);
-                dst_z[(size_t)r * ng + g] = zb;
+            }
+            if (W.sz) ((u32*)W.sz)[at + (size_t)g * stride] = (u32)s | ((u32)zb << 16);
+            else {
+                ((f16_t*)W.s)[at + g] = s;
+                if (W.wd == W_INT4) ((f16_t*)W.z)[at + g] = zb;
             }
         }
     }

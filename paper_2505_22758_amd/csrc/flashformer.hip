@@ -66,8 +66,8 @@ size_t mat_s_bytes(int n, int k, int wd) { return wd == W_INT8 ? (size_t)n * 2 :
 MatPlan plan_mat(size_t& off, int n, int k, int wd, int tiled, bool solo) {
     MatPlan p{0, 0, 0, 0, wd == W_INT4 && tiled && solo ? 2 * mat_s_bytes(n, k, wd) : 0, n, k, wd, tiled};
     p.w = off; off = align256(off + (size_t)n * PMat::row_bytes_of(k, wd, tiled));
-    p.s = off; off = align256(off + mat_s_bytes(n, k, wd));
-    p.z = off; off = align256(off + (wd == W_INT4 ? mat_s_bytes(n, k, wd) : 0));
+    p.s = off; off = align256(off + (p.sz_bytes ? 0 : mat_s_bytes(n, k, wd)));
+    p.z = off; off = align256(off + (wd == W_INT4 && !p.sz_bytes ? mat_s_bytes(n, k, wd) : 0));
     p.sz = off; off = align256(off + p.sz_bytes);
     return p;
 }
@@ -206,10 +206,10 @@ namespace {
 PMat to_pmat(const MatPlan& p, uint8_t* base) {
     PMat m;
     m.w = base + p.w;
-    m.s = (const f16_t*)(base + p.s);
-    m.z = (const f16_t*)(base + p.z);
+    m.s = p.sz_bytes ? nullptr : (const f16_t*)(base + p.s);
+    m.z = p.sz_bytes ? nullptr : (const f16_t*)(base + p.z);
     m.n = p.n; m.k = p.k; m.wd = p.wd; m.tiled = p.tiled;
-    m.sz = (const u32*)(base + p.sz);
+    m.sz = p.sz_bytes ? (const u32*)(base + p.sz) : nullptr;
     m.panels = 0;
     if (p.tiled) {   // as few panels as possible, of equal size (by the workgroup that has most rows)
         const int tiles = (4 * (((p.n + 3) / 4 + p.tiled - 1) / p.tiled) + 15) / 16, np = (tiles + kPanelTiles - 1) / kPanelTiles;
@@ -222,10 +222,6 @@ PMat to_pmat(const MatPlan& p, uint8_t* base) {
 dim3 tile_grid(const MatPlan& p) {
     const int rows = 4 * (((p.n + 3) / 4 + p.tiled - 1) / p.tiled);
     return dim3((unsigned)p.tiled, (unsigned)((rows + 15) / 16));
-}
-// int4, one-sequence step: scales and zeros of packed rows [dst_row, dst_row + n_rows) once more, in the tiles' order
-void tile_scales(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, hipStream_t st) {
-    if (dst.sz_bytes) k_tile_scales<<<std::min(n_rows, 4096), kThreads, 0, st>>>(to_pmat(dst, packed), (u32*)(packed + dst.sz), dst_row, n_rows);
 }
 // copy canonical rows [n_rows] of `src` into packed rows starting at dst_row, with row mapping
 int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const ff_matrix& a, const ff_matrix* b, int mode, int hd,
@@ -242,13 +238,16 @@ int repack(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, const f
     if (dst.wd != W_BF16) {
         if (!a.s || (b && !b->s)) return fail(FF_ERR_ARG, "scale pointer is null for a quantised matrix");
         size_t sb = dst.wd == W_INT8 ? 2 : (size_t)(dst.k / 128) * 2;
-        k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.s + (size_t)dst_row * sb, (const uint8_t*)a.s, b ? (const uint8_t*)b->s : nullptr,
-                                                 n_rows, sb, map);
-        if (dst.wd == W_INT4) {
-            if (!a.z || (b && !b->z)) return fail(FF_ERR_ARG, "zero-point pointer is null for an int4 matrix");
-            k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.z + (size_t)dst_row * sb, (const uint8_t*)a.z,
-                                                     b ? (const uint8_t*)b->z : nullptr, n_rows, sb, map);
-            tile_scales(dst, packed, dst_row, n_rows, st);
+        if (dst.wd == W_INT4 && (!a.z || (b && !b->z))) return fail(FF_ERR_ARG, "zero-point pointer is null for an int4 matrix");
+        if (dst.sz_bytes)
+            k_tile_scales<<<grid, kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, (const f16_t*)a.s, b ? (const f16_t*)b->s : nullptr,
+                                                     (const f16_t*)a.z, b ? (const f16_t*)b->z : nullptr, map);
+        else {
+            k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.s + (size_t)dst_row * sb, (const uint8_t*)a.s, b ? (const uint8_t*)b->s : nullptr,
+                                                     n_rows, sb, map);
+            if (dst.wd == W_INT4)
+                k_repack_rows<<<grid, kThreads, 0, st>>>(packed + dst.z + (size_t)dst_row * sb, (const uint8_t*)a.z,
+                                                         b ? (const uint8_t*)b->z : nullptr, n_rows, sb, map);
         }
     }
     HIPCHK(hipGetLastError());
@@ -282,9 +281,9 @@ int launch_gemv(ff_model* m, const PMat& W, const float* in, int in_stride, floa
     kern<<<m->n_cta, kThreads, m->lds_bytes, st>>>(W, in, in_stride, out, batch, epi, skip_tokens);
     return FF_OK;
 }
-template <int WD, int B, int T, bool RUNS>
+template <int WD, int B, int T, int SCALES>
 int launch_gemv_tiled_form(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
-    auto kern = op_gemv_tiled<WD, B, T, RUNS>;
+    auto kern = op_gemv_tiled<WD, B, T, SCALES>;
     constexpr size_t lds = kLdsActBytes + (size_t)kWideWaves * T * 16 * B * 4 + (WD == W_INT4 ? kLdsActBytes / 32 : 0);
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -295,8 +294,12 @@ int launch_gemv_tiled_form(const PMat& W, const float* in, int in_stride, float*
 }
 template <int WD, int B, int T>
 int launch_gemv_tiled(const PMat& W, const float* in, int in_stride, float* out, int batch, int epi, hipStream_t st, const int* skip_tokens) {
-    if (WD == W_INT4 && W.k % 512 == 0) return launch_gemv_tiled_form<WD, B, T, WD == W_INT4>(W, in, in_stride, out, batch, epi, st, skip_tokens);
-    return launch_gemv_tiled_form<WD, B, T, false>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    if constexpr (WD == W_INT4) {
+        if constexpr (B == 1)
+            if (W.sz) return launch_gemv_tiled_form<WD, B, T, SCALES_TILES>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+        if (W.k % 512 == 0) return launch_gemv_tiled_form<WD, B, T, SCALES_RUNS>(W, in, in_stride, out, batch, epi, st, skip_tokens);
+    }
+    return launch_gemv_tiled_form<WD, B, T, SCALES_EACH>(W, in, in_stride, out, batch, epi, st, skip_tokens);
 }
 // Panels of one or two tiles where a workgroup has no more rows, else of four (the staged inputs are read once per panel).
 template <int WD, int B>
@@ -534,9 +537,7 @@ int synth_part(const MatPlan& dst, uint8_t* packed, int dst_row, int n_rows, con
     if (dst.tiled) {
         k_synth_tiles<<<tile_grid(dst), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, a, b, map, (float)(0.02 / kIh4Std));
         if (dst.wd != W_BF16)
-            k_synth_scales<<<std::min(n_rows, 8192), kThreads, 0, st>>>((f16_t*)(packed + dst.s + (size_t)dst_row * sb), (f16_t*)(packed + dst.z + (size_t)dst_row * sb),
-                                                                       n_rows, dst.wd, a, b, map);
-        tile_scales(dst, packed, dst_row, n_rows, st);
+            k_synth_scales<<<std::min(n_rows, 8192), kThreads, 0, st>>>(to_pmat(dst, packed), dst_row, n_rows, a, b, map);
         HIPCHK(hipGetLastError());
         return FF_OK;
     }
