@@ -23,7 +23,7 @@ HBM_PEAK_GBS = 8000.0
 # a plain copy of known size); the summary under profiles/ gives the commands and the raw figures.
 def measured_traffic(workload):
     """traffic_bytes_per_launch of the workload's committed rocprofv3 summary, if it has one."""
-    for kernel in ("fused", "wide"):
+    for kernel in ("solo", "wide"):
         path = os.path.join(ROOT, "profiles", f"{kernel}_decode_kernel_{workload}.md")
         for line in open(path) if os.path.isfile(path) else ():
             if line.startswith("traffic_bytes_per_launch="):
@@ -40,7 +40,7 @@ WORKLOADS = {
     "llama3-8b-int8-b16-ctx4096": ("llama3-8b", 1, 16, 4096),   # one wide pass (int8 codes converted to bf16 in registers)
     "llama3-8b-int4-b1-ctx2048": ("llama3-8b", 2, 1, 2048),
     "llama3-8b-int4-b4-ctx2048": ("llama3-8b", 2, 4, 2048),
-    "llama3-8b-int4-b16-ctx2048": ("llama3-8b", 2, 16, 2048),   # one wide pass (int4 codes as bf16 128 + n on the matrix cores)
+    "llama3-8b-int4-b16-ctx2048": ("llama3-8b", 2, 16, 2048),   # one wide pass (int4 codes as bf16 16 + n on the matrix cores)
     # the full 80-layer model: 139 GB of packed weights, generated and packed layer by layer on the GPU
     "llama3-70b-bf16-b1-ctx2048": ("llama3-70b", 0, 1, 2048),
     "llama3-70b-bf16-b16-ctx2048": ("llama3-70b", 0, 16, 2048),
@@ -293,7 +293,7 @@ def main():
         "latency_us_p10_p50_p90": [float(np.percentile(per_step_ms, q)) * 1e3 for q in (10, 50, 90)],
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None if (args.batch or args.ctx or args.ctx_list) else measured_traffic(args.workload),
-                     "kernel": "wide_decode_kernel" if batch > 1 else "fused_decode_kernel", "kernel_ms": kern_ms, "algorithmic_bytes": alg_bytes,
+                     "kernel": "wide_decode_kernel" if batch > 1 else "solo_decode_kernel", "kernel_ms": kern_ms, "algorithmic_bytes": alg_bytes,
                      "ceiling_gbs": ceiling_gbs, "frac_of_ceiling": None if ceiling_gbs is None else achieved / ceiling_gbs},
     }
 

@@ -13,7 +13,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"] + os.environ.get("FF_EXTRA_FLAGS", "").split()
 
-# The int8 kernels' loops start on whole 128-byte instruction-cache lines.  Where the single-sequence kernel's stream happens to
+# The int8 kernels' loops start on whole 128-byte instruction-cache lines.  Where the row-partitioned kernel's stream happens to
 # lie is worth up to 0.9 %: 8B int8, eight layers, context 4096 / 1024, us per step 600 / 559 and 597 / 556 by chance,
 # 593 / 552 aligned; bf16 does not change (734 / 734), int4 is slower aligned (594 / 598).
 def source_flags(src):

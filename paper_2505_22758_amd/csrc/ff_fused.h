@@ -1,4 +1,6 @@
-// The fused whole-model decode kernel (one persistent launch per decode step).
+// The row-partitioned whole-model decode kernel (one persistent launch per decode step of one sequence), for what the one-sequence
+// kernel (ff_solo.h) and the wide pass do not take: models wider than 8192, grids whose workgroups would own more than 32 rows of
+// d_model; there it also serves the sequences of a model for several one after another.
 #pragma once
 #include <mutex>
 #include "ff_solo.h"
@@ -333,7 +335,7 @@ inline hipError_t launch_fused_family(const FusedLaunch& a, const char** what) {
     // (the host decides whether a pass is wide, and sizes the buffers for it; up to eight sequences share an operand tile with their remainders)
     if (a.wide) return a.batch == 1 ? launch_wide_instance<WD, 1, HD, G>(a, what) : a.batch <= 8 ? launch_wide_instance<WD, 8, HD, G>(a, what) : launch_wide_instance<WD, 16, HD, G>(a, what);
     if (a.batch != 1) {
-        *what = "several sequences on the single-sequence kernel";
+        *what = "several sequences on the row-partitioned kernel";
         return hipErrorInvalidValue;
     }
     return launch_fused_instance<WD, HD, G>(a, what);

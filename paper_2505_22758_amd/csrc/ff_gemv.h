@@ -28,7 +28,7 @@ template <int WD> constexpr int kUnrOf = WD == W_INT4 ? 2 : FF_UNR;
 #endif
 template <int WD> constexpr int kDepthOf = WD == W_INT4 ? 2 * FF_DEPTH : FF_DEPTH;
 template <int WD> constexpr int kChunkUnitsOf = 64 * kUnrOf<WD>;   // units of one row covered by one stage of one wave
-// Refill granularity of the single-sequence streams: a ring slot is refilled in kRefillParts parts,
+// Refill granularity of the streams: a ring slot is refilled in kRefillParts parts,
 // each right behind the multiply-accumulates that freed its registers, so that 16 - 8 / parts of
 // the wave's 16 loads stay in flight while a stage is being multiplied (8 with whole-stage refills).
 #ifndef FF_REFILL_PARTS

@@ -1,5 +1,5 @@
 // Gate/up projection, SwiGLU and down projection of one layer as ONE weight stream per wave, with
-// the down projection's input staged chunk by chunk while the stream runs (single sequence).
+// the down projection's input staged chunk by chunk while the stream runs (row-partitioned kernel).
 //
 // The paper fuses the GLU so that no device-wide synchronisation separates its two projections
 // (Section 4.2 "GLU": every workgroup multiplies its slice of the intermediate vector at once and

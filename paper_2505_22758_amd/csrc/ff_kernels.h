@@ -83,7 +83,7 @@ __device__ __forceinline__ int attn_share_of(const int* tokens, const int* pos, 
     return 1 + (int)((u32)((u64)budget * mine / tot) / (u32)Hkv);
 }
 
-// Attention form of the single-sequence kernel (see attn_item): 0 = row by row on the vector
+// Attention form of a step of one sequence (see attn_item): 0 = row by row on the vector
 // ALU, 1 = scores of 16 cached rows at a time on the matrix cores (head dimension 128 only).  With
 // eight query heads per KV head the row-wise form is bound by the vector ALU (the 70B shape at batch
 // 1: 23.8 -> 23.3 ms per step with form 1); with four, form 1 is ahead by 0.2 % (8B bf16, batch 1,

@@ -1,8 +1,7 @@
 // The wide pass: exchange between workgroups, epilogues and the kernel.
 //
-// The single-sequence kernel has every workgroup stage the whole input itself (load
-// the tagged words, add the sublayer output, normalise, convert to the matrix cores' head/remainder
-// form), replicated 256 times, which would grow with the batch.  The wide pass exchanges activations in
+// In the kernels for one sequence every workgroup prepares the whole input itself (load
+// the exchanged words, normalise, convert), replicated 256 times, which would grow with the batch.  The wide pass exchanges activations in
 // the form their consumers multiply, produced once by the workgroup that OWNS the value:
 //   * every workgroup owns a fixed range of rows of the residual stream (the rows of the output
 //     and down projections it computes, N / workgroups) and keeps them in its LDS for the whole step;
@@ -27,8 +26,9 @@
 // Measured us per step of an 8-layer block, before (four waves, images copied through LDS, row-major weights) / with
 // this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 834, int8 x 11 992 / 936 / 770, int4 x 16 1628 /
 // 978 / 783, 70B bf16 x 16 3283 / 3098 / 2619; against a row-partitioned pass of up to four sequences (4x4x4 matrix-core
-// tiles, inputs staged by every workgroup): bf16 x 2 858 / 769, int4 x 4 1038 / 570, int8 x 4 879 / 581; one sequence, on a
-// model for several, against the single-sequence kernel: bf16 737 / 749, int8 556 / 548, int4 580 / 503.
+// tiles, inputs staged by every workgroup): bf16 x 2 858 / 769, int4 x 4 1038 / 570, int8 x 4 879 / 581.  Since (merge of the attention
+// slices shared out, descriptors in LDS, attention form 1, int4 panels without tails): bf16 x 2 735, x 8 779, int8 x 4 534, x 11 701, int4 x 4
+// 509, x 16 723.
 // What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
 #pragma once
 #include "ff_dense.h"
