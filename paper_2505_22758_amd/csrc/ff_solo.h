@@ -26,7 +26,7 @@
 // QKV -> attention -> output -> gate/up -> down consumes every word of each of the vectors.
 //
 // Us per step, row-partitioned kernel (ff_fused.h) / this one: 8B, eight layers, bf16 context 1024 719 / 711, int8 context 4096 576 / 494, int4
-// context 2048 577 / 364; 70B, six layers, context 2048, bf16 1745 / 1688, int4 1105 / 634; tiny, four layers 101 / 94.
+// context 2048 577 / 364; 70B, six layers, context 2048, bf16 1745 / 1688, int4 1105 / 634; tiny, four layers 101 / 93.
 //
 // No register may be spilled to memory in this kernel: a reload is a vector load, and the wait for it drains the ring (8 spilled
 // registers outside of the loops cost 8 % of the 8B bf16 step).
