@@ -285,6 +285,63 @@ def test_one_sequence_digits_of_any_magnitude(wdtype):
     dec.close()
 
 
+@pytest.mark.parametrize("wdtype,ratio", ((synth.WDTYPE_INT8, 10), (synth.WDTYPE_INT8, 14), (synth.WDTYPE_INT8, 20), (synth.WDTYPE_INT4, 10), (synth.WDTYPE_INT4, 14)),
+                         ids=("int8-2^10", "int8-2^14", "int8-2^20", "int4-2^10", "int4-2^14"))
+def test_one_sequence_outliers_take_no_bits_from_their_neighbours(wdtype, ratio):
+    """Quantised one-sequence steps whose inputs hold a value 2^ratio times the others in columns whose code is zero (int4: the zero point too, so that
+    nothing is subtracted again) in every row, so that nothing of it is in the logits: a gain of each norm, three rows of the up projection, one of the value projection.  The other
+    groups of 128 columns differ in size too, five and more of them to a wave.  Bound, int8: that of the test above, 16 x 2^-22, unless a key or value
+    falls on the other side of a bf16 rounding.  int4: in each of the five projections also half a unit, 2^-30 of the outlier, of every value of its group."""
+    from oracle import oracle
+    from paper_2505_22758_amd import binding
+    S = synth.TINY.replace(name="outliers", n_layers=1, d_model=4224, d_ffn=4480, vocab=515)
+    seed, c, units, dim = 0x2505227f5, 77, (300, 1700, 4400), 5
+    layer, head = synth.make_layer(S, seed, 0, wdtype, "cpu"), synth.make_head(S, seed, wdtype, "cpu")
+
+    def blank(m, col):   # nothing of this column in any row
+        if wdtype == synth.WDTYPE_INT8:
+            m["w"][:, col] = 0
+        else:
+            m["z"][:, col // 128] = 0
+            m["w"][:, col // 2] &= 0xF0 if col % 2 == 0 else 0x0F
+
+    size = 2.0 ** (torch.arange(S.d_model) // 128 % 3)
+    for gain in (layer["attn_norm"], layer["ffn_norm"], head["final_norm"]):
+        gain *= size.bfloat16()
+        gain[c] *= 2.0 ** ratio
+    for m in (layer["wq"], layer["wk"], layer["wv"], layer["w_gate"], layer["w_up"], head["lm_head"]):
+        blank(m, c)
+    for f in units:
+        layer["w_up"]["s"][f] *= 2.0 ** (ratio - 4)   # (the products are a few times the size of the others' already; fp16)
+        blank(layer["w_down"], f)
+    layer["wv"]["s"][dim] *= 2.0 ** min(ratio, 14)
+    for h in range(S.n_q_heads // S.n_kv_heads):
+        blank(layer["wo"], h * S.head_dim + dim)
+    M = oracle.OracleModel(S, [layer], head)
+    dec = binding.Decoder(S, wdtype, max_batch=1)
+    to_gpu = lambda o: {k: to_gpu(v) for k, v in o.items()} if isinstance(o, dict) else o.to("cuda:0")
+    dec.load_layer(0, to_gpu(layer))
+    dec.load_head(to_gpu(head))
+    dec.alloc_kv(1, 4)
+    lg, pos = torch.zeros(1, S.vocab, device="cuda:0"), torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    k, v = (torch.zeros(1, S.n_kv_heads, S.head_dim, dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    tight = 0
+    for tok in range(6):
+        dec.step(torch.tensor([tok], dtype=torch.int32, device="cuda:0"), pos, lg)
+        binding.ff_status(dec.model)
+        okv = M.new_kv(1, 4)
+        ref = M.decode_step(np.array([tok], dtype=np.int32), np.zeros(1, dtype=np.int32), okv)[0]
+        binding.ff_kv_read(dec.kv, 0, 0, 0, k, v)
+        flips = int((torch.cat([k, v]).double().cpu().numpy().reshape(2, -1) != oracle.bf16_bits_to_f64(okv[0, 0, :, 0]).reshape(2, -1)).sum())
+        rel = float(np.linalg.norm(lg[0].double().cpu().numpy() - ref) / np.linalg.norm(ref))
+        print(f"token {tok}: relative error {rel:.2e}, {flips} cache elements on the other side of a rounding")
+        bound = 4e-6 if wdtype == synth.WDTYPE_INT8 else 4e-6 + 5 * 2.0 ** (ratio - 30)
+        assert rel <= (bound if flips == 0 else helpers.REL_L2_TOL), (tok, rel, flips)
+        tight += flips == 0
+    assert tight >= 2, tight
+    dec.close()
+
+
 def test_tiny_batches_above_one_pass():
     """Batches 5..16, one wide pass each (workgroups that own one row group or none): both operand forms for several
     sequences, bf16 and int8 weights; the per-operation path runs them as passes of four (7: a full and a ragged one)."""
