@@ -163,9 +163,9 @@ __device__ __forceinline__ u32x4 i4_to_bf16(u32 w, u32 mask = 0x00780078u, u32 o
 typedef __attribute__((address_space(3))) f16_t lds_f16;
 // Where a wave finds a panel's int4 scales and zeros.
 struct PanelSz {
-    const lds_f16* lds;          // scales of the panel's rows as they lie in memory, [row][group]; null: too many of them, read in place
+    const lds_f16* lds;          // scales of the panel's rows, as they lie in memory, [row][group]
     int zeros;                   // elements from a scale to its zero
-    const PMat* M; int p0, r1;
+    int ng;                      // groups of a row
 };
 template <int WD, int NC, int T, class Refill>
 __device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, int slot, int xslot, int it, const PanelSz& sz, int lane, mfma_f4 (&acc)[T], Refill&& refill) {
@@ -177,7 +177,7 @@ __device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, in
         const u32x4 ones{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
 #pragma unroll
         for (int i = 0; i < 4 * NP; i++) X = mfma16(R.x[xslot][i], ones, X);
-        ng = sz.M->k / 128;
+        ng = sz.ng;
         szp = sz.lds + ((lane & 15) * ng + it);
     }
 #pragma unroll
@@ -204,12 +204,7 @@ __device__ __forceinline__ void panel_multiply(const PanelRing<WD, NC, T>& R, in
 #pragma unroll
                 for (int h = 0; h < NP; h++) d = mfma16(R.x[xslot][q * NP + h], b, d);
             }
-            f16_t sv, zv;
-            if (T > 2 || sz.lds) { sv = szp[16 * t * ng]; zv = szp[16 * t * ng + sz.zeros]; }
-            else {   // (only rows much longer than their number: one or two tiles)
-                const size_t e = (size_t)max(min(sz.p0 + 16 * t + (lane & 15), sz.r1 - 1), 0) * ng + it;
-                sv = as_global(sz.M->s)[e]; zv = as_global(sz.M->z)[e];
-            }
+            const f16_t sv = szp[16 * t * ng], zv = szp[16 * t * ng + sz.zeros];
             const float s = f16_to_f(sv), zp = kI4Offset + f16_to_f(zv);
 #pragma unroll
             for (int i = 0; i < 4; i++) acc[t][i] = fmaf(s, fmaf(-zp, X[i], d[i]), acc[t][i]);
@@ -240,6 +235,27 @@ __device__ __forceinline__ void panel_scales_send(const PMat& M, int p0, int nro
                      ::"s"(__builtin_amdgcn_readfirstlane(lds + o)), "v"((u32)lane * 16u), "s"(rs), "s"(o), "s"(rz), "s"(__builtin_amdgcn_readfirstlane(z + o)) : "memory", "m0");
     }
 }
+// Rows too long for that (one or two tiles, more than 1023 or 511 groups): a wave brings the scales of its own next kSzFar iterations into its share of
+// the space.  (Read from memory within the loop over tiles, on a branch for such rows, every tile waited for all of the ring where the branch ended, whatever the length of
+// its rows.  Us per step with / without it: 8B int4, eight layers, one sequence on a model for eight 438 / 426, x 4 460 / 447, x 16 655 / 645; 70B, four layers, one 517 /
+// 457, x 4 532 / 476, x 16 669 / 647.  That the 16 rows of a read meet in two to eight banks, rows of 32 to 224 groups, costs less than changing the places of a row's
+// pieces on their way does, 8B x 4 446, x 16 647, or about as much, 70B x 4 470, x 16 643.)
+constexpr int kSzFar = 60;   // a multiple of every ring depth
+struct PanelSzFar { const f16_t *s, *z; int ng, rows; };   // of the panel's first row; groups of a row, rows
+template <int T, class At>
+__device__ __forceinline__ void panel_scales_far(const PanelSzFar& far, lds_f16* lds, int lane, At&& at) {   // at: iteration (group) of the i-th
+    static_assert(T > 2 || kWideWaves * 2 * 16 * T * kSzFar * 2 <= kWideSzBytes, "scales of a wave's iterations");
+#pragma unroll 1
+    for (int t = 0; t < T; t++)
+#pragma unroll 1
+        for (int i = lane >> 4; i < kSzFar; i += 4) {
+            const int r = 16 * t + (lane & 15);
+            const size_t e = (size_t)max(min(r, far.rows - 1), 0) * far.ng + at(i);
+            lds[r * kSzFar + i] = as_global(far.s)[e];
+            lds[(16 * T + r) * kSzFar + i] = as_global(far.z)[e];
+        }
+    settled();
+}
 template <int LATER> __device__ __forceinline__ void panel_scales_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory"); }
 
 // A wave's iterations of a panel: every eighth one, so that the workgroup's waves together read contiguous pieces of
@@ -259,19 +275,28 @@ struct WaveIters {
 // product per slot and step (a layer uses three or four panel widths, and the instruction cache holds 64 KB: kernel 272 -> 184 KB, spilled
 // registers 56 -> 16, 8B x 4, eight layers, 529 -> 516 us per step).  The others are ahead with the last iterations peeled off the loop (735 /
 // 770 bf16 x 2, 534 / 555 int8 x 4, 779 / 811 bf16 x 8, 724 / 737 int4 x 16).
-template <int WD, int NC, int T>
-__device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC, T>& R, const PanelImg& img, const WaveIters& I, const PanelSz& sz, int lane,
+// FAR: rows too long for LDS to hold the panel's scales (far; sz: the space).
+template <int WD, int NC, int T, bool FAR = false>
+__device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC, T>& R, const PanelImg& img, const WaveIters& I, const PanelSz& sz_, const PanelSzFar* far, int wave, int lane,
                                           mfma_f4 (&acc)[T]) {
     constexpr int D = PanelRing<WD, NC, T>::D, DX = PanelRing<WD, NC, T>::DX;
-    static_assert(DX % D == 0, "slots");
-    if constexpr (WD == W_INT4 && NC <= 8) {
+    static_assert(DX % D == 0 && kSzFar % DX == 0, "slots");
+    lds_f16* own = (lds_f16*)sz_.lds + wave * 2 * 16 * T * kSzFar;
+    int i0 = 0;
+    auto bring = [&](int i) {
+        i0 = i;
+        panel_scales_far<T>(*far, own, lane, [&](int k) { return I.at(i + k); });
+    };
+    auto group = [&](int i) { return FAR ? i - i0 : I.at(i); };
+    if constexpr (WD == W_INT4 && (NC <= 8 || FAR)) {
         for (int i = 0; i < I.n; i += DX) {
+            if constexpr (FAR) if (i % kSzFar == 0) bring(i);
 #pragma unroll
             for (int j = 0; j < DX; j++) {
                 if (j > 0 && i + j >= I.n) break;
                 const int nw = i + j + D, nx = i + j + DX;
                 // a tile's weights are requested again right behind its products
-                panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz, lane, acc, [&](int t) {
+                panel_multiply<WD, NC, T>(R, j % D, j, group(i + j), FAR ? PanelSz{own, 16 * T * kSzFar, kSzFar} : sz_, lane, acc, [&](int t) {
                     __builtin_amdgcn_sched_barrier(0);
                     R.load_wt(S, j % D, I.at(nw), t, nw < I.n);
                     __builtin_amdgcn_sched_barrier(0);
@@ -289,7 +314,7 @@ __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC
         for (int j = 0; j < DX; j++) {
             const int nw = I.at(i + j + D), nx = I.at(i + j + DX);
             // a tile's weights are requested again right behind its products
-            panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz, lane, acc, [&](int t) {
+            panel_multiply<WD, NC, T>(R, j % D, j, I.at(i + j), sz_, lane, acc, [&](int t) {
                 __builtin_amdgcn_sched_barrier(0);
                 R.load_wt(S, j % D, nw, t, true);
                 __builtin_amdgcn_sched_barrier(0);
@@ -302,7 +327,7 @@ __device__ __forceinline__ void panel_run(const PanelSrc<T>& S, PanelRing<WD, NC
 #pragma unroll
     for (int j = 0; j < DX + D - 1; j++) {
         if (i + j < I.n) {
-            panel_multiply<WD, NC, T>(R, j % D, j % DX, I.at(i + j), sz, lane, acc, keep);
+            panel_multiply<WD, NC, T>(R, j % D, j % DX, I.at(i + j), sz_, lane, acc, keep);
             __builtin_amdgcn_sched_barrier(0);
             if (i + j + D < I.n) R.load_w(S, j % D, I.at(i + j + D), true);
             if (i + j + DX < I.n) R.load_x(img, j % DX, I.at(i + j + DX), true);

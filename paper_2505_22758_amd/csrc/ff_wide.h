@@ -253,7 +253,8 @@ __device__ __forceinline__ void wide_store_ss(float* ss, int ncta, int t, int la
 // img: the input image; ssin: the workgroups' sums of squares of a normalised input (null: not normalised).
 // epoch: what to wait for.  Returns false (uniformly) on a time-out.
 // RES: the projections that add to the residual (output, down), whose outputs the next norm's gains multiply; at most two tiles, one panel.
-template <int WD, int NC, int T, bool RES>
+// FAR: int4 rows too long for their panel's scales in LDS (panel_scales_far).
+template <int WD, int NC, int T, bool RES, bool FAR>
 __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, int npanels, const uint8_t* img, const float* ssin, const bf16_t* gain, u32 epoch,
                                              WideSync& sync, const WideCtx& C, uint8_t* lds, int wave, int lane_in, int ph) {
     // (what depends on the lane only is cheap to compute again: kept from being hoisted out of the phase loop, where it would be spilled)
@@ -268,7 +269,6 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     const WaveIters I = WaveIters::of(ni, wave);
     const int q = lane >> 4, seq = lane & 15;
     constexpr int D = PanelRing<WD, NC, T>::D;
-    const bool sz_fits = T > 2 || 4 * panel_zeros(W.k, T) <= (npanels > 1 ? kSzHalf : 2 * kSzHalf);   // (long rows: the host checks the wider panels)
     PanelRing<WD, NC, T> R;
     PanelSrc<T> S;
     u32x2 pre = {0u, 0u}, gpre = {0u, 0u};
@@ -278,7 +278,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     auto prefetch = [&](int p) {
         const int p0 = min(rr.r0 + 16 * T * p, W.n - 1), nr = prows(p);
         if constexpr (WD == W_INT8) pre = *as_global((const u32x2*)(W.s + (min(item_row(p), W.n - 1) & ~3)));   // row scales of the item
-        if constexpr (WD == W_INT4) if (sz_fits && nr > 0) panel_scales_send(W, p0, nr, T, (u32)(size_t)(sz + (p & 1) * (kSzHalf / 2)), wave, lane);
+        if constexpr (WD == W_INT4 && !FAR) if (nr > 0) panel_scales_send(W, p0, nr, T, (u32)(size_t)(sz + (p & 1) * (kSzHalf / 2)), wave, lane);
         __builtin_amdgcn_sched_barrier(0);
         S = PanelSrc<T>::make(W, p0, max(rr.r1, p0 + 1), lane);
 #pragma unroll
@@ -288,7 +288,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     if constexpr (RES) gpre = *as_global((const u32x2*)(gain + (min(item_row(0), W.n - 1) & ~3)));   // gains of the next norm
     prefetch(0);
     timed(EV_PF_ISSUED);
-    if constexpr (WD == W_INT4) panel_scales_wait<D * T>();   // (read behind the barrier in the wait)
+    if constexpr (WD == W_INT4 && !FAR) panel_scales_wait<D * T>();   // (read behind the barrier in the wait)
     if (!sync.wait(epoch, wave, lane)) return false;
     timed(EV_SYNCED);
     const PanelImg X = PanelImg::make<WD, NC>(img, W.k, C.batch, lane);
@@ -299,8 +299,13 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
 #pragma unroll
         for (int j = 0; j < PanelRing<WD, NC, T>::DX; j++) R.load_x(X, j, I.at(j), WD != W_INT4 || NC > 8 || j < I.n);
         __builtin_amdgcn_sched_barrier(0);
-        panel_run<WD, NC, T>(S, R, X, I, PanelSz{sz_fits ? sz + (p & 1) * (kSzHalf / 2) + panel_skew(min(rr.r0 + 16 * T * p, W.n - 1), W.k) : (const lds_f16*)nullptr, panel_zeros(W.k, T),
-                                                &W, min(rr.r0 + 16 * T * p, W.n - 1), rr.r1}, lane, acc);
+        const int p0 = min(rr.r0 + 16 * T * p, W.n - 1);
+        const PanelSz from{sz + (p & 1) * (kSzHalf / 2) + panel_skew(p0, W.k), panel_zeros(W.k, T), W.k / 128};
+        if constexpr (!FAR) panel_run<WD, NC, T>(S, R, X, I, from, nullptr, wave, lane, acc);
+        else {
+            const PanelSzFar far{W.s + (size_t)p0 * from.ng, W.z + (size_t)p0 * from.ng, from.ng, rr.r1 - p0};
+            panel_run<WD, NC, T, true>(S, R, X, I, PanelSz{sz, 0, 0}, &far, wave, lane, acc);
+        }
         timed(p == 0 ? 4 : 8);
         if (p == 0 && C.M.dbg && C.layer == 1 && lane == 0) as_global(C.M.dbg)[(size_t)(4 * C.M.L + 1) * kEvSlots + (blockIdx.x * kWideWaves + wave) * 4 + (C.kind & 3)] = wall_clock64();
         __builtin_amdgcn_sched_barrier(0);
@@ -321,7 +326,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         const bool more = !RES && p + 1 < npanels;
         if (more) {   // the next panel's first weights, while this one is finished
             prefetch(p + 1);
-            if constexpr (WD == W_INT4) panel_scales_wait<D * T>();
+            if constexpr (WD == W_INT4 && !FAR) panel_scales_wait<D * T>();
         }
         __syncthreads();
         timed(p == 0 ? 5 : 9);
@@ -347,15 +352,23 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     }
 }
 
-template <int WD, int NC, bool RES>
+// int4: whether rows of k columns are too long for LDS to hold the scales of a panel of T tiles.  (One or two tiles are one panel; for inputs of d_model columns, those
+// of wider ones, the host checks that they fit.)
+__host__ __device__ __forceinline__ bool wide_sz_far(int k, int T) { return T <= 2 && 4 * panel_zeros(k, T) > kWideSzBytes; }
+// LONG: there may be such rows.
+template <int WD, int NC, bool RES, bool LONG>
 __device__ __forceinline__ bool wide_project_any(const PMat& W, const WideShape& S, const uint8_t* img, const float* ssin, const bf16_t* gain, u32 epoch, WideSync& sync, const WideCtx& C,
                                                  uint8_t* lds, int wave, int lane, int ph) {
-#define FF_WIDE_T(t) case t: return wide_project<WD, NC, t, RES>(W, S.rr, S.np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph);
+#define FF_WIDE_T(t, far) case t: return wide_project<WD, NC, t, RES, far>(W, S.rr, S.np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph);
+    if constexpr (WD == W_INT4 && LONG) if (wide_sz_far(W.k, S.T)) {
+        switch (S.T) { FF_WIDE_T(1, true) FF_WIDE_T(2, true) }
+        return false;
+    }
     if constexpr (RES) {
         static_assert(kWideResRows <= 32, "tiles of a workgroup's residual rows");
-        switch (S.T) { FF_WIDE_T(1) FF_WIDE_T(2) }
+        switch (S.T) { FF_WIDE_T(1, false) FF_WIDE_T(2, false) }
     } else
-        switch (S.T) { FF_WIDE_T(1) FF_WIDE_T(2) FF_WIDE_T(3) FF_WIDE_T(4) FF_WIDE_T(5) FF_WIDE_T(6) FF_WIDE_T(7) }
+        switch (S.T) { FF_WIDE_T(1, false) FF_WIDE_T(2, false) FF_WIDE_T(3, false) FF_WIDE_T(4, false) FF_WIDE_T(5, false) FF_WIDE_T(6, false) FF_WIDE_T(7, false) }
 #undef FF_WIDE_T
     return false;
 }
@@ -471,8 +484,8 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         const PMat W = wide_mat<WD>(tab, M, C.kind, l);
         timed(ph, EV_H_START);
         const WideShape S = wide_shape(tab + C.kind);
-        const bool ok = gain ? wide_project_any<WD, NC, true>(W, S, img, nullptr, gain, epoch, sync, C, lds, wave, lane, ph)
-                             : wide_project_any<WD, NC, false>(W, S, img, ssin, nullptr, epoch, sync, C, lds, wave, lane, ph);
+        const bool ok = gain ? wide_project_any<WD, NC, true, true>(W, S, img, nullptr, gain, epoch, sync, C, lds, wave, lane, ph)
+                             : wide_project_any<WD, NC, false, false>(W, S, img, ssin, nullptr, epoch, sync, C, lds, wave, lane, ph);
         timed(ph, EV_RUN_DONE);
         if (!ok) {
             if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);

@@ -905,6 +905,51 @@ def test_wide_pass_int4_scale_slabs_at_their_edges(monkeypatch, grid, batch):
     _run_teacher_forced(S, 0x2505227f1, synth.WDTYPE_INT4, batch=batch, T0=[7, 70, 0, 129, 31, 64, 3, 1, 90, 12, 55, 33][:batch], steps=2)
 
 
+def _best_us(call):
+    """Microseconds of a call: best of eight runs of five."""
+    times = []
+    for _ in range(8):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(5):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 200)
+    return min(times)
+
+
+@pytest.mark.parametrize("batch", (3, 12))
+def test_wide_pass_int4_rows_too_long_for_their_scales_on_chip(monkeypatch, batch):
+    """Several sequences, int4, a down projection of two tiles per workgroup (32 rows on eight workgroups) whose 516 groups' scales do not fit into LDS: a wave
+    brings those of its own 64 and 65 iterations in two goes."""
+    monkeypatch.setenv("FF_GRID", "8")
+    S = synth.TINY.replace(name="far", n_layers=2, d_model=256, n_q_heads=4, n_kv_heads=1, d_ffn=66048, vocab=515)
+    _run_teacher_forced(S, 0x2505227f3, synth.WDTYPE_INT4, batch=batch, T0=[7, 70, 0, 129, 31, 64, 3, 1, 90, 12, 55, 33][:batch], steps=2)
+
+
+def test_wide_pass_int4_tiles_do_not_wait_for_each_other():
+    """Rows of 28672 columns, two tiles per workgroup (70B shape): one and four sequences on a model for eight, against reading a buffer of the weights' size once (272 us).
+    Measured 1.62 and 1.65; where every tile waited for the whole ring, at the end of a branch around loads, 1.84 and 1.86."""
+    from paper_2505_22758_amd import binding
+    S = synth.LLAMA_70B.replace(n_layers=4, vocab=8192)
+    weights = torch.zeros(synth.weight_bytes_per_step(S, synth.WDTYPE_INT4), dtype=torch.uint8, device="cuda:0")
+    stream = _best_us(lambda: binding.ff_debug_stream_read(weights))
+    del weights
+    dec = binding.Decoder.synthetic(S, 3, synth.WDTYPE_INT4, max_batch=8)
+    us = {}
+    for batch in (1, 4):
+        dec.alloc_kv(batch, 80)
+        binding.ff_kv_fill_synthetic(dec.kv, 3, 64)
+        tok, pos = torch.full((batch,), 5, dtype=torch.int32, device="cuda:0"), torch.full((batch,), 64, dtype=torch.int32, device="cuda:0")
+        lg = torch.zeros(batch, S.vocab, device="cuda:0")
+        us[batch] = _best_us(lambda: dec.step(tok, pos, lg))
+        binding.ff_status(dec.model)
+    dec.close()
+    print(f"reading the weights {stream:.0f} us, steps {us}")
+    assert max(us.values()) <= 1.75 * stream, (us, stream)
+
+
 KSPLIT = synth.TINY.replace(name="ksplit", n_layers=2, d_model=1024, n_q_heads=64, n_kv_heads=8, head_dim=128, d_ffn=8192, vocab=2000)
 
 
