@@ -2,6 +2,7 @@
 // kernel (ff_solo.h) and the wide pass do not take: models wider than 8192, grids whose workgroups would own more than 32 rows of
 // d_model; there it also serves the sequences of a model for several one after another.
 #pragma once
+#include <algorithm>
 #include <mutex>
 #include "ff_solo.h"
 
@@ -312,9 +313,11 @@ inline hipError_t launch_fused_instance(const FusedLaunch& a, const char** what)
     *what = "fused kernel launch";
     return hipGetLastError();
 }
-template <int WD, int NC, int HD, int G>
+template <int WD, int NC, int HD, int G, bool LONG = kWideLong<WD, NC>>
 inline hipError_t launch_wide_instance(const FusedLaunch& a, const char** what) {
-    auto kern = wide_decode_kernel<WD, NC, HD, G>;
+    if constexpr (WD == W_INT4 && !LONG)
+        if (wide_sz_far(std::max(a.M.Hq * a.M.hd, a.M.F), panel_tiles(a.M.d, a.n_cta))) return launch_wide_instance<WD, NC, HD, G, true>(a, what);
+    auto kern = wide_decode_kernel<WD, NC, HD, G, LONG>;
     static KernelSetup setup;
     if (hipError_t e = setup.run((const void*)kern, kWideThreads, kWideLdsBytes)) { *what = setup.what; return e; }
     kern<<<a.n_cta, kWideThreads, kWideLdsBytes, a.stream>>>(a.M, a.KV, a.tokens, a.pos, a.logits, a.batch, a.lm_in_kernel, a.n_cta, a.mute_wg, a.switches);

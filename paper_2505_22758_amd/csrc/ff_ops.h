@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_gemv_kernel(DevModel M, Dev
     const UDiv n_ctas = UDiv::of((u32)ncta);
     WideSync sync{nullptr, ncta, false, nullptr, 0u};
     const WideCtx C{M, KV, pos_lds, nullptr, out, batch, 0, PH_LM, 0u, WideImg{nullptr, 0, 1, NC}, nullptr, nullptr, RowRange{0, 0}};
-    wide_project_any<WD, NC, false, true>(W, WideShape::of(W.n, n_ctas), img, nullptr, nullptr, 0u, sync, C, lds, wave, lane, 0);
+    wide_project_any<WD, NC, false, true, true>(W, WideShape::of(W.n, n_ctas), img, nullptr, nullptr, 0u, sync, C, lds, wave, lane, 0);
 }
 // Its input: rows of fp32 [img.batch][K] as a wide image of cols columns (those behind K: zero).
 __global__ void __launch_bounds__(256) wide_image_kernel(WideImg img, const float* in, int K, int cols) {

@@ -254,7 +254,12 @@ __device__ __forceinline__ void wide_store_ss(float* ss, int ncta, int t, int la
 // epoch: what to wait for.  Returns false (uniformly) on a time-out.
 // RES: the projections that add to the residual (output, down), whose outputs the next norm's gains multiply; at most two tiles, one panel.
 // FAR: int4 rows too long for their panel's scales in LDS (panel_scales_far).
-template <int WD, int NC, int T, bool RES, bool FAR>
+// LATE: where the panel's end takes what it knows of the lane anew, behind the products: else its addresses are computed ahead of them.  They are then spilled over the products with int4
+// weights, with head dimension 64 and in the bf16 and int8 steps of one sequence, which are the faster for it all the same.  (Us per step, ahead / late: int4, 8B, eight layers, one
+// sequence 426 / 421, x 4 447 / 440; bf16 x 2 681 / 671, x 8 737 / 729; one sequence, head dimension 64, eight layers, bf16 353 / 351, int8 300 / 298; but one sequence 8B bf16 684 / 693, int8 477 /
+// 485, and int8, tiny, x 16 124 / 128.)
+template <int WD, int NC, int HD> constexpr bool kWideLate = WD == W_INT4 || (WD == W_BF16 && NC > 1) || (NC == 1 && HD == 64);
+template <int WD, int NC, int T, bool RES, bool FAR, bool LATE>
 __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, int npanels, const uint8_t* img, const float* ssin, const bf16_t* gain, u32 epoch,
                                              WideSync& sync, const WideCtx& C, uint8_t* lds, int wave, int lane_in, int ph) {
     // (what depends on the lane only is cheap to compute again: kept from being hoisted out of the phase loop, where it would be spilled)
@@ -267,17 +272,16 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
     float* rms = (float*)(lds + kWideRmsOff);
     const int ni = (W.k + kWCols<WD> - 1) / kWCols<WD>;
     const WaveIters I = WaveIters::of(ni, wave);
-    const int q = lane >> 4, seq = lane & 15;
     constexpr int D = PanelRing<WD, NC, T>::D;
     PanelRing<WD, NC, T> R;
     PanelSrc<T> S;
     u32x2 pre = {0u, 0u}, gpre = {0u, 0u};
     auto prows = [&](int p) { return min(16 * T, rr.r1 - (rr.r0 + 16 * T * p)); };   // rows of panel p (<= 0 for a workgroup without rows)
-    auto item_row = [&](int p) { return rr.r0 + 16 * (T * p + wave) + 4 * q; };      // first row of the item this thread finishes
+    auto item_row = [&](int p, int lane_) { return rr.r0 + 16 * (T * p + wave) + 4 * (lane_ >> 4); };   // first row of the item this thread finishes
     // Everything a panel needs that does not depend on this step's activations.  All of it is loaded unconditionally, from clamped addresses.
     auto prefetch = [&](int p) {
         const int p0 = min(rr.r0 + 16 * T * p, W.n - 1), nr = prows(p);
-        if constexpr (WD == W_INT8) pre = *as_global((const u32x2*)(W.s + (min(item_row(p), W.n - 1) & ~3)));   // row scales of the item
+        if constexpr (WD == W_INT8) pre = *as_global((const u32x2*)(W.s + (min(item_row(p, lane), W.n - 1) & ~3)));   // row scales of the item
         if constexpr (WD == W_INT4 && !FAR) if (nr > 0) panel_scales_send(W, p0, nr, T, (u32)(size_t)(sz + (p & 1) * (kSzHalf / 2)), wave, lane);
         __builtin_amdgcn_sched_barrier(0);
         S = PanelSrc<T>::make(W, p0, max(rr.r1, p0 + 1), lane);
@@ -285,7 +289,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         for (int j = 0; j < D; j++) R.load_w(S, j, I.at(j), WD != W_INT4 || NC > 8 || j < I.n);
         __builtin_amdgcn_sched_barrier(0);
     };
-    if constexpr (RES) gpre = *as_global((const u32x2*)(gain + (min(item_row(0), W.n - 1) & ~3)));   // gains of the next norm
+    if constexpr (RES) gpre = *as_global((const u32x2*)(gain + (min(item_row(0, lane), W.n - 1) & ~3)));   // gains of the next norm
     prefetch(0);
     timed(EV_PF_ISSUED);
     if constexpr (WD == W_INT4 && !FAR) panel_scales_wait<D * T>();   // (read behind the barrier in the wait)
@@ -309,6 +313,12 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         timed(p == 0 ? 4 : 8);
         if (p == 0 && C.M.dbg && C.layer == 1 && lane == 0) as_global(C.M.dbg)[(size_t)(4 * C.M.L + 1) * kEvSlots + (blockIdx.x * kWideWaves + wave) * 4 + (C.kind & 3)] = wall_clock64();
         __builtin_amdgcn_sched_barrier(0);
+        int late = lane;
+        if constexpr (LATE) {
+            late = lane_in;
+            asm volatile("" : "+v"(late));
+        }
+        const int tid = wave * 64 + late, q = late >> 4, seq = late & 15;
         if (!RES && p == 0 && ssin) {   // the workgroups' sums of squares, in a fixed order
             float ssv[16], t = 0.f;
 #pragma unroll
@@ -318,10 +328,10 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
             for (int i = 0; i < 16; i++) t += (tid >> 4) + 32 * (i & 7) < sync.ncta ? ssv[i] : 0.f;
             t += __shfl_xor(t, 16);
             t += __shfl_xor(t, 32);
-            if (lane < kMaxBatchWide) rms[wave * kMaxBatchWide + lane] = t;
+            if (late < kMaxBatchWide) rms[wave * kMaxBatchWide + late] = t;
         }
         if (p > 0) __syncthreads();   // the previous panel's partial tiles have been read
-        panel_put<T, NC>(red, acc, wave, lane);
+        panel_put<T, NC>(red, acc, wave, late);
         const u32x2 rowscale = pre;
         const bool more = !RES && p + 1 < npanels;
         if (more) {   // the next panel's first weights, while this one is finished
@@ -331,7 +341,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
         __syncthreads();
         timed(p == 0 ? 5 : 9);
         if (wave < T) {
-            const int row = item_row(p);
+            const int row = item_row(p, late);
             float rs = 1.f;
             if (!RES && ssin) {
                 float t = 0.f;
@@ -345,7 +355,7 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
             const bool mine = row < rr.r1 && seq < C.batch;
             if constexpr (RES) {
                 const float v = mine ? wide_residual(C, row, seq, c, gpre) : 0.f;
-                wide_store_ss(C.ss, sync.ncta, wave, lane, v);
+                wide_store_ss(C.ss, sync.ncta, wave, late, v);
             } else if (mine) wide_epilogue(C, row, seq, c, min(4, rr.r1 - row));
         }
         if (!more) return true;
@@ -356,10 +366,10 @@ __device__ __forceinline__ bool wide_project(const PMat& W, const RowRange rr, i
 // of wider ones, the host checks that they fit.)
 __host__ __device__ __forceinline__ bool wide_sz_far(int k, int T) { return T <= 2 && 4 * panel_zeros(k, T) > kWideSzBytes; }
 // LONG: there may be such rows.
-template <int WD, int NC, bool RES, bool LONG>
+template <int WD, int NC, bool RES, bool LONG, bool LATE>
 __device__ __forceinline__ bool wide_project_any(const PMat& W, const WideShape& S, const uint8_t* img, const float* ssin, const bf16_t* gain, u32 epoch, WideSync& sync, const WideCtx& C,
                                                  uint8_t* lds, int wave, int lane, int ph) {
-#define FF_WIDE_T(t, far) case t: return wide_project<WD, NC, t, RES, far>(W, S.rr, S.np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph);
+#define FF_WIDE_T(t, far) case t: return wide_project<WD, NC, t, RES, far, LATE>(W, S.rr, S.np, img, ssin, gain, epoch, sync, C, lds, wave, lane, ph);
     if constexpr (WD == W_INT4 && LONG) if (wide_sz_far(W.k, S.T)) {
         switch (S.T) { FF_WIDE_T(1, true) FF_WIDE_T(2, true) }
         return false;
@@ -376,8 +386,11 @@ __device__ __forceinline__ bool wide_project_any(const PMat& W, const WideShape&
 // ---------------------------------------------------------------- the kernel
 // One launch = one step of up to NC sequences (phases as in fused_decode_kernel).  One sequence has an instance of its own:
 // its step on a model for several sequences is as exact as on a model for one.
-// n_lm: 1 = the LM head runs here, 0 = launched separately.
-template <int WD, int NC, int HD, int G>
+// n_lm: 1 = the LM head runs here, 0 = launched separately.  LONG: rows of the output and down projections may be too long for their scales in LDS (wide_sz_far).  Above
+// eight sequences they have an instance of their own: their code in the way of the others costs these up to 2 % (us per step, eight layers, x 16, with / without: 1b 334 / 332,
+// 3b 397 / 394; tiny 127 / 125); up to eight it does not (8B int4 x 1 423 / 424, x 4 420 / 421, tiny x 8 127 / 128).
+template <int WD, int NC> constexpr bool kWideLong = WD == W_INT4 && NC <= 8;
+template <int WD, int NC, int HD, int G, bool LONG = kWideLong<WD, NC>>
 __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, DevKV KV, const int* __restrict__ tokens, const int* __restrict__ pos,
                                                                    float* __restrict__ logits, int n_seq, int lm_in_kernel, int ncta, int mute_wg, int switches) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -484,8 +497,8 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
         const PMat W = wide_mat<WD>(tab, M, C.kind, l);
         timed(ph, EV_H_START);
         const WideShape S = wide_shape(tab + C.kind);
-        const bool ok = gain ? wide_project_any<WD, NC, true, true>(W, S, img, nullptr, gain, epoch, sync, C, lds, wave, lane, ph)
-                             : wide_project_any<WD, NC, false, false>(W, S, img, ssin, nullptr, epoch, sync, C, lds, wave, lane, ph);
+        const bool ok = gain ? wide_project_any<WD, NC, true, LONG, kWideLate<WD, NC, HD>>(W, S, img, nullptr, gain, epoch, sync, C, lds, wave, lane, ph)
+                             : wide_project_any<WD, NC, false, false, kWideLate<WD, NC, HD>>(W, S, img, ssin, nullptr, epoch, sync, C, lds, wave, lane, ph);
         timed(ph, EV_RUN_DONE);
         if (!ok) {
             if (threadIdx.x == 0) atomicCAS(M.status, 0, -55 - 10 * ph);
