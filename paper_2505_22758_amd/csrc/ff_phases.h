@@ -478,6 +478,14 @@ __device__ __forceinline__ bool stage_tagged(const TSrc& S, int batch, int K, in
 // the attention's critical path.
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The thread's index, unknown to the compiler: what depends on the lane only is cheap to compute again in every layer, and hoisted out of the loop over layers it
+// takes registers from the projections' loops (spilled there, 8B bf16 x 8: 20 of them).
+__device__ __forceinline__ int thread_again() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // ---------------------------------------------------------------- split-KV attention
 // One work item = (sequence b, kv head j, rows [t0, t1) of its cache [+ this step's own k,v]).
 // All G query heads that share kv head j are processed together, so each cached K and V element
@@ -486,18 +494,8 @@ __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2
 // from the cache).  Result: per query head the partial (max score, denominator, unnormalised
 // output) of a FlashDecoding-style split, in base-2 exponent units.
 //
-// Thread mapping: a cache row is hd*2 bytes = LPR lanes x 16 bytes, so one wave load covers
-// 64/LPR rows; lane (grp, sub) holds dims [8*sub, 8*sub+8) of row grp.  Every (wave, grp) keeps its
-// own online-softmax state; the NW*64/LPR states are merged through LDS at the end (NW = waves of
-// the workgroup, all of which take part).  XIO supplies the exchange accesses (plain buffers for
-// the per-operation kernels, tagged buffers for the fused kernel); returns false on a time-out.
-// The thread's index, unknown to the compiler: what depends on the lane only is cheap to compute again in every layer, and hoisted out of the loop over layers it
-// takes registers from the projections' loops (spilled there, 8B bf16 x 8: 20 of them).
-__device__ __forceinline__ int thread_again() {
-    int t = threadIdx.x;
-    asm volatile("" : "+v"(t));
-    return t;
-}
+// XIO supplies the exchange accesses (plain buffers for the per-operation kernels, tagged buffers for the decode kernels).
+//
 struct PlainAttnIO {
     // Workgroup-collective: the G query rows of kv head j, then (with_cur) this step's own key and
     // value row, as floats into dst[G*HD + 2*HD] (LDS); ends with a workgroup barrier.
@@ -521,7 +519,7 @@ struct PlainAttnIO {
         if (dim == 0) { PlainIO::st(M.part_m + hs, mx); PlainIO::st(M.part_l + hs, lt); }
     }
 };
-// Staged inputs of the attention on the matrix cores (attn_item, forms 3 and 4), in words of two bf16: rows of 16 bytes more than a query's
+// Staged inputs of the attention on the matrix cores (attn_item_mfma), in words of two bf16: rows of 16 bytes more than a query's
 // (without them the 16 rows of an operand would lie in the same banks): the G queries' heads, their remainders, their third parts, rows of zeros up to whole
 // operands; then the step's own key and value.
 template <int HD, int G>
@@ -824,6 +822,9 @@ __device__ __forceinline__ bool attn_item_mfma(const DevModel& M, const DevKV& K
     if (ev && threadIdx.x == 0) as_global(ev)[3] = wall_clock64();
     return true;
 }
+// One item, row by row on the vector ALU (head dimension 64, and the per-operation kernels).  A cache row is hd*2 bytes = LPR lanes x 16 bytes, so one wave load covers 64/LPR rows; lane
+// (grp, sub) holds dims [8*sub, 8*sub+8) of row grp.  Every (wave, grp) keeps its own online-softmax state; a wave's merge in registers, the waves' through LDS (NW = waves of the
+// workgroup, all of which take part).  Returns false on a time-out.
 template <int HD, int G, int NW, class XIO, bool MFMA = false>   // MFMA: attn_item_mfma where the head dimension allows it
 __device__ __forceinline__ bool attn_item(const DevModel& M, const DevKV& KV, const XIO& xio, int layer, int b, int j, int t0, int t1, bool with_cur,
                           int split, int nsplit, uint8_t* lds, u64* ev = nullptr) {
@@ -1079,8 +1080,9 @@ __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, const Tagge
 // Number of KV splits for a sequence with `ncache` cached rows when `share` workgroups are
 // available per (sequence, kv head).
 __device__ __forceinline__ int attn_nsplit(int ncache, int share, int hd) {
-    // A slice is as long as four of the workgroup's waves take at once (16 rows each; head dimension 64: 8): a fifth wave shares a SIMD with the
-    // first, and both take longer than the merge gets shorter.  Up to eight slices a power of two, whose shares of the merge are equal; eleven to sixteen are sixteen.
+    // Up to 640 rows (head dimension 64: 320) slices are no longer than four of the workgroup's waves take at once (16 rows each; head dimension 64: 8): a fifth wave shares a SIMD with the
+    // first, and both take longer than the merge gets shorter.  Up to eight slices their number is a power of two, whose shares of the merge are equal, unless there are fewer workgroups;
+    // from eleven on it is sixteen, with as many rows as it takes.
     // (Us per step, one sequence, ncache / 64 slices / this.  8B int4, eight layers, context 200 295 / 291, 400 307 / 294, 512 297 / 295, 900 316 / 309; 600, as
     // 10 slices 305, as 16 311; 100 as one slice 289, as two 291; 70B bf16, six layers, 400 1628 / 1613; tiny, context 128 81.5 / 79.2, 400 87.2 / 81.0, 1000 85.6 / 83.3.
     // 8B int4 x 4, context 500, 459 / 440.)
@@ -1088,9 +1090,10 @@ __device__ __forceinline__ int attn_nsplit(int ncache, int share, int hd) {
     if (ncache < 2 * rows) return 1;
     int ns = (ncache + rows - 1) / rows;
     if (ns <= 8) ns = ns <= 2 ? 2 : ns <= 4 ? 4 : 8;
-    // The merge gathers the partials 16 at a time, two or four to a lane: 16 slices, 32 as soon as these are 50 rows long, whole rounds of 16
-    // behind 256 rows each.  (Us per step, one sequence, 16 / 32 slices: 8B, eight layers, int4, context 1600 321 / 318, 2048 325 / 321, 4096 343 / 330; int8, 1500
-    // 418 / 423, 2500 430 / 425, 4096 441 / 431; bf16 4096 737 / 721; 70B bf16, six layers, 4096 1659 / 1646.)
+    // The merge gathers the partials 16 at a time, two or four to a lane: 16 slices up to 1599 rows (100 each), 32 up to 8192 (50 to 256), then whole rounds of 16 of at most 256 rows, up to
+    // kMaxSplits; behind 16384 rows these grow.  (Us per step, one sequence, 16 / 32 slices: 8B, eight layers, int4, context 1600 321 / 318, 2048 325 / 321, 4096 343 / 330; int8, 1500
+    // 418 / 423, 2500 430 / 425, 4096 441 / 431; bf16 4096 737 / 721; 70B bf16, six layers, 4096 1659 / 1646.  Head dimension 64, d 2048, eight layers, 1599 rows as 16 / 1600 as 32: bf16 297 / 294, int8
+    // 225 / 220, int4 211 / 208; tiny 86 / 84, 84 / 81, 84 / 83.)
     constexpr int kRound = 16, kRoundRows = kRound * 256;
     if (ns > 10) ns = ncache >= 1600 && ncache <= 2 * kRoundRows ? 2 * kRound : kRound * ((ncache + kRoundRows - 1) / kRoundRows);
     return max(min(ns, min(share, kMaxSplits)), 1);

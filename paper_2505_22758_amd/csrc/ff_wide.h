@@ -27,7 +27,7 @@
 // this kernel on row-major / on tiled weights: 8B bf16 x 8 1127 / 1003 / 834, int8 x 11 992 / 936 / 770, int4 x 16 1628 /
 // 978 / 783, 70B bf16 x 16 3283 / 3098 / 2619; against a row-partitioned pass of up to four sequences (4x4x4 matrix-core
 // tiles, inputs staged by every workgroup): bf16 x 2 858 / 769, int4 x 4 1038 / 570, int8 x 4 879 / 581.  Since (merge of the attention
-// slices shared out, descriptors in LDS, attention form 1, int4 panels without tails): bf16 x 2 735, x 8 779, int8 x 4 534, x 11 701, int4 x 4
+// slices shared out, descriptors in LDS, attention scores on the matrix cores, int4 panels without tails): bf16 x 2 735, x 8 779, int8 x 4 534, x 11 701, int4 x 4
 // 509, x 16 723.
 // What bounds it: the weight stream, then the attention's chain of hand-overs (a third of a layer).
 #pragma once
