@@ -236,7 +236,11 @@ __global__ void __launch_bounds__(kFusedThreads) fused_decode_kernel(DevModel M,
             return;
         }
         if (wave == 0) dbg_event(M, min(ph, n_phases - 1), EV_SYNCED, lane);
-        if (kHasSwitch && (switches & kSwNoOverlap)) prefetch_stream(S, ring, lane, 0, kPrefetchOf<WD>);
+        if (kHasSwitch && (switches & kSwNoOverlap)) {
+            prefetch_stream(S, ring, lane, 0, kPrefetchOf<WD>);
+            // (a shorter ring has to have arrived: else the compiler has every pass of the loop below wait as on a ring that was never longer, half of it)
+            if (S.n_it < kPrefetchOf<WD>) settled();
+        }
         if constexpr (kPrefetchOf<WD> < kDepthOf<WD>) prefetch_stream(S, ring, lane, kPrefetchOf<WD>, kDepthOf<WD>);   // the rest of the ring, behind the input
         u64* wv = D.kind < 4 ? dbg_wave_slots(M, n_phases, D.layer, wave) : nullptr;
         if (wv && lane == 0) as_global(wv)[4 + D.kind] = wall_clock64();
