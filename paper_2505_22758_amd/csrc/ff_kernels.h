@@ -91,12 +91,13 @@ struct AttnItem {
 typedef __attribute__((address_space(3))) AttnItem lds_item;
 constexpr int kAttnListed = 8;   // items of a workgroup that are listed once per step; a layer works out again what is behind them
 // Item number k of this workgroup.  (32-bit unsigned arithmetic throughout: 64-bit or signed divisions are long instruction sequences.)
-__device__ __forceinline__ AttnItem attn_item_at(const int* pos, const int* share, int batch, int Hkv, int hd, const UDiv& nc, int k) {
+template <int HD, int NW>
+__device__ __forceinline__ AttnItem attn_item_at(const int* pos, const int* share, int batch, int Hkv, const UDiv& nc, int k) {
     const int ncta = (int)nc.n;
     int base = 0;
     for (int b = 0; b < batch; b++) {
         const int T = max(pos[b], 0);   // (-1: the sequence sits this step out and is carried as a placeholder with an empty cache)
-        const int ns = attn_nsplit(T, share[b], hd), nitems = Hkv * ns;
+        const int ns = HD == 64 && NW == 4 ? attn_nsplit_few(T, share[b]) : attn_nsplit(T, share[b], HD), nitems = Hkv * ns;
         const int first = (int)nc.mod((u32)blockIdx.x + (u32)ncta - (u32)base);   // base < ncta
         const int here = first < nitems ? (int)nc.div((u32)(nitems - first + ncta - 1)) : 0;
         if (k < here) {
@@ -110,9 +111,10 @@ __device__ __forceinline__ AttnItem attn_item_at(const int* pos, const int* shar
 }
 // The workgroup's list, the same for every layer, by its first kAttnListed threads.  (Worked out layer by layer, sequence by sequence, it stood with
 // its divisions between the QKV projection and the first request for a cached row.)
-__device__ __forceinline__ void attn_list(lds_item* list, const int* pos, const int* share, int batch, int Hkv, int hd, const UDiv& nc) {
+template <int HD, int NW>
+__device__ __forceinline__ void attn_list(lds_item* list, const int* pos, const int* share, int batch, int Hkv, const UDiv& nc) {
     if (threadIdx.x < kAttnListed) {
-        const AttnItem e = attn_item_at(pos, share, batch, Hkv, hd, nc, threadIdx.x);
+        const AttnItem e = attn_item_at<HD, NW>(pos, share, batch, Hkv, nc, threadIdx.x);
         *(__attribute__((address_space(3))) u32x4*)(list + threadIdx.x) = __builtin_bit_cast(u32x4, e);
     }
 }
@@ -130,7 +132,7 @@ __device__ __forceinline__ bool attention_phase_tagged(const DevModel& M, const 
     for (int k = 0;; k++) {
         u32x4 e;
         if (list && k < kAttnListed) e = *(const __attribute__((address_space(3))) u32x4*)(list + k);
-        else e = __builtin_bit_cast(u32x4, attn_item_at(pos, share, batch, M.Hkv, HD, nc, k));
+        else e = __builtin_bit_cast(u32x4, attn_item_at<HD, NW>(pos, share, batch, M.Hkv, nc, k));
         const int bj = __builtin_amdgcn_readfirstlane((int)e.x), sn = __builtin_amdgcn_readfirstlane((int)e.y);
         const int t0 = __builtin_amdgcn_readfirstlane((int)e.z), t1 = __builtin_amdgcn_readfirstlane((int)e.w);
         const int ns = sn >> 16, s = sn & 0xFFFF, b = bj & 0xFF, j = bj >> 8;

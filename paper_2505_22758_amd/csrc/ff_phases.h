@@ -1079,6 +1079,13 @@ __device__ __forceinline__ bool attn_merge_tagged(const DevModel& M, const Tagge
 
 // Number of KV splits for a sequence with `ncache` cached rows when `share` workgroups are
 // available per (sequence, kv head).
+// Slices for workgroups of four waves at head dimension 64 (row-partitioned kernel): whole 64 rows, up to 16, then 16 for every 4096 rows.  (Shorter ones are
+// done sooner there by less than the merge of more parts takes.  Us per step, three layers of d 2048 on 40 workgroups, by attn_nsplit / this: context 100 bf16 311 / 306, int8 379 / 374, int4
+// 435 / 430; 250 int4 437 / 436; 2500 bf16 336 / 334, int4 458 / 459.)
+__device__ __forceinline__ int attn_nsplit_few(int ncache, int share) {
+    const int ns = ncache / 64;
+    return max(min(ns > 16 ? 16 * ((ncache + 4095) / 4096) : ns, min(share, kMaxSplits)), 1);
+}
 __device__ __forceinline__ int attn_nsplit(int ncache, int share, int hd) {
     // Up to 640 rows (head dimension 64: 320) slices are no longer than four of the workgroup's waves take at once (16 rows each; head dimension 64: 8): a fifth wave shares a SIMD with the
     // first, and both take longer than the merge gets shorter.  Up to eight slices their number is a power of two, whose shares of the merge are equal, unless there are fewer workgroups;

@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(kWideThreads) wide_decode_kernel(DevModel M, D
     auto timed = [&](int ph, int ev) { if (M.dbg && blockIdx.x == 0 && threadIdx.x == 0) as_global(M.dbg)[ph * kEvSlots + ev] = wall_clock64(); };
     __syncthreads();
     lds_item* items = (lds_item*)(lds + kWideItemOff);
-    attn_list(items, pos_lds, share_lds, batch, M.Hkv, HD, n_ctas);   // (read behind the first projection's barriers)
+    attn_list<HD, kWideWaves>(items, pos_lds, share_lds, batch, M.Hkv, n_ctas);   // (read behind the first projection's barriers)
     WideCtx C{M, KV, pos_lds, rope_lds, logits, batch, 0, PH_DOWN, 0u, image(block(0) + WL.x1), (float*)(block(0) + WL.ss1), xres, own, HD};
     // the step's embedding rows enter like the output of a projection onto zero
     if (16 * wave < kWideResRows) {
