@@ -1185,6 +1185,27 @@ def test_row_partitioned_kernel_all_instances(monkeypatch, heads, wdtype):
     _run_teacher_forced(S, 0x2505227f0 + wdtype, wdtype, batch=1, T0=300, steps=2)
 
 
+@pytest.mark.parametrize("heads", ((32, 8, 128), (64, 16, 64)), ids=("hd128", "hd64"))
+def test_row_partitioned_bf16_stream_keeps_its_ring(monkeypatch, heads):
+    """Row-partitioned kernel on 100 workgroups (8B width, bf16), whose waves own rows of several counts: a step against reading a buffer of the weights' size once with as many
+    workgroups.  Measured 1.33 to 1.36; with a loop that waited for half of the ring in every pass 1.45 and 1.46."""
+    from paper_2505_22758_amd import binding
+    monkeypatch.setenv("FF_GRID", "100")
+    S = synth.LLAMA_8B.replace(n_layers=2, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=heads[2], vocab=4096)
+    weights = torch.zeros(synth.weight_bytes_per_step(S, synth.WDTYPE_BF16), dtype=torch.uint8, device="cuda:0")
+    stream = _best_us(lambda: binding.ff_debug_stream_read(weights, 100))
+    dec = binding.Decoder.synthetic(S, 3, synth.WDTYPE_BF16, max_batch=1)
+    dec.alloc_kv(1, 80)
+    binding.ff_kv_fill_synthetic(dec.kv, 3, 64)
+    tok, pos = torch.full((1,), 5, dtype=torch.int32, device="cuda:0"), torch.full((1,), 64, dtype=torch.int32, device="cuda:0")
+    lg = torch.zeros(1, S.vocab, device="cuda:0")
+    us = _best_us(lambda: dec.step(tok, pos, lg))
+    binding.ff_status(dec.model)
+    dec.close()
+    print(f"reading the weights {stream:.0f} us, step {us:.0f}")
+    assert us <= 1.4 * stream, (us, stream)
+
+
 def test_wide_pass_of_up_to_16_sequences_small_model():
     """Several sequences run as ONE wide pass: projections on 16x16x32 matrix-core tiles, inputs from images
     written by the workgroups that own the values, the RMSNorm factor applied to the projection outputs, the
